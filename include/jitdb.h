@@ -97,6 +97,10 @@ typedef struct {
                                           level l (0 for level 0), -1 = not known.  Optional: with it the forward
                                           recognises levels in which every node has exactly one child (chains:
                                           sequences, the thin tail of a forest) and runs each as a single launch */
+    int32_t tree_window;     /* out: > 0 = the trees are filed one after another and no tree (no run of interleaved
+                                          trees) is longer than this many ids: any tree_window + 1 consecutive places
+                                          between ids hold one that no edge crosses.  0 = not known (set it to 0 in a
+                                          schedule made by hand); the forward then runs level by level */
 } jitdb_schedule_t;
 
 /* Bytes of device workspace jitdb_schedule needs for a forest of n_nodes (0 if n_nodes is invalid). */
@@ -109,8 +113,9 @@ size_t jitdb_schedule_workspace_bytes(int64_t n_nodes);
  *   parent  dev [N] int32, -1 = root.
  *   s       in/out, see jitdb_schedule_t.
  *
- * Runs on `hip_stream` and synchronises that stream twice (to learn the number
- * of levels, then to hand back level_ptr).  On JITDB_E_PARENT_RANGE or
+ * Runs on `hip_stream` and synchronises that stream: once where the trees' ids lie
+ * close together (or the forest is small), else twice (to learn the number of levels, then to
+ * hand back level_ptr).  On JITDB_E_PARENT_RANGE or
  * JITDB_E_CYCLE the output arrays hold unspecified values; no kernel reads or
  * writes out of bounds for any input.  N == 0 succeeds with n_levels = 0.
  * The schedule depends only on `parent` and may be reused for any number of
@@ -220,7 +225,7 @@ size_t jitdb_schedule_typed_workspace_bytes(int64_t n_nodes, int32_t n_sig);
  * `s` receives what jitdb_schedule returns except that positions are ordered by
  * (height, sig, psig, id), so every level is a run of n_sig slots of n_sig sub-slots each;
  * `slots` receives the boundaries.  Errors as jitdb_schedule, plus JITDB_E_SIGNATURE.
- * Synchronises the stream twice.
+ * Synchronises the stream as jitdb_schedule does.
  */
 int jitdb_schedule_typed(const int32_t *parent, const int32_t *sig, jitdb_schedule_t *s,
                          jitdb_slots_t *slots, void *workspace, size_t workspace_bytes,

@@ -7,11 +7,13 @@ There is no CPU fallback.
 """
 from __future__ import annotations
 
+import contextlib
 import ctypes
 import os
 from typing import Optional, Tuple
 
 import numpy as np
+import torch as _torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "libjitdb.so")
@@ -44,6 +46,7 @@ class _ScheduleStruct(ctypes.Structure):
         ("n_levels", ctypes.c_int32),
         ("n_edges", ctypes.c_int64),
         ("host_level_kids", ctypes.c_void_p),
+        ("tree_window", ctypes.c_int32),
     ]
 
 
@@ -269,9 +272,19 @@ def _check(code: int):
 
 
 def _stream_ptr(stream) -> int:
-    import torch
-    s = torch.cuda.current_stream() if stream is None else stream
-    return int(s.cuda_stream)
+    if stream is not None:
+        return int(stream.cuda_stream)
+    # the handle alone: torch.cuda.current_stream() builds a Stream object around it on every call
+    return int(_torch._C._cuda_getCurrentRawStream(_torch.cuda.current_device()))
+
+
+_NO_SWITCH = contextlib.nullcontext()
+
+
+def _on_device(device):
+    """Context in which `device` is current; nothing is switched where it is already."""
+    i = device.index
+    return _NO_SWITCH if i is None or i == _torch.cuda.current_device() else _torch.cuda.device(device)
 
 
 def _empty(stream, *args, **kw):
@@ -290,9 +303,7 @@ def _on_stream(stream):
     """Context in which default buffers are allocated: the stream the launches go to.  Memory the
     caching allocator hands out belongs to the stream that is current at that moment; allocated under
     another stream it could be given to other work while these kernels still use it."""
-    import contextlib
-    import torch
-    return contextlib.nullcontext() if stream is None else torch.cuda.stream(stream)
+    return _NO_SWITCH if stream is None else _torch.cuda.stream(stream)
 
 
 class Schedule:
@@ -346,7 +357,7 @@ def jitdb_schedule(parent, stream=None, workspace=None, out: Optional[Schedule] 
     need = jitdb_schedule_workspace_bytes(n)
     if workspace is None:
         workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=parent.device)
-    with torch.cuda.device(parent.device):
+    with _on_device(parent.device):
         code = lib.jitdb_schedule(parent.data_ptr() if n else None, ctypes.byref(sched.struct),
                                   workspace.data_ptr(), workspace.numel(), _stream_ptr(stream))
     _check(code)
@@ -377,7 +388,7 @@ def jitdb_schedule_append(base: Schedule, parent_new, stream=None, workspace=Non
     need = jitdb_schedule_append_workspace_bytes(base.n_nodes, m)
     if workspace is None:
         workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=parent_new.device)
-    with torch.cuda.device(parent_new.device):
+    with _on_device(parent_new.device):
         code = lib.jitdb_schedule_append(ctypes.byref(base.struct), parent_new.data_ptr() if m else None, m,
                                          ctypes.byref(sched.struct), workspace.data_ptr(), workspace.numel(),
                                          _stream_ptr(stream))
@@ -412,7 +423,7 @@ def jitdb_treelstm_forward_static(x, W, U, b, schedule: Schedule, out: Tuple, st
     if (x.shape != (n, D) or W.shape[0] != 4 * H or U.shape[0] != 4 * H or b.numel() != 4 * H
             or h.shape != (n, H) or c.shape != (n, H)):
         raise ValueError("shape mismatch between x, W, U, b, out and the schedule")
-    with torch.cuda.device(x.device):
+    with _on_device(x.device):
         code = lib.jitdb_treelstm_forward_static(
             x.data_ptr() if n else None, W.data_ptr(), U.data_ptr(), b.data_ptr(), D, H, dt,
             ctypes.byref(schedule.struct), h.data_ptr() if n else None, c.data_ptr() if n else None,
@@ -472,7 +483,7 @@ def jitdb_treelstm_backward(x, W, U, schedule: Schedule, h, c, gates, fgate, gh=
     if workspace is None:
         workspace = _empty(stream, max(need, 256), dtype=torch.uint8, device=x.device)
     ptr = lambda t: t.data_ptr() if (t is not None and t.numel()) else None
-    with torch.cuda.device(x.device):
+    with _on_device(x.device):
         code = lib.jitdb_treelstm_backward(
             ptr(x), W.data_ptr(), U.data_ptr(), D, H, dt, ctypes.byref(schedule.struct),
             ptr(h), ptr(c), ptr(gates), ptr(fgate), ptr(gh), ptr(gc),
@@ -515,7 +526,7 @@ def _forward(x, W, U, b, schedule, stream, workspace, out, train):
     need = jitdb_treelstm_workspace_bytes(n, schedule.n_edges, D, H, dt)
     if workspace is None:
         workspace = _empty(stream, max(need, 256), dtype=torch.uint8, device=x.device)
-    with torch.cuda.device(x.device):
+    with _on_device(x.device):
         if train:
             code = lib.jitdb_treelstm_forward_train(
                 x.data_ptr() if n else None, W.data_ptr(), U.data_ptr(), b.data_ptr(), D, H, dt,
@@ -540,7 +551,7 @@ def jitdb_forest_fingerprint(parent, stream=None, fp_dev=None) -> Tuple[int, int
         fp_dev = torch.empty(2, dtype=torch.int64, device=parent.device)
     host = (ctypes.c_uint64 * 2)()
     n = parent.numel()
-    with torch.cuda.device(parent.device):
+    with _on_device(parent.device):
         _check(load_library().jitdb_forest_fingerprint(parent.data_ptr() if n else None, n, fp_dev.data_ptr(),
                                                        host, _stream_ptr(stream)))
     return int(host[0]), int(host[1])
@@ -653,7 +664,7 @@ def jitdb_schedule_typed(parent, sig, n_sig: int, stream=None, workspace=None,
     need = jitdb_schedule_typed_workspace_bytes(n, n_sig)
     if workspace is None:
         workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=parent.device)
-    with torch.cuda.device(parent.device):
+    with _on_device(parent.device):
         code = lib.jitdb_schedule_typed(parent.data_ptr() if n else None, sig.data_ptr() if n else None,
                                         ctypes.byref(sched.struct), ctypes.byref(sched.slots),
                                         workspace.data_ptr(), workspace.numel(), _stream_ptr(stream))
@@ -699,7 +710,7 @@ def jitdb_treelstm_forward_typed(x, W, U, b, schedule: TypedSchedule, stream=Non
     need = jitdb_treelstm_typed_workspace_bytes(n, schedule.n_edges, D, H, dt, T)
     if workspace is None:
         workspace = _empty(stream, max(need, 256), dtype=torch.uint8, device=x.device)
-    with torch.cuda.device(x.device):
+    with _on_device(x.device):
         code = lib.jitdb_treelstm_forward_typed(
             x.data_ptr() if n else None, W.data_ptr(), U.data_ptr(), b.data_ptr(), D, H, dt,
             ctypes.byref(schedule.struct), ctypes.byref(schedule.slots),
@@ -770,7 +781,7 @@ def jitdb_treelstm_forward_cells(x, cells, schedule: TypedSchedule, stream=None,
     need = int(lib.jitdb_treelstm_cells_workspace_bytes(n, schedule.n_edges, D, H, dt, arr, T))
     if workspace is None:
         workspace = _empty(stream, max(need, 256), dtype=torch.uint8, device=x.device)
-    with torch.cuda.device(x.device):
+    with _on_device(x.device):
         code = lib.jitdb_treelstm_forward_cells(
             x.data_ptr() if n else None, arr, T, D, H, dt,
             ctypes.byref(schedule.struct), ctypes.byref(schedule.slots),
@@ -804,7 +815,7 @@ def jitdb_treelstm_pack(W, U, b, stream=None) -> PackedWeights:
         raise ValueError("shape mismatch between W, U, b")
     need = int(lib.jitdb_treelstm_packed_bytes(D, H, dt, T))
     buf = _empty(stream, max(need, 256), dtype=torch.uint8, device=W.device)
-    with torch.cuda.device(W.device):
+    with _on_device(W.device):
         _check(lib.jitdb_treelstm_pack(W.data_ptr(), U.data_ptr(), b.data_ptr(), D, H, dt, T, buf.data_ptr(),
                                        buf.numel(), _stream_ptr(stream)))
     return PackedWeights(buf, D, H, dt, T, W.dtype)
@@ -832,7 +843,7 @@ def jitdb_treelstm_forward_packed(x, packed: PackedWeights, schedule: Schedule, 
     need = jitdb_treelstm_typed_workspace_bytes(n, schedule.n_edges, D, H, packed.dtype, packed.n_sig)
     if workspace is None:
         workspace = _empty(stream, max(need, 256), dtype=torch.uint8, device=x.device)
-    with torch.cuda.device(x.device):
+    with _on_device(x.device):
         code = lib.jitdb_treelstm_forward_packed(
             x.data_ptr() if n else None, packed.buffer.data_ptr(), D, H, packed.dtype,
             ctypes.byref(schedule.struct), ctypes.byref(schedule.slots) if typed else None,

@@ -601,7 +601,7 @@ AppendWs carve_append_ws(int64_t n_new, void *base) {
     w.inv_perm = c.take<int32_t>(n_new);
     w.child_ptr = c.take<int32_t>(n_new + 1);
     w.child_idx = c.take<int32_t>(n_new);
-    w.sched_ws_bytes = carve_schedule_ws(n_new, nullptr).bytes;
+    w.sched_ws_bytes = jitdb_schedule_workspace_bytes(n_new);
     w.sched_ws = c.take<char>(w.sched_ws_bytes);
     w.bytes = c.off;
     return w;
@@ -610,14 +610,57 @@ AppendWs carve_append_ws(int64_t n_new, void *base) {
 }  // namespace
 }  // namespace jitdb
 
+#include "schedule_local.h"
+
 using namespace jitdb;
+
+namespace {
+// Workspace of one analysis: the general path and the LDS path take turns in the same memory.
+size_t schedule_ws_bytes(int64_t n, int64_t n_keys) {
+    const size_t g = carve_schedule_ws(n, nullptr, n_keys).bytes, l = carve_local_ws(n, nullptr, n_keys).bytes;
+    return g > l ? g : l;
+}
+}  // namespace
 
 extern "C" size_t jitdb_schedule_workspace_bytes(int64_t n_nodes) {
     if (n_nodes < 0 || n_nodes > JITDB_MAX_NODES) return 0;
-    return carve_schedule_ws(n_nodes, nullptr).bytes;
+    return schedule_ws_bytes(n_nodes, 1);
 }
 
 namespace {
+constexpr int kTakeGeneralPath = 1;
+
+// The analysis in LDS (schedule_local.h); kTakeGeneralPath if the forest does not fit it.
+int schedule_local(const int32_t *parent, const int32_t *sig, jitdb_slots_t *slots, jitdb_schedule_t *s, void *workspace,
+                   LocalReport *rep, hipStream_t st) {
+    const int32_t n_sig = slots ? slots->n_sig : 1;
+    LocalArgs a = carve_local_ws(s->n_nodes, workspace, (int64_t)n_sig * n_sig).a;
+    a.parent = parent; a.sig = slots ? sig : nullptr;
+    a.n = (int32_t)s->n_nodes; a.n_sig = n_sig;
+    a.height = s->height; a.level_ptr = s->level_ptr; a.perm = s->perm; a.inv_perm = s->inv_perm;
+    a.child_ptr = s->child_ptr; a.child_idx = s->child_idx;
+    a.key = slots ? slots->key : nullptr;
+    a.slot_ptr = slots ? slots->slot_ptr : nullptr;
+    a.slot_capacity = slots ? slots->slot_capacity : 0;
+    a.report = rep;
+    __atomic_store_n(&rep->done, 0, __ATOMIC_RELEASE);
+    const int rc = launch_local_schedule(a, st);
+    if (rc != JITDB_OK) return rc;
+    JITDB_HIP_CHECK(wait_for_report(rep, st));
+    if (rep->flags & LF_RANGE) return JITDB_E_PARENT_RANGE;
+    if (rep->flags & LF_GENERAL) return kTakeGeneralPath;
+    if (rep->flags & LF_SIG) return JITDB_E_SIGNATURE;
+    if (rep->flags & LF_CYCLE) return JITDB_E_CYCLE;
+    const int32_t L = rep->n_levels;
+    s->n_levels = L;
+    s->n_edges = rep->n_edges;
+    s->tree_window = rep->tree_window;
+    memcpy(s->host_level_ptr, rep->level_ptr, sizeof(int32_t) * ((size_t)L + 1));
+    if (s->host_level_kids) memcpy(s->host_level_kids, rep->kids, sizeof(int32_t) * (size_t)L);
+    if (slots) memcpy(slots->host_slot_ptr, rep->slot_ptr, sizeof(int32_t) * ((size_t)L * n_sig * n_sig + 1));
+    return JITDB_OK;
+}
+
 // The analysis, plain (sig == nullptr: one slot per level) or filed by (depth, signature).
 int schedule_impl(const int32_t *parent, const int32_t *sig, jitdb_slots_t *slots, jitdb_schedule_t *s,
                   void *workspace, size_t workspace_bytes, void *hip_stream) {
@@ -637,6 +680,7 @@ int schedule_impl(const int32_t *parent, const int32_t *sig, jitdb_slots_t *slot
     if (!s->host_level_ptr) return JITDB_E_NULL;
     s->n_levels = 0;
     s->n_edges = 0;
+    s->tree_window = 0;
     if (n64 == 0) {
         s->host_level_ptr[0] = 0;
         if (s->host_level_kids) s->host_level_kids[0] = 0;
@@ -660,10 +704,15 @@ int schedule_impl(const int32_t *parent, const int32_t *sig, jitdb_slots_t *slot
     if (slots && (!sig || !slots->key || !slots->slot_ptr)) return JITDB_E_NULL;
     if ((reinterpret_cast<uintptr_t>(workspace) & 255) != 0) return JITDB_E_BADARG;
     ScheduleWs w = carve_schedule_ws(n64, workspace, n_keys);
-    if (workspace_bytes < w.bytes) return JITDB_E_WORKSPACE;
+    if (workspace_bytes < schedule_ws_bytes(n64, n_keys)) return JITDB_E_WORKSPACE;
 
     hipStream_t st = (hipStream_t)hip_stream;
     const int32_t n = (int32_t)n64;
+    if (LocalReport *rep = report_pool().take()) {
+        const int code = schedule_local(parent, sig, slots, s, workspace, rep, st);
+        if (code != JITDB_E_HIP) report_pool().give(rep);      // (after a failed launch its kernels may still write it)
+        if (code != kTakeGeneralPath) return code;
+    }
     const unsigned grid = (unsigned)ceil_div(n64, kThreads);
     int rc;
 
@@ -783,7 +832,7 @@ extern "C" int jitdb_schedule(const int32_t *parent, jitdb_schedule_t *s,
 extern "C" size_t jitdb_schedule_typed_workspace_bytes(int64_t n_nodes, int32_t n_sig) {
     if (n_nodes < 0 || n_nodes > JITDB_MAX_NODES || n_sig < 1 || n_sig > JITDB_MAX_SIGNATURES) return 0;
     if (n_nodes * (int64_t)n_sig * n_sig >= (int64_t(1) << 31)) return 0;
-    return carve_schedule_ws(n_nodes, nullptr, (int64_t)n_sig * n_sig).bytes;
+    return schedule_ws_bytes(n_nodes, (int64_t)n_sig * n_sig);
 }
 
 extern "C" int jitdb_schedule_typed(const int32_t *parent, const int32_t *sig, jitdb_schedule_t *s,
@@ -835,7 +884,7 @@ extern "C" int jitdb_schedule_append(const jitdb_schedule_t *base, const int32_t
     // children per level add up like the level sizes; known only if both parts know theirs
     const bool kids_known = out->host_level_kids && (na == 0 || base->host_level_kids);
     fresh.host_level_kids = kids_known ? out->host_level_kids + na : nullptr;
-    fresh.n_levels = 0; fresh.n_edges = 0;
+    fresh.n_levels = 0; fresh.n_edges = 0; fresh.tree_window = 0;
     if (n_new > 0) {
         const int rc = jitdb_schedule(parent_new, &fresh, w.sched_ws, w.sched_ws_bytes, hip_stream);
         if (rc != JITDB_OK) return rc;
@@ -855,6 +904,8 @@ extern "C" int jitdb_schedule_append(const jitdb_schedule_t *base, const int32_t
     }
     out->n_levels = l_out;
     out->n_edges = ea + en;
+    const int32_t wa = na > 0 ? base->tree_window : fresh.tree_window, wn = n_new > 0 ? fresh.tree_window : wa;
+    out->tree_window = wa > 0 && wn > 0 ? (wa > wn ? wa : wn) : 0;
     if (n_out == 0) return JITDB_OK;
 
     const int64_t span = (na > n_new ? na : n_new) + 1;

@@ -160,3 +160,54 @@ def test_largest_forest_the_interface_accepts():
     assert int(s.child_ptr[n]) == 3 * t
     e = v[:3 * t]
     assert torch.equal(s.child_idx[:3 * t], 4 * torch.div(e, 3, rounding_mode="floor") + e % 3 + 1)
+
+
+def _lay_out(trees, shuffle_seed=None):
+    """Trees one after another; with a seed, ids inside each tree in any order."""
+    rng = np.random.default_rng(shuffle_seed) if shuffle_seed is not None else None
+    parts, off = [], 0
+    for t in trees:
+        if rng is not None:
+            t = relabel(t, int(rng.integers(1 << 30)))[0]
+        parts.append(np.where(t < 0, -1, t + off))
+        off += t.shape[0]
+    return np.concatenate(parts).astype(np.int32)
+
+
+@pytest.mark.parametrize("n_sig", [0, 1, 3])
+@pytest.mark.parametrize("name", ["one-block", "window-edges", "word-order", "large-windows", "span-512", "span-513", "arity-256",
+                                  "arity-257", "levels-256", "levels-257", "one-long-edge"])
+def test_trees_filed_one_after_another(name, n_sig):
+    """The analysis in LDS at the edges of what it takes (ids an edge may span, children, levels, window boundaries inside
+    and between trees) and one step beyond, where the general path must give the same table."""
+    import paper_1904_07421_amd as J
+    rng = np.random.default_rng(len(name))
+    small = [make_forest(1)] * 3
+    trees = {
+        "one-block": lambda: [chain_forest(1000)] * 2 + [star_forest(200)] * 20 + small,
+        "window-edges": lambda: [chain_forest(16)] * 2048 + [np.full(1, -1, np.int32)] * 5 + [star_forest(33)] * 60,
+        "word-order": lambda: [perfect_kary_tree(3, 3)] * 700 + [chain_forest(7)] * 900,
+        "large-windows": lambda: [perfect_kary_tree(2, 4)] * 17000 + small,
+        "span-512": lambda: [star_forest(250)] * 8 + [chain_forest(64)] * 200 + [np.concatenate([[512], np.full(512, -1)]).astype(np.int32)],
+        "span-513": lambda: [star_forest(250)] * 8 + [chain_forest(64)] * 200 + [np.concatenate([[513], np.full(513, -1)]).astype(np.int32)],
+        "arity-256": lambda: [star_forest(257)] * 40,
+        "arity-257": lambda: [star_forest(258)] * 40,
+        "levels-256": lambda: [chain_forest(256)] * 40,
+        "levels-257": lambda: [chain_forest(257)] * 40,
+        "one-long-edge": lambda: [chain_forest(9)] * 2000,
+    }[name]()
+    p = _lay_out(trees, 5 if name == "word-order" else None)
+    if name == "one-long-edge":
+        p[9 * 1000] = 3                          # the root of a late tree hangs under a node of the first
+    print(f"schedule filed trees {name} n_sig={n_sig} N={p.shape[0]}", flush=True)
+    if n_sig == 0:
+        s = J.jitdb_schedule(dev_parent(p))
+        assert_schedule_equal(s.to_numpy(), S.schedule_fast(p))
+        general = name in ("span-513", "arity-257", "levels-257", "one-long-edge")
+        assert (s.struct.tree_window == 0) == general
+    else:
+        sig = rng.integers(0, n_sig, size=p.shape[0]).astype(np.int32)
+        got = J.jitdb_schedule_typed(dev_parent(p), dev_parent(sig), n_sig).to_numpy()
+        want = S.schedule_typed_fast(p, sig, n_sig)
+        for k in ("height", "level_ptr", "perm", "inv_perm", "child_ptr", "child_idx", "key", "slot_ptr"):
+            assert np.array_equal(got[k], want[k]), k
