@@ -504,6 +504,14 @@ def main():
     if prof is not None:
         proj_rows = (prof["proj"]["rows"] + prof["thin_proj"]["rows"]) / args.steps   # includes roots, whose P nobody reads
         chain_rows = prof["chain"]["edges"] / args.steps     # edges projected inside the chain launches (one per row)
+        if prof["trees"]["launches"]:       # every level below the chain levels in one launch: all of the forward's work but theirs
+            ms, rows = prof["trees"]["ms"] / args.steps, prof["trees"]["rows"] / args.steps
+            fl = sum(flops_total.values()) - chain_rows * flops_row["chain"]
+            by = bytes_min - chain_rows * bytes_row["chain"]
+            kernels["trees"] = {"ms_per_step": ms, "launches_per_step": prof["trees"]["launches"] / args.steps, "rows_per_step": rows,
+                                "flops_per_step": fl, "tflops": fl / (ms * 1e-3) / 1e12, "frac_mfma_peak": fl / (ms * 1e-3) / 1e12 / peak_tflops,
+                                "bytes_per_step": by, "gbs": by / (ms * 1e-3) / 1e9, "frac_hbm_peak": by / (ms * 1e-3) / 1e9 / PEAK_HBM_GBS,
+                                "flop_per_byte": fl / by, "bound": "mfma" if fl / by >= ridge else "hbm"}
         for name in ("leaf", "internal", "proj", "thin_leaf", "thin_internal", "thin_proj", "chain"):
             job = name.replace("thin_", "")
             ms = prof[name]["ms"] / args.steps
@@ -537,11 +545,11 @@ def main():
                                 "xcopy_bytes_per_step": bytes_xcopy,
                                 "gbs_with_xcopy": (bytes_gather + bytes_xcopy) / (ms * 1e-3) / 1e9}
         kernels["pack"] = {"ms_per_step": prof["pack"]["ms"] / args.steps}
-        mfma_names = [n for n in ("leaf", "internal", "proj", "thin_leaf", "thin_internal", "thin_proj", "chain") if n in kernels]
+        mfma_names = [n for n in ("leaf", "internal", "proj", "thin_leaf", "thin_internal", "thin_proj", "chain", "trees") if n in kernels]
         dom = max(mfma_names, key=lambda k: kernels[k]["ms_per_step"])
         k = kernels[dom]
         kname = (f"thin_kernel<{cfg.dtype},{dom[5:]}>" if dom.startswith("thin_") else
-                 f"chain_kernel<{cfg.dtype}>" if dom == "chain" else f"level_kernel<{cfg.dtype},{dom}>")
+                 f"chain_kernel<{cfg.dtype}>" if dom == "chain" else f"trees_kernel<{cfg.dtype}>" if dom == "trees" else f"level_kernel<{cfg.dtype},{dom}>")
         # the dominant kernel against the roof that binds a kernel of its own intensity; the other
         # roof's fraction is given beside it
         launches = max(k["launches_per_step"], 1)

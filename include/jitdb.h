@@ -456,7 +456,8 @@ typedef enum {
     JITDB_K_THIN_PROJ = 7,      /* includes the next slot's stack step when the two share a launch */
     JITDB_K_CHAIN = 8,          /* a level whose nodes all have one child: gather, all four gates and the cell
                                    update in one launch (no stack step, no projection) */
-    JITDB_K_CLASSES = 9
+    JITDB_K_TREES = 9,          /* a forest of small trees: every level below the chain levels in one launch */
+    JITDB_K_CLASSES = 10
 } jitdb_kernel_class;
 
 typedef struct {

@@ -60,7 +60,8 @@ class _SlotsStruct(ctypes.Structure):
     ]
 
 
-K_CLASSES = ("pack", "stack", "leaf", "internal", "proj", "thin_leaf", "thin_internal", "thin_proj", "chain")
+K_CLASSES = ("pack", "stack", "leaf", "internal", "proj", "thin_leaf", "thin_internal", "thin_proj", "chain",
+             "trees")
 
 
 class _CellStruct(ctypes.Structure):
@@ -69,8 +70,8 @@ class _CellStruct(ctypes.Structure):
 
 
 class _ProfileStruct(ctypes.Structure):
-    _fields_ = [("ms", ctypes.c_double * 9), ("launches", ctypes.c_int64 * 9),
-                ("rows", ctypes.c_int64 * 9), ("edges", ctypes.c_int64 * 9), ("dropped", ctypes.c_int64)]
+    _fields_ = [("ms", ctypes.c_double * len(K_CLASSES)), ("launches", ctypes.c_int64 * len(K_CLASSES)),
+                ("rows", ctypes.c_int64 * len(K_CLASSES)), ("edges", ctypes.c_int64 * len(K_CLASSES)), ("dropped", ctypes.c_int64)]
 
 
 _lib = None

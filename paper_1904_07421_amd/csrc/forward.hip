@@ -21,6 +21,7 @@
 //   chain_kernel       a thin level whose nodes all have exactly one child (sequences, the long
 //                      tail of a deep forest) as ONE launch: x and the child's h read in place,
 //                      all four gates over the full K, no stack step and no projection
+//   trees_kernel       (trees.hip) a forest of small trees filed one after another: all of the above in one launch
 //   tile256_kernel     (level256.hip) the level kernel on 256 x 256 tiles, bf16; switched off
 //
 // With cells of different type in the table (jitdb_treelstm_forward_cells) a slot of N-ary cells
@@ -197,16 +198,16 @@ __device__ __forceinline__ void row_record_body(const int32_t *__restrict__ perm
     }
 }
 
-// Once per forward, in one launch: the row records of every level position (blocks
+// Once per forward, in one launch: the row records of every level position from window first_window on (blocks
 // [0, n_windows)) and the first cell's packed weights (the remaining blocks); neither needs
 // the other.
 template <typename T>
 __global__ void __launch_bounds__(kThreads)
 prepare_kernel(const int32_t *__restrict__ perm, const int32_t *__restrict__ key,
                const int32_t *__restrict__ child_ptr, const int32_t *__restrict__ child_idx,
-               int4 *__restrict__ row_rec, int n, int n_windows, const PackArgs p) {
+               int4 *__restrict__ row_rec, int n, int first_window, int n_windows, const PackArgs p) {
     if ((int)blockIdx.x < n_windows)
-        row_record_body<kThreads>(perm, key, child_ptr, child_idx, row_rec, n, blockIdx.x);
+        row_record_body<kThreads>(perm, key, child_ptr, child_idx, row_rec, n, first_window + (int)blockIdx.x);
     else
         pack_weights_body<T>(static_cast<const T *>(p.W), static_cast<const T *>(p.U), p.b, p.D, p.H, p.Dp, p.Hp,
                              p.NP, p.NPU, static_cast<T *>(p.Bp), p.bp, static_cast<T *>(p.Bf),
@@ -1197,7 +1198,10 @@ __device__ __forceinline__ void chain_piece_ok(bool kid_ok, int kb, int x_bytes,
     ok1 = (ESZ == 2 && in_x) ? (k0 + 4 < D) : ok0;       // bf16: the second four elements of the piece
 }
 
-template <typename T, int KS>
+//
+// HAS_Z: the x part of the pre-activations (and the bias) is in Z already (tree_x_kernel has been over all nodes): A is the
+// child's h alone and K is H.
+template <typename T, int KS, bool HAS_Z = false>
 __global__ void __launch_bounds__(kThinWaves * 64 * KS, KS == 1 ? 2 : 1)
 chain_kernel(const LevelArgs a) {
     constexpr int ESZ = (int)sizeof(T);
@@ -1220,7 +1224,7 @@ chain_kernel(const LevelArgs a) {
     //      group.  Every load of the ring is unconditional (a group index past the end is clamped to the
     //      last group, whose data is then not used): the number of loads between a request and its use is
     //      the same on every path, so the waits the compiler places are counted, not "all".
-    const int x_bytes = a.Dp * ESZ;                      // K bytes of the x part
+    const int x_bytes = HAS_Z ? 0 : a.Dp * ESZ;          // K bytes of the x part
     const int k_bytes = x_bytes + a.Hp * ESZ;
     const int pitch = chain_row_pitch(k_bytes);
     const int n_all = k_bytes / 32;                      // K groups of a row (a multiple of four)
@@ -1230,7 +1234,7 @@ chain_kernel(const LevelArgs a) {
     const int n_groups = n_all - g_begin < per_part ? n_all - g_begin : per_part;
     const int last_group = n_groups > 0 ? g_begin + n_groups - 1 : n_all - 1;   // (a part without groups loads the row's last one, unused)
     const int64_t brow = (int64_t)col * kGateTile + gate * kUnit + l32;
-    const char *bp = static_cast<const char *>(a.Bp) + operand_offset(brow, 0, a.NPU) + hf * 16;
+    const char *bp = static_cast<const char *>(a.Bp) + operand_offset(brow, HAS_Z ? (int64_t)a.Dp * ESZ : 0, a.NPU) + hf * 16;
     const int64_t b_pair = (int64_t)a.NPU * 64;
     u32x4 fb[kChainAhead];
     auto request = [&](int g, int slot) __attribute__((always_inline)) {
@@ -1341,7 +1345,9 @@ chain_kernel(const LevelArgs a) {
     const int unit_ld = unit0 < a.Hq ? unit0 : 0;        // unit groups past the padded width read the first group (and store nothing)
     float4 ck = make_float4(0.f, 0.f, 0.f, 0.f);
     if (kid >= 0) ck = *reinterpret_cast<const float4 *>(a.cs + (int64_t)kid * a.Hq + unit_ld);
-    const float *bias = a.bp + col * kGateTile + u4;
+    // what is added to the products: the packed bias, or Z with the bias in it (unit groups past its width read the first)
+    const float *bias = HAS_Z ? a.Z + (int64_t)node * 4 * a.Hz + (unit0 < a.Hz ? unit0 : 0) : a.bp + col * kGateTile + u4;
+    const int bias_gate = HAS_Z ? a.Hz : kUnit;
     float z[4][4];
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
@@ -1351,7 +1357,7 @@ chain_kernel(const LevelArgs a) {
             const float4 qp = *reinterpret_cast<const float4 *>(&zt[4 * p + g][tr * kEpiStride + u4]);
             q.x += qp.x; q.y += qp.y; q.z += qp.z; q.w += qp.w;
         }
-        const float4 bq = *reinterpret_cast<const float4 *>(bias + g * kUnit);
+        const float4 bq = *reinterpret_cast<const float4 *>(bias + g * bias_gate);
         z[g][0] = q.x + bq.x; z[g][1] = q.y + bq.y; z[g][2] = q.z + bq.z; z[g][3] = q.w + bq.w;
     }
     const float ckv[4] = {ck.x, ck.y, ck.z, ck.w};
@@ -1440,11 +1446,18 @@ struct ScopedLaunchTimer {
     }
 };
 
+// Forests of up to this many nodes, filed tree after tree, run in one launch (trees.hip) up to kTreesMaxLevels levels.
+constexpr int64_t kTreesMaxNodes = 262144;
+constexpr int kTreesMaxLevels = 32;
+constexpr int kTreesMaxSpan = 256;         // ... of trees of up to this many ids: one block runs a tree alone
+
 struct ForwardWs {
     void *Bp;
     float *bp;
     void *Bf;     // fragment-major copy of the packed weights (bf16 with one cell), else nullptr
     void *stack;  // the current level's stacked input, (N + 256) rows of Dp + Hp
+    float *Z;     // trees.hip: x parts of the gates [N][4][H rounded up to 16], in the same memory; nullptr: no room
+    float *FC;    // trees.hip: every node's f c, [N, H rounded up to 16], in the memory of P
     int4 *row_rec; // row records of all level positions, two int4 each
     void *hs;     // nullptr when h_out can serve (H == Hp)
     void *P;
@@ -1488,7 +1501,7 @@ size_t packed_w_bytes(const Dims &d) { return (size_t)d.NPU * (d.Dp + d.Hp) * d.
 bool has_fragment_copy(const Dims &d, int n_sig) { return d.esz == 2 && n_sig == 1; }
 
 ForwardWs carve_forward_ws(int64_t n, int64_t e, const Dims &d, void *base, int n_sig = 1,
-                           const jitdb_cell_t *cells = nullptr) {
+                           const jitdb_cell_t *cells = nullptr, bool with_z = true) {
     Carver c(base);
     ForwardWs w = {};
     (void)e;
@@ -1496,10 +1509,20 @@ ForwardWs carve_forward_ws(int64_t n, int64_t e, const Dims &d, void *base, int 
     w.bp = c.take<float>((size_t)d.NP * n_sig);
     w.Bf = has_fragment_copy(d, n_sig) ? c.take<char>(packed_w_bytes(d)) : nullptr;
     // one level at a time; whole row tiles are read, hence the 256 spare rows
-    w.stack = c.take<char>((size_t)(n + kRowPad) * (d.Dp + d.Hp) * d.esz);
+    size_t stack_bytes = (size_t)(n + kRowPad) * (d.Dp + d.Hp) * d.esz;
+    // the same sizes for tables of more than one signature: what they ask for grows with n_sig from there
+    with_z = with_z && n <= kTreesMaxNodes && d.H <= kTreesMaxWidth;
+    const size_t z_bytes = (size_t)n * 4 * round_up(d.H, 16) * 4;
+    if (with_z && z_bytes > stack_bytes) stack_bytes = z_bytes;
+    w.stack = c.take<char>(stack_bytes);
+    w.Z = with_z && n_sig == 1 ? static_cast<float *>(w.stack) : nullptr;
     w.row_rec = c.take<int4>((size_t)2 * (n + kRowPad));   // every level position
     w.hs = (d.H == d.Hp) ? nullptr : c.take<char>((size_t)n * d.Hp * d.esz);
-    w.P = c.take<char>((size_t)n * d.Hq * d.esz);
+    size_t p_bytes = (size_t)n * d.Hq * d.esz;
+    const size_t fc_bytes = (size_t)n * round_up(d.H, 16) * 4;
+    if (with_z && fc_bytes > p_bytes) p_bytes = fc_bytes;
+    w.P = c.take<char>(p_bytes);
+    w.FC = with_z && n_sig == 1 ? static_cast<float *>(w.P) : nullptr;
     w.cs = (d.H == d.Hq) ? nullptr : c.take<float>((size_t)n * d.Hq);
     w.tiles_each = n / kDmaBM + (int64_t)n_sig * n_sig + 1;
     w.tiles = n_sig > 1 ? c.take<int4>((size_t)(2 * w.tiles_each)) : nullptr;
@@ -1536,7 +1559,7 @@ template <typename T, bool SAVE>
 int run_forward(const void *x, const void *W, const void *U, const float *b, const Dims &d,
                 const jitdb_schedule_t *s, const jitdb_slots_t *slots, const jitdb_cell_t *cells,
                 void *h_out, float *c_out, void *gates, void *fgate,
-                const ForwardWs &w_in, const void *packed, hipStream_t st) {
+                const ForwardWs &w_in, const void *packed, bool chains, hipStream_t st) {
     // weights packed by an earlier jitdb_treelstm_pack are used where they lie
     ForwardWs w = w_in;
     const int n_sig_w = slots ? slots->n_sig : 1;
@@ -1553,6 +1576,46 @@ int run_forward(const void *x, const void *W, const void *U, const float *b, con
     auto is_nary = [&](int t) { return cells != nullptr && t >= 0 && cells[t].kind == JITDB_CELL_NARY; };
     bool any_nary = false;
     for (int t = 0; t < n_sig; ++t) any_nary = any_nary || is_nary(t);
+
+    // Levels from chain_from on are thin and hold only nodes with exactly one child (the schedule says
+    // how many children each level has): one launch each, no stack step, no projection.  A child
+    // below chain_from whose parent is such a node needs no projection either, so the level right
+    // below skips it too.
+    int chain_from = L;
+    const int chain_k_bytes = (d.Dp + d.Hp) * d.esz;
+    const size_t chain_lds = chain_lds_bytes(chain_k_bytes);      // the tile's A rows live in LDS
+    // waves per gate: fp32 (long MFMA chains) two if the LDS beside the A tile allows, bf16 one.  (Four measured
+    // slower than two: blocks of 1024 threads start later than they finish earlier.)
+    const int chain_ks = (sizeof(T) == 4 && chain_lds <= (size_t)chain_lds_max(2)) ? 2 : 1;
+    if (!SAVE && !slots && chains && s->host_level_kids && (d.D & 3) == 0 && chain_lds <= (size_t)chain_lds_max(chain_ks)) {
+        for (int l = L - 1; l >= 1; --l) {
+            const int rows = sp[l + 1] - sp[l];
+            if (rows > kThinMaxRows || s->host_level_kids[l] != rows) break;
+            chain_from = l;
+        }
+    }
+    if (chain_from < L) {    // more dynamic LDS than a launch may ask for by default
+        for (bool z : {false, true}) {
+            const void *fn = chain_ks == 2 ? (z ? reinterpret_cast<const void *>(&chain_kernel<T, 2, true>)
+                                                : reinterpret_cast<const void *>(&chain_kernel<T, 2>))
+                                           : (z ? reinterpret_cast<const void *>(&chain_kernel<T, 1, true>)
+                                                : reinterpret_cast<const void *>(&chain_kernel<T, 1>));
+            JITDB_HIP_CHECK(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, chain_lds_max(chain_ks)));
+        }
+    }
+    const size_t chain_z_lds = chain_lds_bytes(d.Hp * (int)d.esz);    // ... their h part alone
+    // A forest of small trees filed one after another: its levels below the chain levels in one launch
+    TreesArgs ta = {};
+    bool trees = false;
+    if (!slots && !any_nary && w.Z && s->tree_window > 0 && s->tree_window <= kTreesMaxSpan && s->inv_perm && chain_from <= kTreesMaxLevels && s->n_nodes <= kTreesMaxNodes) {
+        ta.x = x; ta.Bp = w.Bp; ta.bp = w.bp;
+        ta.height = s->height; ta.perm = s->perm; ta.inv_perm = s->inv_perm; ta.child_ptr = s->child_ptr; ta.child_idx = s->child_idx;
+        ta.h_out = h_out; ta.hs = w.hs ? w.hs : h_out; ta.FC = w.FC; ta.gates = gates; ta.fgate = fgate;
+        ta.c_out = c_out; ta.cs = chain_from < L ? w.cs : nullptr; ta.Z = w.Z;
+        ta.n = (int)s->n_nodes; ta.n_leaves = sp[1]; ta.tree_window = s->tree_window; ta.l_end = chain_from;
+        ta.D = d.D; ta.H = d.H; ta.Hp = d.Hp; ta.Hq = d.Hq; ta.NPU = d.NPU; ta.sx_packed = (int)(d.Dp * d.esz / 64);
+        trees = plan_trees(ta, d.esz);
+    }
 
     {   // row records and packed weights (one launch; further cells' weights one launch each)
         const int64_t total = (int64_t)d.NPU * (d.Dp + d.Hp);
@@ -1573,9 +1636,19 @@ int run_forward(const void *x, const void *W, const void *U, const float *b, con
             return p;
         };
         const bool large = s->n_nodes >= kRecLargeMinNodes;
-        {
+        const bool pack_here = !(packed || is_nary(0));
+        if (trees) {     // records of the chain levels only
+            const int first = chain_from < L ? sp[chain_from] / kRecWindow : 0;
+            const int n_windows = chain_from < L ? (int)ceil_div(s->n_nodes, kRecWindow) - first : 0;
+            const unsigned grid = (unsigned)n_windows + (pack_here ? pack_grid : 0u);
+            if (grid > 0) {
+                ScopedLaunchTimer tm(JITDB_K_PACK, 0, st);
+                prepare_kernel<T><<<grid, kThreads, 0, st>>>(s->perm, s->height, s->child_ptr, s->child_idx, w.row_rec, (int)s->n_nodes,
+                                                             first, n_windows, pack_args(0));
+                JITDB_LAUNCH_CHECK();
+            }
+        } else {
             ScopedLaunchTimer tm(JITDB_K_PACK, 0, st);
-            const bool pack_here = !(packed || is_nary(0));
             if (large) {
                 const int n_windows = (int)ceil_div(s->n_nodes, kRecWindowLarge);
                 const unsigned pg = pack_here ? (unsigned)(ceil_div(total, kRecThreadsLarge) < 1024 ? ceil_div(total, kRecThreadsLarge) : 1024) : 0u;
@@ -1586,7 +1659,7 @@ int run_forward(const void *x, const void *W, const void *U, const float *b, con
                 const int n_windows = (int)ceil_div(s->n_nodes, kRecWindow);
                 prepare_kernel<T><<<(unsigned)n_windows + (pack_here ? pack_grid : 0u), kThreads, 0, st>>>(
                     s->perm, slots ? slots->key : s->height, s->child_ptr, s->child_idx, w.row_rec, (int)s->n_nodes,
-                    n_windows, pack_args(0));
+                    0, n_windows, pack_args(0));
             }
             JITDB_LAUNCH_CHECK();
         }
@@ -1623,6 +1696,8 @@ int run_forward(const void *x, const void *W, const void *U, const float *b, con
     a.hs_out = w.hs ? w.hs : h_out;
     a.gates = gates;
     a.fgate = fgate;
+    a.Z = w.Z;
+    a.Hz = (int)round_up(d.H, 16);
     a.D = d.D; a.Dp = d.Dp; a.H = d.H; a.Hp = d.Hp; a.Hu = d.Hu;
     a.NPU = d.NPU;
 
@@ -1671,33 +1746,17 @@ int run_forward(const void *x, const void *W, const void *U, const float *b, con
         return (unsigned)ceil_div((int64_t)g.rows * (Kp / Traits<T>::VEC), kThreads);
     };
     bool stacked_ahead = false;     // the slot's stack step already ran with the projection before it
-    // Levels from chain_from on are thin and hold only nodes with exactly one child (the schedule says
-    // how many children each level has): one launch each, no stack step, no projection.  A child
-    // below chain_from whose parent is such a node needs no projection either, so the level right
-    // below skips it too.
-    int chain_from = L;
-    const int chain_k_bytes = (d.Dp + d.Hp) * d.esz;
-    const size_t chain_lds = chain_lds_bytes(chain_k_bytes);      // the tile's A rows live in LDS
-    // waves per gate: fp32 (long MFMA chains) two if the LDS beside the A tile allows, bf16 one.  (Four measured
-    // slower than two: blocks of 1024 threads start later than they finish earlier.)
-    const int chain_ks = (sizeof(T) == 4 && chain_lds <= (size_t)chain_lds_max(2)) ? 2 : 1;
-    if (!SAVE && !slots && s->host_level_kids && (d.D & 3) == 0 && chain_lds <= (size_t)chain_lds_max(chain_ks)) {
-        for (int l = L - 1; l >= 1; --l) {
-            const int rows = sp[l + 1] - sp[l];
-            if (rows > kThinMaxRows || s->host_level_kids[l] != rows) break;
-            chain_from = l;
-        }
-    }
-    if (chain_from < L) {    // more dynamic LDS than a launch may ask for by default
-        const void *fn = chain_ks == 2 ? reinterpret_cast<const void *>(&chain_kernel<T, 2>)
-                                       : reinterpret_cast<const void *>(&chain_kernel<T, 1>);
-        JITDB_HIP_CHECK(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, chain_lds_max(chain_ks)));
-    }
     const int n_unit_tiles = d.Hu / kUnit;
     a.w_bytes = (int64_t)packed_w_bytes(d);
     a.NP = d.NP;
 
+    if (trees) {
+        ScopedLaunchTimer tm(JITDB_K_TREES, chain_from < L ? sp[chain_from] : s->n_nodes, st);
+        const int rc = launch_trees(dtype, SAVE, ta, st);
+        if (rc != JITDB_OK) return rc;
+    }
     for (size_t i = 0; i < segs.size(); ++i) {
+        if (trees && segs[i].l < chain_from) continue;
         const int l = segs[i].l, sig = segs[i].sig, n_rows = segs[i].rows;
         const bool grouped = sig < 0;
         a.Bp = static_cast<char *>(w.Bp) + packed_w_bytes(d) * (grouped ? 0 : sig);
@@ -1720,8 +1779,14 @@ int run_forward(const void *x, const void *W, const void *U, const float *b, con
             a.n_tiles = (int)ceil_div(n_rows, 32) * a.n_col_tiles;
             a.n_blocks = a.n_tiles;
             ScopedLaunchTimer tm(JITDB_K_CHAIN, n_rows, st, s->host_level_kids[l]);
-            if (chain_ks == 2) chain_kernel<T, 2><<<a.n_blocks, kThinWaves * 64 * 2, chain_lds, st>>>(a);
-            else chain_kernel<T, 1><<<a.n_blocks, kThinWaves * 64, chain_lds, st>>>(a);
+            if (trees) {
+                if (chain_ks == 2) chain_kernel<T, 2, true><<<a.n_blocks, kThinWaves * 64 * 2, chain_z_lds, st>>>(a);
+                else chain_kernel<T, 1, true><<<a.n_blocks, kThinWaves * 64, chain_z_lds, st>>>(a);
+            } else if (chain_ks == 2) {
+                chain_kernel<T, 2><<<a.n_blocks, kThinWaves * 64 * 2, chain_lds, st>>>(a);
+            } else {
+                chain_kernel<T, 1><<<a.n_blocks, kThinWaves * 64, chain_lds, st>>>(a);
+            }
             JITDB_LAUNCH_CHECK();
             continue;
         }
@@ -1990,7 +2055,7 @@ int forward_entry(const void *x, const void *W, const void *U, const float *b, i
                   jitdb_dtype dtype, const jitdb_schedule_t *s, const jitdb_slots_t *slots,
                   void *h_out, float *c_out, void *gates, void *fgate, bool save,
                   void *workspace, size_t workspace_bytes, void *hip_stream, const void *packed = nullptr,
-                  const jitdb_cell_t *cells = nullptr) {
+                  const jitdb_cell_t *cells = nullptr, bool fixed_scratch = false) {
     if (!s) return JITDB_E_NULL;
     const int n_sig = slots ? slots->n_sig : 1;
     if (n_sig < 1 || n_sig > JITDB_MAX_SIGNATURES) return JITDB_E_BADARG;
@@ -2029,17 +2094,22 @@ int forward_entry(const void *x, const void *W, const void *U, const float *b, i
     }
 
     const Dims d = make_dims(D, H, dtype);
-    const ForwardWs w = carve_forward_ws(n, s->n_edges, d, workspace, n_sig, cells);
+    ForwardWs w = carve_forward_ws(n, s->n_edges, d, workspace, n_sig, cells);
+    if (fixed_scratch && workspace_bytes < w.bytes)     // the fixed array: without the room for the one-launch form
+        w = carve_forward_ws(n, s->n_edges, d, workspace, n_sig, cells, false);
     if (workspace_bytes < w.bytes) return JITDB_E_WORKSPACE;
+    // a table with one child-sum cell is the plain forward (but keeps the general launches for chain levels)
+    const bool chains = slots == nullptr;
+    if (n_sig == 1 && !cells) slots = nullptr;
     hipStream_t st = (hipStream_t)hip_stream;
     // run_forward keeps its list of launches in a std::vector: an allocation failure becomes a status
     JITDB_ABI_TRY
     if (dtype == JITDB_F32) {
-        if (save) return run_forward<float, true>(x, W, U, b, d, s, slots, cells, h_out, c_out, gates, fgate, w, packed, st);
-        return run_forward<float, false>(x, W, U, b, d, s, slots, cells, h_out, c_out, nullptr, nullptr, w, packed, st);
+        if (save) return run_forward<float, true>(x, W, U, b, d, s, slots, cells, h_out, c_out, gates, fgate, w, packed, chains, st);
+        return run_forward<float, false>(x, W, U, b, d, s, slots, cells, h_out, c_out, nullptr, nullptr, w, packed, chains, st);
     }
-    if (save) return run_forward<bf16_t, true>(x, W, U, b, d, s, slots, cells, h_out, c_out, gates, fgate, w, packed, st);
-    return run_forward<bf16_t, false>(x, W, U, b, d, s, slots, cells, h_out, c_out, nullptr, nullptr, w, packed, st);
+    if (save) return run_forward<bf16_t, true>(x, W, U, b, d, s, slots, cells, h_out, c_out, gates, fgate, w, packed, chains, st);
+    return run_forward<bf16_t, false>(x, W, U, b, d, s, slots, cells, h_out, c_out, nullptr, nullptr, w, packed, chains, st);
     JITDB_ABI_CATCH
 }
 
@@ -2195,7 +2265,7 @@ extern "C" int jitdb_treelstm_forward_static(const void *x, const void *W, const
     if (!s) return JITDB_E_NULL;
     if (!dims_ok(s->n_nodes, s->n_edges, D, H, (int)dtype)) return JITDB_E_BADARG;
     if (s->n_nodes == 0) return JITDB_OK;
-    const size_t need = carve_forward_ws(s->n_nodes, s->n_edges, make_dims(D, H, dtype), nullptr).bytes;
+    const size_t need = carve_forward_ws(s->n_nodes, s->n_edges, make_dims(D, H, dtype), nullptr, 1, nullptr, false).bytes;
     if (need > (size_t)JITDB_STATIC_SCRATCH_BYTES) return JITDB_E_WORKSPACE;
     drop_stale_hip_error();
     void *ws = nullptr;
@@ -2206,5 +2276,5 @@ extern "C" int jitdb_treelstm_forward_static(const void *x, const void *W, const
     // Nothing in the workspace has to start at zero: every region is written in full by this call
     // before anything reads it (packed weights, row records, the stacked level, P, padded copies).
     return forward_entry(x, W, U, b, D, H, dtype, s, nullptr, h_out, c_out, nullptr, nullptr, false,
-                         ws, (size_t)JITDB_STATIC_SCRATCH_BYTES, hip_stream);
+                         ws, (size_t)JITDB_STATIC_SCRATCH_BYTES, hip_stream, nullptr, nullptr, true);
 }

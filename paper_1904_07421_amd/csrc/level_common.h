@@ -94,7 +94,8 @@ struct LevelArgs {
     // training only: activations the backward pass needs
     void *gates;          // [N, 3H] of T: i | o | u after their non-linearities, rows by node id
     void *fgate;          // [N, H] of T: row k = forget gate the parent of k applied to k
-    int D, Dp, H, Hp, Hu, Hq;
+    const float *Z;       // [N][4][Hz] x parts of the gates' pre-activations (chain levels behind tree_x_kernel)
+    int D, Dp, H, Hp, Hu, Hq, Hz;
     int n_rows;
     int n_rows_alloc;     // rows per slab of the stacked input (n_rows rounded up to whole tiles)
     int NPU;              // rows per slab of the packed weights
@@ -502,6 +503,25 @@ size_t nary_packed_bytes(int D, int H, int Dp, int Hp, int N, size_t esz);
 int nary_pack(jitdb_dtype dtype, const void *W, const void *U, int D, int H, int Dp, int Hp, int N, void *Bn,
               int *err_to_clear, hipStream_t st);
 int run_nary_slot(jitdb_dtype dtype, const LevelArgs &a, const NarySlot &s, hipStream_t st);
+
+// trees.hip: a forest of small trees in two launches
+constexpr int kTreeMaxLevels = 64;         // levels a block tells apart
+constexpr int kTreesMaxWidth = 256;        // widest H of the one-launch form (plan_trees says why)
+constexpr int kTreeCus = 256;              // compute units of the chip
+struct TreesArgs {
+    const void *x, *Bp;
+    const float *bp;
+    const int32_t *height, *perm, *inv_perm, *child_ptr, *child_idx;
+    void *h_out, *hs, *gates, *fgate;      // hs == h_out where rows need no padding; gates, fgate: training only
+    float *c_out, *cs, *Z, *FC;            // cs: padded copy of c, or nullptr where nothing after this reads one
+    int n, n_leaves, tree_window, l_end;   // levels [0, l_end) run here
+    int D, H, Hp, Hq, NPU, sx_packed;      // sx_packed: slab of the packed weights at which the h part begins
+    // by plan_trees
+    int sx, sh, Hz, n_ut, pitch_h, group_rows, G, cap, n_waves, n_blocks, x_slabs, x_chunks;
+    size_t lds_bytes;
+};
+bool plan_trees(TreesArgs &a, size_t esz);
+int launch_trees(jitdb_dtype dtype, bool save, const TreesArgs &a, hipStream_t st);
 
 // level256.hip
 bool tile256_applies(int mode, const LevelArgs &a);

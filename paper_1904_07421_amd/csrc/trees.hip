@@ -1,0 +1,694 @@
+// The forward of a forest of small trees in TWO launches: every node's x part, then whole trees, all levels, in a block.
+//
+// Level by level, a forest of a few thousand nodes costs two launches per level and the latencies inside them
+// (gather, K loop, cell update, projection): 25 - 30 us a level whatever the level holds.  Two things do not depend on
+// the levels: W x + b is the same for every node whenever it is evaluated, and a block that owns whole trees needs
+// nothing from other blocks, so its levels may follow one another behind block barriers.
+//
+//   tree_x_kernel    Z = W x + b for all nodes, spread evenly over the chip; leaves finish their cells right there, the
+//                    other nodes leave Z [node][i | o | u | f] in fp32
+//   trees_kernel     block b takes the trees from the first cut at or after id b G to the first at or after (b + 1) G (a
+//                    cut is a place between ids that no edge crosses; jitdb_schedule_t::tree_window says that they are
+//                    close together).  Rows are the block's nodes in (height, id) order, in groups of 16 or 32:
+//                      gather    for a row of level l: sum of the children's h (operand, LDS) and of their f c (fp32, LDS)
+//                      (barrier) i, o, u = Z + U hs;  c = i u + sum f c,  h = o tanh c; h goes out and into LDS
+//                      (barrier) P = U_f h from LDS; f = sigmoid(Z_f of the PARENT + P), f c goes out for the parent
+//                    A child's forget gate needs nothing of its parent but Z_f, which is there already: no P row and no
+//                    c row is fetched by a parent, child sums are the only gather, in 16-byte pieces with four
+//                    children in flight.
+//                      (barrier, at the end of a level)
+//
+// A wave multiplies the gates of 16 hidden units (v_mfma_f32_16x16x32_bf16 / 16x16x4_f32), so the cell update finds a unit's
+// gates in one lane.  A comes from LDS, the weights from L2 in 1 KB pieces (64-byte slabs of 16 packed rows), kTreeAhead
+// slabs ahead.  What bounds it: the chain of three barriers and four memory latencies per level (bf16), the fp32
+// matrix rate on 16-row tiles (fp32).  Two blocks share a compute unit, so one's latencies hide behind the other.
+#include "level_common.h"
+
+namespace jitdb {
+namespace {
+
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+
+constexpr int kTreeMaxWaves = 16;          // at most 128 registers each: four waves per SIMD
+constexpr int kTreeRows = 32;              // most rows of a group (16 where LDS holds no more)
+// weight slabs in flight per wave: the fewer MFMAs a slab feeds, the more
+template <int NRT, int NG> constexpr int kTreeAhead = NRT * NG <= 1 ? 6 : NRT <= 1 ? 4 : NG == 1 ? 4 : 2;
+constexpr uint16_t kNoLocal = 0xFFFF;
+
+template <typename T>
+__device__ __forceinline__ void mfma16(const u32x4 &a, const u32x4 &b, floatx4 &acc) {
+    if constexpr (sizeof(T) == 2) {
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), acc, 0, 0, 0);
+    } else {
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a[j]), __uint_as_float(b[j]), acc, 0, 0, 0);
+    }
+}
+
+// The same weights times at most FOUR rows: 4 x 4 blocks, sixteen of them in one MFMA, block lane / 4 taking the columns and
+// the quarter of the slab's K that this lane's 16 bytes hold.  A quarter of the 16-row form's time for fp32, and each lane
+// ends up with one row of its column (quarter_sum).  a: row lane & 3, piece lane >> 4.
+typedef short short4v __attribute__((ext_vector_type(4)));
+template <typename T>
+__device__ __forceinline__ void mfma4(const u32x4 &a, const u32x4 &b, floatx4 &acc) {
+    if constexpr (sizeof(T) == 2) {
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const u32x2 aj = {a[2 * j], a[2 * j + 1]}, bj = {b[2 * j], b[2 * j + 1]};
+            acc = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(__builtin_bit_cast(short4v, aj), __builtin_bit_cast(short4v, bj), acc, 0, 0, 0);
+        }
+    } else {
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            acc = __builtin_amdgcn_mfma_f32_4x4x1f32(__uint_as_float(a[j]), __uint_as_float(b[j]), acc, 0, 0, 0);
+    }
+}
+
+// acc[v] of the four lanes of a column (n, n + 16, n + 32, n + 48) hold row v's sums over their quarters of K; lane n + 16 q
+// gets the total of row q.
+__device__ __forceinline__ float quarter_sum(const floatx4 &acc, int lane) {
+    const bool b1 = lane & 32, b0 = lane & 16;
+    float k0 = (b1 ? acc[2] : acc[0]) + __shfl_xor(b1 ? acc[0] : acc[2], 32, 64);
+    float k1 = (b1 ? acc[3] : acc[1]) + __shfl_xor(b1 ? acc[1] : acc[3], 32, 64);
+    return (b0 ? k1 : k0) + __shfl_xor(b0 ? k0 : k1, 16, 64);
+}
+
+// acc[rt][g] += A rows (16 rt ..; NRT == 0: at most four rows) x packed rows of gate g, over n_slabs slabs of 64 bytes of K.
+// a_lane: this lane's bytes of slab 0 (row lane & 15 or lane & 3, piece lane >> 4) in LDS or memory; b_lane likewise in the
+// packed weights, the gates 2048 bytes apart.  A_AHEAD: A comes from memory and is requested with the weights.
+template <typename T, int NRT, int NG, bool A_AHEAD = false, typename ALoad>
+__device__ __forceinline__ void tree_gemm(floatx4 (&acc)[NRT ? NRT : 1][NG], ALoad &&load_a, const char *b_lane, int64_t b_slab, int n_slabs) {
+    constexpr int AHEAD = kTreeAhead<NRT, NG>;
+    constexpr int NA = NRT ? NRT : 1;
+    u32x4 fb[AHEAD][NG], fr[A_AHEAD ? AHEAD : 1][NA];
+    auto request = [&](int s, int slot) __attribute__((always_inline)) {
+        if constexpr (A_AHEAD) {
+#pragma unroll
+            for (int rt = 0; rt < NA; ++rt) fr[slot][rt] = load_a(rt, s < n_slabs ? s : n_slabs - 1);
+        }
+        const char *p = b_lane + (int64_t)(s < n_slabs ? s : n_slabs - 1) * b_slab;
+#pragma unroll
+        for (int g = 0; g < NG; ++g) fb[slot][g] = *reinterpret_cast<const u32x4 *>(p + g * 2048);
+    };
+    auto multiply = [&](int s, int slot) __attribute__((always_inline)) {
+        u32x4 fa[NA];
+#pragma unroll
+        for (int rt = 0; rt < NA; ++rt) fa[rt] = A_AHEAD ? fr[A_AHEAD ? slot : 0][rt] : load_a(rt, s);
+#pragma unroll
+        for (int rt = 0; rt < NA; ++rt)
+#pragma unroll
+            for (int g = 0; g < NG; ++g) {
+                if constexpr (NRT == 0) mfma4<T>(fa[rt], fb[slot][g], acc[rt][g]);
+                else mfma16<T>(fa[rt], fb[slot][g], acc[rt][g]);
+            }
+    };
+#pragma unroll
+    for (int p = 0; p < AHEAD; ++p) request(p, p);
+    const int full = n_slabs / AHEAD;
+    for (int c = 0; c < full; ++c) {
+#pragma unroll
+        for (int p = 0; p < AHEAD; ++p) {
+            multiply(c * AHEAD + p, p);
+            request((c + 1) * AHEAD + p, p);
+        }
+    }
+#pragma unroll
+    for (int p = 0; p < AHEAD - 1; ++p)
+        if (full * AHEAD + p < n_slabs) multiply(full * AHEAD + p, p);
+}
+
+// 16 bytes of a row of x from element k0 on, zero past D (rows may start on any element boundary).
+template <typename T>
+__device__ __forceinline__ u32x4 load_x_piece(const T *row, int k0, int D) {
+    constexpr int VEC = Traits<T>::VEC;
+    u32x4 v = {0, 0, 0, 0};
+    if ((D & 3) == 0) {                      // whole or half pieces
+        if constexpr (sizeof(T) == 4) {
+            if (k0 < D) __builtin_memcpy(&v, row + k0, 16);
+        } else {
+            u32x2 lo = {0, 0}, hi = {0, 0};
+            if (k0 < D) __builtin_memcpy(&lo, row + k0, 8);
+            if (k0 + 4 < D) __builtin_memcpy(&hi, row + k0 + 4, 8);
+            v = u32x4{lo[0], lo[1], hi[0], hi[1]};
+        }
+    } else if (k0 + VEC <= D) {
+        __builtin_memcpy(&v, row + k0, 16);
+    } else if (k0 < D) {
+        T e[VEC];
+#pragma unroll
+        for (int j = 0; j < VEC; ++j) e[j] = k0 + j < D ? row[k0 + j] : T(0);
+        __builtin_memcpy(&v, e, 16);
+    }
+    return v;
+}
+
+template <typename T>
+__device__ __forceinline__ void add_h_piece(float (&s)[Traits<T>::VEC], const u32x4 &v) {
+    if constexpr (sizeof(T) == 4) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) s[j] += __uint_as_float(v[j]);
+    } else {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            s[2 * j] += __uint_as_float(v[j] << 16);
+            s[2 * j + 1] += __uint_as_float(v[j] & 0xFFFF0000u);
+        }
+    }
+}
+
+// The lane number, worked out anew: what is derived from it then belongs to one group of rows.  (Left to itself the
+// compiler computes every variant's offsets ahead of the level loop and keeps them in registers it does not have.)
+__device__ __forceinline__ int fresh_lane(int lane) {
+    asm volatile("" : "+v"(lane));
+    return lane;
+}
+
+__device__ __forceinline__ const char *tree_weights(const TreesArgs &a, int lane, int ut, int slab, int gate) {
+    const int row = (ut >> 1) * kGateTile + gate * kUnit + (ut & 1) * 16 + (lane & 15);
+    return static_cast<const char *>(a.Bp) + ((int64_t)slab * a.NPU + row) * 64 + (lane >> 4) * 16;
+}
+
+// h and c of one unit of one node, to every place that wants them.
+template <typename T>
+__device__ __forceinline__ void store_unit(const TreesArgs &a, int64_t node, int unit, float c, T hv) {
+    if (unit < a.H) {
+        a.c_out[node * a.H + unit] = c;
+        static_cast<T *>(a.h_out)[node * a.H + unit] = hv;
+        if (a.cs) a.cs[node * a.Hq + unit] = c;         // (only where chain levels follow)
+    }
+    if (a.hs != a.h_out) {
+        T *hs = static_cast<T *>(a.hs) + node * a.Hp;
+        hs[unit] = hv;
+        if (unit >= a.Hz - 16)                                // the pad columns past the last unit tile
+            for (int p = unit + 16; p < a.Hp; p += 16) hs[p] = T(0);
+    }
+}
+
+template <typename T>
+__device__ __forceinline__ void save_gates(const TreesArgs &a, int64_t node, int unit, float gi, float go, float gu) {
+    T *g = static_cast<T *>(a.gates) + node * 3 * a.H + unit;
+    g[0] = from_f32<T>(gi);
+    g[a.H] = from_f32<T>(go);
+    g[2 * a.H] = from_f32<T>(gu);
+}
+
+// ---- the x part ----------------------------------------------------------------------------
+// A wave keeps the weights of its 16 units' four gates in registers (NS slabs: 16 NS registers, which is what decides how
+// many waves share a SIMD: two up to ten slabs, one beyond) and multiplies one tile of 16 nodes after another; their x rows
+// come straight from memory in operand layout, the next tile's slab requested as soon as this one's is used.  No LDS, no
+// barrier: waves of a block take different units of the same nodes, which meet in L1.
+template <typename T, int NS> constexpr int kXWavesPerSimd = NS <= 10 ? 2 : 1;
+constexpr int kXSlabs[] = {4, 7, 10, 16, 20};      // its instances: D up to 640 in bf16, 320 in fp32
+constexpr int slabs_below(int ns) {                // the instance before: slabs up to there lie inside D whenever ns is chosen
+    int below = 0;
+    for (int k : kXSlabs)
+        if (k < ns) below = k;
+    return below;
+}
+
+template <typename T, bool SAVE, int NS>
+__global__ void __launch_bounds__(256, (kXWavesPerSimd<T, NS>))
+tree_x_kernel(const TreesArgs a) {
+    constexpr int VEC = Traits<T>::VEC;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int gw = blockIdx.x * 4 + wave;
+    const int ut = gw % a.n_ut, chunk = gw / a.n_ut;
+    if (chunk >= a.x_chunks) return;
+    const int hf = lane >> 4, n = lane & 15;
+    u32x4 fb[NS][4];
+    {
+        const char *w = tree_weights(a, lane, ut, 0, 0);
+#pragma unroll
+        for (int s = 0; s < NS; ++s)
+#pragma unroll
+            for (int g = 0; g < 4; ++g)
+                fb[s][g] = *reinterpret_cast<const u32x4 *>(w + (int64_t)(s < a.sx_packed ? s : 0) * a.NPU * 64 + g * 2048);
+    }
+    const T *x = static_cast<const T *>(a.x);
+    // tiles in the schedule's order: first the leaves', then the others', so that a tile's nodes all go the same way
+    const int leaf_tiles = (a.n_leaves + 15) >> 4, n_tiles = leaf_tiles + ((a.n - a.n_leaves + 15) >> 4);
+    auto node_of = [&](int tile, int i) __attribute__((always_inline)) {      // (past the end: the last one again)
+        const bool leaf = tile < leaf_tiles;
+        const int p = (leaf ? 0 : a.n_leaves - leaf_tiles * 16) + tile * 16 + i, last = (leaf ? a.n_leaves : a.n) - 1;
+        return (int64_t)a.perm[p < last ? p : last];
+    };
+    auto row_of = [&](int tile) __attribute__((always_inline)) { return x + node_of(tile, n) * a.D + hf * VEC; };
+    // slab s of a row: whole 16 bytes where all four pieces lie inside D; the slab that straddles D, and those past it,
+    // piece by piece (the weights read for slabs past the packed x part are not zero)
+    auto load_slab = [&](const T *row, int s) __attribute__((always_inline)) {
+        u32x4 v;
+        if (s < slabs_below(NS) || (s + 1) * 4 * VEC <= a.D) __builtin_memcpy(&v, row + s * 4 * VEC, 16);
+        else v = load_x_piece<T>(row - hf * VEC, (s * 4 + hf) * VEC, a.D);
+        return v;
+    };
+    // (ten slabs leave no registers for the last ones across the cell update: those come at the tile's start)
+    constexpr int PF = NS == 10 ? (SAVE || sizeof(T) == 2 ? 6 : 8) : NS;
+    u32x4 fa[NS];
+    const T *row = row_of(chunk);
+#pragma unroll
+    for (int s = 0; s < PF; ++s) fa[s] = load_slab(row, s);
+    for (int tile = chunk; tile < n_tiles; tile += a.x_chunks) {
+        int64_t node[4];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) node[v] = node_of(tile, hf * 4 + v);
+        const bool leaf = tile < leaf_tiles;
+        floatx4 acc[4];
+#pragma unroll
+        for (int g = 0; g < 4; ++g) acc[g] = floatx4{0, 0, 0, 0};
+#pragma unroll
+        for (int s = PF; s < NS; ++s) fa[s] = load_slab(row, s);
+        row = row_of(tile + a.x_chunks < n_tiles ? tile + a.x_chunks : tile);
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+#pragma unroll
+            for (int g = 0; g < 4; ++g) mfma16<T>(fa[s], fb[s][g], acc[g]);
+            if (s < PF) fa[s] = load_slab(row, s);
+        }
+        const int unit = ut * 16 + (fresh_lane(lane) & 15);       // (nothing derived from it stays in registers meanwhile)
+        const float *bias = a.bp + (ut >> 1) * kGateTile + (ut & 1) * 16 + (unit & 15);
+        const float bi = bias[0], bo = bias[kUnit], bu = bias[2 * kUnit], bf = bias[3 * kUnit];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            __builtin_amdgcn_sched_barrier(0);
+            const float zi = acc[0][v] + bi, zo = acc[1][v] + bo, zu = acc[2][v] + bu;
+            if (leaf) {
+                const float gi = sigmoid_t<T>(zi), go = sigmoid_t<T>(zo), gu = tanh_t<T>(zu);
+                const float c = gi * gu;
+                store_unit<T>(a, node[v], unit, c, unit < a.H ? from_f32<T>(go * tanh_t<T>(c)) : T(0));
+                if constexpr (SAVE) {
+                    if (unit < a.H) save_gates<T>(a, node[v], unit, gi, go, gu);
+                }
+            } else {
+                float *z = a.Z + node[v] * 4 * a.Hz + unit;
+                z[0] = zi; z[a.Hz] = zo; z[2 * a.Hz] = zu; z[3 * a.Hz] = acc[3][v] + bf;
+            }
+        }
+    }
+}
+
+// ---- the levels ------------------------------------------------------------------------------
+// The block's view of its trees.
+struct TreeBlock {
+    char *A, *Ht;                          // LDS: child sums and h of the group's rows, [group_rows][pitch_h]
+    float *Fs;                             // LDS: sums of the children's f c, [group_rows][Hz]
+    const uint16_t *order, *cstart, *kids, *par;   // local ids by row; child list starts, children, parents by local id
+    int lo, own;
+    int lane, wave, n_waves;
+};
+
+// Child sums of rows [r0, r_end) into A and Fs.  A wave takes 64 of a row's 16-byte pieces at a time, eight children in flight.
+template <typename T>
+__device__ __forceinline__ void gather_sums(const TreesArgs &a, const TreeBlock &b, int r0, int r_end) {
+    constexpr int VEC = Traits<T>::VEC;
+    const int ph = a.sh * 4, pf = a.Hz / 4;      // 16-byte pieces of an h row and of an f c row
+    const int per_row = (ph + pf + 63) >> 6, n_tasks = (r_end - r0) * per_row;
+    for (int q = b.wave; q < n_tasks; q += b.n_waves) {
+        const int rr = q / per_row, k = (q - rr * per_row) * 64 + fresh_lane(b.lane);
+        if (k >= ph + pf) continue;
+        const int i = __builtin_amdgcn_readfirstlane((int)b.order[r0 + rr]);
+        const int c0 = b.cstart[i], c1 = b.cstart[i + 1];
+        const bool is_h = k < ph;
+        if (is_h && k * VEC >= a.Hz) {           // the slab's pieces past the last unit tile
+            *reinterpret_cast<u32x4 *>(b.A + rr * a.pitch_h + k * 16) = u32x4{0, 0, 0, 0};
+            continue;
+        }
+        // an h row or an f c row: the same loads, summed as what they are
+        const char *col = is_h ? static_cast<const char *>(a.hs) + (int64_t)b.lo * a.Hp * (int)sizeof(T) + k * 16
+                               : reinterpret_cast<const char *>(a.FC) + (int64_t)b.lo * a.Hz * 4 + (k - ph) * 16;
+        const int pitch = is_h ? a.Hp * (int)sizeof(T) : a.Hz * 4;
+        float s[VEC];
+#pragma unroll
+        for (int j = 0; j < VEC; ++j) s[j] = 0.0f;
+        for (int c = c0; c < c1; c += 8) {       // ascending ids
+            u32x4 w[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                w[e] = u32x4{0, 0, 0, 0};
+                if (c + e < c1) w[e] = *reinterpret_cast<const u32x4 *>(col + (int64_t)b.kids[c + e] * pitch);
+            }
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                if (c + e >= c1) break;
+                if (sizeof(T) == 4 || is_h) {
+                    add_h_piece<T>(s, w[e]);
+                } else {
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) s[j] += __uint_as_float(w[e][j]);
+                }
+            }
+        }
+        if (is_h) {
+            T e[VEC];
+#pragma unroll
+            for (int j = 0; j < VEC; ++j) e[j] = from_f32<T>(s[j]);
+            u32x4 v;
+            __builtin_memcpy(&v, e, 16);
+            *reinterpret_cast<u32x4 *>(b.A + rr * a.pitch_h + k * 16) = v;
+        } else {
+            *reinterpret_cast<float4 *>(b.Fs + rr * a.Hz + (k - ph) * 4) = make_float4(s[0], s[1], s[2], s[3]);
+        }
+    }
+}
+
+// All of the block's LDS writes are visible after it; stores to memory are not waited for (__syncthreads would).
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+// The cells of rows [r0, r_end): at most 16 NRT, NRT == 0: at most four, one per lane quarter.
+template <typename T, bool SAVE, int NRT>
+__device__ __forceinline__ void level_group(const TreesArgs &a, const TreeBlock &b, int r0, int r_end) {
+    constexpr int NA = NRT ? NRT : 1, NV = NRT ? 4 : 1;
+    for (int ut = b.wave; ut < a.n_ut; ut += b.n_waves) {
+        const int lane = fresh_lane(b.lane), hf = lane >> 4, n = lane & 15;
+        const int unit = ut * 16 + n;
+        floatx4 acc[NA][3];
+        float z4[3];
+#pragma unroll
+        for (int rt = 0; rt < NA; ++rt)
+#pragma unroll
+            for (int v = 0; v < NV; ++v) {
+                const int r = r0 + (NRT ? rt * 16 + hf * 4 + v : hf);
+                const float *zp = a.Z + (int64_t)(b.lo + b.order[r < r_end ? r : r_end - 1]) * 4 * a.Hz + unit;
+#pragma unroll
+                for (int g = 0; g < 3; ++g) {
+                    if constexpr (NRT) acc[rt][g][v] = zp[g * a.Hz];
+                    else { z4[g] = zp[g * a.Hz]; acc[0][g] = floatx4{0, 0, 0, 0}; }
+                }
+            }
+        const char *a_lane = b.A + (NRT ? n : lane & 3) * a.pitch_h + hf * 16;
+        tree_gemm<T, NRT, 3>(acc, [&](int rt, int s) { return *reinterpret_cast<const u32x4 *>(a_lane + rt * 16 * a.pitch_h + s * 64); },
+                             tree_weights(a, lane, ut, a.sx_packed, 0), (int64_t)a.NPU * 64, a.sh);
+#pragma unroll
+        for (int rt = 0; rt < NA; ++rt) {
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int v = 0; v < NV; ++v) {
+                const int rr = NRT ? rt * 16 + hf * 4 + v : hf, r = r0 + rr;
+                float z[3];
+#pragma unroll
+                for (int g = 0; g < 3; ++g) z[g] = NRT ? acc[rt][g][v] : z4[g] + quarter_sum(acc[0][g], lane);
+                const float gi = sigmoid_t<T>(z[0]), go = sigmoid_t<T>(z[1]), gu = tanh_t<T>(z[2]);
+                const float c = gi * gu + b.Fs[rr * a.Hz + unit];
+                b.Fs[rr * a.Hz + unit] = c;          // for the forget gates' step
+                const T hv = unit < a.H ? from_f32<T>(go * tanh_t<T>(c)) : T(0);
+                *reinterpret_cast<T *>(b.Ht + rr * a.pitch_h + unit * (int)sizeof(T)) = hv;
+                if (r >= r_end) continue;
+                const int64_t node = b.lo + b.order[r];
+                store_unit<T>(a, node, unit, c, hv);
+                if constexpr (SAVE) {
+                    if (unit < a.H) save_gates<T>(a, node, unit, gi, go, gu);
+                }
+            }
+        }
+    }
+}
+
+// f c of rows [r0, r_end) from P = U_f h, f with the parent's Z_f.  LEAF: h and c come from memory (tree_x_kernel has
+// finished the leaves' cells), else from LDS.
+template <typename T, bool SAVE, int NRT, bool LEAF>
+__device__ __forceinline__ void forget_tile(const TreesArgs &a, const TreeBlock &b, int ut, int r0, int r_end) {
+    constexpr int NA = NRT ? NRT : 1, NV = NRT ? 4 : 1;
+    const int lane = fresh_lane(b.lane), hf = lane >> 4, n = lane & 15;
+    const int unit = ut * 16 + n, unit_ld = unit < a.H ? unit : 0;
+    floatx4 acc[NA][1];
+    float zf[NA][NV], c[NA][NV];             // on their way during the product
+#pragma unroll
+    for (int rt = 0; rt < NA; ++rt) {
+#pragma unroll
+        for (int v = 0; v < NV; ++v) {
+            const int rr = NRT ? rt * 16 + hf * 4 + v : hf, r = r0 + rr < r_end ? r0 + rr : r_end - 1;
+            const int i = b.order[r], p = b.par[i];
+            zf[rt][v] = a.Z[((int64_t)(b.lo + (p != kNoLocal ? p : i)) * 4 + 3) * a.Hz + unit];
+            c[rt][v] = LEAF ? a.c_out[(int64_t)(b.lo + i) * a.H + unit_ld] : b.Fs[rr * a.Hz + unit];
+        }
+        acc[rt][0] = floatx4{0, 0, 0, 0};
+    }
+    const char *w = tree_weights(a, lane, ut, a.sx_packed, 3);
+    if constexpr (LEAF) {
+        const char *row[NA];
+#pragma unroll
+        for (int rt = 0; rt < NA; ++rt) {
+            const int r = r0 + (NRT ? rt * 16 + n : lane & 3);
+            row[rt] = static_cast<const char *>(a.hs) + (int64_t)(b.lo + b.order[r < r_end ? r : r_end - 1]) * a.Hp * (int)sizeof(T) + hf * 16;
+        }
+        tree_gemm<T, NRT, 1, true>(acc, [&](int rt, int s) { return *reinterpret_cast<const u32x4 *>(row[rt] + s * 64); }, w, (int64_t)a.NPU * 64, a.sh);
+    } else {
+        const char *a_lane = b.Ht + (NRT ? n : lane & 3) * a.pitch_h + hf * 16;
+        tree_gemm<T, NRT, 1>(acc, [&](int rt, int s) { return *reinterpret_cast<const u32x4 *>(a_lane + rt * 16 * a.pitch_h + s * 64); }, w,
+                             (int64_t)a.NPU * 64, a.sh);
+    }
+#pragma unroll
+    for (int rt = 0; rt < NA; ++rt)
+#pragma unroll
+        for (int v = 0; v < NV; ++v) {
+            const int r = r0 + (NRT ? rt * 16 + hf * 4 + v : hf);
+            const float pf = NRT ? acc[rt][0][v] : quarter_sum(acc[0][0], lane);
+            if (r >= r_end) continue;
+            const int i = b.order[r];
+            if (b.par[i] == kNoLocal) continue;
+            const float f = sigmoid_t<T>(pf + zf[rt][v]);
+            a.FC[(int64_t)(b.lo + i) * a.Hz + unit] = unit < a.H ? f * c[rt][v] : 0.0f;
+            if constexpr (SAVE) {
+                if (unit < a.H) static_cast<T *>(a.fgate)[(int64_t)(b.lo + i) * a.H + unit] = from_f32<T>(f);
+            }
+        }
+}
+
+template <typename T, bool SAVE>
+__global__ void __launch_bounds__(kTreeMaxWaves * 64, 4)
+trees_kernel(const TreesArgs a) {
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    __shared__ int s_cut[2];
+    __shared__ int s_min[kTreeMaxLevels];
+    __shared__ int s_cnt[kTreeMaxLevels];
+    __shared__ int s_start[kTreeMaxLevels + 1];
+    const int t = threadIdx.x, nt = blockDim.x;
+    TreeBlock b;
+    b.A = lds;
+    b.Ht = b.A + a.group_rows * a.pitch_h;
+    b.Fs = reinterpret_cast<float *>(b.Ht + a.group_rows * a.pitch_h);
+    uint16_t *order = reinterpret_cast<uint16_t *>(b.Fs + a.group_rows * a.Hz);
+    uint16_t *cstart = order + a.cap, *kids = cstart + a.cap + 2, *par = kids + a.cap;
+    b.order = order; b.cstart = cstart; b.kids = kids; b.par = par;
+    b.lane = t & 63;
+    b.wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    b.n_waves = nt >> 6;
+
+    // ---- where the block's trees begin and end: for both places, how many parent-child intervals cross every position
+    //      from i0 - tw on (the first and the last child bound a node's interval: child lists ascend)
+    const int tw = a.tree_window, span = 2 * tw + 1;
+    int *cover = reinterpret_cast<int *>(lds);                 // [2][span + 1]
+    for (int i = t; i < 2 * (span + 1); i += nt) cover[i] = 0;
+    if (t < kTreeMaxLevels) { s_min[t] = INT32_MAX; s_cnt[t] = 0; }
+    __syncthreads();
+    for (int side = 0; side < 2; ++side) {
+        const int64_t i0 = ((int64_t)blockIdx.x + side) * a.G;
+        if (i0 == 0 || i0 >= a.n) continue;
+        const int base = (int)i0 - tw;
+        const int j1 = i0 + 2 * tw < a.n ? (int)i0 + 2 * tw : a.n;
+        for (int j = (base > 0 ? base : 0) + t; j < j1; j += nt) {
+            const int c0 = a.child_ptr[j], c1 = a.child_ptr[j + 1];
+            if (c1 <= c0) continue;
+            const int first = a.child_idx[c0], last = a.child_idx[c1 - 1];
+            int p0 = min(j, first) + 1 - base, p1 = max(j, last) + 1 - base;
+            p0 = p0 < 0 ? 0 : p0;
+            p1 = p1 < 0 ? 0 : p1;
+            if (p0 <= span) atomicAdd(&cover[side * (span + 1) + p0], 1);
+            if (p1 <= span) atomicAdd(&cover[side * (span + 1) + p1], -1);
+        }
+    }
+    __syncthreads();
+    if (b.wave < 2) {
+        const int64_t i0 = ((int64_t)blockIdx.x + b.wave) * a.G;
+        int cut;
+        if (i0 == 0 || i0 >= a.n) {
+            cut = i0 == 0 ? 0 : a.n;
+        } else {
+            const int *cv = cover + b.wave * (span + 1);
+            const int per = (span + 63) / 64;
+            int sum = 0;
+            for (int q = b.lane * per; q < (b.lane + 1) * per && q < span; ++q) sum += cv[q];
+            int run = sum;
+#pragma unroll
+            for (int d = 1; d < 64; d <<= 1) {
+                const int v = __shfl_up(run, d, 64);
+                if (b.lane >= d) run += v;
+            }
+            run -= sum;
+            cut = INT32_MAX;
+            for (int q = b.lane * per; q < (b.lane + 1) * per && q < span; ++q) {
+                run += cv[q];
+                if (run == 0 && q >= tw && cut == INT32_MAX) cut = (int)i0 - tw + q;
+            }
+#pragma unroll
+            for (int d = 32; d > 0; d >>= 1) cut = min(cut, __shfl_xor(cut, d, 64));
+            if (cut > a.n) cut = a.n;                          // (past the last node, or no cut: not a schedule of jitdb_schedule)
+        }
+        if (b.lane == 0) s_cut[b.wave] = cut;
+    }
+    __syncthreads();
+    b.lo = s_cut[0];
+    b.own = s_cut[1] - b.lo;
+    if (b.own > a.cap) b.own = a.cap;
+    if (b.own <= 0) return;
+
+    // ---- rows: a level's nodes of this block are consecutive positions of the schedule
+    const int e0 = a.child_ptr[b.lo], n_edges = min(a.child_ptr[b.lo + b.own] - e0, b.own);
+    for (int i = t; i < b.own; i += nt) {
+        const int h = a.height[b.lo + i];
+        if (h < kTreeMaxLevels) {
+            atomicMin(&s_min[h], a.inv_perm[b.lo + i]);
+            atomicAdd(&s_cnt[h], 1);
+        }
+        order[i] = 0;
+        par[i] = kNoLocal;
+    }
+    for (int i = t; i <= b.own; i += nt) cstart[i] = (uint16_t)min(max(a.child_ptr[b.lo + i] - e0, 0), n_edges);
+    for (int e = t; e < n_edges; e += nt) {
+        const int k = a.child_idx[e0 + e] - b.lo;
+        kids[e] = (uint16_t)(k >= 0 && k < b.own ? k : 0);
+    }
+    __syncthreads();
+    if (b.wave == 0) {
+        const int c = b.lane < kTreeMaxLevels ? s_cnt[b.lane] : 0;
+        int inc = c;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const int v = __shfl_up(inc, d, 64);
+            if (b.lane >= d) inc += v;
+        }
+        if (b.lane < kTreeMaxLevels) s_start[b.lane] = inc - c;
+        if (b.lane == kTreeMaxLevels - 1) s_start[kTreeMaxLevels] = inc;
+    }
+    __syncthreads();
+    for (int i = t; i < b.own; i += nt) {
+        const int h = a.height[b.lo + i];
+        if (h < kTreeMaxLevels) {
+            const int r = s_start[h] + a.inv_perm[b.lo + i] - s_min[h];
+            if (r >= 0 && r < b.own) order[r] = (uint16_t)i;
+        }
+        for (int e = cstart[i]; e < cstart[i + 1]; ++e) par[kids[e]] = (uint16_t)i;
+    }
+    for (int i = t * 16; i < a.group_rows * a.pitch_h; i += nt * 16)      // pad columns of the h rows stay zero
+        *reinterpret_cast<u32x4 *>(b.Ht + i) = u32x4{0, 0, 0, 0};
+    // levels of this block that run here: [0, n_lvl)
+    int n_lvl = 0;
+    while (n_lvl < a.l_end && s_cnt[n_lvl] > 0) ++n_lvl;
+    __syncthreads();
+
+    if (n_lvl < 2) return;
+    {   // the leaves: every wave for itself, 16 or 32 rows of 16 units at a time (waves side by side share the rows' lines in L1)
+        const int n_leaf = s_cnt[0], n32 = n_leaf >> 5, rest = n_leaf & 31, n_tasks = (n32 + (rest > 0)) * a.n_ut;
+        for (int q = b.wave; q < n_tasks; q += b.n_waves) {
+            const int tile = q / a.n_ut, ut = q - tile * a.n_ut;
+            if (tile < n32) forget_tile<T, SAVE, 2, true>(a, b, ut, tile * 32, tile * 32 + 32);
+            else if (rest > 16) forget_tile<T, SAVE, 2, true>(a, b, ut, tile * 32, n_leaf);
+            else if (rest > 4) forget_tile<T, SAVE, 1, true>(a, b, ut, tile * 32, n_leaf);
+            else forget_tile<T, SAVE, 0, true>(a, b, ut, tile * 32, n_leaf);
+        }
+        __syncthreads();
+    }
+    for (int l = 1; l < n_lvl; ++l) {
+        const int l0 = s_start[l], l1 = s_start[l + 1];
+        for (int r0 = l0; r0 < l1; r0 += a.group_rows) {
+            const int r_end = r0 + a.group_rows < l1 ? r0 + a.group_rows : l1, rows = r_end - r0;
+            if (r0 > l0) lds_barrier();               // the group before is done with Fs
+            gather_sums<T>(a, b, r0, r_end);
+            lds_barrier();
+            if (rows > 16) level_group<T, SAVE, 2>(a, b, r0, r_end);
+            else if (rows > 4) level_group<T, SAVE, 1>(a, b, r0, r_end);
+            else level_group<T, SAVE, 0>(a, b, r0, r_end);
+            if (l + 1 >= n_lvl) continue;
+            lds_barrier();
+            for (int ut = b.wave; ut < a.n_ut; ut += b.n_waves) {
+                if (rows > 16) forget_tile<T, SAVE, 2, false>(a, b, ut, r0, r_end);
+                else if (rows > 4) forget_tile<T, SAVE, 1, false>(a, b, ut, r0, r_end);
+                else forget_tile<T, SAVE, 0, false>(a, b, ut, r0, r_end);
+            }
+        }
+        __syncthreads();                              // the next level's sums read what this one left in memory
+    }
+}
+
+constexpr int kTreeLdsMax = 156 * 1024;
+constexpr int kTreeNodesPerBlock = 128;
+constexpr int kTreeLdsStatic = 1024;               // trees_kernel's static LDS, rounded up
+
+}  // namespace
+
+// Fills the launch geometry of `a`; false if the forest is better run level by level.
+bool plan_trees(TreesArgs &a, size_t esz) {
+    // Every block reads the recurrent weights once per level, so the gain shrinks with their size and, where the level kernels
+    // fill the chip, with the number of nodes.  Forward alone, 32 to 8192 trees of 4 - 48 nodes, D = 300, level by level ->
+    // here: H = 64 fp32 201 -> 67 us (949 nodes), 1115 -> 522 (214 k), bf16 149 -> 58, 541 -> 242; H = 150 fp32 244 -> 126,
+    // 1937 -> 1428, bf16 163 -> 83, 887 -> 637; H = 256 fp32 275 -> 217, 2438 -> 2437, bf16 169 -> 146 (949), 272 -> 209 (26 k),
+    // 532 -> 552 (106 k); H = 384 slower throughout.
+    if (a.H > kTreesMaxWidth || (esz == 2 && a.H > 160 && a.n > 65536)) return false;
+    a.sx = (int)ceil_div((int64_t)a.D * (int64_t)esz, 64);
+    a.sh = (int)ceil_div((int64_t)a.H * (int64_t)esz, 64);
+    a.Hz = (int)round_up(a.H, 16);
+    a.n_ut = a.Hz / 16;
+    a.pitch_h = a.sh * 64 + 16;
+    const int passes = (int)ceil_div(a.n_ut, kTreeMaxWaves);
+    a.n_waves = (int)round_up(ceil_div(a.n_ut, passes), 4);  // whole rounds of the four SIMDs, so that blocks share them evenly
+    if (a.n_waves < 8) a.n_waves = 8;                       // for the gathers
+    const size_t row_bytes = (size_t)2 * a.pitch_h + 4 * a.Hz;
+    a.group_rows = kTreeRows * row_bytes <= (size_t)kTreeLdsMax * 9 / 10 ? kTreeRows : kTreeRows / 2;
+    const size_t tiles = a.group_rows * row_bytes, cuts = (size_t)2 * (2 * a.tree_window + 2) * 4;
+    // one block per compute unit up to kTreeNodesPerBlock nodes each, then as many as registers and LDS let it hold (two blocks
+    // hide each other's latencies, but a small forest's blocks should not share a compute unit while others idle)
+    int per_cu = (int)ceil_div(a.n, (int64_t)kTreeCus * kTreeNodesPerBlock);
+    if (per_cu > kTreeMaxWaves / a.n_waves) per_cu = kTreeMaxWaves / a.n_waves;
+    for (;; --per_cu) {
+        a.G = (int)ceil_div(a.n, kTreeCus * per_cu);
+        a.cap = a.G + a.tree_window;
+        if (a.cap > a.n) a.cap = a.n;
+        a.lds_bytes = (tiles > cuts ? tiles : cuts) + (size_t)(4 * a.cap + 8) * 2;
+        if (per_cu == 1 || (a.lds_bytes + kTreeLdsStatic) * per_cu <= (size_t)kTreeLdsMax) break;
+    }
+    if (a.lds_bytes > (size_t)kTreeLdsMax || a.cap >= kNoLocal) return false;
+    a.n_blocks = (int)ceil_div(a.n, a.G);
+    // x part: one wave per unit tile and run of node tiles; as many waves as the chip holds at a time
+    if (a.sx > kXSlabs[sizeof(kXSlabs) / sizeof(int) - 1]) return false;
+    a.x_slabs = 0;
+    for (int ns : kXSlabs)
+        if (a.x_slabs == 0 && ns >= a.sx) a.x_slabs = ns;
+    const int64_t waves = (int64_t)kTreeCus * 4 * (a.x_slabs <= 10 ? 2 : 1), tiles16 = ceil_div(a.n_leaves, 16) + ceil_div(a.n - a.n_leaves, 16);
+    a.x_chunks = (int)(waves / a.n_ut);
+    if (a.x_chunks > tiles16) a.x_chunks = (int)tiles16;
+    if (a.x_chunks < 1) a.x_chunks = 1;
+    return true;
+}
+
+namespace {
+template <typename T, bool SAVE, int NS>
+int launch_tree_x(const TreesArgs &a, hipStream_t st) {
+    tree_x_kernel<T, SAVE, NS><<<(unsigned)ceil_div((int64_t)a.x_chunks * a.n_ut, 4), 256, 0, st>>>(a);
+    JITDB_LAUNCH_CHECK();
+    return JITDB_OK;
+}
+template <typename T, bool SAVE>
+int launch_trees_t(const TreesArgs &a, hipStream_t st) {
+    int rc = JITDB_E_BADARG;
+    switch (a.x_slabs) {
+        case 4: rc = launch_tree_x<T, SAVE, 4>(a, st); break;
+        case 7: rc = launch_tree_x<T, SAVE, 7>(a, st); break;
+        case 10: rc = launch_tree_x<T, SAVE, 10>(a, st); break;
+        case 16: rc = launch_tree_x<T, SAVE, 16>(a, st); break;
+        case 20: rc = launch_tree_x<T, SAVE, 20>(a, st); break;
+    }
+    if (rc != JITDB_OK || a.l_end < 2) return rc;
+    if (a.lds_bytes > 64 * 1024)
+        JITDB_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void *>(&trees_kernel<T, SAVE>), hipFuncAttributeMaxDynamicSharedMemorySize, kTreeLdsMax));
+    trees_kernel<T, SAVE><<<a.n_blocks, a.n_waves * 64, a.lds_bytes, st>>>(a);
+    JITDB_LAUNCH_CHECK();
+    return JITDB_OK;
+}
+}  // namespace
+
+int launch_trees(jitdb_dtype dtype, bool save, const TreesArgs &a, hipStream_t st) {
+    if (dtype == JITDB_F32) return save ? launch_trees_t<float, true>(a, st) : launch_trees_t<float, false>(a, st);
+    return save ? launch_trees_t<bf16_t, true>(a, st) : launch_trees_t<bf16_t, false>(a, st);
+}
+
+}  // namespace jitdb

@@ -1,0 +1,83 @@
+"""The forward of small forests filed tree after tree (trees.hip) against the C oracle, at the sizes where its row groups,
+unit tiles, weight slabs and waves have remainders, and at the limits of what it takes."""
+import numpy as np
+import pytest
+
+from workloads import make_forest, make_values, chain_forest, star_forest, perfect_kary_tree, relabel
+from gpu_util import run_gpu_forward
+
+pytestmark = pytest.mark.gpu
+
+TOL = {"f32": 1e-4, "bf16": 2e-2}
+
+
+def _lay_out(trees):
+    off = np.concatenate([[0], np.cumsum([t.shape[0] for t in trees])])
+    return np.concatenate([np.where(t < 0, -1, t + o) for t, o in zip(trees, off)]).astype(np.int32)
+
+
+def _word_order(p, seed):
+    """Ids inside every tree in any order."""
+    cuts = np.append(np.flatnonzero(p < 0), p.shape[0])
+    return _lay_out([relabel(np.where(p[a:b] < 0, -1, p[a:b] - a).astype(np.int32), seed + int(a))[0]
+                     for a, b in zip(cuts[:-1], cuts[1:])])
+
+
+def _broom(k):
+    """A root with k children that have one leaf each: k rows on the middle level."""
+    return np.concatenate([[-1], np.zeros(k), 1 + np.arange(k)]).astype(np.int32)
+
+
+FORESTS = {
+    "one-tree": lambda: perfect_kary_tree(2, 4),
+    "leaves-and-stars": lambda: _lay_out([np.full(1, -1, np.int32)] * 3 + [star_forest(k) for k in (2, 5, 6, 17, 18, 34, 70)]),
+    # 4, 5, 16, 17, 32, 33 rows of one level inside a block, levels of all sizes above
+    "row-groups": lambda: _lay_out([perfect_kary_tree(2, 5)] + [_broom(k) for k in (4, 5, 16, 17, 32, 33, 65)] * 2),
+    "word-order": lambda: _word_order(make_forest(2), 3),
+    # 32 levels, two trees wide; sequences of up to 12 nodes leave chain levels on top
+    "deep": lambda: _lay_out([chain_forest(31), star_forest(4)] * 5 + [_lay_out([perfect_kary_tree(2, 2)])]),
+    "many": lambda: _lay_out([make_forest(1)] * 700),
+}
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("forest,D,H", [
+    ("one-tree", 300, 150), ("leaves-and-stars", 7, 33), ("row-groups", 128, 16), ("row-groups", 129, 99), ("word-order", 300, 150),
+    ("word-order", 225, 256), ("deep", 44, 50), ("many", 320, 128), ("row-groups", 300, 240), ("word-order", 31, 256),
+])
+def test_trees_in_one_block_each(c_oracle, forest, D, H, dtype):
+    import torch
+    import paper_1904_07421_amd as J
+    p = FORESTS[forest]()
+    x, W, U, b = make_values(1, p.shape[0], "random", D=D, H=H)
+    J.jitdb_profile_start(256)
+    try:
+        s, h, c, seen = run_gpu_forward(p, x, W, U, b, dtype)
+    finally:
+        prof = J.jitdb_profile_stop()
+    launches = {k: v["launches"] for k, v in prof.items() if isinstance(v, dict)}
+    print(f"trees {forest} D={D} H={H} {dtype} N={p.shape[0]} L={s.n_levels} launches={launches}", flush=True)
+    assert launches["trees"] == 1 and launches["thin_internal"] == launches["internal"] == 0
+    ho, co, _ = c_oracle(p, *seen)
+    eh, ec = np.abs(h - ho).max(), np.abs(c - co).max()
+    # |c| grows with the arity: the flat bound holds up to max|c| = 8 (bf16) / 50 (fp32), in proportion beyond
+    assert eh <= TOL[dtype] and ec <= TOL[dtype] * max(1.0, np.abs(co).max() / (8.0 if dtype == "bf16" else 50.0))
+    torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("what", ["wide-x", "wide-h", "long-tree", "scrambled"])
+def test_what_does_not_fit_runs_level_by_level(c_oracle, what):
+    """D past the largest instance, a tree longer than one block should take, ids all over the forest."""
+    import paper_1904_07421_amd as J
+    p = _lay_out([perfect_kary_tree(2, 8), make_forest(1)]) if what == "long-tree" else make_forest(2)
+    if what == "scrambled":
+        p = relabel(p, 9)[0]
+    x, W, U, b = make_values(1, p.shape[0], "random", D=700 if what == "wide-x" else 40, H=260 if what == "wide-h" else 40)
+    J.jitdb_profile_start(4096)
+    try:
+        s, h, c, seen = run_gpu_forward(p, x, W, U, b, "f32")
+    finally:
+        prof = J.jitdb_profile_stop()
+    ho, co, _ = c_oracle(p, *seen)
+    assert prof["trees"]["launches"] == 0
+    assert np.abs(h - ho).max() <= 1e-4 and np.abs(c - co).max() <= 1e-4 * max(1.0, np.abs(co).max() / 50.0)
