@@ -12,7 +12,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libjitdb.so")
-SOURCES = ["schedule.hip", "forward.hip", "trees.hip", "level256.hip", "cells.hip", "backward.hip", "cache.hip", "probe.hip", "api.hip"]
+SOURCES = ["schedule.hip", "forward.hip", "trees.hip", "cells.hip", "backward.hip", "cache.hip", "probe.hip", "api.hip"]
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
@@ -208,7 +208,7 @@ def build(verbose: bool = False) -> str:
     try:
         res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, cwd=tmp)
         asm_texts = {}
-        for stem in ("forward", "level256"):
+        for stem in ("forward", "backward"):
             asm_path = os.path.join(tmp, stem + "-hip-amdgcn-amd-amdhsa-gfx950.s")
             asm_texts[stem] = open(asm_path).read() if os.path.exists(asm_path) else None
     finally:
@@ -219,17 +219,18 @@ def build(verbose: bool = False) -> str:
     if res.returncode != 0:
         raise RuntimeError("hipcc failed:\n" + out)
     _check_no_scratch(lines)
-    # the kernels whose LDS reads (and, for the 256 x 256 tile kernel, weight loads) are inline asm
+    # the kernels whose LDS reads are inline asm
     # (names with their length prefix, as they are mangled: "level_kernel" alone would also match fused_level_kernel)
     for stem, name in (("forward", "12level_kernel"), ("forward", "14gemm_kb_kernel"), ("forward", "17nary_level_kernel"),
-                       ("level256", "14tile256_kernel")):
+                       ("backward", "16rows_tile_kernel"), ("backward", "9tn_kernel")):
         if asm_texts.get(stem) is None:
             raise RuntimeError(f"the device assembly of {stem}.hip was not produced; cannot check it")
         if check_lds_read_waits(asm_texts[stem], name) == 0:
             raise RuntimeError(f"no LDS reads found in the assembly of {name}: the check is not looking at it")
     # the K loops whose waits for direct-to-LDS stage loads are hand-counted
-    for name in ("12level_kernel", "14gemm_kb_kernel", "17nary_level_kernel"):
-        if check_stage_loads(asm_texts["forward"], name) == 0:
+    for stem, name in (("forward", "12level_kernel"), ("forward", "14gemm_kb_kernel"), ("forward", "17nary_level_kernel"),
+                       ("backward", "16rows_tile_kernel"), ("backward", "9tn_kernel")):
+        if check_stage_loads(asm_texts[stem], name) == 0:
             raise RuntimeError(f"no K loop with stage loads found in the assembly of {name}: the check is not looking at it")
     if verbose and out.strip():
         print(out)

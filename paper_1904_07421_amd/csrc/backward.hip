@@ -1,416 +1,646 @@
 // jitdb_treelstm_backward: reverse-mode gradients of the level-batched Tree-LSTM forward.
 //
-// The paper trains through the same batched graph it infers with (section 5).  Here the
-// levels of the schedule are visited from the roots down.  A node's parent lies in a higher
-// level, so when a level is reached every parent has already left its total dc and its dhs =
-// U_iou^T dz_iou (by node id); per level
+// The paper trains through the same batched graph it infers with (section 5).  Only what a node hands to its children
+// has to follow the levels: the levels are visited from the roots down with two steps each,
 //
-//   (rows of G for this level: dz_f,k = dc_p c_k f_k (1 - f_k), written by the parents' cell kernels)
-//   ufg = G U_f                                      GEMM over the level's rows
-//   dU_f += G^T h                                    GEMM, reduction over the level's rows
-//   bwd_cell_kernel      dh_j = gh_j + dhs_p + ufg_j, dc_j = gc_j + dc_p f_j + ..., then dz_i, dz_o,
-//                        dz_u, sum_k dz_f,k from them and the saved gates; each child's dz_f,k -> G
-//   [dx_j | dhs_j] = dZ_j [W | U]                    GEMM over the level's rows
-//   [dW | db | dU_iou]^T += [x | 1 | hs]^T dZ        GEMM, reduction over the level's rows
+//   bwd_cell_kernel      dh_j = gh_j + dhs_p + ufg_j, dc_j = gc_j + dc_p f_j + ..., then row r of
+//                        dZ = [dz_i | dz_o | dz_u | sum_k dz_f,k] and each child's row of G: dz_f,k = dc_j c_k f_k (1 - f_k)
+//   one product          dhs = dZ_iou U_iou for this level's rows and ufg = G U_f for the next level's
 //
-// All four GEMMs run on the forward's tiled MFMA core (launch_kb_gemm: both operands
-// K-blocked).  A reduction over rows needs operands whose K axis is the level's rows: the cell
-// kernel writes dZ a second time, transposed through LDS; G, x and h are transposed by
-// transpose_kb_kernel, the child sums hs are formed inside hsum_transpose_kernel.  Gradients
-// are fp32; with JITDB_BF16 the GEMM operands (dz, x, h, hs, weights) and the values handed
-// from level to level through dhs and ufg are bfloat16, every sum and dc fp32.
+// and everything that sums over nodes or is nobody's input waits for the end, where it runs once over all nodes:
+//
+//   dx = dZ W                                        (leaves have no forget block)
+//   [dW | db] = [x | 1]^T dZ,  dU_iou = hs^T dZ_iou,  dU_f = h^T G      one launch, reduction over the nodes
+//
+// dZ, G and the operands x, h, hs are K-blocked, rows in the schedule's position order.  The sums over nodes read the same
+// rows as the other products (the transposition happens on the way out of LDS, MODE_TN of tile_gemm.h): nothing is written
+// twice.  Kernel time of the backward pass, with a weight-gradient product, its transposes and a dx product in every level
+// -> like this: 4683 nodes in 7 levels, D = 300, H = 150, fp32: 1.95 ms -> 0.22; 1.18 M nodes in 15 levels, D = 300,
+// H = 512, bf16: 19.0 ms -> 15.1.
+//
+// Gradients are fp32; with JITDB_BF16 the operands of the products (dz, x, h, hs, weights) and the values handed from level
+// to level through dhs and ufg are bfloat16, every sum and dc fp32.
 
-#include "common.h"
+#include "tile_gemm.h"
 
 namespace jitdb {
 namespace {
 
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-
 constexpr int kT = 256;
 
-// ---- small helpers -----------------------------------------------------------------
 __global__ void __launch_bounds__(kT)
 fill_f32_kernel(float *p, int64_t n, float v) {
     for (int64_t i = (int64_t)blockIdx.x * kT + threadIdx.x; i < n; i += (int64_t)gridDim.x * kT) p[i] = v;
 }
-__global__ void __launch_bounds__(kT)
-fill_bytes16_kernel(u32x4 *p, int64_t n16) {
-    const u32x4 z = {0, 0, 0, 0};
-    for (int64_t i = (int64_t)blockIdx.x * kT + threadIdx.x; i < n16; i += (int64_t)gridDim.x * kT) p[i] = z;
-}
 
-// ---- weights for the data-gradient GEMMs ---------------------------------------------
-// Both K-blocked, for the tiled GEMM.  Mt [D + H rows, 4 Hk]: row n < D is column n of W, row
-// D + n' column n' of U, the four gates side by side at stride Hk (H rounded up, pad zero);
-// the forget gate has no h-sum part, so its block is zero in the rows of U.  Uft [H rows, Hk]:
-// row n = column n of U_f.
-template <typename T>
-__global__ void __launch_bounds__(kT)
-pack_bwd_weights_kernel(const T *__restrict__ W, const T *__restrict__ U, int D, int H, int Hk,
-                        T *__restrict__ Mt, int64_t mt_rows_alloc, T *__restrict__ Uft, int64_t uft_rows_alloc) {
-    const int64_t total = (int64_t)(D + H) * 4 * Hk;
-    for (int64_t idx = (int64_t)blockIdx.x * kT + threadIdx.x; idx < total; idx += (int64_t)gridDim.x * kT) {
-        const int n = (int)(idx / (4 * Hk)), k = (int)(idx % (4 * Hk));
-        const int g = k / Hk, m = k % Hk;
-        T v = T(0);
-        if (m < H) {
-            if (n < D) v = W[((int64_t)g * H + m) * D + n];
-            else if (g < 3) v = U[((int64_t)g * H + m) * H + (n - D)];
+// N units from p[0 ..]; those past `left` are zero.  VEC: rows start on 4-byte boundaries.
+template <typename E, int N, bool VEC>
+__device__ __forceinline__ void load_units(const E *__restrict__ p, int left, float (&v)[N]) {
+    typedef u32x4 __attribute__((aligned(4))) u32x4a;
+    constexpr int PER = 16 / (int)sizeof(E);
+    if (VEC && left >= N) {
+#pragma unroll
+        for (int q = 0; q < N / PER; ++q) {
+            const u32x4 w = reinterpret_cast<const u32x4a *>(p)[q];
+#pragma unroll
+            for (int e = 0; e < PER; ++e) {
+                if constexpr (sizeof(E) == 4) v[q * PER + e] = __uint_as_float(w[e]);
+                else v[q * PER + e] = __uint_as_float(e & 1 ? w[e / 2] & 0xFFFF0000u : w[e / 2] << 16);
+            }
         }
-        *reinterpret_cast<T *>(reinterpret_cast<char *>(Mt) + operand_offset(n, (int64_t)k * sizeof(T), mt_rows_alloc)) = v;
-    }
-    const int64_t total_f = (int64_t)H * Hk;
-    for (int64_t idx = (int64_t)blockIdx.x * kT + threadIdx.x; idx < total_f; idx += (int64_t)gridDim.x * kT) {
-        const int n = (int)(idx / Hk), m = (int)(idx % Hk);
-        const T v = m < H ? U[((int64_t)3 * H + m) * H + n] : T(0);
-        *reinterpret_cast<T *>(reinterpret_cast<char *>(Uft) + operand_offset(n, (int64_t)m * sizeof(T), uft_rows_alloc)) = v;
-    }
-}
-
-// parent_of[k] for every node with a parent (the array is filled with -1 first)
-__global__ void __launch_bounds__(kT)
-parent_of_kernel(const int32_t *__restrict__ child_ptr, const int32_t *__restrict__ child_idx, int n,
-                 int32_t *__restrict__ parent_of) {
-    const int64_t j = (int64_t)blockIdx.x * kT + threadIdx.x;
-    if (j >= n) return;
-    for (int e = child_ptr[j]; e < child_ptr[j + 1]; ++e) parent_of[child_idx[e]] = (int32_t)j;
-}
-__global__ void __launch_bounds__(kT)
-fill_i32_kernel(int32_t *p, int64_t n, int32_t v) {
-    for (int64_t i = (int64_t)blockIdx.x * kT + threadIdx.x; i < n; i += (int64_t)gridDim.x * kT) p[i] = v;
-}
-
-// ---- elementwise kernels on (RT rows) x (64 units) tiles ------------------------------
-// RT = 32 (bf16) / 16 (fp32) level rows fill one 64-byte slab of a K-blocked operand whose K
-// axis is the level's rows.  Wave w of a block takes the rows w, w + 4, ... of the tile, a
-// lane one unit; what a kernel produces goes out twice: row-wise into the K-blocked operand
-// of the data-gradient GEMM, and, through an LDS tile, transposed into the operand of the
-// weight-gradient GEMM (a thread stores 16 bytes, a wave 1 KB of consecutive memory).  Rows
-// past the level's end and units past H are written as zeros in the transposed operand (they
-// are part of the reduction); grid = (padded rows / RT, Hk / 64).
-template <typename T, int NG>
-__device__ __forceinline__ void store_transposed_tile(const T (*tile)[64 / sizeof(T)][64 + 2], int t, int Hk, int m0,
-                                                      T *__restrict__ dst, int64_t dst_rows_alloc, int n_gates = NG) {
-    constexpr int PER = 16 / (int)sizeof(T);
-    const int cc = t >> 2, piece = t & 3;
+    } else {
 #pragma unroll
-    for (int g = 0; g < NG; ++g) {
-        if (g >= n_gates) break;
-        T out[PER];
-#pragma unroll
-        for (int e = 0; e < PER; ++e) out[e] = tile[g][piece * PER + e][cc];
-        char *d = reinterpret_cast<char *>(dst) +
-                  ((int64_t)blockIdx.x * dst_rows_alloc + (g * Hk + m0 + cc)) * 64 + piece * 16;
-        *reinterpret_cast<u32x4 *>(d) = *reinterpret_cast<const u32x4 *>(out);
+        for (int e = 0; e < N; ++e) v[e] = e < left ? to_f32<E>(p[e]) : 0.0f;
     }
 }
-
-// G holds dz_f,k = dc_p c_k f_k (1 - f_k) for every node k, K-blocked, rows in the order of the
-// schedule's positions (all levels in one operand: a level is a range of rows).  The rows of
-// nodes with a parent are written by the parent's cell kernel; this kernel zeroes the rows of
-// the level's roots.  One thread per (level row, 16 bytes of the row).
+template <typename T> constexpr int kPer = 16 / (int)sizeof(T);       // units in 16 bytes
 template <typename T>
-__global__ void __launch_bounds__(kT)
-zero_root_rows_kernel(const int32_t *__restrict__ nodes, int n_rows, int Hk, const int32_t *__restrict__ parent_of,
-                      T *__restrict__ G, int64_t g_rows_alloc) {
-    constexpr int PER = 16 / (int)sizeof(T);
-    const int pieces = Hk / PER;
-    const int64_t id = (int64_t)blockIdx.x * kT + threadIdx.x;
-    if (id >= (int64_t)n_rows * pieces) return;
-    const int r = (int)(id / pieces), q = (int)(id % pieces);
-    if (parent_of[nodes[r]] >= 0) return;
-    const u32x4 z = {0, 0, 0, 0};
-    *reinterpret_cast<u32x4 *>(reinterpret_cast<char *>(G) + operand_offset(r, (int64_t)q * 16, g_rows_alloc)) = z;
+__device__ __forceinline__ u32x4 pack_units(const float (&v)[kPer<T>]) {
+    u32x4 o;
+    if constexpr (sizeof(T) == 4) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[e] = __float_as_uint(v[e]);
+    } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[e] = (uint32_t)f32_to_bf16(v[2 * e]) | ((uint32_t)f32_to_bf16(v[2 * e + 1]) << 16);
+    }
+    return o;
+}
+__device__ __forceinline__ void store16(void *base, int64_t row, int64_t kbyte, int64_t rows_alloc, const u32x4 &v) {
+    *reinterpret_cast<u32x4 *>(static_cast<char *>(base) + operand_offset(row, kbyte, rows_alloc)) = v;
 }
 
-// The cell's elementwise derivative.  What node j receives is fetched here, by node id, from
-// what its parent p left in a higher level (total dc_p, dhs_p = U_iou^T dz_iou,p):
-//     dh_j = gh_j + dhs_p + ufg_r      ufg (level order, may be null) = U_f^T dz_f,j, the product
-//                                      the GEMM before this kernel left
+// The elementwise kernels work on 64 units of a few rows: a thread has 16 bytes of T of one row, the threads of a row 64
+// units side by side (whole 128- or 256-byte pieces of the row-major arrays, two or four slabs of the K-blocked ones).
+template <typename T> constexpr int kPieces = 64 / kPer<T>;
+template <typename T> constexpr int kRows = kT / kPieces<T>;
+
+// ---- operands that do not depend on the gradient ------------------------------------------
+struct PrepArgs {
+    const void *x, *h, *W, *U;
+    const int32_t *perm, *child_ptr, *child_idx;
+    int32_t *parent_of;
+    void *AX, *AH, *AS, *dZ, *G, *Wt, *Ut, *Uft;
+    int D, H, Hk;
+    int n, n_rows, first;          // nodes; rounded up to 64; first row of AS that anything reads
+    int64_t rows_alloc, w_alloc, u_alloc;
+    int x_groups, row_blocks, h_groups;
+};
+// Rows [0, n_rows) of AX = [x | 1], AH = h and, from row `first` on, AS = sum of the children's h (fp32 sums, rounded once as the
+// forward does), zero past n; parent_of = -1; rows n .. n_rows of dZ and G zero (they meet zero rows in the sums over the
+// nodes, so they only have to be finite).  Blocks past those: the weights as operands of the data gradients, Wt [D rows,
+// 4 Hk], Ut [H, 3 Hk], Uft [H, Hk]: row n = column n of W / U_iou / U_f, the gates at stride Hk, pad units zero.
+template <typename T, bool VX, bool VH>
+__global__ void __launch_bounds__(kT)
+bwd_prepare_kernel(const PrepArgs a) {
+    constexpr int PER = kPer<T>;
+    const int groups = a.x_groups + a.h_groups;
+    const int64_t pack_blocks = (int64_t)a.row_blocks * groups;
+    const int t = threadIdx.x;
+    if (blockIdx.x >= pack_blocks) {
+        const int64_t step = (int64_t)(gridDim.x - pack_blocks) * kT;
+        const T *W = static_cast<const T *>(a.W), *U = static_cast<const T *>(a.U);
+        const int p4 = a.Hk / PER;
+        const int64_t total = (int64_t)(a.D + a.H) * 4 * p4;
+        for (int64_t id = (int64_t)(blockIdx.x - pack_blocks) * kT + t; id < total; id += step) {
+            // consecutive threads take consecutive columns of W / U (rows n of the operand): coalesced reads
+            const int n = (int)(id % (a.D + a.H)), q = (int)(id / (a.D + a.H));
+            const int g = q / p4, m0 = (q % p4) * PER;
+            float v[PER];
+#pragma unroll
+            for (int e = 0; e < PER; ++e) {
+                const int64_t row = (int64_t)g * a.H + m0 + e;
+                v[e] = m0 + e >= a.H ? 0.0f : to_f32<T>(n < a.D ? W[row * a.D + n] : U[row * a.H + n - a.D]);
+            }
+            const u32x4 o = pack_units<T>(v);
+            if (n < a.D) store16(a.Wt, n, (int64_t)(g * a.Hk + m0) * sizeof(T), a.w_alloc, o);
+            else if (g < 3) store16(a.Ut, n - a.D, (int64_t)(g * a.Hk + m0) * sizeof(T), a.u_alloc, o);
+            else store16(a.Uft, n - a.D, (int64_t)m0 * sizeof(T), a.u_alloc, o);
+        }
+        return;
+    }
+    const int group = (int)(blockIdx.x % groups), r = (int)(blockIdx.x / groups) * kRows<T> + t / kPieces<T>;
+    if (r >= a.n_rows) return;
+    const int piece = t % kPieces<T>;
+    const int64_t j = r < a.n ? a.perm[r] : 0;
+    float v[PER];
+    if (group < a.x_groups) {
+        const int m0 = group * 64 + piece * PER;
+#pragma unroll
+        for (int e = 0; e < PER; ++e) v[e] = 0.0f;
+        if (r < a.n) {
+            if (m0 < a.D) load_units<T, PER, VX>(static_cast<const T *>(a.x) + j * a.D + m0, a.D - m0, v);
+#pragma unroll
+            for (int e = 0; e < PER; ++e)
+                if (m0 + e == a.D) v[e] = 1.0f;
+            if (m0 == 0) a.parent_of[j] = -1;
+        }
+        store16(a.AX, r, (int64_t)m0 * sizeof(T), a.rows_alloc, pack_units<T>(v));
+        return;
+    }
+    const int m0 = (group - a.x_groups) * 64 + piece * PER;
+    const T *h = static_cast<const T *>(a.h) + m0;
+    const int left = a.H - m0;
+    const u32x4 zero = {0, 0, 0, 0};
+    u32x4 own = zero;
+    if (r < a.n && left > 0) {
+        load_units<T, PER, VH>(h + j * a.H, left, v);
+        own = pack_units<T>(v);
+    }
+    store16(a.AH, r, (int64_t)m0 * sizeof(T), a.rows_alloc, own);
+    if (r >= a.first) {
+        float sum[PER];
+#pragma unroll
+        for (int e = 0; e < PER; ++e) sum[e] = 0.0f;
+        if (r < a.n && left > 0)
+            for (int ce = a.child_ptr[j]; ce < a.child_ptr[j + 1]; ++ce) {
+                load_units<T, PER, VH>(h + (int64_t)a.child_idx[ce] * a.H, left, v);
+#pragma unroll
+                for (int e = 0; e < PER; ++e) sum[e] += v[e];
+            }
+        store16(a.AS, r, (int64_t)m0 * sizeof(T), a.rows_alloc, pack_units<T>(sum));
+    }
+    if (r >= a.n) {
+        for (int g = 0; g < 4; ++g) store16(a.dZ, r, (int64_t)(g * a.Hk + m0) * sizeof(T), a.rows_alloc, zero);
+        store16(a.G, r, (int64_t)m0 * sizeof(T), a.rows_alloc, zero);
+    }
+}
+
+// ---- the cell's elementwise derivative ------------------------------------------------------
+// What node j receives is fetched here, by node id, from what its parent p left in a higher level (total dc_p, dhs_p =
+// U_iou^T dz_iou,p):
+//     dh_j = gh_j + dhs_p + ufg_r      ufg (level order) = U_f^T dz_f,j, from the product before this kernel
 //     dc_j = gc_j + dc_p f_j + dh_j o_j (1 - tanh^2 c_j)
-// Every child k of j gets its dz_f,k = dc_j c_k f_k (1 - f_k) written to row inv_perm[k] of G (the
-// operand of the child level's GEMMs; pad units as zeros).
-// Writes dZ row r = [dz_i | dz_o | dz_u | sum_k dz_f,k] (K-blocked, gate stride Hk), the same
-// transposed into dZt, and leaves the total dc_j in dc[j] for the children's level.  Only the
-// first n_gates blocks are written (3 at the leaf level, whose forget block is zero and unused).
-template <typename T>
+// Every child k of j gets its dz_f,k = dc_j c_k f_k (1 - f_k) written to row inv_perm[k] of G; a root writes its own row of
+// zeros.  Row r of dZ = [dz_i | dz_o | dz_u | sum_k dz_f,k]; a leaf's forget block is read by few and written only from row
+// zero_from on.  dc_j stays in dc[j] for the children's level.
+// Bound by memory: 36 bytes a unit of the node (bf16, with gh) and 8 per child, read and written in 16-byte pieces: 591 k
+// leaves, H = 512: 1.96 ms (4.6 TB/s), all 15 levels of 1.18 M nodes 5.9 ms (8.0 one unit a lane and dZ written twice).
+// Few rows: bound by the chain node -> children -> their rows, so several children's rows are in flight.
+struct CellArgs {
+    const int32_t *perm, *inv_perm, *child_ptr, *child_idx;
+    int32_t *parent_of;
+    const float *c, *gh, *gc;
+    const void *gates, *fgate, *dhs, *ufg;
+    float *dc;
+    void *dZ, *G;
+    int64_t rows_alloc;
+    int row0, n_rows, H, Hk, zero_from;      // the level's rows are positions row0 .. row0 + n_rows
+};
+template <typename T> constexpr int kKidsAhead = sizeof(T) == 4 ? 4 : 2;
+template <typename T, bool VEC, bool LEAVES>
 __global__ void __launch_bounds__(kT)
-bwd_cell_kernel(const int32_t *__restrict__ nodes, int n_rows, int H, int Hk,
-                const int32_t *__restrict__ child_ptr, const int32_t *__restrict__ child_idx,
-                const int32_t *__restrict__ parent_of,
-                const float *__restrict__ c, const T *__restrict__ gates, const T *__restrict__ fgate,
-                const float *__restrict__ gh, const float *__restrict__ gc, const T *__restrict__ dhs,
-                const T *__restrict__ ufg, float *__restrict__ dc,
-                const int32_t *__restrict__ inv_perm, T *__restrict__ G, int64_t g_rows_alloc,
-                T *__restrict__ dZ, int64_t dz_rows_alloc, T *__restrict__ dZt, int64_t zt_rows_alloc, int n_gates) {
-    constexpr int RT = 64 / (int)sizeof(T);
-    __shared__ T tile[4][RT][64 + 2];
-    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-    const int r0 = blockIdx.x * RT, m0 = blockIdx.y * 64, m = m0 + lane;
-    char *zb = reinterpret_cast<char *>(dZ);
-#pragma unroll
-    for (int i = 0; i < RT / 4; ++i) {
-        const int rr = w + 4 * i, r = r0 + rr;
-        float dz[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-        if (r < n_rows && m < H) {
-            const int64_t j = nodes[r];
-            const float gi = to_f32<T>(gates[j * 3 * H + m]), go = to_f32<T>(gates[j * 3 * H + H + m]),
-                        gu = to_f32<T>(gates[j * 3 * H + 2 * H + m]);
-            const float th = tanhf(c[j * H + m]);
-            const int64_t p = parent_of[j];
-            float dhj = (gh ? gh[j * H + m] : 0.0f) + (ufg ? to_f32<T>(ufg[(int64_t)r * H + m]) : 0.0f);
-            float dcj = gc ? gc[j * H + m] : 0.0f;
-            if (p >= 0) {
-                dhj += to_f32<T>(dhs[p * H + m]);
-                dcj += dc[p * H + m] * to_f32<T>(fgate[j * H + m]);
-            }
-            dcj += dhj * go * (1.0f - th * th);
-            dc[j * H + m] = dcj;
-            float dzf_sum = 0.0f;
-            for (int e = child_ptr[j]; e < child_ptr[j + 1]; ++e) {
-                const int64_t k = child_idx[e];
-                const float fk = to_f32<T>(fgate[k * H + m]);
-                const float dzf = dcj * c[k * H + m] * fk * (1.0f - fk);
-                dzf_sum += dzf;
-                *reinterpret_cast<T *>(reinterpret_cast<char *>(G) +
-                                       operand_offset(inv_perm[k], (int64_t)m * sizeof(T), g_rows_alloc)) = from_f32<T>(dzf);
-            }
-            dz[0] = dcj * gu * gi * (1.0f - gi);
-            dz[1] = dhj * th * go * (1.0f - go);
-            dz[2] = dcj * gi * (1.0f - gu * gu);
-            dz[3] = dzf_sum;
-        } else if (r < n_rows) {    // pad units of the children's rows
-            const int64_t j = nodes[r];
-            for (int e = child_ptr[j]; e < child_ptr[j + 1]; ++e)
-                *reinterpret_cast<T *>(reinterpret_cast<char *>(G) +
-                                       operand_offset(inv_perm[child_idx[e]], (int64_t)m * sizeof(T), g_rows_alloc)) = T(0);
-        }
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-            if (g >= n_gates) break;
-            const T v = from_f32<T>(dz[g]);
-            tile[g][rr][lane] = v;
-            if (r < n_rows)
-                *reinterpret_cast<T *>(zb + operand_offset(r, (int64_t)(g * Hk + m) * sizeof(T), dz_rows_alloc)) = v;
-        }
-    }
-    __syncthreads();
-    store_transposed_tile<T, 4>(tile, t, Hk, m0, dZt, zt_rows_alloc, n_gates);
-}
-
-// ---- transposes into K-blocked operands ---------------------------------------------
-// dst row c, K position r  =  src[row(r)][c]  for r < n_rows, 0 for n_rows <= r < k_pad: the rows
-// of a level become the reduction axis of the weight-gradient GEMMs.  row(r) = index[r] or r;
-// the source is row-major with stride ld_src, or K-blocked itself when src_rows_alloc > 0.  A
-// block moves one 64-byte slab of the destination's K axis (RT = 32 bf16 / 16 fp32 source rows)
-// times 64 columns; a thread stores 16 bytes, and since consecutive destination rows are
-// consecutive inside a slab a wave stores 1 KB of consecutive memory.
-// SRC selects how the tile is read: SRC_SCALAR one element per thread and step (any row
-// stride), SRC_VEC LW bytes per thread and step (row-major rows that start on LW-byte
-// boundaries; LW = 16 or 8), SRC_KB 16 bytes per thread from a K-blocked source whose width is
-// a multiple of 64.
-enum { SRC_SCALAR = 0, SRC_VEC = 1, SRC_KB = 2 };
-template <typename T, int SRC, int LW = 16>
-__global__ void __launch_bounds__(kT)
-transpose_kb_kernel(const T *__restrict__ src, const int32_t *__restrict__ index, int64_t ld_src,
-                    int64_t src_rows_alloc, int n_rows, int n_cols, T *__restrict__ dst, int64_t dst_rows_alloc) {
-    constexpr int RT = 64 / (int)sizeof(T);
-    constexpr int PER = 16 / (int)sizeof(T);        // elements in 16 bytes
-    __shared__ T tile[RT][64 + 2];
-    const int r0 = blockIdx.x * RT, c0 = blockIdx.y * 64;
+bwd_cell_kernel(const CellArgs a) {
+    constexpr int PER = kPer<T>;
     const int t = threadIdx.x;
-    if (SRC == SRC_SCALAR) {
-        const int tx = t & 63, ty = t >> 6;          // 64 columns x 4 rows per sweep
+    const int i = blockIdx.x * kRows<T> + t / kPieces<T>;          // row of the level
+    if (i >= a.n_rows) return;
+    const int m0 = blockIdx.y * 64 + (t % kPieces<T>) * PER, left = a.H - m0;
+    const int64_t r = a.row0 + i, j = a.perm[r];
+    const int64_t p = a.parent_of[j];
+    const int kid0 = LEAVES ? 0 : a.child_ptr[j], kid1 = LEAVES ? 0 : a.child_ptr[j + 1];
+    const int64_t kb = (int64_t)m0 * sizeof(T), gate_kb = (int64_t)a.Hk * sizeof(T);
+    const u32x4 zero = {0, 0, 0, 0};
+    const int64_t at = j * a.H + m0;
+    float dh[PER], dcj[PER], dzf[PER];
 #pragma unroll
-        for (int i = 0; i < RT / 4; ++i) {
-            const int r = r0 + ty + 4 * i, cc = c0 + tx;
-            T v = T(0);
-            if (r < n_rows && cc < n_cols) v = src[(int64_t)(index ? index[r] : r) * ld_src + cc];
-            tile[ty + 4 * i][tx] = v;
+    for (int e = 0; e < PER; ++e) dh[e] = dcj[e] = dzf[e] = 0.0f;
+    if (left > 0) {
+        float v[PER], w[PER], o[PER], cj[PER];
+        load_units<T, PER, VEC>(static_cast<const T *>(a.gates) + j * 3 * a.H + a.H + m0, left, o);
+        load_units<float, PER, true>(a.c + at, left, cj);
+        if (a.gh) load_units<float, PER, true>(a.gh + at, left, dh);
+        if (a.gc) load_units<float, PER, true>(a.gc + at, left, dcj);
+        if (p >= 0) {
+            load_units<T, PER, VEC>(static_cast<const T *>(a.ufg) + (int64_t)i * a.H + m0, left, v);
+            load_units<T, PER, VEC>(static_cast<const T *>(a.dhs) + p * a.H + m0, left, w);
+#pragma unroll
+            for (int e = 0; e < PER; ++e) dh[e] = dh[e] + v[e] + w[e];
+            load_units<T, PER, VEC>(static_cast<const T *>(a.fgate) + at, left, v);
+            load_units<float, PER, true>(a.dc + p * a.H + m0, left, w);
+#pragma unroll
+            for (int e = 0; e < PER; ++e) dcj[e] += w[e] * v[e];
         }
-    } else if (SRC == SRC_VEC) {
-        // a row's 64 columns are 64 / PL pieces of LW bytes; 256 threads sweep the tile
-        constexpr int PL = LW / (int)sizeof(T);
-        constexpr int PPR = 64 / PL;
+        float dzo[PER];
 #pragma unroll
-        for (int it = 0; it < RT * PPR / kT; ++it) {
-            const int idx = t + kT * it;
-            const int row = idx / PPR, col = (idx % PPR) * PL;
-            T v[PL];
+        for (int e = 0; e < PER; ++e) {
+            const float th = tanhf(cj[e]);
+            dcj[e] += dh[e] * o[e] * (1.0f - th * th);
+            dzo[e] = dh[e] * th * o[e] * (1.0f - o[e]);
+        }
+        store16(a.dZ, r, gate_kb + kb, a.rows_alloc, pack_units<T>(dzo));
+        load_units<T, PER, VEC>(static_cast<const T *>(a.gates) + j * 3 * a.H + m0, left, v);
+        load_units<T, PER, VEC>(static_cast<const T *>(a.gates) + j * 3 * a.H + 2 * a.H + m0, left, w);
+        float dzi[PER], dzu[PER];
 #pragma unroll
-            for (int e = 0; e < PL; ++e) v[e] = T(0);
-            if (r0 + row < n_rows && c0 + col < n_cols) {
-                const T *a = src + (int64_t)(index ? index[r0 + row] : r0 + row) * ld_src + c0 + col;
-                if (c0 + col + PL <= n_cols) {
-                    if constexpr (LW == 16) *reinterpret_cast<u32x4 *>(v) = *reinterpret_cast<const u32x4 *>(a);
-                    else *reinterpret_cast<uint2 *>(v) = *reinterpret_cast<const uint2 *>(a);
-                } else {
+        for (int e = 0; e < PER; ++e) {
+            dzi[e] = dcj[e] * w[e] * v[e] * (1.0f - v[e]);
+            dzu[e] = dcj[e] * v[e] * (1.0f - w[e] * w[e]);
+        }
+        store16(a.dZ, r, kb, a.rows_alloc, pack_units<T>(dzi));
+        store16(a.dZ, r, 2 * gate_kb + kb, a.rows_alloc, pack_units<T>(dzu));
+        if (!LEAVES) {      // the children's level reads it
+            if (left >= PER) {
+                typedef u32x4 __attribute__((aligned(4))) u32x4a;
 #pragma unroll
-                    for (int e = 0; e < PL; ++e)
-                        if (c0 + col + e < n_cols) v[e] = a[e];
+                for (int q = 0; q < PER / 4; ++q) {
+                    const u32x4 b = {__float_as_uint(dcj[4 * q]), __float_as_uint(dcj[4 * q + 1]), __float_as_uint(dcj[4 * q + 2]), __float_as_uint(dcj[4 * q + 3])};
+                    reinterpret_cast<u32x4a *>(a.dc + at)[q] = b;
                 }
-            }
-#pragma unroll
-            for (int e = 0; e < PL; ++e) tile[row][col + e] = v[e];
-        }
-    } else {
-        // the tile is 64 / RT slabs of RT rows x 64 bytes: 256 threads x 16 bytes
-        const int piece = t & 3, sl = (t >> 2) / RT;
-        const int row = (t >> 2) % RT, col = sl * RT + piece * PER;
-        T v[PER];
-#pragma unroll
-        for (int e = 0; e < PER; ++e) v[e] = T(0);
-        if (r0 + row < n_rows)
-            *reinterpret_cast<u32x4 *>(v) = *reinterpret_cast<const u32x4 *>(
-                reinterpret_cast<const char *>(src) + ((int64_t)((c0 + col) / RT) * src_rows_alloc + r0 + row) * 64 + piece * 16);
-#pragma unroll
-        for (int e = 0; e < PER; ++e) tile[row][col + e] = v[e];
-    }
-    __syncthreads();
-    const int cc = t >> 2, piece = t & 3;
-    if (c0 + cc >= n_cols) return;
-    T out[PER];
-#pragma unroll
-    for (int e = 0; e < PER; ++e) out[e] = tile[piece * PER + e][cc];
-    char *d = reinterpret_cast<char *>(dst) + ((int64_t)blockIdx.x * dst_rows_alloc + (c0 + cc)) * 64 + piece * 16;
-    *reinterpret_cast<u32x4 *>(d) = *reinterpret_cast<const u32x4 *>(out);
-}
-
-// picks the widest read the source allows
-template <typename T>
-int launch_transpose(const T *src, const int32_t *index, int64_t ld_src, int64_t src_rows_alloc, int n_rows, int n_cols,
-                     int k_pad, T *dst, int64_t dst_rows_alloc, hipStream_t st) {
-    constexpr int RT = 64 / (int)sizeof(T);
-    const dim3 grid((unsigned)(k_pad / RT), (unsigned)ceil_div(n_cols, 64));
-    const uintptr_t base = reinterpret_cast<uintptr_t>(src);
-    const int64_t row_bytes = ld_src * (int64_t)sizeof(T);
-    if (src_rows_alloc > 0) {
-        if (n_cols % 64 != 0) return JITDB_E_BADARG;
-        transpose_kb_kernel<T, SRC_KB><<<grid, kT, 0, st>>>(src, index, ld_src, src_rows_alloc, n_rows, n_cols, dst, dst_rows_alloc);
-    } else if (row_bytes % 16 == 0 && base % 16 == 0) {
-        transpose_kb_kernel<T, SRC_VEC, 16><<<grid, kT, 0, st>>>(src, index, ld_src, 0, n_rows, n_cols, dst, dst_rows_alloc);
-    } else if (row_bytes % 8 == 0 && base % 8 == 0) {
-        transpose_kb_kernel<T, SRC_VEC, 8><<<grid, kT, 0, st>>>(src, index, ld_src, 0, n_rows, n_cols, dst, dst_rows_alloc);
-    } else {
-        transpose_kb_kernel<T, SRC_SCALAR><<<grid, kT, 0, st>>>(src, index, ld_src, 0, n_rows, n_cols, dst, dst_rows_alloc);
-    }
-    JITDB_LAUNCH_CHECK();
-    return JITDB_OK;
-}
-
-// The child sums of a level, transposed: dst row c, K position r = sum over the children k of
-// node nodes[r] of h_k[c], summed in fp32 and rounded once as the forward does.  Same tiles
-// and stores as transpose_kb_kernel; VEC reads 16 bytes of a child's row per thread.
-template <typename T, bool VEC>
-__global__ void __launch_bounds__(kT)
-hsum_transpose_kernel(const T *__restrict__ h, const int32_t *__restrict__ nodes, int n_rows, int H,
-                      const int32_t *__restrict__ child_ptr, const int32_t *__restrict__ child_idx,
-                      T *__restrict__ dst, int64_t dst_rows_alloc) {
-    constexpr int RT = 64 / (int)sizeof(T);
-    constexpr int PER = 16 / (int)sizeof(T);
-    __shared__ T tile[RT][64 + 2];
-    const int r0 = blockIdx.x * RT, c0 = blockIdx.y * 64;
-    const int t = threadIdx.x;
-    const int row = t / (64 / PER), col = (t % (64 / PER)) * PER;
-    float sum[PER];
-#pragma unroll
-    for (int e = 0; e < PER; ++e) sum[e] = 0.0f;
-    if (r0 + row < n_rows && c0 + col < H) {
-        const int64_t j = nodes[r0 + row];
-        for (int ce = child_ptr[j]; ce < child_ptr[j + 1]; ++ce) {
-            const T *a = h + (int64_t)child_idx[ce] * H + c0 + col;
-            if (VEC && c0 + col + PER <= H) {
-                T v[PER];
-                *reinterpret_cast<u32x4 *>(v) = *reinterpret_cast<const u32x4 *>(a);
-#pragma unroll
-                for (int e = 0; e < PER; ++e) sum[e] += to_f32<T>(v[e]);
             } else {
 #pragma unroll
                 for (int e = 0; e < PER; ++e)
-                    if (c0 + col + e < H) sum[e] += to_f32<T>(a[e]);
+                    if (e < left) a.dc[at + e] = dcj[e];
+            }
+        }
+    } else {
+#pragma unroll
+        for (int g = 0; g < 3; ++g) store16(a.dZ, r, g * gate_kb + kb, a.rows_alloc, zero);
+    }
+    if (!LEAVES) {
+        // kKidsAhead children at a time: their ids, then their rows, then their arithmetic (the last one's again past the end)
+        constexpr int K = kKidsAhead<T>;
+        for (int ce = kid0; ce < kid1; ce += K) {
+            int64_t kid[K];
+            float fk[K][PER], ck[K][PER];
+            int pos[K];
+#pragma unroll
+            for (int q = 0; q < K; ++q) kid[q] = a.child_idx[ce + q < kid1 ? ce + q : kid1 - 1];
+#pragma unroll
+            for (int q = 0; q < K; ++q) {
+                pos[q] = a.inv_perm[kid[q]];
+#pragma unroll
+                for (int e = 0; e < PER; ++e) fk[q][e] = ck[q][e] = 0.0f;
+                if (left > 0) {
+                    load_units<T, PER, VEC>(static_cast<const T *>(a.fgate) + kid[q] * a.H + m0, left, fk[q]);
+                    load_units<float, PER, true>(a.c + kid[q] * a.H + m0, left, ck[q]);
+                }
+            }
+#pragma unroll
+            for (int q = 0; q < K; ++q) {
+                if (ce + q >= kid1) break;
+#pragma unroll
+                for (int e = 0; e < PER; ++e) {
+                    ck[q][e] = dcj[e] * ck[q][e] * fk[q][e] * (1.0f - fk[q][e]);
+                    dzf[e] += ck[q][e];
+                }
+                store16(a.G, pos[q], kb, a.rows_alloc, pack_units<T>(ck[q]));
+                if (m0 == 0) a.parent_of[kid[q]] = (int32_t)j;
             }
         }
     }
-#pragma unroll
-    for (int e = 0; e < PER; ++e) tile[row][col + e] = from_f32<T>(sum[e]);
-    __syncthreads();
-    const int cc = t >> 2, piece = t & 3;
-    if (c0 + cc >= H) return;
-    T out[PER];
-#pragma unroll
-    for (int e = 0; e < PER; ++e) out[e] = tile[piece * PER + e][cc];
-    char *d = reinterpret_cast<char *>(dst) + ((int64_t)blockIdx.x * dst_rows_alloc + (c0 + cc)) * 64 + piece * 16;
-    *reinterpret_cast<u32x4 *>(d) = *reinterpret_cast<const u32x4 *>(out);
+    if (!LEAVES || r >= a.zero_from) store16(a.dZ, r, 3 * gate_kb + kb, a.rows_alloc, pack_units<T>(dzf));
+    if (p < 0) store16(a.G, r, kb, a.rows_alloc, zero);
 }
 
-// one K-blocked row of ones (r < n_rows) and zeros (up to k_pad): the column of the weight
-// GEMM's right operand that turns its result into the bias gradient
+// ---- data gradients: rows of nodes times a weight operand -----------------------------------
+// C [node row, feature] = A [node rows, K] B [features, K]^T, both K-blocked.  out row = map ? map[row] : row.
+struct RowProduct {
+    const char *A; int n_rows;
+    const char *B; int64_t b_alloc; int n_feat;
+    int n_slabs;                   // 64-byte slabs of K
+    void *out; const int32_t *map; int ld; int f32_out;
+};
 template <typename T>
-__global__ void __launch_bounds__(kT)
-ones_row_kernel(T *__restrict__ dst, int64_t dst_rows_alloc, int row, int n_rows, int k_pad) {
-    const int r = blockIdx.x * kT + threadIdx.x;
-    if (r >= k_pad) return;
-    *reinterpret_cast<T *>(reinterpret_cast<char *>(dst) + operand_offset(row, (int64_t)r * sizeof(T), dst_rows_alloc)) =
-        from_f32<T>(r < n_rows ? 1.0f : 0.0f);
+__device__ __forceinline__ void store4(const RowProduct &g, int64_t row, int feat, const float (&v)[4], bool vec) {
+    const int64_t at = row * g.ld + feat;
+    if (g.f32_out || sizeof(T) == 4) {
+        float *o = static_cast<float *>(g.out) + at;
+        if (vec && feat + 4 <= g.n_feat) *reinterpret_cast<float4 *>(o) = make_float4(v[0], v[1], v[2], v[3]);
+        else
+            for (int e = 0; e < 4; ++e)
+                if (feat + e < g.n_feat) o[e] = v[e];
+    } else {
+        T *o = static_cast<T *>(g.out) + at;
+        if (vec && feat + 4 <= g.n_feat) {
+            const u32x2 b = {(uint32_t)f32_to_bf16(v[0]) | ((uint32_t)f32_to_bf16(v[1]) << 16),
+                             (uint32_t)f32_to_bf16(v[2]) | ((uint32_t)f32_to_bf16(v[3]) << 16)};
+            *reinterpret_cast<u32x2 *>(o) = b;
+        } else
+            for (int e = 0; e < 4; ++e)
+                if (feat + e < g.n_feat) o[e] = from_f32<T>(v[e]);
+    }
 }
 
-// dW [4H, D], dU [4H, H], db [4H] from the packed accumulators: dMp [D + 1 + H, 4 Hk] (transposed:
-// row n < D belongs to x_n, row D to the bias, row D + 1 + n' to hs_n'), dUfp [Hk, H]
-__global__ void __launch_bounds__(kT)
-unpack_grads_kernel(const float *__restrict__ dMp, const float *__restrict__ dUfp,
-                    int D, int H, int Hk, float *__restrict__ dW, float *__restrict__ dU, float *__restrict__ db) {
-    const int ld = D + 1 + H;
-    const int64_t total = (int64_t)4 * H * ld;
-    for (int64_t idx = (int64_t)blockIdx.x * kT + threadIdx.x; idx < total; idx += (int64_t)gridDim.x * kT) {
-        const int row = (int)(idx / ld), col = (int)(idx % ld);
-        const int g = row / H, m = row % H;
-        const float v = dMp[(int64_t)col * 4 * Hk + g * Hk + m];
-        if (col < D) dW[(int64_t)row * D + col] = v;
-        else if (col == D) db[row] = v;
-        else dU[(int64_t)row * H + (col - D - 1)] = g < 3 ? v : dUfp[(int64_t)m * H + (col - D - 1)];
+// Many rows (kTileMinBlocks tiles; 188 of them took 35 us, the thin kernel 56): the 128 x 256 tiles of the level kernel, features as the tile's rows and nodes as its columns (300 features
+// pad to 384 that way, not to 512), so that a lane ends up with four consecutive features of one node.
+template <typename T>
+__global__ void __launch_bounds__(kDmaThreads, 2)
+rows_tile_kernel(LevelArgs a, const RowProduct g) {
+    __shared__ __attribute__((aligned(1024))) char lds[kDmaBufs * kDmaBuf];
+    __shared__ __attribute__((aligned(256))) char sink[4 * 256];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int wm = wave >> 1, wn = wave & 1, hf = lane >> 5, l32 = lane & 31;
+    int row_tile, col_tile;
+    if (!block_to_tile(blockIdx.x, a.n_col_tiles, a.n_row_tiles, col_tile, row_tile)) return;
+    floatx16 acc[2][4];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[i][q][v] = 0.0f;
+    __shared__ int s_row[kBN];
+    {
+        const int row = col_tile * kBN + (int)threadIdx.x;
+        s_row[threadIdx.x] = row >= g.n_rows ? -1 : g.map ? g.map[row] : row;
     }
+    dma_gemm<T, MODE_SWAP>(a, lds, nullptr, row_tile * kDmaBM, col_tile, acc, sink, []() {});
+    const int step = g.f32_out || sizeof(T) == 4 ? 16 : 8;
+    const bool vec = (g.ld & 3) == 0 && (reinterpret_cast<uintptr_t>(g.out) & (step - 1)) == 0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int row = s_row[wn * 128 + q * 32 + l32];
+        if (row < 0) continue;
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int feat = row_tile * kDmaBM + wm * 64 + i * 32 + v * 8 + hf * 4;
+                if (feat >= g.n_feat) continue;
+                const float four[4] = {acc[i][q][4 * v], acc[i][q][4 * v + 1], acc[i][q][4 * v + 2], acc[i][q][4 * v + 3]};
+                store4<T>(g, row, feat, four, vec);
+            }
+    }
+}
+
+// Few rows: 16 RT rows x 16 CT features in a block, K dealt to its four waves in slabs, fragments straight from L2 (16 rows x
+// 64 bytes are 1 KB of consecutive memory), partial sums added through LDS.  Two products share a launch (a level's dhs and
+// the next level's ufg).  Bound by the latency of a wave's slabs, so small tiles (16 x 32) until they fill the chip.
+struct ThinArgs {
+    RowProduct g[2];
+    int64_t rows_alloc;
+    int blocks0;                   // blocks of the first product
+};
+template <typename T, int RT, int CT>
+__global__ void __launch_bounds__(kT)
+rows_thin_kernel(const ThinArgs a) {
+    constexpr int kStride = 16 * CT + 4;
+    __shared__ __attribute__((aligned(16))) float part[4][16 * RT * kStride];
+    const bool second = (int)blockIdx.x >= a.blocks0;
+    const RowProduct &g = a.g[second ? 1 : 0];
+    const int b = (int)blockIdx.x - (second ? a.blocks0 : 0);
+    const int col_tiles = (g.n_feat + 16 * CT - 1) / (16 * CT);
+    const int row0 = b / col_tiles * 16 * RT, col0 = b % col_tiles * 16 * CT;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    floatx4 acc[RT][CT];
+#pragma unroll
+    for (int i = 0; i < RT; ++i)
+#pragma unroll
+        for (int c = 0; c < CT; ++c) acc[i][c] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+    const int64_t lane_off = (lane & 15) * 64 + (lane >> 4) * 16;
+    const char *pa = g.A + (int64_t)row0 * 64 + lane_off, *pb = g.B + (int64_t)col0 * 64 + lane_off;
+    const int64_t a_slab = a.rows_alloc * 64, b_slab = g.b_alloc * 64;
+    struct Frags { u32x4 a[RT], b[CT]; };
+    auto load = [&](int s, Frags &f) __attribute__((always_inline)) {
+#pragma unroll
+        for (int c = 0; c < CT; ++c) f.b[c] = *reinterpret_cast<const u32x4 *>(pb + s * b_slab + c * 1024);
+#pragma unroll
+        for (int i = 0; i < RT; ++i) f.a[i] = *reinterpret_cast<const u32x4 *>(pa + s * a_slab + i * 1024);
+    };
+    auto multiply = [&](const Frags &f) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < RT; ++i)
+#pragma unroll
+            for (int c = 0; c < CT; ++c) mfma16<T>(f.a[i], f.b[c], acc[i][c]);
+    };
+    Frags F[3];                                     // three slabs in flight
+    const int n = g.n_slabs;
+#pragma unroll
+    for (int q = 0; q < 3; ++q)
+        if (wave + 4 * q < n) load(wave + 4 * q, F[q]);
+    for (int s = wave; s < n; s += 12) {
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+            if (s + 4 * q < n) multiply(F[q]);
+            if (s + 4 * q + 12 < n) load(s + 4 * q + 12, F[q]);
+        }
+    }
+    const int u = lane & 15;
+#pragma unroll
+    for (int i = 0; i < RT; ++i)
+#pragma unroll
+        for (int c = 0; c < CT; ++c)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) part[wave][(i * 16 + (lane >> 4) * 4 + v) * kStride + c * 16 + u] = acc[i][c][v];
+    __syncthreads();
+    const int step = g.f32_out || sizeof(T) == 4 ? 16 : 8;
+    const bool vec = (g.ld & 3) == 0 && (reinterpret_cast<uintptr_t>(g.out) & (step - 1)) == 0;
+    for (int q = threadIdx.x; q < 16 * RT * 4 * CT; q += kT) {
+        const int i = q / (4 * CT), c = q % (4 * CT) * 4;
+        if (row0 + i >= g.n_rows || col0 + c >= g.n_feat) continue;
+        float four[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int w = 0; w < 4; ++w)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) four[e] += part[w][i * kStride + c + e];
+        store4<T>(g, g.map ? g.map[row0 + i] : row0 + i, col0 + c, four, vec);
+    }
+}
+
+// ---- weight gradients: sums over the nodes --------------------------------------------------
+// Up to three products A^T B over rows [begin, n_rows) of K-blocked operands, cut into 128 x 256 tiles and `splits` ranges of
+// rows_per_split rows.  Bound by the matrix cores and LDS reads (fragments are read transposed at the rate of the plain ones):
+// 1.18 M nodes, D = 300, H = 512, bf16: 3.6 ms, 890 TFLOP/s of padded tiles.  A block leaves its tile of partial sums in register order (whole 1 KB stores); grad_reduce_kernel adds
+// the ranges in order, so the result does not depend on timing.  Blocks of one range run on one XCD (b % 8), whose L2 then
+// reads that range of every operand once.
+struct TnProblem {
+    const char *A, *B;
+    int m_tiles, n_tiles;
+    int tile0;                 // index of its first tile
+    int begin, begin_f;        // first row of the reduction; of the tiles from column tile f_tile on
+    int f_tile;
+};
+struct TnArgs {
+    TnProblem p[3];
+    int64_t rows_alloc;
+    int n_rows, rows_per_split, splits, tiles;
+    float *partial;
+    float *dW, *dU, *db;
+    int D, H, Hk;
+};
+__device__ __forceinline__ int tn_decode(const TnArgs &a, int tile, int &m, int &n, int &begin) {
+    const int q = tile >= a.p[2].tile0 ? 2 : tile >= a.p[1].tile0 ? 1 : 0;
+    const TnProblem &p = a.p[q];
+    m = (tile - p.tile0) / p.n_tiles;
+    n = (tile - p.tile0) % p.n_tiles;
+    begin = n >= p.f_tile ? p.begin_f : p.begin;
+    return q;
+}
+template <typename T>
+__global__ void __launch_bounds__(kDmaThreads, 2)
+tn_kernel(const TnArgs e) {
+    __shared__ __attribute__((aligned(1024))) char lds[kDmaBufs * kDmaBuf];
+    const int q = blockIdx.x >> 3, split = (blockIdx.x & 7) + 8 * (q / e.tiles), tile = q % e.tiles;
+    if (split >= e.splits) return;
+    int mt, nt, begin;
+    const int which = tn_decode(e, tile, mt, nt, begin);
+    int k0 = split * e.rows_per_split, k1 = k0 + e.rows_per_split;
+    if (k0 < begin) k0 = begin;
+    if (k1 > e.n_rows) k1 = e.n_rows;
+    if (k0 >= k1) return;
+    constexpr int ESZ = (int)sizeof(T);
+    LevelArgs a = {};
+    a.n_rows_alloc = (int)e.rows_alloc;
+    a.NPU = (int)e.rows_alloc;
+    a.stack = e.p[which].A + (int64_t)(mt * 128 * ESZ / 64) * e.rows_alloc * 64 + (int64_t)k0 * 64;
+    a.Bp = e.p[which].B + (int64_t)(nt * 256 * ESZ / 64) * e.rows_alloc * 64 + (int64_t)k0 * 64;
+    a.Dp = (k1 - k0) / (64 / ESZ) * kDmaStage / ESZ;         // stages of 64 / ESZ rows
+    floatx16 acc[2][4];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[i][g][v] = 0.0f;
+    dma_gemm<T, MODE_TN>(a, lds, nullptr, 0, 0, acc, nullptr, []() {});
+    float4 *out = reinterpret_cast<float4 *>(e.partial + ((int64_t)split * e.tiles + tile) * (128 * 256)) + threadIdx.x;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+                out[((i * 4 + g) * 4 + v) * kDmaThreads] = make_float4(acc[i][g][4 * v], acc[i][g][4 * v + 1], acc[i][g][4 * v + 2], acc[i][g][4 * v + 3]);
+}
+
+__global__ void __launch_bounds__(kT)
+grad_reduce_kernel(const TnArgs e) {
+    const int tile = blockIdx.y, rest = blockIdx.x, t = threadIdx.x;
+    int mt, nt, begin;
+    const int which = tn_decode(e, tile, mt, nt, begin);
+    const int lane = t & 63, wave = t >> 6, i = rest >> 4, g = (rest >> 2) & 3, v = rest & 3;
+    const int m = mt * 128 + (wave >> 1) * 64 + i * 32 + v * 8 + (lane >> 5) * 4;
+    const int n = nt * 256 + (wave & 1) * 128 + g * 32 + (lane & 31);
+    const int gate = which == 2 ? 3 : n / e.Hk, u = which == 2 ? n : n % e.Hk;
+    const int width = which == 0 ? e.D + 1 : e.H;
+    if (m >= width || u >= e.H || gate > 3 || (which == 1 && gate == 3)) return;
+    const float4 *in = reinterpret_cast<const float4 *>(e.partial + (int64_t)tile * (128 * 256)) + rest * kT + t;
+    float4 s = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    if (begin < e.n_rows)
+#pragma unroll 4
+        for (int k = begin / e.rows_per_split; k < e.splits; ++k) {
+            const float4 p = in[(int64_t)k * e.tiles * (128 * 256 / 4)];
+            s.x += p.x; s.y += p.y; s.z += p.z; s.w += p.w;
+        }
+    const int64_t row = (int64_t)gate * e.H + u;
+    const int ld = which == 0 ? e.D : e.H;
+    float *o = (which == 0 ? e.dW : e.dU) + row * ld + m;
+    if ((ld & 3) == 0 && m + 4 <= ld && (reinterpret_cast<uintptr_t>(o) & 15) == 0) {
+        *reinterpret_cast<float4 *>(o) = s;
+    } else {
+        const float four[4] = {s.x, s.y, s.z, s.w};
+#pragma unroll
+        for (int x = 0; x < 4; ++x) {
+            if (m + x < ld) o[x] = four[x];
+            else if (m + x == ld && which == 0) e.db[row] = four[x];
+        }
+        return;
+    }
+    // (a vector store never covers column D: m + 4 <= D)
 }
 
 // ---- workspace ---------------------------------------------------------------------
 struct BwdDims {
     int D, H, Hk;         // Hk: H rounded up to 64 elements (whole stages of the tiled GEMM)
-    int n_max, n_pad;     // largest level; rounded up to 64 (reduction axis of the weight GEMMs)
+    int n_max;            // largest level
     size_t esz;
 };
 struct BwdWs {
-    float *dc, *dMp, *dUfp;
+    float *dc, *partial;
     void *dhs, *ufg;      // in the operands' element type
     int32_t *parent_of;
-    void *Mt, *Uft, *dZ, *G, *dZt, *At, *Gt, *Hkt;
+    void *Wt, *Ut, *Uft, *dZ, *G, *AX, *AH, *AS;
+    int64_t rows_alloc, w_alloc, u_alloc;
     size_t bytes;
 };
+
+// How the sums over nodes are cut: as many ranges as give every compute unit two blocks, but no range under kMinSplitRows rows
+// (each costs 128 KB of partial sums a tile).  Long sums are cut eight times finer: the ranges, dealt whole to the XCDs, then
+// come out even (13 ranges of 90 k rows: 5.4 ms, two on five of the XCDs and one on the others).
+constexpr int kMinSplitRows = 128, kLongSplitRows = 4096;
+struct TnPlan { int tiles[3], begin[3], f_tile, rows, rows_per_split, splits, total_tiles; };
+TnPlan plan_tn(int64_t n, int64_t first_internal, const BwdDims &d) {
+    TnPlan p = {};
+    p.rows = n > 0 ? (int)round_up(n, 64) : 64;
+    const int fi = (int)(first_internal / 64 * 64), n4 = 4 * d.Hk / 256;
+    p.begin[1] = fi;
+    // the column tiles that hold nothing but the forget gate
+    p.f_tile = 3 * d.Hk % 256 == 0 ? 3 * d.Hk / 256 : n4;
+    const int mx = (int)ceil_div(d.D + 1, 128), mh = (int)ceil_div(d.H, 128);
+    p.tiles[0] = mx * n4;
+    p.tiles[1] = mh * (int)ceil_div(3 * d.Hk, 256);
+    p.tiles[2] = mh * (int)ceil_div(d.Hk, 256);
+    p.total_tiles = p.tiles[0] + p.tiles[1] + p.tiles[2];
+    const int f_tiles = mx * (n4 - p.f_tile);
+    const int64_t work = (int64_t)(p.tiles[0] - f_tiles + p.tiles[2]) * p.rows + (int64_t)(p.tiles[1] + f_tiles) * (p.rows - fi);
+    int64_t rps = round_up(ceil_div(work, 512), 64);
+    if (rps >= 4 * kLongSplitRows) rps = round_up(rps / 8, 64);
+    if (rps < kMinSplitRows) rps = kMinSplitRows;
+    if (rps > p.rows) rps = p.rows;
+    p.rows_per_split = (int)rps;
+    p.splits = (int)ceil_div(p.rows, rps);
+    return p;
+}
 
 BwdWs carve_bwd_ws(int64_t n, const BwdDims &d, void *base) {
     Carver c(base);
     BwdWs w;
+    w.rows_alloc = round_up(n, 64) + 256;             // whole tiles of 256 rows are read from any row on
+    w.w_alloc = round_up(d.D, 256); w.u_alloc = round_up(d.H, 256);
+    const size_t row = (size_t)w.rows_alloc * d.esz;
     w.dc = c.take<float>((size_t)n * d.H);
     w.dhs = c.take<char>((size_t)n * d.H * d.esz);
     w.ufg = c.take<char>((size_t)d.n_max * d.H * d.esz);
-    w.dMp = c.take<float>((size_t)4 * d.Hk * (d.D + 1 + d.H));
-    w.dUfp = c.take<float>((size_t)d.Hk * d.H);
     w.parent_of = c.take<int32_t>((size_t)n);
-    w.Mt = c.take<char>((size_t)round_up(d.D + d.H, 256) * 4 * d.Hk * d.esz);
-    w.Uft = c.take<char>((size_t)round_up(d.H, 256) * d.Hk * d.esz);
-    w.dZ = c.take<char>((size_t)round_up(d.n_max, 128) * 4 * d.Hk * d.esz);
-    w.G = c.take<char>((size_t)(round_up(n, 128) + 128) * d.Hk * d.esz);   // all levels; whole row tiles are read
-    w.dZt = c.take<char>((size_t)round_up(4 * d.Hk, 128) * d.n_pad * d.esz);
-    w.At = c.take<char>((size_t)round_up(d.D + 1 + d.H, 256) * d.n_pad * d.esz);
-    w.Gt = c.take<char>((size_t)round_up(d.Hk, 128) * d.n_pad * d.esz);
-    w.Hkt = c.take<char>((size_t)round_up(d.H, 256) * d.n_pad * d.esz);
+    w.Wt = c.take<char>((size_t)w.w_alloc * 4 * d.Hk * d.esz);
+    w.Ut = c.take<char>((size_t)w.u_alloc * 3 * d.Hk * d.esz);
+    w.Uft = c.take<char>((size_t)w.u_alloc * d.Hk * d.esz);
+    // whole tiles of columns are read: 128 of the left operands, 256 of the right ones
+    w.dZ = c.take<char>(row * round_up(4 * d.Hk, 256));
+    w.G = c.take<char>(row * round_up(d.Hk, 256));
+    w.AX = c.take<char>(row * round_up(d.D + 1, 128));
+    w.AH = c.take<char>(row * round_up(d.H, 128));
+    w.AS = c.take<char>(row * round_up(d.H, 128));
+    // no forest is cut into more ranges than one of leaves alone: the less there is to sum, the shorter the ranges
+    const TnPlan p = plan_tn(n, n, d);
+    w.partial = c.take<float>((size_t)p.splits * p.total_tiles * 128 * 256);
     w.bytes = c.off;
     return w;
 }
 
-int zero_bytes(void *p, size_t bytes, hipStream_t st) {    // bytes is a multiple of 16 (256-byte pieces)
-    const int64_t n16 = (int64_t)((bytes + 15) / 16);
-    const unsigned grid = (unsigned)(ceil_div(n16, kT) < 8192 ? ceil_div(n16, kT) : 8192);
-    fill_bytes16_kernel<<<grid ? grid : 1, kT, 0, st>>>(static_cast<u32x4 *>(p), n16);
+constexpr int kTileMinBlocks = 128;
+template <typename T>
+int launch_rows(const RowProduct *g, int n_products, int64_t rows_alloc, hipStream_t st) {
+    RowProduct todo[2];
+    int m = 0;
+    for (int q = 0; q < n_products; ++q)
+        if (g[q].n_rows > 0 && g[q].n_feat > 0) todo[m++] = g[q];
+    // enough 128 x 256 tiles for the chip: the tile kernel
+    int thin = 0;
+    for (int q = 0; q < m; ++q) {
+        const int64_t ft = ceil_div(todo[q].n_feat, 128), rt = ceil_div(todo[q].n_rows, kBN);
+        if (ft * rt < kTileMinBlocks) { todo[thin++] = todo[q]; continue; }
+        LevelArgs a = {};
+        a.stack = todo[q].B; a.n_rows_alloc = (int)todo[q].b_alloc;
+        a.Bp = todo[q].A; a.NPU = (int)rows_alloc;
+        a.Dp = todo[q].n_slabs * kDmaStage / (int)sizeof(T);
+        a.n_row_tiles = (int)ft; a.n_col_tiles = (int)rt;
+        rows_tile_kernel<T><<<(unsigned)(8 * ceil_div(rt, 8) * ft), kDmaThreads, 0, st>>>(a, todo[q]);
+        JITDB_LAUNCH_CHECK();
+    }
+    if (thin == 0) return JITDB_OK;
+    ThinArgs t = {};
+    t.rows_alloc = rows_alloc;
+    auto blocks = [&](const RowProduct &p, int rows, int cols) { return (int)(ceil_div(p.n_rows, rows) * ceil_div(p.n_feat, cols)); };
+    int big = 0;
+    for (int q = 0; q < thin; ++q) { t.g[q] = todo[q]; big += blocks(todo[q], 32, 64); }
+    const bool small = big < 2 * 256;
+    t.blocks0 = small ? blocks(t.g[0], 16, 32) : blocks(t.g[0], 32, 64);
+    int all = t.blocks0;
+    if (thin == 2) all += small ? blocks(t.g[1], 16, 32) : blocks(t.g[1], 32, 64);
+    if (small) rows_thin_kernel<T, 1, 2><<<(unsigned)all, kT, 0, st>>>(t);
+    else rows_thin_kernel<T, 2, 4><<<(unsigned)all, kT, 0, st>>>(t);
     JITDB_LAUNCH_CHECK();
     return JITDB_OK;
 }
@@ -420,105 +650,84 @@ int run_backward(const T *x, const T *W, const T *U, const BwdDims &d, const jit
                  const T *h, const float *c, const T *gates, const T *fgate,
                  const float *gh, const float *gc, float *dx, float *dW, float *dU, float *db,
                  const BwdWs &w, hipStream_t st) {
-    const int64_t n = s->n_nodes;
+    const int n = (int)s->n_nodes;
     const int L = s->n_levels;
     const int32_t *lp = s->host_level_ptr;
     const int D = d.D, H = d.H, Hk = d.Hk;
-    const jitdb_dtype dtype = sizeof(T) == 4 ? JITDB_F32 : JITDB_BF16;
+    for (int l = 0; l < L; ++l)
+        if (lp[l + 1] <= lp[l]) return JITDB_E_SCHEDULE;
     int rc;
-    if ((rc = zero_bytes(w.dMp, round_up((size_t)4 * Hk * (D + 1 + H) * 4, 256), st)) != JITDB_OK) return rc;
-    if ((rc = zero_bytes(w.dUfp, round_up((size_t)Hk * H * 4, 256), st)) != JITDB_OK) return rc;
-    const int64_t mt_alloc = round_up(D + H, 256), uft_alloc = round_up(H, 256);
-    const int64_t zt_alloc = round_up(4 * Hk, 128), at_alloc = round_up(D + 1 + H, 256);
-    const int64_t gt_alloc = round_up(Hk, 128), ht_alloc = round_up(H, 256);
-    pack_bwd_weights_kernel<T><<<1024, kT, 0, st>>>(W, U, D, H, Hk, static_cast<T *>(w.Mt), mt_alloc,
-                                                    static_cast<T *>(w.Uft), uft_alloc);
-    JITDB_LAUNCH_CHECK();
+    const TnPlan plan = plan_tn(n, lp[1], d);
     {
-        const unsigned g = (unsigned)ceil_div(n, kT);
-        fill_i32_kernel<<<g < 8192 ? g : 8192, kT, 0, st>>>(w.parent_of, n, -1);
-        JITDB_LAUNCH_CHECK();
-        parent_of_kernel<<<g, kT, 0, st>>>(s->child_ptr, s->child_idx, (int)n, w.parent_of);
+        PrepArgs a = {};
+        a.x = x; a.h = h; a.W = W; a.U = U; a.perm = s->perm; a.child_ptr = s->child_ptr; a.child_idx = s->child_idx;
+        a.parent_of = w.parent_of; a.AX = w.AX; a.AH = w.AH; a.AS = w.AS; a.dZ = w.dZ; a.G = w.G; a.Wt = w.Wt; a.Ut = w.Ut; a.Uft = w.Uft;
+        a.D = D; a.H = H; a.Hk = Hk; a.n = n; a.n_rows = plan.rows; a.first = plan.begin[1];
+        a.rows_alloc = w.rows_alloc; a.w_alloc = w.w_alloc; a.u_alloc = w.u_alloc;
+        a.x_groups = (int)ceil_div(D + 1, 64); a.h_groups = Hk / 64; a.row_blocks = (int)ceil_div(plan.rows, kRows<T>);
+        const int64_t w_blocks = ceil_div((int64_t)(D + H) * 4 * (Hk / kPer<T>), kT);
+        const dim3 grid((unsigned)((int64_t)a.row_blocks * (a.x_groups + a.h_groups) + (w_blocks < 1024 ? w_blocks : 1024)));
+        const bool vx = D * sizeof(T) % 4 == 0, vh = H * sizeof(T) % 4 == 0;
+        if (vx && vh) bwd_prepare_kernel<T, true, true><<<grid, kT, 0, st>>>(a);
+        else if (vx) bwd_prepare_kernel<T, true, false><<<grid, kT, 0, st>>>(a);
+        else if (vh) bwd_prepare_kernel<T, false, true><<<grid, kT, 0, st>>>(a);
+        else bwd_prepare_kernel<T, false, false><<<grid, kT, 0, st>>>(a);
         JITDB_LAUNCH_CHECK();
     }
-
-    T *dZ = static_cast<T *>(w.dZ), *G_all = static_cast<T *>(w.G);
-    const int64_t g_alloc = round_up(n, 128) + 128;
-    T *dZt = static_cast<T *>(w.dZt), *At = static_cast<T *>(w.At), *Gt = static_cast<T *>(w.Gt), *Hkt = static_cast<T *>(w.Hkt);
+    const int slabs = Hk * (int)sizeof(T) / 64;             // of one gate
+    auto rows_at = [](void *base, int row) { return static_cast<const char *>(base) + (int64_t)row * 64; };
+    CellArgs a = {};
+    a.perm = s->perm; a.inv_perm = s->inv_perm; a.child_ptr = s->child_ptr; a.child_idx = s->child_idx; a.parent_of = w.parent_of;
+    a.c = c; a.gh = gh; a.gc = gc; a.gates = gates; a.fgate = fgate; a.dhs = w.dhs; a.ufg = w.ufg; a.dc = w.dc; a.dZ = w.dZ; a.G = w.G;
+    a.rows_alloc = w.rows_alloc; a.H = H; a.Hk = Hk;
+    // a leaf's forget block is read where a column tile of the sums holds other gates too, or a range starts among the leaves
+    a.zero_from = plan.f_tile * 256 == 3 * Hk ? plan.begin[1] : 0;
+    const bool vec = H * sizeof(T) % 4 == 0 && ((reinterpret_cast<uintptr_t>(gates) | reinterpret_cast<uintptr_t>(fgate)) & 3) == 0;
     for (int l = L - 1; l >= 0; --l) {
-        const int rows = lp[l + 1] - lp[l];
-        if (rows <= 0) return JITDB_E_SCHEDULE;
-        const int32_t *nodes = s->perm + lp[l];
-        const int kpad = (int)round_up(rows, 64);           // reduction length of the weight GEMMs
-        const int64_t lvl_alloc = round_up(rows, 128);
-        const dim3 tile_grid((unsigned)(kpad / (64 / (int)sizeof(T))), (unsigned)(Hk / 64));
-        auto weight_gemm = [&](const T *A, int64_t a_alloc, int M, const T *B, int64_t b_alloc, int N, float *C, int ldc) {
-            KbGemm g = {};
-            g.A = A; g.a_rows_alloc = a_alloc; g.M = M; g.B = B; g.b_rows_alloc = b_alloc; g.N = N;
-            g.k_bytes = (int64_t)kpad * sizeof(T);
-            const int64_t tiles = ceil_div(M, 128) * ceil_div(N, 256);
-            // one round of blocks (two per CU), in multiples of eight splits: a split's XCD is split % 8
-            int64_t want = 8 * (512 / (8 * tiles));
-            if (want < 8) want = tiles >= 512 ? 1 : 8;
-            const int64_t most = kpad / 512 > 0 ? kpad / 512 : 1;
-            g.k_splits = (int)(want < most ? want : most);
-            g.epilogue = KB_EPI_ATOMIC_ACC; g.out0 = C; g.ldc = ldc;
-            return launch_kb_gemm(dtype, g, st);
-        };
-        // leaves have no children: their forget-gate block of dZ is zero and is left out of both GEMMs
-        const int n_gates = l > 0 ? 4 : 3;
-        // what the level receives from above
-        if (l < L - 1) {
-            // the level's rows of G: written by the parents' cell kernels, zero for roots
-            T *G = reinterpret_cast<T *>(reinterpret_cast<char *>(G_all) + (int64_t)lp[l] * 64);
-            const int pieces = Hk / (16 / (int)sizeof(T));
-            zero_root_rows_kernel<T><<<(unsigned)ceil_div((int64_t)rows * pieces, kT), kT, 0, st>>>(
-                nodes, rows, Hk, w.parent_of, G, g_alloc);
-            JITDB_LAUNCH_CHECK();
-            if ((rc = launch_transpose<T>(G, nullptr, 0, g_alloc, rows, Hk, kpad, Gt, gt_alloc, st)) != JITDB_OK) return rc;
-            // ufg_r = U_f^T dz_f,k (level order), and dU_f += sum_k dz_f,k (x) h_k
-            KbGemm g = {};
-            g.A = G; g.a_rows_alloc = g_alloc; g.M = rows;
-            g.B = w.Uft; g.b_rows_alloc = uft_alloc; g.N = H;
-            g.k_bytes = (int64_t)Hk * sizeof(T); g.k_splits = 1;
-            g.epilogue = KB_EPI_STORE; g.out0 = w.ufg; g.ldc = H;
-            if ((rc = launch_kb_gemm(dtype, g, st)) != JITDB_OK) return rc;
-            if ((rc = launch_transpose<T>(h, nodes, H, 0, rows, H, kpad, Hkt, ht_alloc, st)) != JITDB_OK) return rc;
-            if ((rc = weight_gemm(Gt, gt_alloc, Hk, Hkt, ht_alloc, H, w.dUfp, H)) != JITDB_OK) return rc;
+        a.row0 = lp[l]; a.n_rows = lp[l + 1] - lp[l];
+        const dim3 grid((unsigned)ceil_div(a.n_rows, kRows<T>), (unsigned)(Hk / 64));
+        if (l == 0) {
+            if (vec) bwd_cell_kernel<T, true, true><<<grid, kT, 0, st>>>(a);
+            else bwd_cell_kernel<T, false, true><<<grid, kT, 0, st>>>(a);
+        } else {
+            if (vec) bwd_cell_kernel<T, true, false><<<grid, kT, 0, st>>>(a);
+            else bwd_cell_kernel<T, false, false><<<grid, kT, 0, st>>>(a);
         }
-        bwd_cell_kernel<T><<<tile_grid, kT, 0, st>>>(nodes, rows, H, Hk, s->child_ptr, s->child_idx, w.parent_of, c,
-                                                     gates, fgate, gh, gc, static_cast<const T *>(w.dhs),
-                                                     l < L - 1 ? static_cast<const T *>(w.ufg) : nullptr, w.dc,
-                                                     s->inv_perm, G_all, g_alloc, dZ, lvl_alloc, dZt, zt_alloc, n_gates);
         JITDB_LAUNCH_CHECK();
-        {   // [dx | dhs] = dZ [W | U]; leaves have nobody to pass dhs to
-            KbGemm g = {};
-            g.A = dZ; g.a_rows_alloc = lvl_alloc; g.M = rows;
-            g.B = w.Mt; g.b_rows_alloc = mt_alloc; g.N = l > 0 ? D + H : D;
-            g.k_bytes = (int64_t)n_gates * Hk * sizeof(T); g.k_splits = 1;
-            g.epilogue = KB_EPI_DX_DHS; g.out0 = dx; g.out1 = w.dhs; g.node = nodes; g.D = D; g.H = H;
-            if ((rc = launch_kb_gemm(dtype, g, st)) != JITDB_OK) return rc;
-        }
-        // weight gradients: dMp += [x | 1 | hs]^T dZ (leaves have hs = 0: the x and bias rows only)
-        if ((rc = launch_transpose<T>(x, nodes, D, 0, rows, D, kpad, At, at_alloc, st)) != JITDB_OK) return rc;
-        ones_row_kernel<T><<<(unsigned)ceil_div(kpad, kT), kT, 0, st>>>(At, at_alloc, D, rows, kpad);
-        JITDB_LAUNCH_CHECK();
-        int q_cols = D + 1;
-        if (l > 0) {
-            T *hs_rows = reinterpret_cast<T *>(reinterpret_cast<char *>(At) + (int64_t)(D + 1) * 64);
-            const dim3 grid((unsigned)(kpad / (64 / (int)sizeof(T))), (unsigned)ceil_div(H, 64));
-            if ((H * sizeof(T)) % 16 == 0)
-                hsum_transpose_kernel<T, true><<<grid, kT, 0, st>>>(h, nodes, rows, H, s->child_ptr, s->child_idx, hs_rows, at_alloc);
-            else
-                hsum_transpose_kernel<T, false><<<grid, kT, 0, st>>>(h, nodes, rows, H, s->child_ptr, s->child_idx, hs_rows, at_alloc);
-            JITDB_LAUNCH_CHECK();
-            q_cols = D + 1 + H;
-        }
-        // [x | 1 | hs]^T dZ rather than its transpose: the narrow side (813 or 301) then pads to
-        // 128-row tiles instead of 256-column tiles
-        if ((rc = weight_gemm(At, at_alloc, q_cols, dZt, zt_alloc, n_gates * Hk, w.dMp, 4 * Hk)) != JITDB_OK) return rc;
+        if (l == 0) break;
+        RowProduct g[2] = {};
+        g[0].A = rows_at(w.dZ, lp[l]); g[0].n_rows = a.n_rows; g[0].n_slabs = 3 * slabs;
+        g[0].B = static_cast<const char *>(w.Ut); g[0].out = w.dhs; g[0].map = s->perm + lp[l];
+        g[1].A = rows_at(w.G, lp[l - 1]); g[1].n_rows = lp[l] - lp[l - 1]; g[1].n_slabs = slabs;
+        g[1].B = static_cast<const char *>(w.Uft); g[1].out = w.ufg;
+        for (RowProduct &p : g) { p.b_alloc = w.u_alloc; p.n_feat = H; p.ld = H; }
+        if ((rc = launch_rows<T>(g, 2, w.rows_alloc, st)) != JITDB_OK) return rc;
     }
-    unpack_grads_kernel<<<1024, kT, 0, st>>>(w.dMp, w.dUfp, D, H, Hk, dW, dU, db);
+    {
+        RowProduct g[2] = {};
+        for (int q = 0; q < 2; ++q) {
+            const int r0 = q ? lp[1] : 0, r1 = q ? n : lp[1];
+            g[q].A = rows_at(w.dZ, r0); g[q].n_rows = r1 - r0; g[q].n_slabs = (q ? 4 : 3) * slabs;
+            g[q].B = static_cast<const char *>(w.Wt); g[q].b_alloc = w.w_alloc; g[q].n_feat = D;
+            g[q].out = dx; g[q].map = s->perm + r0; g[q].ld = D; g[q].f32_out = 1;
+        }
+        if ((rc = launch_rows<T>(g, 2, w.rows_alloc, st)) != JITDB_OK) return rc;
+    }
+    TnArgs e = {};
+    const void *A[3] = {w.AX, w.AS, w.AH}, *B[3] = {w.dZ, w.dZ, w.G};
+    for (int q = 0, at = 0; q < 3; ++q) {
+        TnProblem &p = e.p[q];
+        p.A = static_cast<const char *>(A[q]); p.B = static_cast<const char *>(B[q]);
+        p.m_tiles = (int)ceil_div(q == 0 ? D + 1 : H, 128); p.n_tiles = plan.tiles[q] / p.m_tiles;
+        p.tile0 = at; p.begin = plan.begin[q]; p.begin_f = q == 0 ? plan.begin[1] : plan.begin[q];
+        p.f_tile = q == 0 ? plan.f_tile : p.n_tiles;
+        at += plan.tiles[q];
+    }
+    e.rows_alloc = w.rows_alloc; e.n_rows = plan.rows; e.rows_per_split = plan.rows_per_split; e.splits = plan.splits;
+    e.tiles = plan.total_tiles; e.partial = w.partial; e.dW = dW; e.dU = dU; e.db = db; e.D = D; e.H = H; e.Hk = Hk;
+    tn_kernel<T><<<(unsigned)(8 * ceil_div(e.splits, 8) * e.tiles), kDmaThreads, 0, st>>>(e);
+    JITDB_LAUNCH_CHECK();
+    grad_reduce_kernel<<<dim3(32, (unsigned)e.tiles), kT, 0, st>>>(e);
     JITDB_LAUNCH_CHECK();
     return JITDB_OK;
 }
@@ -536,7 +745,6 @@ bool bwd_dims(const jitdb_schedule_t *s, int32_t D, int32_t H, jitdb_dtype dtype
             if (r > n_max) n_max = r;
         }
     d.n_max = n_max;
-    d.n_pad = (int)round_up(n_max, 64);
     return true;
 }
 

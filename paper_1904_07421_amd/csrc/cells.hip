@@ -162,8 +162,8 @@ int run_nary_slot(jitdb_dtype dtype, const LevelArgs &a, const NarySlot &s, hipS
         x.A = s.A; x.a_rows_alloc = rows_alloc; x.M = s.n_rows;
         x.B = static_cast<const char *>(s.Bn) + nary_main_bytes(a.H, a.Dp, a.Hp, s.N, esz);
         x.b_rows_alloc = nary_rows_extra(a.H, s.N); x.N = (s.N - 1) * a.H;
-        x.k_bytes = (int64_t)Kn * (int64_t)esz; x.k_splits = 1;
-        x.epilogue = KB_EPI_STORE_F32; x.out0 = s.F; x.ldc = x.N;
+        x.k_bytes = (int64_t)Kn * (int64_t)esz;
+        x.out = s.F; x.ldc = x.N;
         const int rc = launch_kb_gemm(dtype, x, st);
         if (rc != JITDB_OK) return rc;
     }

@@ -22,14 +22,13 @@
 //                      tail of a deep forest) as ONE launch: x and the child's h read in place,
 //                      all four gates over the full K, no stack step and no projection
 //   trees_kernel       (trees.hip) a forest of small trees filed one after another: all of the above in one launch
-//   tile256_kernel     (level256.hip) the level kernel on 256 x 256 tiles, bf16; switched off
 //
 // With cells of different type in the table (jitdb_treelstm_forward_cells) a slot of N-ary cells
 // runs nary_level_kernel below: the same GEMM core with the N-ary cell update as its epilogue.
 // With a typed table (jitdb_treelstm_forward_typed) a slot is (level, signature): each
 // signature has its own packed weights, the projection of a sub-slot uses the parent
 // cell's, and the slots of a large level run in one grouped launch through a tile table.
-// gemm_kb_kernel is the same GEMM core as a plain C = A B^T for the backward pass.
+// gemm_kb_kernel is the same GEMM core as a plain C = A B^T.
 //
 // "Stack" is the row gather through perm (level-major order) done by
 // stack_kernel, "slice" is the scatter of rows back to node-id order in the
@@ -40,7 +39,7 @@
 // gates of a hidden unit in its own accumulators and the cell update needs no
 // exchange between lanes; rows and K are zero padded to tile multiples.
 
-#include "level_common.h"
+#include "tile_gemm.h"
 
 #include <mutex>
 #include <vector>
@@ -56,7 +55,6 @@ struct PackArgs {
     const void *W, *U; const float *b;
     int D, H, Dp, Hp, NP, NPU;
     void *Bp; float *bp;
-    void *Bf;       // the same rows fragment-major for the 256 x 256 tile kernel (bf16, one cell), or null
 };
 
 // block `block` of `n_blocks` (NT threads each, stride loop)
@@ -64,7 +62,7 @@ template <typename T, int NT = kThreads>
 __device__ __forceinline__ void pack_weights_body(const T *__restrict__ W, const T *__restrict__ U,
                                                   const float *__restrict__ b, int D, int H, int Dp, int Hp,
                                                   int NP, int NPU, T *__restrict__ Bp, float *__restrict__ bp,
-                                                  T *__restrict__ Bf, int64_t block, int64_t n_blocks) {
+                                                  int64_t block, int64_t n_blocks) {
     const int Kp = Dp + Hp;
     const int64_t total = (int64_t)NPU * Kp;
     for (int64_t idx = block * NT + threadIdx.x; idx < total; idx += n_blocks * NT) {
@@ -80,8 +78,6 @@ __device__ __forceinline__ void pack_weights_body(const T *__restrict__ W, const
         }
         *reinterpret_cast<T *>(reinterpret_cast<char *>(Bp) +
                                operand_offset(r, (int64_t)k * sizeof(T), NPU)) = v;
-        if (Bf)
-            *reinterpret_cast<T *>(reinterpret_cast<char *>(Bf) + fragment_offset(r, (int64_t)k * sizeof(T), Kp * (int)sizeof(T) / 32)) = v;
         if (k == 0 && r < NP) bp[r] = row_ok ? b[src] : 0.0f;
     }
 }
@@ -90,7 +86,7 @@ template <typename T>
 __global__ void __launch_bounds__(kThreads)
 pack_weights_kernel(const PackArgs p) {
     pack_weights_body<T>(static_cast<const T *>(p.W), static_cast<const T *>(p.U), p.b, p.D, p.H, p.Dp, p.Hp, p.NP,
-                         p.NPU, static_cast<T *>(p.Bp), p.bp, static_cast<T *>(p.Bf), blockIdx.x, gridDim.x);
+                         p.NPU, static_cast<T *>(p.Bp), p.bp, blockIdx.x, gridDim.x);
 }
 
 // ---- row records -------------------------------------------------------------------
@@ -210,7 +206,7 @@ prepare_kernel(const int32_t *__restrict__ perm, const int32_t *__restrict__ key
         row_record_body<kThreads>(perm, key, child_ptr, child_idx, row_rec, n, first_window + (int)blockIdx.x);
     else
         pack_weights_body<T>(static_cast<const T *>(p.W), static_cast<const T *>(p.U), p.b, p.D, p.H, p.Dp, p.Hp,
-                             p.NP, p.NPU, static_cast<T *>(p.Bp), p.bp, static_cast<T *>(p.Bf),
+                             p.NP, p.NPU, static_cast<T *>(p.Bp), p.bp,
                              (int64_t)blockIdx.x - n_windows, (int64_t)gridDim.x - n_windows);
 }
 
@@ -225,8 +221,7 @@ prepare_large_kernel(const int32_t *__restrict__ perm, const int32_t *__restrict
     else
         pack_weights_body<T, kRecThreadsLarge>(static_cast<const T *>(p.W), static_cast<const T *>(p.U), p.b, p.D, p.H,
                                                p.Dp, p.Hp, p.NP, p.NPU, static_cast<T *>(p.Bp), p.bp,
-                                               static_cast<T *>(p.Bf), (int64_t)blockIdx.x - n_windows,
-                                               (int64_t)gridDim.x - n_windows);
+                                               (int64_t)blockIdx.x - n_windows, (int64_t)gridDim.x - n_windows);
 }
 
 // ---- stack -------------------------------------------------------------------------
@@ -339,294 +334,6 @@ stack_kernel(const T *__restrict__ x, int D, int Dp, const T *__restrict__ hs, i
     stack_body<T, WITH_H>(x, D, Dp, hs, Hp, row_rec, child_idx, A, n_rows, n_rows_alloc, blockIdx.x);
 }
 
-// Block id -> tile of the level kernel.  The hardware deals consecutive block ids
-// round-robin to the 8 XCDs, each with its own L2.  Row tile r belongs to XCD r % 8, so
-// that the blocks of all its column tiles read the same A rows through one L2.  Inside an
-// XCD the column tiles are taken in groups of kColGroup: the XCD sweeps all its row tiles
-// with one group of columns, then with the next, which bounds the B rows in use at a
-// time; A is fetched once per group.  (With 8 column tiles, H = 512, one group measured
-// faster than two: re-reading A costs more than the B rows that fall out of L2.)  The
-// grid holds 8 * ceil(R / 8) * C blocks; blocks past an XCD's share return at once.
-constexpr int kColGroup = 8;
-__device__ __forceinline__ bool block_to_tile(int b, int n_row_tiles, int n_col_tiles, int &row_tile, int &col_tile) {
-    const int xcd = b & 7, idx = b >> 3;
-    const int rows_x = (n_row_tiles - xcd + 7) >> 3;        // row tiles of this XCD
-    if (idx >= rows_x * n_col_tiles) return false;
-    const int g = idx / (rows_x * kColGroup);
-    const int rem = idx - g * rows_x * kColGroup;
-    const int left = n_col_tiles - g * kColGroup;
-    const int cg = left < kColGroup ? left : kColGroup;    // columns in this group
-    row_tile = xcd + 8 * (rem / cg);
-    col_tile = g * kColGroup + rem % cg;
-    return true;
-}
-
-// ---- the level GEMM ------------------------------------------------------------------
-// One block of four waves computes 128 rows x 256 packed columns (2 unit tiles x 4 gates x
-// 32 units); each wave a 64 x 128 sub-tile, i.e. 2 x 4 MFMA tiles of 32 x 32, so that all
-// four gates of a hidden unit end up in one wave's accumulators.  Two blocks share a CU
-// (half the LDS and at most 256 registers each): the start-up and the memory-bound cell
-// update of one leave the matrix cores to the other.
-//
-// A is the level's stacked input [x | hsum], B the packed [W | U]; K runs over stages of
-// 64 bytes per row, n_x stages of the x part, then n_h of the h part, in which the forget
-// gate is skipped (U_f applies to each child's own h, not to the sum).  The projection
-// instead reads A rows from h by node id and uses only the U part of the forget rows.
-// Stages travel from global memory straight into LDS (global_load_lds, 16 bytes per lane)
-// without passing through registers.  Three stage buffers: while stage g is multiplied,
-// g+1 and g+2 (and for half the time g+3) are in flight; one barrier per stage.
-//
-// In each 16-wide (bf16) or 8-wide (fp32) K group, lanes 0-31 take the first 16 bytes and
-// lanes 32-63 the next 16 for A and B alike; since the same assignment is used on both
-// operands any such split of K is a valid MFMA schedule.
-//
-// A direct load writes the 64 lanes' pieces to 1024 consecutive LDS bytes, i.e. 16 rows of
-// 64 bytes with no room for padding, so bank conflicts are avoided by permuting the four
-// 16-byte pieces of a row instead: piece p of row r is kept in slot p ^ ((r >> 2) & 3).
-// The lane that fills slot s of row r therefore fetches piece s ^ ((r >> 2) & 3), and a
-// fragment read of 16 consecutive rows touches 16 distinct 16-byte columns.
-constexpr int kDmaThreads = 256;
-constexpr int kDmaBM = 128;        // rows per block
-constexpr int kDmaStage = 64;      // bytes of K per row and stage
-constexpr int kDmaBuf = (kDmaBM + kBN) * kDmaStage;
-constexpr int kDmaBufs = 3;
-constexpr int kWarmMaxStages = 256; // longest K loop whose A tile is requested up front (2 MB)
-
-
-// Waits until at most N of this wave's loads are outstanding and all its LDS operations
-// are done, then meets the block at a barrier.  Written as one asm statement with a memory
-// clobber so that nothing moves across it, and without the fence of __syncthreads(), which
-// would wait for every direct-to-LDS load in flight.
-template <int N>
-__device__ __forceinline__ void dma_wait_barrier() {
-    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
-}
-
-template <typename T, int MODE, int NBUF = kDmaBufs, typename Hook>
-__device__ __forceinline__ void dma_gemm(const LevelArgs &a, char *lds, const int *row_node,
-                                         int tile_row0, int col_tile, floatx16 (&acc)[2][4],
-                                         char *sink, Hook &&after_first_requests) {
-    constexpr int ESZ = (int)sizeof(T);
-    constexpr int NG_X = (MODE == MODE_LEAF) ? 3 : 4;      // gate tiles multiplied in the x part
-    constexpr int NG_H = (MODE == MODE_INTERNAL) ? 3 : 4;  // ... in the h part
-    constexpr int NB = (MODE == MODE_LEAF) ? 3 : 4;        // 16-row B units a wave moves per stage
-    constexpr int NLOAD = 2 + NB;                          // loads per wave and stage
-
-    const int t = threadIdx.x;
-    const int lane = t & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
-    const int wm = wave >> 1, wn = wave & 1;
-    const int hf = lane >> 5, l32 = lane & 31;
-
-    const int n_x = (MODE == MODE_PROJ) ? 0 : a.Dp * ESZ / kDmaStage;
-    const int n_h = (MODE == MODE_LEAF) ? 0 : a.Hp * ESZ / kDmaStage;
-    const int n_stages = n_x + n_h;   // even and >= 2: K is padded to 128 bytes
-
-    // ---- mover: lane l fills slot l&3 of row l>>2 of each 16-row unit it is given
-    const int lrow = lane >> 2;
-    const int piece16 = ((lane & 3) ^ ((lane >> 4) & 3)) * 16;
-    const char *pa[2];
-    int a_lds[2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        const int r = (wave + 4 * i) * 16 + lrow;      // row of the tile
-        a_lds[i] = (wave + 4 * i) * 16 * kDmaStage;
-        if constexpr (MODE == MODE_PROJ) {
-            int g = tile_row0 + r;
-            if (g >= a.n_rows) g = a.n_rows - 1;
-            pa[i] = static_cast<const char *>(a.hs) + (int64_t)row_node[g - tile_row0] * a.Hp * ESZ + piece16;
-        } else {
-            pa[i] = static_cast<const char *>(a.stack) + (int64_t)(tile_row0 + r) * kDmaStage + piece16;
-        }
-    }
-    // bytes from one stage to the next: a slab of A / of B; the projection's A rows are
-    // rows of h in node order, K contiguous
-    const int64_t a_stage = (MODE == MODE_PROJ) ? kDmaStage : (int64_t)a.n_rows_alloc * kDmaStage;
-    const int64_t b_stage = (int64_t)a.NPU * kDmaStage;
-    const char *pb[NB];
-    int b_lds[NB];
-#pragma unroll
-    for (int i = 0; i < NB; ++i) {
-        const int idx = wave * NB + i;
-        int lds_row;
-        int64_t src_row;
-        if constexpr (MODE == MODE_PROJ) {
-            // LDS row q*32 + u holds the forget row of unit u of unit tile col_tile*8 + q
-            const int q = idx >> 1;
-            lds_row = q * kUnit + (idx & 1) * 16;
-            src_row = (int64_t)(col_tile * 8 + q) * kGateTile + 3 * kUnit + (idx & 1) * 16 + lrow;
-        } else {
-            // LDS row = packed row within the block's 256; the leaf level skips the forget rows
-            const int ut = idx / (2 * NB), gate = (idx % (2 * NB)) >> 1;
-            lds_row = ut * kGateTile + gate * kUnit + (idx & 1) * 16;
-            src_row = (int64_t)col_tile * kBN + lds_row + lrow;
-        }
-        b_lds[i] = (kDmaBM + lds_row) * kDmaStage;
-        pb[i] = static_cast<const char *>(a.Bp) +
-                operand_offset(src_row, MODE == MODE_PROJ ? (int64_t)a.Dp * ESZ : 0, a.NPU) + piece16;
-    }
-    // load i (0 .. NLOAD-1) of stage s
-    auto issue_one = [&](int s, int buf, int i) __attribute__((always_inline)) {
-        char *dst = lds + buf * kDmaBuf;
-        if (i < 2)
-            __builtin_amdgcn_global_load_lds(JITDB_GLOBAL_PTR(pa[i] + s * a_stage), JITDB_LDS_PTR(dst + a_lds[i]), 16, 0, 0);
-        else
-            __builtin_amdgcn_global_load_lds(JITDB_GLOBAL_PTR(pb[i - 2] + s * b_stage), JITDB_LDS_PTR(dst + b_lds[i - 2]), 16, 0, 0);
-    };
-    auto issue = [&](int s, int buf) __attribute__((always_inline)) {
-        char *dst = lds + buf * kDmaBuf;
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-            __builtin_amdgcn_global_load_lds(JITDB_GLOBAL_PTR(pa[i] + s * a_stage), JITDB_LDS_PTR(dst + a_lds[i]), 16, 0, 0);
-#pragma unroll
-        for (int i = 0; i < NB; ++i)
-            __builtin_amdgcn_global_load_lds(JITDB_GLOBAL_PTR(pb[i] + s * b_stage), JITDB_LDS_PTR(dst + b_lds[i]), 16, 0, 0);
-    };
-
-    // ---- fragments: K group h (0, 1) of a stage is pieces 2h (lanes 0-31) and 2h+1 (lanes 32-63)
-    const int sw = (l32 >> 2) & 3;
-    int a_rd[2], b_rd[2];
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        const int slot16 = ((2 * h + hf) ^ sw) * 16;
-        a_rd[h] = (wm * 64 + l32) * kDmaStage + slot16;
-        b_rd[h] = (kDmaBM + wn * 128 + l32) * kDmaStage + slot16;
-    }
-    // Fragment reads are written as asm: the compiler would otherwise make every LDS read
-    // wait for all direct-to-LDS loads in flight, which it cannot tell apart from the
-    // buffer being read.  The waits for the reads are therefore placed by hand as well
-    // (LDS operations of a wave complete in order).  A K group's fragments: two of A, NG of B.
-    const uint32_t lds_base = (uint32_t)(uintptr_t)JITDB_LDS_PTR(lds);
-    struct Frags {
-        u32x4 a[2], b[4];
-    };
-    auto read_group = [&](int buf, int h, auto ng_tag, Frags &f) __attribute__((always_inline)) {
-        constexpr int NG = decltype(ng_tag)::value;
-        const uint32_t aa = lds_base + buf * kDmaBuf + a_rd[h];
-        const uint32_t bb = lds_base + buf * kDmaBuf + b_rd[h];
-        asm volatile("ds_read_b128 %0, %1" : "=v"(f.a[0]) : "v"(aa) : "memory");
-        asm volatile("ds_read_b128 %0, %1" : "=v"(f.b[0]) : "v"(bb) : "memory");
-        asm volatile("ds_read_b128 %0, %1 offset:2048" : "=v"(f.a[1]) : "v"(aa) : "memory");
-        asm volatile("ds_read_b128 %0, %1 offset:2048" : "=v"(f.b[1]) : "v"(bb) : "memory");
-        asm volatile("ds_read_b128 %0, %1 offset:4096" : "=v"(f.b[2]) : "v"(bb) : "memory");
-        if constexpr (NG == 4)
-            asm volatile("ds_read_b128 %0, %1 offset:6144" : "=v"(f.b[3]) : "v"(bb) : "memory");
-    };
-    // all LDS reads issued so far have arrived; ties the fragments to the wait
-    auto reads_done = [&](auto ng_tag, Frags &f) __attribute__((always_inline)) {
-        constexpr int NG = decltype(ng_tag)::value;
-        if constexpr (NG == 4)
-            asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(f.a[0]), "+v"(f.a[1]), "+v"(f.b[0]), "+v"(f.b[1]), "+v"(f.b[2]), "+v"(f.b[3]));
-        else
-            asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(f.a[0]), "+v"(f.a[1]), "+v"(f.b[0]), "+v"(f.b[1]), "+v"(f.b[2]));
-    };
-    auto multiply = [&](auto ng_tag, const Frags &f) __attribute__((always_inline)) {
-        constexpr int NG = decltype(ng_tag)::value;
-#pragma unroll
-        for (int m = 0; m < 2 * NG; ++m)
-            mfma_step<T>(f.a[m / NG], f.b[m % NG], acc[m / NG][m % NG]);
-    };
-    // The same with the loads of stage s dealt out between the MFMAs, one after each: a
-    // wave issues in order, and a burst of loads in front of the MFMAs would hold them back
-    // until the memory pipeline has taken the loads of all waves of the CU.
-    // (The condition wraps each load, not the MFMAs: accumulators that meet again after
-    // a branch get copied.)
-    auto multiply_and_issue = [&](auto ng_tag, const Frags &f, int s, int buf, bool wanted) __attribute__((always_inline)) {
-        constexpr int NG = decltype(ng_tag)::value;
-#pragma unroll
-        for (int m = 0; m < 2 * NG; ++m) {
-            mfma_step<T>(f.a[m / NG], f.b[m % NG], acc[m / NG][m % NG]);
-            __builtin_amdgcn_sched_barrier(0);
-            if (m < NLOAD && wanted) issue_one(s, buf, m);
-            __builtin_amdgcn_sched_barrier(0);
-        }
-    };
-    const std::integral_constant<int, NG_X> ngx;
-    const std::integral_constant<int, NG_H> ngh;
-
-    // One stage.  On entry P holds K group 0 of stage g (buffer cur).  The reads of K group 1
-    // go out, K group 0 is multiplied; once those reads are back nobody needs buffer cur any
-    // more, and after the barrier (which also publishes stage g+1) it takes the request for
-    // stage g+3.  K group 0 of stage g+1 is then read while K group 1 of stage g is multiplied.
-    // With two buffers (NBUF == 2) a stage's request follows the barrier that frees its buffer by one stage
-    // instead of two: nothing younger is in flight at a barrier, and every wait is for all loads.
-    static_assert(NBUF == 2 || NBUF == 3, "two or three stage buffers");
-    Frags P, Q;
-    int cur = 0;
-    auto next_buf = [&]() __attribute__((always_inline)) { return cur == NBUF - 1 ? 0 : cur + 1; };
-    auto step = [&](int g, auto ng_cur, auto ng_next, auto wait_tag) __attribute__((always_inline)) {
-        constexpr int WAIT = NBUF == 2 ? 0 : decltype(wait_tag)::value;
-        read_group(cur, 1, ng_cur, Q);
-        __builtin_amdgcn_sched_barrier(0);
-        multiply(ng_cur, P);
-        __builtin_amdgcn_sched_barrier(0);
-        reads_done(ng_cur, Q);
-        dma_wait_barrier<WAIT>();
-        read_group(next_buf(), 0, ng_next, P);
-        __builtin_amdgcn_sched_barrier(0);
-        multiply_and_issue(ng_cur, Q, g + NBUF, cur, g + NBUF < n_stages);
-        __builtin_amdgcn_sched_barrier(0);
-        reads_done(ng_next, P);
-        cur = next_buf();
-    };
-    const std::integral_constant<int, NLOAD> w_more;   // a younger stage stays in flight
-    const std::integral_constant<int, 0> w_none;
-
-    // Warm L2 with the block's share of its A tile, one 4-byte load per 128-byte line (the
-    // data goes to a sink): the stage loads further down the K loop then find their lines
-    // in L2 instead of each waiting for HBM with only two stages of lookahead.  The blocks
-    // of one column group of a row tile run side by side on one XCD and split the lines.
-    // (A long reduction axis, as in the weight-gradient GEMMs, would ask for far more than L2
-    // holds; there the stage loads take their chances.)
-    if (MODE != MODE_PROJ && n_stages <= kWarmMaxStages) {
-        char *sink_w = sink + wave * 256;
-        const int n_lines = n_stages * (kDmaBM * kDmaStage / 128);
-        const char *tile = static_cast<const char *>(a.stack) + (int64_t)tile_row0 * kDmaStage;
-        const int left = a.n_col_tiles - (col_tile / kColGroup) * kColGroup;
-        const int sharers = left < kColGroup ? left : kColGroup;
-        for (int li = col_tile % kColGroup + sharers * t; li < n_lines; li += sharers * kDmaThreads) {
-            const int slab = li >> 6, line = li & 63;
-            __builtin_amdgcn_global_load_lds(JITDB_GLOBAL_PTR(tile + slab * a_stage + line * 128),
-                                             JITDB_LDS_PTR(sink_w), 4, 0, 0);
-        }
-    }
-    issue(0, 0);
-    issue(1, 1);
-    if (NBUF > 2 && n_stages > 2) issue(2, 2);
-    after_first_requests();
-    if (NBUF > 2 && n_stages > 2) dma_wait_barrier<2 * NLOAD>(); else dma_wait_barrier<NLOAD>();   // stage 0 is there
-    int g = 0;
-    if constexpr (MODE == MODE_PROJ) {
-        read_group(0, 0, ngh, P);
-        reads_done(ngh, P);
-    } else {
-        read_group(0, 0, ngx, P);
-        reads_done(ngx, P);
-        const int x_end = n_x - 1 < n_stages - 2 ? n_x - 1 : n_stages - 2;
-        for (; g < x_end; ++g) step(g, ngx, ngx, w_more);
-        if constexpr (MODE == MODE_INTERNAL) {   // n_h >= 2, so this stage is not among the last two
-            step(g, ngx, ngh, w_more);
-            ++g;
-        }
-    }
-    if constexpr (MODE == MODE_LEAF) {
-        step(g, ngx, ngx, w_none);
-        read_group(cur, 1, ngx, Q);
-        multiply(ngx, P);
-        reads_done(ngx, Q);
-        multiply(ngx, Q);
-    } else {
-        for (; g < n_stages - 2; ++g) step(g, ngh, ngh, w_more);
-        step(g, ngh, ngh, w_none);
-        read_group(cur, 1, ngh, Q);
-        multiply(ngh, P);
-        reads_done(ngh, Q);
-        multiply(ngh, Q);
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    dma_wait_barrier<0>();       // every wave is done reading the stage buffers
-}
-
 // The bf16 leaf level's blocks spend more time getting started and in the cell update than in their short K loop
 // (K = D only): there a block keeps two stage buffers instead of three and three blocks share a CU instead of
 // two (its three gate tiles leave the registers for that).  (fp32 leaves, whose K loop is bound by the fp32
@@ -728,23 +435,13 @@ level_kernel(const LevelArgs a_in) {
 }
 
 // ---- the same GEMM core as a plain C = A B^T ------------------------------------------
-// For the backward pass: both operands K-blocked, all four column groups multiplied in every
-// stage, no cell update.  An output element goes to the epilogue named in the arguments.
-// With a split reduction (splits > 1) the grid is one-dimensional and a block's K range
-// decides its XCD: blocks are dealt to the eight XCDs round-robin, so block b runs on XCD
-// b % 8, takes a split s with s % 8 == b % 8 and one of the output tiles of that split.  All
-// tiles of a K range then share one L2, which reads that range of both operands once, and
-// every XCD has work however few output tiles there are.
-struct KbEpiArgs {
-    int kind;
-    void *out0; void *out1; const int32_t *node; int D; int H; int ldc;
-    int M, N;
-    int stages_total, stages_per_split, splits;
-};
+// For the further forget gates of N-ary cells (cells.hip): both operands K-blocked, all four column groups multiplied in
+// every stage, no cell update; C in fp32, row-major.
+struct KbEpiArgs { float *out; int ldc, M, N; };
 
 template <typename T>
 __global__ void __launch_bounds__(kDmaThreads, 2)
-gemm_kb_kernel(LevelArgs a, const KbEpiArgs e) {
+gemm_kb_kernel(const LevelArgs a, const KbEpiArgs e) {
     __shared__ __attribute__((aligned(1024))) char lds[kDmaBufs * kDmaBuf];
     __shared__ __attribute__((aligned(256))) char sink[4 * 256];
     const int t = threadIdx.x;
@@ -752,25 +449,9 @@ gemm_kb_kernel(LevelArgs a, const KbEpiArgs e) {
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
     const int wm = wave >> 1, wn = wave & 1;
     const int hf = lane >> 5, l32 = lane & 31;
-    int row_tile, col_tile, split = 0;
-    if (e.splits > 1) {
-        const int q = blockIdx.x >> 3, tiles = a.n_row_tiles * a.n_col_tiles;
-        split = (blockIdx.x & 7) + 8 * (q / tiles);
-        if (split >= e.splits) return;
-        row_tile = (q % tiles) / a.n_col_tiles;
-        col_tile = (q % tiles) % a.n_col_tiles;
-    } else if (!block_to_tile(blockIdx.x, a.n_row_tiles, a.n_col_tiles, row_tile, col_tile)) {
-        return;
-    }
+    int row_tile, col_tile;
+    if (!block_to_tile(blockIdx.x, a.n_row_tiles, a.n_col_tiles, row_tile, col_tile)) return;
     const int tile_row0 = row_tile * kDmaBM;
-    // this block's range of K stages
-    const int s0 = split * e.stages_per_split;
-    int n_st = e.stages_total - s0;
-    if (n_st > e.stages_per_split) n_st = e.stages_per_split;
-    a.stack = static_cast<const char *>(a.stack) + (int64_t)s0 * a.n_rows_alloc * kDmaStage;
-    a.Bp = static_cast<const char *>(a.Bp) + (int64_t)s0 * a.NPU * kDmaStage;
-    a.Dp = n_st * kDmaStage / (int)sizeof(T);
-    a.Hp = 0;
 
     floatx16 acc[2][4];
 #pragma unroll
@@ -779,39 +460,17 @@ gemm_kb_kernel(LevelArgs a, const KbEpiArgs e) {
         for (int g = 0; g < 4; ++g)
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[i][g][v] = 0.0f;
-    // node ids of the tile's rows, fetched while the GEMM runs (the epilogue would otherwise
-    // wait for one dependent load per output row)
-    __shared__ int s_node[kDmaBM];
-    if (e.kind == KB_EPI_DX_DHS && t < kDmaBM) s_node[t] = tile_row0 + t < e.M ? e.node[tile_row0 + t] : 0;
     dma_gemm<T, MODE_GENERIC>(a, lds, nullptr, tile_row0, col_tile, acc, sink, []() {});
     __syncthreads();
 
-    if (e.kind == KB_EPI_ATOMIC_ACC) {
-        float *out = static_cast<float *>(e.out0);
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const int col = col_tile * kBN + wn * 128 + g * 32 + l32;
-                if (col >= e.N) continue;
-#pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const int row = tile_row0 + wm * 64 + i * 32 + (v >> 2) * 8 + hf * 4 + (v & 3);
-                    if (row < e.M) atomicAdd(&out[(int64_t)row * e.ldc + col], acc[i][g][v]);
-                }
-            }
-        return;
-    }
-    // Row-wise epilogues: a wave turns its 64 x 128 sub-tile, 32 rows at a time, through a
-    // region of the (now free) stage buffers, so that a lane ends up with four consecutive
-    // columns of one row and the wave stores whole 512-byte row segments.
+    // A wave turns its 64 x 128 sub-tile, 32 rows at a time, through a region of the (now free) stage buffers, so
+    // that a lane ends up with four consecutive columns of one row and the wave stores whole 512-byte row segments.
     constexpr int kStride = 128 + 4;
     static_assert(4 * 32 * kStride * 4 <= kDmaBufs * kDmaBuf, "epilogue regions must fit the stage buffers");
     float *region = reinterpret_cast<float *>(lds) + wave * (32 * kStride);
     const int c4 = (lane & 31) * 4;
     const int col = col_tile * kBN + wn * 128 + c4;
-    const bool vec_ok = (e.kind == KB_EPI_STORE || e.kind == KB_EPI_STORE_F32) ? (e.ldc & 3) == 0
-                                                                               : ((e.D & 3) == 0 && (e.H & 3) == 0);
+    const bool vec_ok = (e.ldc & 3) == 0;
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
 #pragma unroll
@@ -829,53 +488,13 @@ gemm_kb_kernel(LevelArgs a, const KbEpiArgs e) {
             if (row >= e.M || col >= e.N) continue;
             const float4 q = *reinterpret_cast<const float4 *>(region + rl * kStride + c4);
             const float f[4] = {q.x, q.y, q.z, q.w};
-            if (e.kind == KB_EPI_STORE_F32) {
-                float *dst = static_cast<float *>(e.out0) + (int64_t)row * e.ldc + col;
-                if (vec_ok && col + 4 <= e.N) {
-                    *reinterpret_cast<float4 *>(dst) = q;
-                } else {
+            float *dst = e.out + (int64_t)row * e.ldc + col;
+            if (vec_ok && col + 4 <= e.N) {
+                *reinterpret_cast<float4 *>(dst) = q;
+            } else {
 #pragma unroll
-                    for (int j = 0; j < 4; ++j)
-                        if (col + j < e.N) dst[j] = f[j];
-                }
-            } else if (e.kind == KB_EPI_STORE) {
-                T *dst = static_cast<T *>(e.out0) + (int64_t)row * e.ldc + col;
-                if (vec_ok && col + 4 <= e.N) {
-                    if constexpr (sizeof(T) == 4) {
-                        *reinterpret_cast<float4 *>(dst) = q;
-                    } else {
-                        *reinterpret_cast<uint2 *>(dst) =
-                            make_uint2((uint32_t)f32_to_bf16(f[0]) | ((uint32_t)f32_to_bf16(f[1]) << 16),
-                                       (uint32_t)f32_to_bf16(f[2]) | ((uint32_t)f32_to_bf16(f[3]) << 16));
-                    }
-                } else {
-#pragma unroll
-                    for (int j = 0; j < 4; ++j)
-                        if (col + j < e.N) dst[j] = from_f32<T>(f[j]);
-                }
-            } else {   // KB_EPI_DX_DHS
-                const int64_t nd = s_node[row - tile_row0];
-                float *dx = static_cast<float *>(e.out0) + nd * e.D;
-                T *dhs = static_cast<T *>(e.out1) + nd * e.H;
-                if (vec_ok && col + 4 <= e.N) {        // D % 4 == 0: the four columns lie on one side of D
-                    if (col < e.D) {
-                        *reinterpret_cast<float4 *>(dx + col) = q;
-                    } else if constexpr (sizeof(T) == 4) {
-                        *reinterpret_cast<float4 *>(dhs + (col - e.D)) = q;
-                    } else {
-                        *reinterpret_cast<uint2 *>(dhs + (col - e.D)) =
-                            make_uint2((uint32_t)f32_to_bf16(f[0]) | ((uint32_t)f32_to_bf16(f[1]) << 16),
-                                       (uint32_t)f32_to_bf16(f[2]) | ((uint32_t)f32_to_bf16(f[3]) << 16));
-                    }
-                } else {
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        const int cj = col + j;
-                        if (cj >= e.N) continue;
-                        if (cj < e.D) dx[cj] = f[j];
-                        else dhs[cj - e.D] = from_f32<T>(f[j]);
-                    }
-                }
+                for (int j = 0; j < 4; ++j)
+                    if (col + j < e.N) dst[j] = f[j];
             }
         }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -1454,7 +1073,6 @@ constexpr int kTreesMaxSpan = 256;         // ... of trees of up to this many id
 struct ForwardWs {
     void *Bp;
     float *bp;
-    void *Bf;     // fragment-major copy of the packed weights (bf16 with one cell), else nullptr
     void *stack;  // the current level's stacked input, (N + 256) rows of Dp + Hp
     float *Z;     // trees.hip: x parts of the gates [N][4][H rounded up to 16], in the same memory; nullptr: no room
     float *FC;    // trees.hip: every node's f c, [N, H rounded up to 16], in the memory of P
@@ -1497,9 +1115,6 @@ Dims make_dims(int D, int H, jitdb_dtype dtype) {
 
 // packed weights of one cell: bytes of Bp, floats of bp (one set per signature, back to back)
 size_t packed_w_bytes(const Dims &d) { return (size_t)d.NPU * (d.Dp + d.Hp) * d.esz; }
-// the 256 x 256 tile kernel (bf16, one cell) reads the weights in a second, fragment-major layout
-bool has_fragment_copy(const Dims &d, int n_sig) { return d.esz == 2 && n_sig == 1; }
-
 ForwardWs carve_forward_ws(int64_t n, int64_t e, const Dims &d, void *base, int n_sig = 1,
                            const jitdb_cell_t *cells = nullptr, bool with_z = true) {
     Carver c(base);
@@ -1507,7 +1122,6 @@ ForwardWs carve_forward_ws(int64_t n, int64_t e, const Dims &d, void *base, int 
     (void)e;
     w.Bp = c.take<char>(packed_w_bytes(d) * n_sig);
     w.bp = c.take<float>((size_t)d.NP * n_sig);
-    w.Bf = has_fragment_copy(d, n_sig) ? c.take<char>(packed_w_bytes(d)) : nullptr;
     // one level at a time; whole row tiles are read, hence the 256 spare rows
     size_t stack_bytes = (size_t)(n + kRowPad) * (d.Dp + d.Hp) * d.esz;
     // the same sizes for tables of more than one signature: what they ask for grows with n_sig from there
@@ -1566,8 +1180,6 @@ int run_forward(const void *x, const void *W, const void *U, const float *b, con
     if (packed) {
         w.Bp = const_cast<void *>(packed);
         w.bp = reinterpret_cast<float *>(static_cast<char *>(w.Bp) + round_up(packed_w_bytes(d) * n_sig_w, 256));
-        w.Bf = has_fragment_copy(d, n_sig_w)
-                   ? reinterpret_cast<char *>(w.bp) + round_up((int64_t)d.NP * n_sig_w * 4, 256) : nullptr;
     }
     const int L = s->n_levels;
     const int n_sig = slots ? slots->n_sig : 1;
@@ -1632,7 +1244,6 @@ int run_forward(const void *x, const void *W, const void *U, const float *b, con
             p.D = d.D; p.H = d.H; p.Dp = d.Dp; p.Hp = d.Hp; p.NP = d.NP; p.NPU = d.NPU;
             p.Bp = static_cast<char *>(w.Bp) + packed_w_bytes(d) * t;
             p.bp = w.bp + (size_t)d.NP * t;
-            p.Bf = t == 0 ? w.Bf : nullptr;
             return p;
         };
         const bool large = s->n_nodes >= kRecLargeMinNodes;
@@ -1682,10 +1293,6 @@ int run_forward(const void *x, const void *W, const void *U, const float *b, con
     LevelArgs a;
     a.proj_nodes = nullptr;
     a.stack = w.stack;
-    a.Bf = w.Bf;
-    // bf16 levels that are large enough run on 256 x 256 tiles (level256.hip); training and typed
-    // tables keep the 128 x 256 kernel, which has those variants
-    const bool may256 = std::is_same<T, bf16_t>::value && !SAVE && !slots && w.Bf != nullptr;
     a.hs = w.hs ? w.hs : h_out;
     a.x = x;
     a.child_idx = s->child_idx;
@@ -1813,7 +1420,7 @@ int run_forward(const void *x, const void *W, const void *U, const float *b, con
                 JITDB_LAUNCH_CHECK();
             }
             stacked_ahead = false;
-            // Levels too small to give every CU a 256 x 256 tile go to the thin kernel.
+            // levels too small to fill the chip with tiles go to the thin kernel
             bool thin = n_rows <= kThinMaxRows;
             if (!thin && !SAVE && !slots && l > 0 && s->host_level_kids && n_rows <= kThinMaxRowsLongLists &&
                 s->host_level_kids[l] >= (int64_t)kThinLongLists * n_rows)
@@ -1836,9 +1443,6 @@ int run_forward(const void *x, const void *W, const void *U, const float *b, con
                         thin_kernel<T, MODE_LEAF, SAVE><<<a.n_blocks, kThinWaves * 64, 0, st>>>(a);
                     else
                         thin_kernel<T, MODE_INTERNAL, SAVE><<<a.n_blocks, kThinWaves * 64, 0, st>>>(a);
-                } else if (may256 && tile256_applies(l == 0 ? MODE_LEAF : MODE_INTERNAL, a)) {
-                    const int rc = launch_tile256(l == 0 ? MODE_LEAF : MODE_INTERNAL, a, st);
-                    if (rc != JITDB_OK) return rc;
                 } else if (grouped) {
                     if (l == 0)
                         level_kernel<T, MODE_LEAF, false, true><<<a.n_blocks, kDmaThreads, 0, st>>>(a);
@@ -1900,9 +1504,6 @@ int run_forward(const void *x, const void *W, const void *U, const float *b, con
                 } else {
                     thin_kernel<T, MODE_PROJ><<<a.n_blocks, kThinWaves * 64, 0, st>>>(a);
                 }
-            } else if (may256 && tile256_applies(MODE_PROJ, a)) {
-                const int rc = launch_tile256(MODE_PROJ, a, st);
-                if (rc != JITDB_OK) return rc;
             } else {
                 a.n_col_tiles = (int)ceil_div(n_unit_tiles, 8);
                 a.n_row_tiles = (int)ceil_div(rows, kDmaBM);
@@ -1958,19 +1559,8 @@ int launch_kb_gemm(jitdb_dtype dtype, const KbGemm &g, hipStream_t st) {
     a.n_row_tiles = (int)ceil_div(g.M, kDmaBM);
     a.n_col_tiles = (int)ceil_div(g.N, kBN);
     a.n_blocks = 8 * (int)ceil_div(a.n_row_tiles, 8) * a.n_col_tiles;
-    KbEpiArgs e;
-    e.kind = g.epilogue; e.out0 = g.out0; e.out1 = g.out1; e.node = g.node; e.D = g.D; e.H = g.H; e.ldc = g.ldc;
-    e.M = g.M; e.N = g.N;
-    e.stages_total = (int)(g.k_bytes / kDmaStage);
-    // ranges of at least two stages (the pipeline's minimum); the last one may be shorter but
-    // not a single stage, in which case the ranges are made a stage longer
-    int splits = g.k_splits < 1 ? 1 : g.k_splits;
-    e.stages_per_split = (int)ceil_div(e.stages_total, splits);
-    if (e.stages_per_split < 2) e.stages_per_split = 2;
-    while (e.stages_per_split < e.stages_total && e.stages_total % e.stages_per_split == 1) ++e.stages_per_split;
-    splits = (int)ceil_div(e.stages_total, e.stages_per_split);
-    e.splits = splits;
-    if (splits > 1) a.n_blocks = 8 * a.n_row_tiles * a.n_col_tiles * (int)ceil_div(splits, 8);
+    a.Dp = (int)(g.k_bytes / (dtype == JITDB_F32 ? 4 : 2));
+    const KbEpiArgs e = {g.out, g.ldc, g.M, g.N};
     dim3 grid((unsigned)a.n_blocks);
     if (dtype == JITDB_F32) gemm_kb_kernel<float><<<grid, kDmaThreads, 0, st>>>(a, e);
     else gemm_kb_kernel<bf16_t><<<grid, kDmaThreads, 0, st>>>(a, e);
@@ -2114,8 +1704,7 @@ int forward_entry(const void *x, const void *W, const void *U, const float *b, i
 }
 
 size_t packed_total_bytes(const Dims &d, int n_sig) {
-    return (size_t)round_up(packed_w_bytes(d) * n_sig, 256) + (size_t)round_up((int64_t)d.NP * n_sig * 4, 256) +
-           (has_fragment_copy(d, n_sig) ? (size_t)round_up(packed_w_bytes(d), 256) : 0);
+    return (size_t)round_up(packed_w_bytes(d) * n_sig, 256) + (size_t)round_up((int64_t)d.NP * n_sig * 4, 256);
 }
 }  // namespace
 
@@ -2146,7 +1735,6 @@ extern "C" int jitdb_treelstm_pack(const void *W, const void *U, const float *b,
         p.D = d.D; p.H = d.H; p.Dp = d.Dp; p.Hp = d.Hp; p.NP = d.NP; p.NPU = d.NPU;
         p.Bp = static_cast<char *>(packed) + packed_w_bytes(d) * t;
         p.bp = bp0 + (size_t)d.NP * t;
-        p.Bf = has_fragment_copy(d, n_sig) ? reinterpret_cast<char *>(bp0) + round_up((int64_t)d.NP * n_sig * 4, 256) : nullptr;
         if (dtype == JITDB_F32) pack_weights_kernel<float><<<grid, kThreads, 0, st>>>(p);
         else pack_weights_kernel<bf16_t><<<grid, kThreads, 0, st>>>(p);
         JITDB_LAUNCH_CHECK();

@@ -1,5 +1,4 @@
-// Device-side pieces shared by the level kernels (forward.hip: 128 x 256 tiles, two blocks per CU,
-// fp32 and bf16, training and typed variants; level256.hip: 256 x 256 tiles, one block per CU, bf16):
+// Device-side pieces shared by the kernels on levels and on whole trees (tile_gemm.h, forward.hip, trees.hip, backward.hip):
 // operand types, the arguments of one level launch, and the fused cell update of one wave.
 #pragma once
 
@@ -11,6 +10,7 @@ namespace jitdb {
 namespace {
 
 typedef float floatx16 __attribute__((ext_vector_type(16)));
+typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 // Native vectors for data in flight (HIP's uint4 is a union-based struct, which the
 // optimiser does not always break up into registers).
@@ -23,16 +23,12 @@ constexpr int kBN = 256;        // packed columns per block = 2 unit tiles x 4 g
 constexpr int kUnit = 32;       // hidden units per MFMA column tile
 constexpr int kGateTile = 128;  // packed rows per unit tile (4 gates x 32 units)
 
-// Smallest level (rows) each kind of launch hands to the 256 x 256 tile kernel (level256.hip), by mode
-// (leaf, internal, projection); INT32_MAX = never.  Measured on config 5: with one wave per SIMD nothing
-// overlaps the cell update's activation arithmetic, so the leaf and internal launches (activation-heavy)
-// are faster on 128 x 256 tiles with two blocks per CU; the projection has no activations.
-constexpr int kTile256MinRows[3] = {INT32_MAX, INT32_MAX, INT32_MAX};
-
 constexpr int kEpiStride = 40;  // floats per row of a wave's epilogue region: 32 units + 8; rows 4 apart fall 32 banks apart
 
 enum : int { MODE_LEAF = 0, MODE_INTERNAL = 1, MODE_PROJ = 2, MODE_GENERIC = 3,   // GENERIC: plain C = A B^T
-             MODE_CHAIN = 4 };   // internal rows with exactly one child: the forget gate's pre-activation is complete
+             MODE_CHAIN = 4,     // internal rows with exactly one child: the forget gate's pre-activation is complete
+       MODE_SWAP = 5,      // GENERIC with the level's rows as B
+       MODE_TN = 6 };      // C = A^T B, reduction over rows
 
 template <typename T> struct Traits;
 template <> struct Traits<float> {
@@ -78,7 +74,6 @@ struct LevelArgs {
     const void *x;        // [N, D] rows by node id (chain levels read them in place)
     // B operand: packed [W | U], NPU rows of Dp + Hp
     const void *Bp;
-    const void *Bf;       // the same rows fragment-major (tile256_kernel), or null
     const float *bp;      // [NP] packed bias
     // schedule
     const int4 *row_rec;         // two int4 per level row (this level's slice of the records)
@@ -127,6 +122,17 @@ __device__ __forceinline__ void mfma_step(const u32x4 &a, const u32x4 &b, floatx
         acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a[1]), __uint_as_float(b[1]), acc, 0, 0, 0);
         acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a[2]), __uint_as_float(b[2]), acc, 0, 0, 0);
         acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a[3]), __uint_as_float(b[3]), acc, 0, 0, 0);
+    }
+}
+
+template <typename T>
+__device__ __forceinline__ void mfma16(const u32x4 &a, const u32x4 &b, floatx4 &acc) {
+    if constexpr (sizeof(T) == 2) {
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), acc, 0, 0, 0);
+    } else {
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a[j]), __uint_as_float(b[j]), acc, 0, 0, 0);
     }
 }
 
@@ -522,9 +528,5 @@ struct TreesArgs {
 };
 bool plan_trees(TreesArgs &a, size_t esz);
 int launch_trees(jitdb_dtype dtype, bool save, const TreesArgs &a, hipStream_t st);
-
-// level256.hip
-bool tile256_applies(int mode, const LevelArgs &a);
-int launch_tile256(int mode, LevelArgs a, hipStream_t st);
 
 }  // namespace jitdb

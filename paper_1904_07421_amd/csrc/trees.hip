@@ -27,24 +27,11 @@
 namespace jitdb {
 namespace {
 
-typedef float floatx4 __attribute__((ext_vector_type(4)));
-
 constexpr int kTreeMaxWaves = 16;          // at most 128 registers each: four waves per SIMD
 constexpr int kTreeRows = 32;              // most rows of a group (16 where LDS holds no more)
 // weight slabs in flight per wave: the fewer MFMAs a slab feeds, the more
 template <int NRT, int NG> constexpr int kTreeAhead = NRT * NG <= 1 ? 6 : NRT <= 1 ? 4 : NG == 1 ? 4 : 2;
 constexpr uint16_t kNoLocal = 0xFFFF;
-
-template <typename T>
-__device__ __forceinline__ void mfma16(const u32x4 &a, const u32x4 &b, floatx4 &acc) {
-    if constexpr (sizeof(T) == 2) {
-        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), acc, 0, 0, 0);
-    } else {
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a[j]), __uint_as_float(b[j]), acc, 0, 0, 0);
-    }
-}
 
 // The same weights times at most FOUR rows: 4 x 4 blocks, sixteen of them in one MFMA, block lane / 4 taking the columns and
 // the quarter of the slab's K that this lane's 16 bytes hold.  A quarter of the 16-row form's time for fp32, and each lane
