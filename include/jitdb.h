@@ -241,7 +241,7 @@ size_t jitdb_treelstm_typed_workspace_bytes(int64_t n_nodes, int64_t n_edges,
  * to its children.  One batched evaluation per non-empty slot, levels in ascending order; a
  * slot's steps are those of a level in jitdb_treelstm_forward (stack, gate GEMM + cell update
  * with the slot's weights; forget projection per sub-slot with the parent cell's weights); the
- * slots of a large level share one grouped launch per step.
+ * slots of a level share one grouped launch per step.
  * `s` and `slots` come from jitdb_schedule_typed (slot_ptr is read on the device).
  */
 int jitdb_treelstm_forward_typed(const void *x, const void *W, const void *U, const float *b,

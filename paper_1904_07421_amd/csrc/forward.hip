@@ -27,7 +27,7 @@
 // runs nary_level_kernel below: the same GEMM core with the N-ary cell update as its epilogue.
 // With a typed table (jitdb_treelstm_forward_typed) a slot is (level, signature): each
 // signature has its own packed weights, the projection of a sub-slot uses the parent
-// cell's, and the slots of a large level run in one grouped launch through a tile table.
+// cell's, and the slots of a level run in one grouped launch (enter_range).
 // gemm_kb_kernel is the same GEMM core as a plain C = A B^T.
 //
 // "Stack" is the row gather through perm (level-major order) done by
@@ -366,12 +366,7 @@ level_kernel(const LevelArgs a_in) {
     if (!block_to_tile(blockIdx.x, a.n_row_tiles, a.n_col_tiles, row_tile, col_tile)) return;
     int tile_row0 = row_tile * kDmaBM;
     if constexpr (GROUPED) {     // the tile's slot: where its rows start and end, whose weights apply
-        const int4 e = a.tiles[row_tile];
-        tile_row0 = __builtin_amdgcn_readfirstlane(e.x);
-        a.n_rows = __builtin_amdgcn_readfirstlane(e.y);
-        const int sig = __builtin_amdgcn_readfirstlane(e.z);
-        a.Bp = static_cast<const char *>(a.Bp) + sig * a.w_bytes;
-        a.bp = a.bp + (int64_t)sig * a.NP;
+        if (!enter_range<kDmaBM>(a, row_tile, tile_row0)) return;
     }
 
     int node_reg = -1;
@@ -647,8 +642,9 @@ constexpr int kThinMaxRowsLongLists = 16384;
 constexpr int kThinLongLists = 5;
 constexpr int kThinAhead = 8;      // K groups in flight per wave
 
-template <typename T, int MODE, bool SAVE = false>
-__device__ __forceinline__ void thin_body(const LevelArgs &a, int tile) {
+template <typename T, int MODE, bool SAVE = false, bool GROUPED = false>
+__device__ __forceinline__ void thin_body(const LevelArgs &a_in, int tile) {
+    LevelArgs a = a_in;
     constexpr int ESZ = (int)sizeof(T);
     __shared__ __attribute__((aligned(16))) float smem[4 * 32 * kEpiStride];    // the four gates' pre-activations
     __shared__ int s_node[32];
@@ -659,7 +655,10 @@ __device__ __forceinline__ void thin_body(const LevelArgs &a, int tile) {
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int hf = lane >> 5, l32 = lane & 31;
-    const int row0 = (tile / a.n_col_tiles) * 32;
+    int row0 = (tile / a.n_col_tiles) * 32;
+    if constexpr (GROUPED) {
+        if (!enter_range<32>(a, tile / a.n_col_tiles, row0)) return;      // (the same for all waves of the block)
+    }
     const int col = tile % a.n_col_tiles;     // unit tile (gates) or group of four unit tiles (projection)
     // (leaves have no forget gate: its wave multiplies nothing, but takes its share of the cell update)
     if (MODE == MODE_PROJ && (col * 4 + wave) * kUnit >= a.Hu) return;            // past the last unit tile
@@ -753,21 +752,21 @@ __device__ __forceinline__ void thin_body(const LevelArgs &a, int tile) {
     }
 }
 
-template <typename T, int MODE, bool SAVE = false>
+template <typename T, int MODE, bool SAVE = false, bool GROUPED = false>
 __global__ void __launch_bounds__(kThinWaves * 64, 2)
 thin_kernel(const LevelArgs a) {
-    thin_body<T, MODE, SAVE>(a, blockIdx.x);
+    thin_body<T, MODE, SAVE, GROUPED>(a, blockIdx.x);
 }
 
 // The projection of a thin slot and the stack step of the slot after it in one launch: both
 // only need what the level kernel before them wrote, and a thin level costs its chain of
 // launches, not its work.  Blocks [0, a.n_blocks) are projection tiles, the rest stack blocks.
-template <typename T>
+template <typename T, bool GROUPED = false>
 __global__ void __launch_bounds__(kThinWaves * 64, 2)
 thin_proj_stack_kernel(const LevelArgs a, const StackArgs s) {
     static_assert(kThinWaves * 64 == kThreads, "both bodies use the same block size");
     if ((int)blockIdx.x < a.n_blocks)
-        thin_body<T, MODE_PROJ>(a, blockIdx.x);
+        thin_body<T, MODE_PROJ, false, GROUPED>(a, blockIdx.x);
     else
         stack_body<T, true>(static_cast<const T *>(s.x), s.D, s.Dp, static_cast<const T *>(s.hs), s.Hp, s.row_rec,
                             s.child_idx, static_cast<T *>(s.A), s.n_rows, s.n_rows_alloc,
@@ -992,48 +991,6 @@ chain_kernel(const LevelArgs a) {
     store_state<T>(a, node, unit0, make_float4(cc[0], cc[1], cc[2], cc[3]), make_float4(go[0], go[1], go[2], go[3]));
 }
 
-// ---- tile tables of a typed level --------------------------------------------------------
-// One block.  bounds[e * stride] .. bounds[(e + 1) * stride], e < n_entries, are consecutive
-// ranges of positions (the level's slots with stride = n_sig, its sub-slots with stride = 1);
-// range e uses weight set e % n_sig when stride == 1 (a sub-slot is named by the parent's
-// signature last), else e.  Entry i of the table describes the i-th 128-row tile when every
-// range is cut into tiles of its own: (first row, end row of its range, weight set), rows
-// relative to the level.
-constexpr int kMaxTableEntries = JITDB_MAX_SIGNATURES * JITDB_MAX_SIGNATURES;
-__global__ void __launch_bounds__(kThreads)
-tile_table_kernel(const int32_t *__restrict__ bounds, int n_entries, int stride, int n_sig, int4 *__restrict__ tiles) {
-    __shared__ int s_first[kMaxTableEntries + 1];      // tiles before entry e
-    __shared__ int s_part[kThreads];
-    // tiles per entry, then an exclusive scan: every thread owns a contiguous run of entries
-    const int per = (n_entries + kThreads - 1) / kThreads;
-    const int e0 = threadIdx.x * per, e1 = min(e0 + per, n_entries);
-    int sum = 0;
-    for (int e = e0; e < e1; ++e) {
-        const int c = (bounds[(e + 1) * stride] - bounds[e * stride] + kDmaBM - 1) / kDmaBM;
-        s_first[e] = sum;
-        sum += c;
-    }
-    s_part[threadIdx.x] = sum;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        int run = 0;
-        for (int t = 0; t < kThreads; ++t) { const int v = s_part[t]; s_part[t] = run; run += v; }
-        s_first[n_entries] = run;
-    }
-    __syncthreads();
-    for (int e = e0; e < e1; ++e) s_first[e] += s_part[threadIdx.x];
-    __syncthreads();
-    const int base = bounds[0];
-    for (int e = 0; e < n_entries; ++e) {
-        const int n_t = s_first[e + 1] - s_first[e];
-        if (n_t == 0) continue;
-        const int lo = bounds[e * stride] - base, hi = bounds[(e + 1) * stride] - base;
-        const int wset = stride == 1 ? e % n_sig : e;
-        for (int j = threadIdx.x; j < n_t; j += kThreads)
-            tiles[s_first[e] + j] = make_int4(lo + j * kDmaBM, hi, wset, 0);
-    }
-}
-
 // ---- host side ---------------------------------------------------------------------
 // Optional per-launch event pairs (see jitdb_profile_start in the header).
 struct Profiler {
@@ -1080,8 +1037,6 @@ struct ForwardWs {
     void *hs;     // nullptr when h_out can serve (H == Hp)
     void *P;
     float *cs;    // nullptr when c_out can serve (H == Hq)
-    int4 *tiles;  // tile tables of one typed level: cell batches, then projection batches (nullptr with one cell)
-    int64_t tiles_each;
     // tables that hold N-ary cells (jitdb_treelstm_forward_cells): one slot's stacked input and
     // pre-activations, each such cell's packed weights, the flag for nodes with too many children
     void *nary_A;
@@ -1138,8 +1093,6 @@ ForwardWs carve_forward_ws(int64_t n, int64_t e, const Dims &d, void *base, int 
     w.P = c.take<char>(p_bytes);
     w.FC = with_z && n_sig == 1 ? static_cast<float *>(w.P) : nullptr;
     w.cs = (d.H == d.Hq) ? nullptr : c.take<float>((size_t)n * d.Hq);
-    w.tiles_each = n / kDmaBM + (int64_t)n_sig * n_sig + 1;
-    w.tiles = n_sig > 1 ? c.take<int4>((size_t)(2 * w.tiles_each)) : nullptr;
     int n_max = 0;
     for (int t = 0; cells && t < n_sig; ++t)
         if (cells[t].kind == JITDB_CELL_NARY) {
@@ -1292,6 +1245,8 @@ int run_forward(const void *x, const void *W, const void *U, const float *b, con
 
     LevelArgs a;
     a.proj_nodes = nullptr;
+    a.ranges = nullptr;
+    a.n_ranges = 0; a.range_stride = 0; a.range_cells = 0;
     a.stack = w.stack;
     a.hs = w.hs ? w.hs : h_out;
     a.x = x;
@@ -1313,30 +1268,35 @@ int run_forward(const void *x, const void *W, const void *U, const float *b, con
     const int T2 = n_sig * n_sig;
     auto slot_begin = [&](int l, int t) { return sp[(l * n_sig + t) * (slots ? n_sig : 1)]; };
     auto sub_begin = [&](int l, int t, int p) { return sp[(l * n_sig + t) * n_sig + p]; };
-    // The launches in order: one per non-empty slot, except that a level of a typed table that
-    // is large enough for the tiled kernel runs all its slots in one grouped launch (sig = -1;
-    // n_tiles / n_proj_tiles = 128-row tiles when every slot / sub-slot is cut into tiles of its own).
-    struct Seg { int l, sig, begin, rows, n_tiles, n_proj_tiles; };
+    // The launches in order: one per non-empty slot, except that a level of a typed table with more than one
+    // slot or sub-slot runs them all in one grouped launch (sig = -1; n_tiles / n_proj_tiles = row tiles of
+    // tile_rows rows when every slot / sub-slot is cut into tiles of its own).  One thin launch costs 12 to 20 us
+    // whatever it holds: four cells in 8192 trees (295 k nodes, H 512, bf16)
+    // took 2.39 ms with a launch per cell on thin levels and takes 2.00 like this, six in 2.6 k nodes (H 118, fp32) 0.89 -> 0.21.
+    struct Seg { int l, sig, begin, rows, tile_rows, n_tiles, n_proj_tiles; };
     std::vector<Seg> segs;
     segs.reserve((size_t)L * n_sig);
     for (int l = 0; l < L; ++l) {
         const int lvl_rows = slot_begin(l + 1, 0) - slot_begin(l, 0);
-        int n_tiles = 0, n_proj_tiles = 0, used = 0;
+        const int tile_rows = lvl_rows <= kThinMaxRows ? 32 : kDmaBM;
+        int n_tiles = 0, n_proj_tiles = 0, used = 0, subs = 0;
         for (int t = 0; t < n_sig; ++t) {
             const int r = slot_begin(l, t + 1) - slot_begin(l, t);
             if (r < 0 || (r == 0 && !slots)) return JITDB_E_SCHEDULE;
-            n_tiles += (int)ceil_div(r, kDmaBM);
+            n_tiles += (int)ceil_div(r, tile_rows);
             used += r > 0;
-            if (slots)
-                for (int p = 0; p < n_sig; ++p)
-                    n_proj_tiles += (int)ceil_div(sub_begin(l, t, p + 1) - sub_begin(l, t, p), kDmaBM);
+            for (int p = 0; slots && p < n_sig; ++p) {
+                const int rp = sub_begin(l, t, p + 1) - sub_begin(l, t, p);
+                n_proj_tiles += (int)ceil_div(rp, tile_rows);
+                subs += rp > 0;
+            }
         }
-        if (used > 1 && lvl_rows > kThinMaxRows && !any_nary) {
-            segs.push_back({l, -1, slot_begin(l, 0), lvl_rows, n_tiles, n_proj_tiles});
+        if ((used > 1 || subs > 1) && !any_nary) {
+            segs.push_back({l, -1, slot_begin(l, 0), lvl_rows, tile_rows, n_tiles, n_proj_tiles});
         } else {
             for (int t = 0; t < n_sig; ++t) {
                 const int r = slot_begin(l, t + 1) - slot_begin(l, t);
-                if (r > 0) segs.push_back({l, t, slot_begin(l, t), r, 0, 0});
+                if (r > 0) segs.push_back({l, t, slot_begin(l, t), r, 0, 0, 0});
             }
         }
     }
@@ -1371,15 +1331,10 @@ int run_forward(const void *x, const void *W, const void *U, const float *b, con
         a.row_rec = w.row_rec + 2 * (int64_t)segs[i].begin;
         a.n_rows = n_rows;
         a.n_rows_alloc = (int)round_up(n_rows, kRowPad);
-        a.tiles = nullptr;
         const int row_tiles = grouped ? segs[i].n_tiles : (int)ceil_div(n_rows, kDmaBM);
-        if (grouped) {      // both tile tables of the level: cell batches, projection batches
-            const int32_t *lvl = slots->slot_ptr + (int64_t)l * T2;
-            tile_table_kernel<<<1, kThreads, 0, st>>>(lvl, n_sig, n_sig, n_sig, w.tiles);
-            JITDB_LAUNCH_CHECK();
-            tile_table_kernel<<<1, kThreads, 0, st>>>(lvl, T2, 1, n_sig, w.tiles + w.tiles_each);
-            JITDB_LAUNCH_CHECK();
-            a.tiles = w.tiles;
+        if (grouped) {      // the level's ranges: its slots for the cell, its sub-slots for the projection
+            a.ranges = slots->slot_ptr + (int64_t)l * T2;
+            a.n_ranges = n_sig; a.range_stride = n_sig; a.range_cells = n_sig;
         }
         if (l >= chain_from) {
             a.n_col_tiles = n_unit_tiles;
@@ -1421,13 +1376,13 @@ int run_forward(const void *x, const void *W, const void *U, const float *b, con
             }
             stacked_ahead = false;
             // levels too small to fill the chip with tiles go to the thin kernel
-            bool thin = n_rows <= kThinMaxRows;
+            bool thin = n_rows <= kThinMaxRows;      // (of a grouped launch: the whole level's)
             if (!thin && !SAVE && !slots && l > 0 && s->host_level_kids && n_rows <= kThinMaxRowsLongLists &&
                 s->host_level_kids[l] >= (int64_t)kThinLongLists * n_rows)
                 thin = true;
             if (thin) {
                 a.n_col_tiles = n_unit_tiles;
-                a.n_tiles = (int)ceil_div(n_rows, 32) * a.n_col_tiles;
+                a.n_tiles = (grouped ? row_tiles : (int)ceil_div(n_rows, 32)) * a.n_col_tiles;
                 a.n_blocks = a.n_tiles;
             } else {
                 a.n_col_tiles = d.NP / kBN;
@@ -1438,7 +1393,12 @@ int run_forward(const void *x, const void *W, const void *U, const float *b, con
             {
                 ScopedLaunchTimer tm(thin ? (l == 0 ? JITDB_K_THIN_LEAF : JITDB_K_THIN_INTERNAL)
                                           : (l == 0 ? JITDB_K_LEAF : JITDB_K_INTERNAL), n_rows, st);
-                if (thin) {
+                if (thin && grouped) {
+                    if (l == 0)
+                        thin_kernel<T, MODE_LEAF, false, true><<<a.n_blocks, kThinWaves * 64, 0, st>>>(a);
+                    else
+                        thin_kernel<T, MODE_INTERNAL, false, true><<<a.n_blocks, kThinWaves * 64, 0, st>>>(a);
+                } else if (thin) {
                     if (l == 0)
                         thin_kernel<T, MODE_LEAF, SAVE><<<a.n_blocks, kThinWaves * 64, 0, st>>>(a);
                     else
@@ -1462,13 +1422,27 @@ int run_forward(const void *x, const void *W, const void *U, const float *b, con
 
         // Forget projections of these nodes (roots' rows go unused), with the PARENT's weights.
         if (grouped) {
-            ScopedLaunchTimer tm(JITDB_K_PROJ, n_rows, st);
+            const bool thin_p = n_rows <= kThinMaxRows;
+            ScopedLaunchTimer tm(thin_p ? JITDB_K_THIN_PROJ : JITDB_K_PROJ, n_rows, st);
             a.Bp = w.Bp; a.bp = w.bp;
-            a.tiles = w.tiles + w.tiles_each;
-            a.n_col_tiles = (int)ceil_div(n_unit_tiles, 8);
-            a.n_row_tiles = segs[i].n_proj_tiles;
-            a.n_blocks = 8 * (int)ceil_div(a.n_row_tiles, 8) * a.n_col_tiles;
-            level_kernel<T, MODE_PROJ, false, true><<<a.n_blocks, kDmaThreads, 0, st>>>(a);
+            a.n_ranges = T2; a.range_stride = 1;
+            if (!thin_p) {
+                a.n_col_tiles = (int)ceil_div(n_unit_tiles, 8);
+                a.n_row_tiles = segs[i].n_proj_tiles;
+                a.n_blocks = 8 * (int)ceil_div(a.n_row_tiles, 8) * a.n_col_tiles;
+                level_kernel<T, MODE_PROJ, false, true><<<a.n_blocks, kDmaThreads, 0, st>>>(a);
+            } else {
+                a.n_col_tiles = (int)ceil_div(n_unit_tiles, 4);
+                a.n_tiles = segs[i].n_proj_tiles * a.n_col_tiles;
+                a.n_blocks = a.n_tiles;
+                if (i + 1 < segs.size() && segs[i + 1].rows <= kThinMaxRows) {     // as below: the next stack step rides along
+                    thin_proj_stack_kernel<T, true><<<a.n_blocks + stack_blocks(segs[i + 1]), kThinWaves * 64, 0, st>>>(
+                        a, stack_args(segs[i + 1]));
+                    stacked_ahead = true;
+                } else {
+                    thin_kernel<T, MODE_PROJ, false, true><<<a.n_blocks, kThinWaves * 64, 0, st>>>(a);
+                }
+            }
             JITDB_LAUNCH_CHECK();
             continue;
         }

@@ -98,9 +98,12 @@ struct LevelArgs {
     int n_col_tiles;      // tiles along the column axis
     int n_tiles;          // thin kernel: number of wave tiles
     int n_blocks;
-    // grouped launch over the slots of one level (typed table): row tile i covers level rows
-    // [tiles[i].x, min(tiles[i].x + 128, tiles[i].y)) and is evaluated by cell tiles[i].z
-    const int4 *tiles;
+    // grouped launch over the ranges of one level (typed table): range e covers positions
+    // ranges[e * range_stride] .. ranges[(e + 1) * range_stride].  A level's slots (stride = range_cells, the
+    // number of cells) belong to cell e, its sub-slots (stride 1, named by the parent's signature last) to cell
+    // e % range_cells; every range is cut into row tiles of its own (enter_range)
+    const int32_t *ranges;
+    int n_ranges, range_stride, range_cells;
     int64_t w_bytes;      // bytes between the packed weights of consecutive cells
     int NP;               // floats between their packed biases
     // tiled projection without a typed table: the level's node ids in position order (ascending ids, so the
@@ -134,6 +137,44 @@ __device__ __forceinline__ void mfma16(const u32x4 &a, const u32x4 &b, floatx4 &
         for (int j = 0; j < 4; ++j)
             acc = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a[j]), __uint_as_float(b[j]), acc, 0, 0, 0);
     }
+}
+
+// ---- grouped launches: which range a row tile lies in ------------------------------------
+// Row tile `tile` of a level whose ranges are cut into tiles of ROWS rows each: its first row (relative to the
+// level), with a.n_rows set to the end of its range and a.Bp / a.bp to the weights of its cell.  Every wave finds
+// the range itself, 64 ranges at a time: the tiles before range e are a prefix sum over the lanes, and the first
+// lane whose sum passes `tile` holds the range.  One load and six shuffles per tile; a table written by a launch
+// of its own cost 5 us twice per level and memory in the workspace.  False: past the last tile.
+template <int ROWS>
+__device__ __forceinline__ bool enter_range(LevelArgs &a, int tile, int &row0) {
+    const int lane = threadIdx.x & 63;
+    const int base = a.ranges[0];
+    int before = 0;
+    for (int e0 = 0; e0 < a.n_ranges; e0 += 64) {
+        const bool live = e0 + lane < a.n_ranges;
+        const int e = live ? e0 + lane : a.n_ranges - 1;
+        const int lo = a.ranges[e * a.range_stride], hi = a.ranges[(e + 1) * a.range_stride];
+        const int n_t = live ? (hi - lo + ROWS - 1) / ROWS : 0;
+        int sum = n_t;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const int v = __shfl_up(sum, d, 64);
+            if (lane >= d) sum += v;
+        }
+        const uint64_t past = __ballot(before + sum > tile);
+        if (past != 0) {
+            const int src = __builtin_ctzll(past);
+            const int first = before + __builtin_amdgcn_readlane(sum - n_t, src);
+            row0 = __builtin_amdgcn_readlane(lo, src) - base + (tile - first) * ROWS;
+            a.n_rows = __builtin_amdgcn_readlane(hi, src) - base;
+            const int cell = a.range_stride == 1 ? (e0 + src) % a.range_cells : e0 + src;
+            a.Bp = static_cast<const char *>(a.Bp) + cell * a.w_bytes;
+            a.bp = a.bp + (int64_t)cell * a.NP;
+            return true;
+        }
+        before += __builtin_amdgcn_readlane(sum, 63);
+    }
+    return false;
 }
 
 // ---- the cell update of one wave: 32 rows x 32 hidden units ---------------------------

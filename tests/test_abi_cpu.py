@@ -52,7 +52,7 @@ def test_workspace_queries(lib):
     assert J.jitdb_treelstm_workspace_bytes(100, 90, 300, 0, J.JITDB_F32) == 0
     assert J.jitdb_treelstm_workspace_bytes(100, 90, 300, 150, 7) == 0
     assert J.jitdb_treelstm_workspace_bytes(-1, 0, 300, 150, 0) == 0
-    # typed table: more weight sets and the tile tables; signature count and N * n_sig^2 are bounded
+    # typed table: more weight sets; signature count and N * n_sig^2 are bounded
     one = J.jitdb_treelstm_workspace_bytes(1000, 900, 300, 150, J.JITDB_BF16)
     assert J.jitdb_treelstm_typed_workspace_bytes(1000, 900, 300, 150, J.JITDB_BF16, 1) == one
     assert J.jitdb_treelstm_typed_workspace_bytes(1000, 900, 300, 150, J.JITDB_BF16, 3) > one

@@ -261,3 +261,28 @@ def test_packed_weights_on_a_typed_table():
     pk = J.jitdb_treelstm_pack(Wt, Ut, bt)
     h1, c1 = J.jitdb_treelstm_forward_packed(xt, pk, s)
     assert torch.equal(h0, h1) and torch.equal(c0, c1)
+
+
+@pytest.mark.parametrize("n_sig,sizes,dtype", [(2, (1, 31), "f32"), (3, (32, 33, 64), "bf16"), (10, (0, 1, 31, 32, 33, 63, 64, 65, 2, 0), "f32"),
+                                               (9, (900, 1, 128, 129, 0, 2000, 3, 255, 64), "bf16")])
+def test_grouped_ranges_at_tile_edges(n_sig, sizes, dtype):
+    """One launch per level for all cells: ranges that are empty or end on, before and after a tile, more ranges than a
+    wave has lanes, and (the last case) leaves past the thin kernel's rows.  Roots of cell p, two leaves of every other."""
+    parent, sig = [], []
+    for p, count in enumerate(sizes):
+        for j in range(count):
+            root = len(parent)
+            parent += [-1, root, root]
+            sig += [p, (p + j) % n_sig, (p + 2 * j + 1) % n_sig]
+    if sum(sizes) > 3000:                    # and leaves of one level in excess of the thin kernel's rows
+        root = len(parent)
+        parent += [-1] + [root] * 3000
+        sig += [1] + [j % n_sig for j in range(3000)]
+    p, sig = np.array(parent, np.int32), np.array(sig, np.int32)
+    x, W, U, b = make_values_typed(1, p.shape[0], n_sig, D=36, H=40)
+    print(f"typed ranges n_sig={n_sig} {dtype} N={p.shape[0]}", flush=True)
+    _, h, c, (xo, Wo, Uo, bo) = _gpu_forward_typed(p, sig, n_sig, x, W, U, b, dtype)
+    ho, co = TT.forward_typed(p, sig, xo, Wo, Uo, bo)
+    eh, ec = float(np.abs(h - ho).max()), float(np.abs(c - co).max())
+    # c of the wide root is a sum over its children: its bound grows with max |c| as elsewhere in this file
+    assert eh <= TOL[dtype] and ec <= TOL[dtype] * max(1.0, float(np.abs(co).max()) / 8.0)
