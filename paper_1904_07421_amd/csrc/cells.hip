@@ -19,6 +19,7 @@
 //   nary_level_kernel   (forward.hip) the gates i, o, u, f_1 on the tiled MFMA core with the cell update as
 //                       its epilogue: c = i u + sum_l f_l c_{k_l}, h = o tanh(c), rows written by node id
 //                       (the "slice")
+//   nary_thin_kernel    (forward.hip) a slot of few tiles: the two steps above in one launch, one wave per gate
 #include "level_common.h"
 
 namespace jitdb {
@@ -157,10 +158,12 @@ int run_nary_slot(jitdb_dtype dtype, const LevelArgs &a, const NarySlot &s, hipS
                                                                static_cast<const bf16_t *>(a.hs), a.Hp, s.N, Nk, s.row_rec,
                                                                static_cast<bf16_t *>(s.A), s.n_rows, rows_alloc, s.err);
     JITDB_LAUNCH_CHECK();
-    if (!s.leaves && s.N > 1) {       // f_2 .. f_N of every row, before the kernel that uses them
+    const int n_col_tiles = (int)ceil_div(ceil_div(a.H, kUnit), 2);
+    const char *extra = static_cast<const char *>(s.Bn) + nary_main_bytes(a.H, a.Dp, a.Hp, s.N, esz);
+    if (!s.leaves && s.N > 1 && !nary_slot_is_thin(s.n_rows, n_col_tiles)) {   // f_2 .. f_N of every row, before the kernel that uses them
         KbGemm x = {};
         x.A = s.A; x.a_rows_alloc = rows_alloc; x.M = s.n_rows;
-        x.B = static_cast<const char *>(s.Bn) + nary_main_bytes(a.H, a.Dp, a.Hp, s.N, esz);
+        x.B = extra;
         x.b_rows_alloc = nary_rows_extra(a.H, s.N); x.N = (s.N - 1) * a.H;
         x.k_bytes = (int64_t)Kn * (int64_t)esz;
         x.out = s.F; x.ldc = x.N;
@@ -170,7 +173,8 @@ int run_nary_slot(jitdb_dtype dtype, const LevelArgs &a, const NarySlot &s, hipS
     NaryLevel g = {};
     g.A = s.A; g.a_rows_alloc = rows_alloc; g.M = s.n_rows;
     g.B = s.Bn; g.b_rows_alloc = nary_rows_main(a.H);
-    g.n_col_tiles = (int)ceil_div(ceil_div(a.H, kUnit), 2);
+    g.Bx = extra; g.bx_rows_alloc = nary_rows_extra(a.H, s.N);
+    g.n_col_tiles = n_col_tiles;
     g.k_bytes = (int64_t)Kn * (int64_t)esz;
     g.row_rec = s.row_rec; g.bias = s.b; g.cs = a.cs; g.F = s.F;
     g.c_out = a.c_out; g.h_out = a.h_out; g.hs_out = a.hs_out; g.cs_out = a.cs;

@@ -773,6 +773,122 @@ thin_proj_stack_kernel(const LevelArgs a, const StackArgs s) {
                             (int64_t)blockIdx.x - a.n_blocks);
 }
 
+// ---- thin slots of N-ary nodes ----------------------------------------------------------
+// A slot with few 128 x 256 tiles costs the tiled kernels' latency whatever it holds (16 us for the GEMM of f_2 .. f_N
+// and 30 us for the level kernel behind it, D 300 H 256 N 2).  Here a block owns 32 rows x 32 units as in thin_kernel and
+// has one wave per gate, 3 + N of them (leaves: i, o, u), on the same stacked rows and packed weights: all gates meet in
+// LDS, so F is neither written nor read and the slot is one launch after its stack step.  The children's c are requested
+// before the K loop.  Bound by one wave's chain of K groups.  Schedule + forward, before -> now: 571 nodes D 300 H 256 N 2
+// bf16 438 -> 214 us, 4.5 k nodes fp32 2949 -> 573, 270 k nodes bf16 1732 -> 1551.
+constexpr int kNaryThinWaves = 7;      // 3 + N, N <= 4
+template <typename T, bool LEAF>
+__global__ void __launch_bounds__(kNaryThinWaves * 64, 4)
+nary_thin_kernel(const LevelArgs a, const NaryEpi e, const void *__restrict__ Bx, int rows_x) {
+    constexpr int ESZ = (int)sizeof(T);
+    __shared__ __attribute__((aligned(16))) float smem[(LEAF ? 3 : kNaryThinWaves) * 32 * kEpiStride];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);      // the gate: i, o, u, f_1 .. f_N
+    const int hf = lane >> 5, l32 = lane & 31;
+    const int row0 = ((int)blockIdx.x / a.n_col_tiles) * 32;
+    const int col = (int)blockIdx.x % a.n_col_tiles;
+
+    // ---- the weights' and the rows' K groups (thin_body)
+    const int my_row = min(row0 + l32, e.M - 1);           // past the end: computed twice, stored never
+    const char *ap = static_cast<const char *>(a.stack) + operand_offset(my_row, 0, a.n_rows_alloc) + hf * 16;
+    const int64_t a_pair = (int64_t)a.n_rows_alloc * 64;
+    const char *bp;
+    int64_t b_pair;
+    if (wave < 4) {
+        bp = static_cast<const char *>(a.Bp) + operand_offset((int64_t)col * kGateTile + wave * kUnit + l32, 0, a.NPU) + hf * 16;
+        b_pair = (int64_t)a.NPU * 64;
+    } else {                                               // row of f_2 .. f_N; a unit past H reads the gate's first row
+        const int unit = col * kUnit + l32;
+        bp = static_cast<const char *>(Bx) + operand_offset((int64_t)(wave - 4) * e.H + (unit < e.H ? unit : 0), 0, rows_x) + hf * 16;
+        b_pair = (int64_t)rows_x * 64;
+    }
+    const int n_groups = a.Dp * ESZ / 32;
+    floatx16 acc;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[v] = 0.0f;
+    u32x4 fa[kThinAhead], fb[kThinAhead];
+    auto request = [&](int g, int slot) __attribute__((always_inline)) {
+        fa[slot] = *reinterpret_cast<const u32x4 *>(ap + (int64_t)(g >> 1) * a_pair + (g & 1) * 32);
+        fb[slot] = *reinterpret_cast<const u32x4 *>(bp + (int64_t)(g >> 1) * b_pair + (g & 1) * 32);
+    };
+#pragma unroll
+    for (int s = 0; s < kThinAhead; ++s)
+        if (s < n_groups) request(s, s);
+
+    // ---- eight lanes per row, four units each, by the first four waves (leaves have three: they go round again)
+    const int u4 = (lane & 7) * 4, unit0 = col * kUnit + u4;
+    int node = -1, m = 0;
+    float4 ck[4];
+    if constexpr (!LEAF) {
+        if (wave < 4) {
+            const int row = row0 + (int)(threadIdx.x >> 3);
+            const int4 r0 = e.row_rec[2 * (int64_t)min(row, e.M - 1)];
+            const int4 kids = e.row_rec[2 * (int64_t)min(row, e.M - 1) + 1];
+            if (row < e.M) { node = r0.x; m = r0.y < e.N ? r0.y : e.N; }
+            const int kid[4] = {kids.x, kids.y, kids.z, kids.w};
+            const int unit_ld = unit0 < e.Hq ? unit0 : 0;
+#pragma unroll
+            for (int l = 0; l < 4; ++l) {
+                ck[l] = make_float4(0.f, 0.f, 0.f, 0.f);
+                if (l < m) ck[l] = *reinterpret_cast<const float4 *>(e.cs + (int64_t)kid[l] * e.Hq + unit_ld);
+            }
+        }
+    }
+    for (int g0 = 0; g0 < n_groups; g0 += kThinAhead) {
+#pragma unroll
+        for (int s = 0; s < kThinAhead; ++s) {
+            const int g = g0 + s;
+            if (g < n_groups) {
+                mfma_step<T>(fa[s], fb[s], acc);
+                if (g + kThinAhead < n_groups) request(g + kThinAhead, s);
+            }
+        }
+    }
+#pragma unroll
+    for (int v = 0; v < 16; ++v)
+        smem[wave * (32 * kEpiStride) + ((v >> 2) * 8 + hf * 4 + (v & 3)) * kEpiStride + l32] = acc[v];
+    __syncthreads();
+
+    auto finish = [&](int tr) __attribute__((always_inline)) {
+        auto gate = [&](int g) __attribute__((always_inline)) {
+            float4 q = *reinterpret_cast<const float4 *>(smem + g * (32 * kEpiStride) + tr * kEpiStride + u4);
+            const float *b = e.bias + (int64_t)g * e.H + unit0;      // (the caller's array: any alignment)
+            if (unit0 < e.H) q.x += b[0];
+            if (unit0 + 1 < e.H) q.y += b[1];
+            if (unit0 + 2 < e.H) q.z += b[2];
+            if (unit0 + 3 < e.H) q.w += b[3];
+            return q;
+        };
+        const float4 zi = gate(0), zo = gate(1), zu = gate(2);
+        float4 cc = make_float4(sigmoid_t<T>(zi.x) * tanh_t<T>(zu.x), sigmoid_t<T>(zi.y) * tanh_t<T>(zu.y),
+                                sigmoid_t<T>(zi.z) * tanh_t<T>(zu.z), sigmoid_t<T>(zi.w) * tanh_t<T>(zu.w));
+        if constexpr (!LEAF) {
+#pragma unroll
+            for (int l = 0; l < 4; ++l)
+                if (l < m) {
+                    const float4 f = gate(3 + l);
+                    cc.x += sigmoid_t<T>(f.x) * ck[l].x;
+                    cc.y += sigmoid_t<T>(f.y) * ck[l].y;
+                    cc.z += sigmoid_t<T>(f.z) * ck[l].z;
+                    cc.w += sigmoid_t<T>(f.w) * ck[l].w;
+                }
+        }
+        store_state<T>(a, node, unit0, cc, make_float4(sigmoid_t<T>(zo.x), sigmoid_t<T>(zo.y), sigmoid_t<T>(zo.z), sigmoid_t<T>(zo.w)));
+    };
+    if constexpr (LEAF) {
+        for (int tr = (int)(threadIdx.x >> 3); tr < 32 && row0 + tr < e.M; tr += 24) {
+            node = e.row_rec[2 * (int64_t)(row0 + tr)].x;
+            finish(tr);
+        }
+    } else if (wave < 4 && node >= 0) {
+        finish((int)(threadIdx.x >> 3));
+    }
+}
+
 // ---- chain levels ---------------------------------------------------------------------
 // A level in which every node has exactly one child (sequences filed as chains, the long thin
 // tail of a forest) needs neither the stack step nor the projection: the child sum is the
@@ -1492,6 +1608,14 @@ int run_forward(const void *x, const void *W, const void *U, const float *b, con
 
 }  // namespace
 
+// Slots of up to this many 128 x 256 tiles (4096 rows at H 256) take the thin kernel.  Schedule + forward, us, at 0 / 64 /
+// 128 / 256 / 512 tiles: 270 k nodes H 256 N 2 bf16 1732 / 1572 / 1551 / 1584 / 1656; 733 k nodes H 150 N 3 bf16 2431 /
+// 2315 / 2293 / 2311 / 2370; 8.9 k nodes H 150 N 2 fp32 1019 / 308 / 293 / 292 / 295.
+constexpr int kNaryThinTiles = 128;
+bool nary_slot_is_thin(int64_t rows, int n_col_tiles) {
+    return ceil_div(rows, kDmaBM) * n_col_tiles <= kNaryThinTiles;
+}
+
 int launch_nary_level(jitdb_dtype dtype, const NaryLevel &g, hipStream_t st) {
     if (g.M <= 0) return JITDB_OK;
     if (g.k_bytes <= 0 || g.k_bytes % 128 != 0) return JITDB_E_BADARG;
@@ -1509,6 +1633,22 @@ int launch_nary_level(jitdb_dtype dtype, const NaryLevel &g, hipStream_t st) {
     NaryEpi e;
     e.row_rec = g.row_rec; e.bias = g.bias; e.cs = g.cs; e.F = g.F; e.c_out = g.c_out; e.h_out = g.h_out; e.hs_out = g.hs_out;
     e.cs_out = g.cs_out; e.M = g.M; e.H = g.H; e.Hp = g.Hp; e.Hq = g.Hq; e.N = g.N;
+    if (nary_slot_is_thin(g.M, g.n_col_tiles)) {
+        a.c_out = g.c_out; a.h_out = g.h_out; a.hs_out = g.hs_out; a.cs = g.cs_out;
+        a.H = g.H; a.Hq = g.Hq; a.Hp = g.Hp;               // (K is a.Dp here; Hp is the padded h copy's stride)
+        a.n_col_tiles = 2 * g.n_col_tiles;
+        const unsigned blocks = (unsigned)(ceil_div(g.M, 32) * a.n_col_tiles);
+        const int threads = 64 * (g.leaves ? 3 : 3 + g.N);
+        if (dtype == JITDB_F32) {
+            if (g.leaves) nary_thin_kernel<float, true><<<blocks, threads, 0, st>>>(a, e, g.Bx, g.bx_rows_alloc);
+            else nary_thin_kernel<float, false><<<blocks, threads, 0, st>>>(a, e, g.Bx, g.bx_rows_alloc);
+        } else {
+            if (g.leaves) nary_thin_kernel<bf16_t, true><<<blocks, threads, 0, st>>>(a, e, g.Bx, g.bx_rows_alloc);
+            else nary_thin_kernel<bf16_t, false><<<blocks, threads, 0, st>>>(a, e, g.Bx, g.bx_rows_alloc);
+        }
+        JITDB_LAUNCH_CHECK();
+        return JITDB_OK;
+    }
     dim3 grid((unsigned)a.n_blocks);
     if (dtype == JITDB_F32) {
         if (g.leaves) nary_level_kernel<float, true><<<grid, kDmaThreads, 0, st>>>(a, e);

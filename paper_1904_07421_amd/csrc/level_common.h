@@ -542,9 +542,11 @@ struct NaryLevel {
     int64_t k_bytes;
     const int4 *row_rec; const float *bias; const float *cs; const float *F;
     float *c_out; void *h_out; void *hs_out; float *cs_out;
+    const void *Bx; int bx_rows_alloc;      // the rows of f_2 .. f_N, for a thin slot (nothing in F then)
     int H, Hp, Hq, N;
     bool leaves;
 };
+bool nary_slot_is_thin(int64_t rows, int n_col_tiles);
 int launch_nary_level(jitdb_dtype dtype, const NaryLevel &g, hipStream_t st);
 size_t nary_packed_bytes(int D, int H, int Dp, int Hp, int N, size_t esz);
 int nary_pack(jitdb_dtype dtype, const void *W, const void *U, int D, int H, int Dp, int Hp, int N, void *Bn,

@@ -177,3 +177,19 @@ def test_random_cells_and_widths(seed):
     sig = arity_signatures(p, positions, 320 + seed)
     print(f"cells random seed={seed} N={N} cells={positions} D={D} H={H} {dtype} nodes={p.shape[0]}", flush=True)
     _check(p, sig, positions, D, H, dtype, 330 + seed)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("N,trees,D,H", [(1, 1, 5, 1), (2, 31, 36, 32), (2, 33, 37, 33), (3, 64, 64, 40), (4, 65, 20, 99),
+                                         (2, 1000, 24, 512), (2, 8200, 8, 64)])
+def test_thin_slots_at_tile_edges(N, trees, D, H, dtype):
+    """Slots on both sides of the thin kernel's rows and tiles: roots with 0 .. N children, some of them with a child."""
+    parent = []
+    for j in range(trees):
+        root = len(parent)
+        parent += [-1] + [root] * (j % (N + 1))
+        if j % (N + 1) and j % 3 == 0:
+            parent.append(root + 1)
+    p = np.array(parent, np.int32)
+    print(f"thin cells N={N} rows={p.shape[0]} {dtype}", flush=True)
+    _check(p, np.zeros(p.shape[0], np.int32), [N], D, H, dtype, 5)
