@@ -636,6 +636,12 @@ nary_level_kernel(LevelArgs a, const NaryEpi e) {
 // rows (cell_rows).  One block barrier, none in the K loop.
 constexpr int kThinWaves = 4;
 constexpr int kThinMaxRows = 8192; // levels up to this many rows use the thin kernel
+// ... in bf16 only where the 128 x 256 tiles are at most this many, one per compute unit: more of them hide behind each
+// other what one costs, and a thin tile reads its weights from L2 for 32 rows.  (fp32's long K loops gain from the thin
+// kernel's spread up to kThinMaxRows.)  Schedule + forward at 2048 / 4096 / 8192 rows, us: H 512 bf16, 256 tiles = 4096
+// rows, 72 k nodes 710 / 698 / 725, four cells over 295 k nodes 1895 / 1894 / 1972; H 320 bf16, 286 k nodes 1270 / 1242 / 1234;
+// H 512 fp32, 72 k nodes 2412 / 2346 / 2282.
+constexpr int kThinMaxTiles = 256;
 // ... and larger ones too, up to this size, if their nodes average kThinLongLists children or more: the thin
 // kernel's cell update walks every row's own child list, the tiled kernel's makes 32 rows wait for the longest
 constexpr int kThinMaxRowsLongLists = 16384;
@@ -1258,6 +1264,9 @@ int run_forward(const void *x, const void *W, const void *U, const float *b, con
     bool any_nary = false;
     for (int t = 0; t < n_sig; ++t) any_nary = any_nary || is_nary(t);
 
+    int thin_max = kThinMaxRows;
+    if (sizeof(T) == 2 && thin_max > kThinMaxTiles * kDmaBM / (d.NP / kBN)) thin_max = kThinMaxTiles * kDmaBM / (d.NP / kBN);
+
     // Levels from chain_from on are thin and hold only nodes with exactly one child (the schedule says
     // how many children each level has): one launch each, no stack step, no projection.  A child
     // below chain_from whose parent is such a node needs no projection either, so the level right
@@ -1394,7 +1403,7 @@ int run_forward(const void *x, const void *W, const void *U, const float *b, con
     segs.reserve((size_t)L * n_sig);
     for (int l = 0; l < L; ++l) {
         const int lvl_rows = slot_begin(l + 1, 0) - slot_begin(l, 0);
-        const int tile_rows = lvl_rows <= kThinMaxRows ? 32 : kDmaBM;
+        const int tile_rows = lvl_rows <= thin_max ? 32 : kDmaBM;
         int n_tiles = 0, n_proj_tiles = 0, used = 0, subs = 0;
         for (int t = 0; t < n_sig; ++t) {
             const int r = slot_begin(l, t + 1) - slot_begin(l, t);
@@ -1492,7 +1501,7 @@ int run_forward(const void *x, const void *W, const void *U, const float *b, con
             }
             stacked_ahead = false;
             // levels too small to fill the chip with tiles go to the thin kernel
-            bool thin = n_rows <= kThinMaxRows;      // (of a grouped launch: the whole level's)
+            bool thin = n_rows <= thin_max;      // (of a grouped launch: the whole level's)
             if (!thin && !SAVE && !slots && l > 0 && s->host_level_kids && n_rows <= kThinMaxRowsLongLists &&
                 s->host_level_kids[l] >= (int64_t)kThinLongLists * n_rows)
                 thin = true;
@@ -1538,7 +1547,7 @@ int run_forward(const void *x, const void *W, const void *U, const float *b, con
 
         // Forget projections of these nodes (roots' rows go unused), with the PARENT's weights.
         if (grouped) {
-            const bool thin_p = n_rows <= kThinMaxRows;
+            const bool thin_p = n_rows <= thin_max;
             ScopedLaunchTimer tm(thin_p ? JITDB_K_THIN_PROJ : JITDB_K_PROJ, n_rows, st);
             a.Bp = w.Bp; a.bp = w.bp;
             a.n_ranges = T2; a.range_stride = 1;
@@ -1551,7 +1560,7 @@ int run_forward(const void *x, const void *W, const void *U, const float *b, con
                 a.n_col_tiles = (int)ceil_div(n_unit_tiles, 4);
                 a.n_tiles = segs[i].n_proj_tiles * a.n_col_tiles;
                 a.n_blocks = a.n_tiles;
-                if (i + 1 < segs.size() && segs[i + 1].rows <= kThinMaxRows) {     // as below: the next stack step rides along
+                if (i + 1 < segs.size() && segs[i + 1].rows <= thin_max) {     // as below: the next stack step rides along
                     thin_proj_stack_kernel<T, true><<<a.n_blocks + stack_blocks(segs[i + 1]), kThinWaves * 64, 0, st>>>(
                         a, stack_args(segs[i + 1]));
                     stacked_ahead = true;
@@ -1577,7 +1586,7 @@ int run_forward(const void *x, const void *W, const void *U, const float *b, con
             a.row_rec = w.row_rec + 2 * (int64_t)begin;
             a.proj_nodes = slots ? nullptr : s->perm + begin;
             a.n_rows = rows;
-            const bool thin_p = rows <= kThinMaxRows;
+            const bool thin_p = rows <= thin_max;
             ScopedLaunchTimer tm(thin_p ? JITDB_K_THIN_PROJ : JITDB_K_PROJ, rows, st);
             if (thin_p) {
                 a.n_col_tiles = (int)ceil_div(n_unit_tiles, 4);
@@ -1586,7 +1595,7 @@ int run_forward(const void *x, const void *W, const void *U, const float *b, con
                 // the stack step of the next slot, if that is thin too, rides along with the slot's
                 // last projection (the level kernel above was the stack buffer's only reader); its
                 // rows are counted with this launch's class
-                if (p == last_sub && i + 1 < segs.size() && segs[i + 1].l > 0 && segs[i + 1].rows <= kThinMaxRows &&
+                if (p == last_sub && i + 1 < segs.size() && segs[i + 1].l > 0 && segs[i + 1].rows <= thin_max &&
                     !is_nary(segs[i + 1].sig)) {
                     thin_proj_stack_kernel<T><<<a.n_blocks + stack_blocks(segs[i + 1]), kThinWaves * 64, 0, st>>>(
                         a, stack_args(segs[i + 1]));
