@@ -249,7 +249,8 @@ tree_x_kernel(const TreesArgs a) {
 #pragma unroll
         for (int s = 0; s < NS; ++s) {
 #pragma unroll
-            for (int g = 0; g < 4; ++g) mfma16<T>(fa[s], fb[s][g], acc[g]);
+            for (int g = 0; g < 3; ++g) mfma16<T>(fa[s], fb[s][g], acc[g]);
+            if (!leaf) mfma16<T>(fa[s], fb[s][3], acc[3]);          // (leaves have no forget gate)
             if (s < PF) fa[s] = load_slab(row, s);
         }
         const int unit = ut * 16 + (fresh_lane(lane) & 15);       // (nothing derived from it stays in registers meanwhile)
