@@ -21,6 +21,8 @@
 // Gradients are fp32; with JITDB_BF16 the operands of the products (dz, x, h, hs, weights) and the values handed from level
 // to level through dhs and ufg are bfloat16, every sum and dc fp32.
 
+#include <algorithm>
+
 #include "tile_gemm.h"
 
 namespace jitdb {
@@ -559,7 +561,7 @@ struct BwdWs {
 // (each costs 128 KB of partial sums a tile).  Long sums are cut eight times finer: the ranges, dealt whole to the XCDs, then
 // come out even (13 ranges of 90 k rows: 5.4 ms, two on five of the XCDs and one on the others).
 constexpr int kMinSplitRows = 128, kLongSplitRows = 4096;
-struct TnPlan { int tiles[3], begin[3], f_tile, rows, rows_per_split, splits, total_tiles; };
+struct TnPlan { int tiles[3], begin[3], f_tile, rows, rows_per_split, splits, total_tiles, leaf_tiles; };
 TnPlan plan_tn(int64_t n, int64_t first_internal, const BwdDims &d) {
     TnPlan p = {};
     p.rows = n > 0 ? (int)round_up(n, 64) : 64;
@@ -573,7 +575,8 @@ TnPlan plan_tn(int64_t n, int64_t first_internal, const BwdDims &d) {
     p.tiles[2] = mh * (int)ceil_div(d.Hk, 256);
     p.total_tiles = p.tiles[0] + p.tiles[1] + p.tiles[2];
     const int f_tiles = mx * (n4 - p.f_tile);
-    const int64_t work = (int64_t)(p.tiles[0] - f_tiles + p.tiles[2]) * p.rows + (int64_t)(p.tiles[1] + f_tiles) * (p.rows - fi);
+    p.leaf_tiles = p.tiles[0] - f_tiles + p.tiles[2];          // tiles that sum over the leaves too
+    const int64_t work = (int64_t)p.leaf_tiles * p.rows + (int64_t)(p.tiles[1] + f_tiles) * (p.rows - fi);
     int64_t rps = round_up(ceil_div(work, 512), 64);
     if (rps >= 4 * kLongSplitRows) rps = round_up(rps / 8, 64);
     if (rps < kMinSplitRows) rps = kMinSplitRows;
@@ -581,6 +584,16 @@ TnPlan plan_tn(int64_t n, int64_t first_internal, const BwdDims &d) {
     p.rows_per_split = (int)rps;
     p.splits = (int)ceil_div(p.rows, rps);
     return p;
+}
+
+// Room for the partial sums: no fewer ranges than plan_tn can make of n nodes, whichever of them are leaves, and no fewer than
+// it makes of a smaller forest.  Leaves alone are the least work, so a range holds at least that work / 512 (long sums: / 4096)
+// and kMinSplitRows (kLongSplitRows / 2) rows.
+int64_t max_splits(int64_t n, const BwdDims &d) {
+    const TnPlan p = plan_tn(n, n, d);
+    const int64_t t = p.leaf_tiles, rows = p.rows;
+    const int64_t lng = std::min(ceil_div(8 * 512, t), ceil_div(rows, kLongSplitRows / 2));
+    return std::min(ceil_div(rows, kMinSplitRows), std::max(ceil_div(512, t), lng));
 }
 
 BwdWs carve_bwd_ws(int64_t n, const BwdDims &d, void *base) {
@@ -602,9 +615,7 @@ BwdWs carve_bwd_ws(int64_t n, const BwdDims &d, void *base) {
     w.AX = c.take<char>(row * round_up(d.D + 1, 128));
     w.AH = c.take<char>(row * round_up(d.H, 128));
     w.AS = c.take<char>(row * round_up(d.H, 128));
-    // no forest is cut into more ranges than one of leaves alone: the less there is to sum, the shorter the ranges
-    const TnPlan p = plan_tn(n, n, d);
-    w.partial = c.take<float>((size_t)p.splits * p.total_tiles * 128 * 256);
+    w.partial = c.take<float>((size_t)max_splits(n, d) * plan_tn(n, n, d).total_tiles * 128 * 256);
     w.bytes = c.off;
     return w;
 }

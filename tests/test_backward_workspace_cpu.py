@@ -1,0 +1,44 @@
+"""Room for the partial sums of the backward pass, worked out on the host (no GPU)."""
+import ctypes
+
+import numpy as np
+import pytest
+
+import paper_1904_07421_amd as J
+from paper_1904_07421_amd import binding
+
+
+def _up(a, b):
+    return -(-a // b) * b
+
+
+def _needed(n, leaves, D, H, esz):
+    """Bytes of the operands by node and of the partial sums as the launch cuts them (128 x 256 tiles of fp32 a range)."""
+    Hk, rows = _up(H, 64), _up(n, 64)
+    n4, mx, mh = Hk // 64, -(-(D + 1) // 128), -(-H // 128)
+    tiles = mx * n4, mh * -(-3 * Hk // 256), mh * -(-Hk // 256)
+    f = mx * (n4 - 3 * Hk // 256) if 3 * Hk % 256 == 0 else 0        # tiles with nothing but the forget gate
+    work = (tiles[0] - f + tiles[2]) * rows + (tiles[1] + f) * (rows - leaves // 64 * 64)
+    per = _up(-(-work // 512), 64)
+    if per >= 16384:
+        per = _up(per // 8, 64)
+    splits = -(-rows // min(max(per, 128), rows))
+    operands = n * (4 * H + esz * (H + _up(4 * Hk, 256) + _up(Hk, 256) + _up(D + 1, 128) + 2 * _up(H, 128)))
+    return operands + splits * sum(tiles) * 128 * 256 * 4
+
+
+def _bytes(n, leaves, D, H, dtype):
+    levels = np.array([0, leaves, n], dtype=np.int32)
+    s = binding._ScheduleStruct(n_nodes=n, host_level_ptr=levels.ctypes.data, n_levels=2)
+    lib = binding.load_library()
+    return int(lib.jitdb_treelstm_backward_workspace_bytes(ctypes.byref(s), D, H, dtype))
+
+
+@pytest.mark.parametrize("D,H", [(300, 150), (300, 512), (64, 1024), (24, 24), (300, 4096)])
+def test_partial_sums_have_room_whatever_the_leaves(D, H):
+    for n in (1, 64, 1000, 6000, 70000, 250000, 650000, 3000000):
+        for share in (0.02, 0.25, 0.5, 0.75, 1.0):
+            leaves = max(1, int(n * share))
+            if leaves < n:
+                got = _bytes(n, leaves, D, H, J.JITDB_BF16)
+                assert got >= _needed(n, leaves, D, H, 2), (n, leaves, D, H)

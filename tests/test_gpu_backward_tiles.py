@@ -68,3 +68,20 @@ def test_backward_at_the_edges_of_its_tiles(leaves, kids, lone, D, H, dtype):
         err = float(np.abs(a.cpu().numpy() - r).max() / max(1.0, np.abs(r).max()))
         print(f"   {name} {err:.2e}", flush=True)
         assert err <= TOL[dtype], (name, err)
+
+
+def test_partial_sums_stay_inside_the_workspace():
+    """Chains: so few leaves that the sums are long ones (cut eight times finer) where those of leaves alone are not."""
+    n, D, H = 70000, 64, 1024
+    v = torch.arange(n, dtype=torch.int32)
+    s = J.jitdb_schedule(torch.where(v % 10 == 0, -1, v - 1).cuda())
+    gen = torch.Generator(device="cuda").manual_seed(1)
+    rand = lambda *size: torch.randn(size, generator=gen, device="cuda") / size[-1] ** 0.5
+    x, W, U, b = rand(n, D).bfloat16(), rand(4 * H, D).bfloat16(), rand(4 * H, H).bfloat16(), rand(4 * H)
+    need = J.jitdb_treelstm_backward_workspace_bytes(s, D, H, J.JITDB_BF16)
+    buf = torch.full((need + (1 << 29),), 0x5A, dtype=torch.uint8, device="cuda")
+    print(f"backward workspace N={n} D={D} H={H} {need >> 20} MiB", flush=True)
+    h, c, gates, fgate = J.jitdb_treelstm_forward_train(x, W, U, b, s)
+    dx, dW, dU, db = J.jitdb_treelstm_backward(x, W, U, s, h, c, gates, fgate, rand(n, H), None, workspace=buf[:need])
+    assert bool((buf[need:] == 0x5A).all())
+    assert all(bool(torch.isfinite(g).all()) for g in (dx, dW, dU, db))
