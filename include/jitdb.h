@@ -97,9 +97,10 @@ typedef struct {
                                           level l (0 for level 0), -1 = not known.  Optional: with it the forward
                                           recognises levels in which every node has exactly one child (chains:
                                           sequences, the thin tail of a forest) and runs each as a single launch */
-    int32_t tree_window;     /* out: > 0 = the trees are filed one after another and no tree (no run of interleaved
-                                          trees) is longer than this many ids: any tree_window + 1 consecutive places
-                                          between ids hold one that no edge crosses.  0 = not known (set it to 0 in a
+    int32_t tree_window;     /* out: > 0 = positions are in (height, id) order, the trees are filed one after
+                                          another and no tree (no run of interleaved trees) is longer than this many
+                                          ids: any tree_window + 1 consecutive places between ids hold one that no edge
+                                          crosses.  0 = not known, or more than one signature (set it to 0 in a
                                           schedule made by hand); the forward then runs level by level */
 } jitdb_schedule_t;
 

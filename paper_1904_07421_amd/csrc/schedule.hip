@@ -654,7 +654,7 @@ int schedule_local(const int32_t *parent, const int32_t *sig, jitdb_slots_t *slo
     const int32_t L = rep->n_levels;
     s->n_levels = L;
     s->n_edges = rep->n_edges;
-    s->tree_window = rep->tree_window;
+    s->tree_window = n_sig == 1 ? rep->tree_window : 0;      // (by signature, a tree's nodes of one level are not neighbours)
     memcpy(s->host_level_ptr, rep->level_ptr, sizeof(int32_t) * ((size_t)L + 1));
     if (s->host_level_kids) memcpy(s->host_level_kids, rep->kids, sizeof(int32_t) * (size_t)L);
     if (slots) memcpy(slots->host_slot_ptr, rep->slot_ptr, sizeof(int32_t) * ((size_t)L * n_sig * n_sig + 1));

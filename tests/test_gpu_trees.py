@@ -81,3 +81,23 @@ def test_what_does_not_fit_runs_level_by_level(c_oracle, what):
     ho, co, _ = c_oracle(p, *seen)
     assert prof["trees"]["launches"] == 0
     assert np.abs(h - ho).max() <= 1e-4 and np.abs(c - co).max() <= 1e-4 * max(1.0, np.abs(co).max() / 50.0)
+
+
+@pytest.mark.parametrize("appended", [False, True])
+def test_a_typed_table_as_a_plain_schedule(c_oracle, appended):
+    """One cell on a table filed by (height, signature): any order inside a level is a valid batch, and a tree's nodes of a
+    level are no longer neighbours."""
+    import torch
+    import paper_1904_07421_amd as J
+    p = FORESTS["word-order"]()
+    sig = (np.arange(p.shape[0]) % 3).astype(np.int32)
+    s = J.jitdb_schedule_typed(torch.from_numpy(p).cuda(), torch.from_numpy(sig).cuda(), 3)
+    if appended:
+        more = perfect_kary_tree(2, 3)
+        s, p = J.jitdb_schedule_append(s, torch.from_numpy(more).cuda()), _lay_out([p, more])
+    x, W, U, b = make_values(1, p.shape[0], "random", D=40, H=48)
+    print(f"typed table as a plain schedule N={p.shape[0]} appended={appended}", flush=True)
+    h, c = J.jitdb_treelstm_forward(*(torch.from_numpy(v).cuda() for v in (x, W, U, b)), s)
+    ho, co, _ = c_oracle(p, x, W, U, b)
+    assert np.abs(h.cpu().numpy() - ho).max() <= 1e-4
+    assert np.abs(c.cpu().numpy() - co).max() <= 1e-4 * max(1.0, np.abs(co).max() / 50.0)
