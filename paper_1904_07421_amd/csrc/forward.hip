@@ -1201,19 +1201,22 @@ ForwardWs carve_forward_ws(int64_t n, int64_t e, const Dims &d, void *base, int 
     w.bp = c.take<float>((size_t)d.NP * n_sig);
     // one level at a time; whole row tiles are read, hence the 256 spare rows
     size_t stack_bytes = (size_t)(n + kRowPad) * (d.Dp + d.Hp) * d.esz;
-    // the same sizes for tables of more than one signature: what they ask for grows with n_sig from there
-    with_z = with_z && n <= kTreesMaxNodes && d.H <= kTreesMaxWidth;
-    const size_t z_bytes = (size_t)n * 4 * round_up(d.H, 16) * 4;
+    // the same sizes for tables of more than one signature: what they ask for grows with n_sig from there; and larger forests
+    // ask for no less than the largest that runs in one launch, so that their workspace holds any smaller one
+    with_z = with_z && d.H <= kTreesMaxWidth;
+    const int64_t n_z = n < kTreesMaxNodes ? n : kTreesMaxNodes;
+    const size_t z_bytes = (size_t)n_z * 4 * round_up(d.H, 16) * 4;
     if (with_z && z_bytes > stack_bytes) stack_bytes = z_bytes;
     w.stack = c.take<char>(stack_bytes);
-    w.Z = with_z && n_sig == 1 ? static_cast<float *>(w.stack) : nullptr;
+    const bool z_used = with_z && n_sig == 1 && n <= kTreesMaxNodes;
+    w.Z = z_used ? static_cast<float *>(w.stack) : nullptr;
     w.row_rec = c.take<int4>((size_t)2 * (n + kRowPad));   // every level position
     w.hs = (d.H == d.Hp) ? nullptr : c.take<char>((size_t)n * d.Hp * d.esz);
     size_t p_bytes = (size_t)n * d.Hq * d.esz;
-    const size_t fc_bytes = (size_t)n * round_up(d.H, 16) * 4;
+    const size_t fc_bytes = (size_t)n_z * round_up(d.H, 16) * 4;
     if (with_z && fc_bytes > p_bytes) p_bytes = fc_bytes;
     w.P = c.take<char>(p_bytes);
-    w.FC = with_z && n_sig == 1 ? static_cast<float *>(w.P) : nullptr;
+    w.FC = z_used ? static_cast<float *>(w.P) : nullptr;
     w.cs = (d.H == d.Hq) ? nullptr : c.take<float>((size_t)n * d.Hq);
     int n_max = 0;
     for (int t = 0; cells && t < n_sig; ++t)

@@ -1,4 +1,4 @@
-"""Room for the partial sums of the backward pass, worked out on the host (no GPU)."""
+"""Workspaces: what their sizes promise, worked out on the host (no GPU)."""
 import ctypes
 
 import numpy as np
@@ -42,3 +42,15 @@ def test_partial_sums_have_room_whatever_the_leaves(D, H):
             if leaves < n:
                 got = _bytes(n, leaves, D, H, J.JITDB_BF16)
                 assert got >= _needed(n, leaves, D, H, 2), (n, leaves, D, H)
+
+
+@pytest.mark.parametrize("D,H,dtype", [(24, 24, J.JITDB_F32), (300, 150, J.JITDB_BF16), (300, 256, J.JITDB_F32), (300, 512, J.JITDB_BF16)])
+def test_a_larger_forests_workspace_holds_a_smaller_ones(D, H, dtype):
+    sizes = [1, 1000, 65536, 65537, 262143, 262144, 262145, 300000, 600000, 2000000]
+    for n_sig in (1, 3):
+        forward = [J.jitdb_treelstm_typed_workspace_bytes(n, n - 1, D, H, dtype, n_sig) for n in sizes]
+        assert forward == sorted(forward), (n_sig, forward)
+    cells = [J.jitdb_treelstm_cells_workspace_bytes(n, n - 1, D, H, dtype, [(J.JITDB_CELL_NARY, 2)]) for n in sizes]
+    assert cells == sorted(cells)
+    backward = [_bytes(n, max(1, n // 2), D, H, dtype) for n in sizes[1:]]
+    assert backward == sorted(backward)
