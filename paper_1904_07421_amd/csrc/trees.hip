@@ -211,6 +211,12 @@ tree_x_kernel(const TreesArgs a) {
 #pragma unroll
             for (int g = 0; g < 4; ++g)
                 fb[s][g] = *reinterpret_cast<const u32x4 *>(w + (int64_t)(s < a.sx_packed ? s : 0) * a.NPU * 64 + g * 2048);
+        // slabs past the packed x part meet zeros, but 0 times an infinite weight would be NaN
+#pragma unroll
+        for (int s = slabs_below(NS); s < NS; ++s)
+#pragma unroll
+            for (int g = 0; g < 4; ++g)
+                if (s >= a.sx_packed) fb[s][g] = u32x4{0, 0, 0, 0};
     }
     const T *x = static_cast<const T *>(a.x);
     // tiles in the schedule's order: first the leaves', then the others', so that a tile's nodes all go the same way
@@ -222,7 +228,7 @@ tree_x_kernel(const TreesArgs a) {
     };
     auto row_of = [&](int tile) __attribute__((always_inline)) { return x + node_of(tile, n) * a.D + hf * VEC; };
     // slab s of a row: whole 16 bytes where all four pieces lie inside D; the slab that straddles D, and those past it,
-    // piece by piece (the weights read for slabs past the packed x part are not zero)
+    // piece by piece
     auto load_slab = [&](const T *row, int s) __attribute__((always_inline)) {
         u32x4 v;
         if (s < slabs_below(NS) || (s + 1) * 4 * VEC <= a.D) __builtin_memcpy(&v, row + s * 4 * VEC, 16);

@@ -101,3 +101,19 @@ def test_a_typed_table_as_a_plain_schedule(c_oracle, appended):
     ho, co, _ = c_oracle(p, x, W, U, b)
     assert np.abs(h.cpu().numpy() - ho).max() <= 1e-4
     assert np.abs(c.cpu().numpy() - co).max() <= 1e-4 * max(1.0, np.abs(co).max() / 50.0)
+
+
+@pytest.mark.parametrize("dtype", ["float32", "bfloat16"])
+def test_infinite_weights_saturate_gates(dtype):
+    """An infinite weight on one unit's gates: that gate is 0 or 1 (u: -1 or 1), not NaN, in every node (D of one weight slab)."""
+    import torch
+    import paper_1904_07421_amd as J
+    p, D, H = FORESTS["row-groups"](), 8, 33
+    x, W, U, b = (torch.from_numpy(v).cuda().to(getattr(torch, dtype)) for v in make_values(1, p.shape[0], "random", D=D, H=H))
+    x[:, 0] = 1.0                                         # (0 times the weight is NaN by right)
+    for g, v in enumerate((float("-inf"), float("inf"), float("-inf"), float("inf"))):
+        W[g * H + 5, 0] = v                               # i = 0, o = 1, u = -1, f = 1: c = 0, h = 0
+    h, c = J.jitdb_treelstm_forward(x, W, U, b.float(), J.jitdb_schedule(torch.from_numpy(p).cuda()))
+    print(f"infinite weights {dtype} N={p.shape[0]}", flush=True)
+    assert bool(torch.isfinite(h).all()) and bool(torch.isfinite(c).all())
+    assert bool((h[:, 5] == 0).all()) and bool((c[:, 5] == 0).all())
