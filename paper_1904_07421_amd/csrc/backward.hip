@@ -508,7 +508,7 @@ tn_kernel(const TnArgs e) {
 
 __global__ void __launch_bounds__(kT)
 grad_reduce_kernel(const TnArgs e) {
-    const int tile = blockIdx.y, rest = blockIdx.x, t = threadIdx.x;
+    const int tile = blockIdx.x >> 5, rest = blockIdx.x & 31, t = threadIdx.x;      // (widest cells: more tiles than a grid has rows)
     int mt, nt, begin;
     const int which = tn_decode(e, tile, mt, nt, begin);
     const int lane = t & 63, wave = t >> 6, i = rest >> 4, g = (rest >> 2) & 3, v = rest & 3;
@@ -738,7 +738,7 @@ int run_backward(const T *x, const T *W, const T *U, const BwdDims &d, const jit
     e.tiles = plan.total_tiles; e.partial = w.partial; e.dW = dW; e.dU = dU; e.db = db; e.D = D; e.H = H; e.Hk = Hk;
     tn_kernel<T><<<(unsigned)(8 * ceil_div(e.splits, 8) * e.tiles), kDmaThreads, 0, st>>>(e);
     JITDB_LAUNCH_CHECK();
-    grad_reduce_kernel<<<dim3(32, (unsigned)e.tiles), kT, 0, st>>>(e);
+    grad_reduce_kernel<<<32u * (unsigned)e.tiles, kT, 0, st>>>(e);
     JITDB_LAUNCH_CHECK();
     return JITDB_OK;
 }
