@@ -84,7 +84,7 @@ struct PrepArgs {
     int32_t *parent_of;
     void *AX, *AH, *AS, *dZ, *G, *Wt, *Ut, *Uft;
     int D, H, Hk;
-    int n, n_rows, first;          // nodes; rounded up to 64; first row of AS that anything reads
+    int n, n_rows, first;          // nodes; rows that the sums over the nodes may read; first row of AS that anything reads
     int64_t rows_alloc, w_alloc, u_alloc;
     int x_groups, row_blocks, h_groups;
 };
@@ -174,8 +174,8 @@ bwd_prepare_kernel(const PrepArgs a) {
 //     dh_j = gh_j + dhs_p + ufg_r      ufg (level order) = U_f^T dz_f,j, from the product before this kernel
 //     dc_j = gc_j + dc_p f_j + dh_j o_j (1 - tanh^2 c_j)
 // Every child k of j gets its dz_f,k = dc_j c_k f_k (1 - f_k) written to row inv_perm[k] of G; a root writes its own row of
-// zeros.  Row r of dZ = [dz_i | dz_o | dz_u | sum_k dz_f,k]; a leaf's forget block is read by few and written only from row
-// zero_from on.  dc_j stays in dc[j] for the children's level.
+// zeros.  Row r of dZ = [dz_i | dz_o | dz_u | sum_k dz_f,k]; a leaf's forget block is written only where something reads
+// it (zero_forget).  dc_j stays in dc[j] for the children's level.
 // Bound by memory: 36 bytes a unit of the node (bf16, with gh) and 8 per child, read and written in 16-byte pieces: 591 k
 // leaves, H = 512: 1.96 ms (4.6 TB/s), all 15 levels of 1.18 M nodes 5.9 ms (8.0 one unit a lane and dZ written twice).
 // Few rows: bound by the chain node -> children -> their rows, so several children's rows are in flight.
@@ -187,7 +187,7 @@ struct CellArgs {
     float *dc;
     void *dZ, *G;
     int64_t rows_alloc;
-    int row0, n_rows, H, Hk, zero_from;      // the level's rows are positions row0 .. row0 + n_rows
+    int row0, n_rows, H, Hk, zero_forget;      // the level's rows are positions row0 .. row0 + n_rows
 };
 template <typename T> constexpr int kKidsAhead = sizeof(T) == 4 ? 4 : 2;
 template <typename T, bool VEC, bool LEAVES>
@@ -291,7 +291,7 @@ bwd_cell_kernel(const CellArgs a) {
             }
         }
     }
-    if (!LEAVES || r >= a.zero_from) store16(a.dZ, r, 3 * gate_kb + kb, a.rows_alloc, pack_units<T>(dzf));
+    if (!LEAVES || a.zero_forget) store16(a.dZ, r, 3 * gate_kb + kb, a.rows_alloc, pack_units<T>(dzf));
     if (p < 0) store16(a.G, r, kb, a.rows_alloc, zero);
 }
 
@@ -450,7 +450,8 @@ struct TnProblem {
     const char *A, *B;
     int m_tiles, n_tiles;
     int tile0;                 // index of its first tile
-    int begin, begin_f;        // first row of the reduction; of the tiles from column tile f_tile on
+    int begin, begin_f;        // first row of the reduction, a multiple of 64; of the tiles from column tile f_tile on
+    int shift, shift_f;        // 0 .. 63, added to all rows: sums over the inner nodes start exactly at the first of them
     int f_tile;
 };
 struct TnArgs {
@@ -461,12 +462,13 @@ struct TnArgs {
     float *dW, *dU, *db;
     int D, H, Hk;
 };
-__device__ __forceinline__ int tn_decode(const TnArgs &a, int tile, int &m, int &n, int &begin) {
+__device__ __forceinline__ int tn_decode(const TnArgs &a, int tile, int &m, int &n, int &begin, int &shift) {
     const int q = tile >= a.p[2].tile0 ? 2 : tile >= a.p[1].tile0 ? 1 : 0;
     const TnProblem &p = a.p[q];
     m = (tile - p.tile0) / p.n_tiles;
     n = (tile - p.tile0) % p.n_tiles;
     begin = n >= p.f_tile ? p.begin_f : p.begin;
+    shift = n >= p.f_tile ? p.shift_f : p.shift;
     return q;
 }
 template <typename T>
@@ -475,12 +477,14 @@ tn_kernel(const TnArgs e) {
     __shared__ __attribute__((aligned(1024))) char lds[kDmaBufs * kDmaBuf];
     const int q = blockIdx.x >> 3, split = (blockIdx.x & 7) + 8 * (q / e.tiles), tile = q % e.tiles;
     if (split >= e.splits) return;
-    int mt, nt, begin;
-    const int which = tn_decode(e, tile, mt, nt, begin);
+    int mt, nt, begin, shift;
+    const int which = tn_decode(e, tile, mt, nt, begin, shift);
     int k0 = split * e.rows_per_split, k1 = k0 + e.rows_per_split;
     if (k0 < begin) k0 = begin;
     if (k1 > e.n_rows) k1 = e.n_rows;
     if (k0 >= k1) return;
+    k0 += shift;
+    k1 += shift;
     constexpr int ESZ = (int)sizeof(T);
     LevelArgs a = {};
     a.n_rows_alloc = (int)e.rows_alloc;
@@ -509,8 +513,8 @@ tn_kernel(const TnArgs e) {
 __global__ void __launch_bounds__(kT)
 grad_reduce_kernel(const TnArgs e) {
     const int tile = blockIdx.x >> 5, rest = blockIdx.x & 31, t = threadIdx.x;      // (widest cells: more tiles than a grid has rows)
-    int mt, nt, begin;
-    const int which = tn_decode(e, tile, mt, nt, begin);
+    int mt, nt, begin, shift;
+    const int which = tn_decode(e, tile, mt, nt, begin, shift);
     const int lane = t & 63, wave = t >> 6, i = rest >> 4, g = (rest >> 2) & 3, v = rest & 3;
     const int m = mt * 128 + (wave >> 1) * 64 + i * 32 + v * 8 + (lane >> 5) * 4;
     const int n = nt * 256 + (wave & 1) * 128 + g * 32 + (lane & 31);
@@ -561,12 +565,16 @@ struct BwdWs {
 // (each costs 128 KB of partial sums a tile).  Long sums are cut eight times finer: the ranges, dealt whole to the XCDs, then
 // come out even (13 ranges of 90 k rows: 5.4 ms, two on five of the XCDs and one on the others).
 constexpr int kMinSplitRows = 128, kLongSplitRows = 4096;
-struct TnPlan { int tiles[3], begin[3], f_tile, rows, rows_per_split, splits, total_tiles, leaf_tiles; };
+// Sums over the inner nodes alone (dU_iou, dW_f) start at the first of them, not at the 64 rows it lies in: a leaf has no part
+// in them, but its zero child sum times an infinite dz would be NaN.  Their ranges are those of all nodes, moved up by less
+// than 64 rows, into zero rows at the end.
+struct TnPlan { int tiles[3], begin[3], shift, f_tile, rows, rows_per_split, splits, total_tiles, leaf_tiles; };
 TnPlan plan_tn(int64_t n, int64_t first_internal, const BwdDims &d) {
     TnPlan p = {};
     p.rows = n > 0 ? (int)round_up(n, 64) : 64;
     const int fi = (int)(first_internal / 64 * 64), n4 = 4 * d.Hk / 256;
     p.begin[1] = fi;
+    p.shift = (int)(first_internal - fi);
     // the column tiles that hold nothing but the forget gate
     p.f_tile = 3 * d.Hk % 256 == 0 ? 3 * d.Hk / 256 : n4;
     const int mx = (int)ceil_div(d.D + 1, 128), mh = (int)ceil_div(d.H, 128);
@@ -673,9 +681,9 @@ int run_backward(const T *x, const T *W, const T *U, const BwdDims &d, const jit
         PrepArgs a = {};
         a.x = x; a.h = h; a.W = W; a.U = U; a.perm = s->perm; a.child_ptr = s->child_ptr; a.child_idx = s->child_idx;
         a.parent_of = w.parent_of; a.AX = w.AX; a.AH = w.AH; a.AS = w.AS; a.dZ = w.dZ; a.G = w.G; a.Wt = w.Wt; a.Ut = w.Ut; a.Uft = w.Uft;
-        a.D = D; a.H = H; a.Hk = Hk; a.n = n; a.n_rows = plan.rows; a.first = plan.begin[1];
+        a.D = D; a.H = H; a.Hk = Hk; a.n = n; a.n_rows = plan.rows + plan.shift; a.first = lp[1];
         a.rows_alloc = w.rows_alloc; a.w_alloc = w.w_alloc; a.u_alloc = w.u_alloc;
-        a.x_groups = (int)ceil_div(D + 1, 64); a.h_groups = Hk / 64; a.row_blocks = (int)ceil_div(plan.rows, kRows<T>);
+        a.x_groups = (int)ceil_div(D + 1, 64); a.h_groups = Hk / 64; a.row_blocks = (int)ceil_div(a.n_rows, kRows<T>);
         const int64_t w_blocks = ceil_div((int64_t)(D + H) * 4 * (Hk / kPer<T>), kT);
         const dim3 grid((unsigned)((int64_t)a.row_blocks * (a.x_groups + a.h_groups) + (w_blocks < 1024 ? w_blocks : 1024)));
         const bool vx = D * sizeof(T) % 4 == 0, vh = H * sizeof(T) % 4 == 0;
@@ -691,8 +699,8 @@ int run_backward(const T *x, const T *W, const T *U, const BwdDims &d, const jit
     a.perm = s->perm; a.inv_perm = s->inv_perm; a.child_ptr = s->child_ptr; a.child_idx = s->child_idx; a.parent_of = w.parent_of;
     a.c = c; a.gh = gh; a.gc = gc; a.gates = gates; a.fgate = fgate; a.dhs = w.dhs; a.ufg = w.ufg; a.dc = w.dc; a.dZ = w.dZ; a.G = w.G;
     a.rows_alloc = w.rows_alloc; a.H = H; a.Hk = Hk;
-    // a leaf's forget block is read where a column tile of the sums holds other gates too, or a range starts among the leaves
-    a.zero_from = plan.f_tile * 256 == 3 * Hk ? plan.begin[1] : 0;
+    // a leaf's forget block is read where a column tile of the sums holds other gates too
+    a.zero_forget = plan.f_tile * 256 != 3 * Hk;
     const bool vec = H * sizeof(T) % 4 == 0 && ((reinterpret_cast<uintptr_t>(gates) | reinterpret_cast<uintptr_t>(fgate)) & 3) == 0;
     for (int l = L - 1; l >= 0; --l) {
         a.row0 = lp[l]; a.n_rows = lp[l + 1] - lp[l];
@@ -731,6 +739,7 @@ int run_backward(const T *x, const T *W, const T *U, const BwdDims &d, const jit
         p.A = static_cast<const char *>(A[q]); p.B = static_cast<const char *>(B[q]);
         p.m_tiles = (int)ceil_div(q == 0 ? D + 1 : H, 128); p.n_tiles = plan.tiles[q] / p.m_tiles;
         p.tile0 = at; p.begin = plan.begin[q]; p.begin_f = q == 0 ? plan.begin[1] : plan.begin[q];
+        p.shift = q == 1 ? plan.shift : 0; p.shift_f = plan.shift;
         p.f_tile = q == 0 ? plan.f_tile : p.n_tiles;
         at += plan.tiles[q];
     }

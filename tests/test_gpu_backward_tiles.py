@@ -85,3 +85,26 @@ def test_partial_sums_stay_inside_the_workspace():
     dx, dW, dU, db = J.jitdb_treelstm_backward(x, W, U, s, h, c, gates, fgate, rand(n, H), None, workspace=buf[:need])
     assert bool((buf[need:] == 0x5A).all())
     assert all(bool(torch.isfinite(g).all()) for g in (dx, dW, dU, db))
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("lone,H", [(1, 256), (3, 150), (60, 64), (64, 256)])
+def test_an_infinite_cotangent_of_a_leaf_stays_out_of_the_inner_nodes_sums(lone, H, dtype):
+    """A lone root is a leaf and nobody's child: its cotangent reaches its own dx row and the i, o, u rows of dW and db, but
+    neither dU nor the forget rows.  The last leaf stands right before the inner nodes, wherever that falls in a range."""
+    parent, D = _stars(100, 7, lone), 40
+    n = len(parent)
+    gen = torch.Generator(device="cuda").manual_seed(lone)
+    rand = lambda *size: torch.randn(size, generator=gen, device="cuda") / size[-1] ** 0.5
+    x, W, U, b = rand(n, D).to(dtype), rand(4 * H, D).to(dtype), rand(4 * H, H).to(dtype), rand(4 * H)
+    s = J.jitdb_schedule(torch.from_numpy(parent).cuda())
+    h, c, gates, fgate = J.jitdb_treelstm_forward_train(x, W, U, b, s)
+    gh = rand(n, H)
+    print(f"infinite cotangent N={n} leaves={int(s.host_level_ptr[1])} H={H} {dtype}", flush=True)
+    want = J.jitdb_treelstm_backward(x, W, U, s, h, c, gates, fgate, gh, None)
+    gh[n - 1, 7] = float("inf")
+    dx, dW, dU, db = J.jitdb_treelstm_backward(x, W, U, s, h, c, gates, fgate, gh, None)
+    assert not bool(torch.isfinite(dx[n - 1]).all())
+    assert torch.equal(dx[:n - 1], want[0][:n - 1])
+    assert torch.equal(dU, want[2])
+    assert torch.equal(dW[3 * H:], want[1][3 * H:]) and torch.equal(db[3 * H:], want[3][3 * H:])
