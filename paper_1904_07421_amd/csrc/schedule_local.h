@@ -240,6 +240,14 @@ window_kernel(const LocalArgs a) {
             s_cnt[i] = 0;
         }
     }
+    // signatures here and not with the keys, which a block with a cycle does not reach: a bad one is reported first
+    if (a.sig) {
+#pragma unroll
+        for (int r = 0; r < IT; ++r) {
+            const int i = r * kLocThreads + t;
+            if (i < own && (a.sig[lo + i] < 0 || a.sig[lo + i] >= a.n_sig)) flags |= LF_SIG;
+        }
+    }
     if (t < KEYS) s_kid[t] = 0;
     __syncthreads();
 #pragma unroll
@@ -326,7 +334,6 @@ window_kernel(const LocalArgs a) {
     for (int k = t; k < kLocWaves * n_keys; k += kLocThreads) wave_cnt[(k / n_keys) * KEYS + k % n_keys] = 0;
     int bits = 1;
     while ((1 << bits) < n_keys) ++bits;
-    int bad_sig = 0;
     if (flags == 0) {
 #pragma unroll
         for (int r = 0; r < IT; ++r) {
@@ -353,20 +360,14 @@ window_kernel(const LocalArgs a) {
             int key = s_hgt[i];
             if (a.sig) {
                 const uint16_t lp = s_par[i];
-                int sg = a.sig[lo + i], ps = lp != kNoParent ? a.sig[lo + lp] : sg;
-                if (sg < 0 || sg >= a.n_sig) { bad_sig = 1; sg = 0; }
-                if (ps < 0 || ps >= a.n_sig) ps = 0;
+                const int sg = a.sig[lo + i], ps = lp != kNoParent ? a.sig[lo + lp] : sg;
                 key = (key * a.n_sig + sg) * a.n_sig + ps;
                 a.key[lo + i] = key;
             }
             keys[i] = (uint16_t)key;
         }
     }
-    if (a.sig) {
-        if (__syncthreads_or(bad_sig)) flags |= LF_SIG;
-    } else {
-        __syncthreads();
-    }
+    __syncthreads();
     int rank[IT], dk[IT];
 #pragma unroll
     for (int r = 0; r < IT; ++r) {

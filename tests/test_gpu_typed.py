@@ -109,6 +109,26 @@ def test_typed_schedule_errors():
     assert s.n_levels == 0 and s.host_slot_ptr[0] == 0
 
 
+@pytest.mark.parametrize("n_sig", [1, 2])
+@pytest.mark.parametrize("trees", [12, 40, 2000])
+def test_a_bad_signature_is_reported_before_a_cycle(trees, n_sig):
+    """Forests of one block and of several, the two faults in one block and far apart."""
+    import paper_1904_07421_amd as J
+    p = chain_forest(5, trees).copy()
+    p[5] = 9                                         # the second tree's root under its own leaf
+    print(f"typed schedule cycle + bad signature N={p.shape[0]} n_sig={n_sig}", flush=True)
+    for at in (0, 7, p.shape[0] - 1):
+        for bad in (-1, n_sig):
+            sig = np.zeros_like(p)
+            sig[at] = bad
+            with pytest.raises(J.JitdbError) as e:
+                _sched(p, sig, n_sig)
+            assert e.value.code == -8
+    with pytest.raises(J.JitdbError) as e:
+        _sched(p, np.zeros_like(p), n_sig)
+    assert e.value.code == -4
+
+
 # ---- forward ---------------------------------------------------------------------------
 def _gpu_forward_typed(p, sig, n_sig, x, W, U, b, dtype):
     import torch
