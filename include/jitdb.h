@@ -78,7 +78,7 @@ typedef enum {
  * paper leaves open, is fixed as ascending node id so that the result is unique.
  *
  * The caller fills n_nodes and all pointers before jitdb_schedule; the call
- * fills the arrays, n_levels and n_edges.
+ * fills the arrays and everything after the pointers.
  */
 typedef struct {
     int64_t n_nodes;         /* in: N, 0 <= N <= JITDB_MAX_NODES */
@@ -100,8 +100,11 @@ typedef struct {
     int32_t tree_window;     /* out: > 0 = positions are in (height, id) order, the trees are filed one after
                                           another and no tree (no run of interleaved trees) is longer than this many
                                           ids: any tree_window + 1 consecutive places between ids hold one that no edge
-                                          crosses.  0 = not known, or more than one signature (set it to 0 in a
-                                          schedule made by hand); the forward then runs level by level */
+                                          crosses.  0 = not known, or more than one signature; the forward then runs
+                                          level by level */
+    uint32_t tree_tag;       /* out: belongs to tree_window, n_nodes, n_levels and n_edges.  A tree_window without its
+                                          tag counts as 0: a schedule made by hand need set neither, and one that is
+                                          kept or sent elsewhere takes both along */
 } jitdb_schedule_t;
 
 /* Bytes of device workspace jitdb_schedule needs for a forest of n_nodes (0 if n_nodes is invalid). */
@@ -504,7 +507,13 @@ const char *jitdb_strerror(int code);
  * which HIP error).  Process-wide, for diagnostics; static storage, never NULL. */
 const char *jitdb_last_hip_error(void);
 
-/* Library version, "major.minor". */
+/*
+ * Library version, "major.minor".  The structs of this header are written by the library and carry no size, so a
+ * program must be compiled against the header of the library it runs with: one whose JITDB_VERSION differs from
+ * jitdb_version() must not call anything else.  0.2 added tree_window and tree_tag to jitdb_schedule_t and
+ * JITDB_K_TREES to the arrays of jitdb_profile_t; both are longer than in 0.1.
+ */
+#define JITDB_VERSION "0.2"
 const char *jitdb_version(void);
 
 #ifdef __cplusplus

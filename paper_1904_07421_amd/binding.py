@@ -18,6 +18,8 @@ import torch as _torch
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "libjitdb.so")
 
+_VERSION = "0.2"            # JITDB_VERSION of the header that the structs below follow
+
 JITDB_F32 = 0
 JITDB_CELL_CHILDSUM = 0
 JITDB_CELL_NARY = 1
@@ -47,6 +49,7 @@ class _ScheduleStruct(ctypes.Structure):
         ("n_edges", ctypes.c_int64),
         ("host_level_kids", ctypes.c_void_p),
         ("tree_window", ctypes.c_int32),
+        ("tree_tag", ctypes.c_uint32),
     ]
 
 
@@ -90,6 +93,10 @@ def load_library():
         from .build import build
         build()
     lib = ctypes.CDLL(_LIB_PATH)
+    lib.jitdb_version.restype = ctypes.c_char_p
+    lib.jitdb_version.argtypes = []
+    if lib.jitdb_version().decode() != _VERSION:
+        raise ImportError(f"{_LIB_PATH} is version {lib.jitdb_version().decode()}, this binding is for {_VERSION}: build the library again")
     lib.jitdb_schedule_workspace_bytes.restype = ctypes.c_size_t
     lib.jitdb_schedule_workspace_bytes.argtypes = [ctypes.c_int64]
     lib.jitdb_schedule.restype = ctypes.c_int
@@ -197,8 +204,6 @@ def load_library():
     lib.jitdb_strerror.argtypes = [ctypes.c_int]
     lib.jitdb_last_hip_error.restype = ctypes.c_char_p
     lib.jitdb_last_hip_error.argtypes = []
-    lib.jitdb_version.restype = ctypes.c_char_p
-    lib.jitdb_version.argtypes = []
     _lib = lib
     return lib
 

@@ -32,4 +32,4 @@ void note_hip_failure(hipError_t e, const char *file, int line) {
 
 extern "C" const char *jitdb_last_hip_error(void) { return jitdb::g_hip_detail; }
 
-extern "C" const char *jitdb_version(void) { return "0.1"; }
+extern "C" const char *jitdb_version(void) { return JITDB_VERSION; }

@@ -49,6 +49,22 @@ void note_hip_failure(hipError_t e, const char *file, int line);
 // that the launch checks only see this library's own launches.
 inline void drop_stale_hip_error() { (void)hipGetLastError(); }
 
+// tree_window decides which kernels may run, and a wrong one would drop nodes without an error: it counts only with the
+// tag that set_tree_window leaves beside it, which uninitialised memory and a value set by hand do not have.
+inline uint32_t tree_window_tag(const jitdb_schedule_t *s) {
+    uint64_t v = (uint64_t)s->n_nodes * 0x9E3779B97F4A7C15ull + (uint64_t)s->n_edges;
+    v = (v ^ (v >> 29)) * 0xBF58476D1CE4E5B9ull + (((uint64_t)(uint32_t)s->n_levels << 32) | (uint32_t)s->tree_window);
+    v = (v ^ (v >> 32)) * 0x94D049BB133111EBull;
+    return (uint32_t)(v >> 32);
+}
+inline void set_tree_window(jitdb_schedule_t *s, int32_t window) {      // after n_levels and n_edges
+    s->tree_window = window;
+    s->tree_tag = window > 0 ? tree_window_tag(s) : 0;
+}
+inline int32_t known_tree_window(const jitdb_schedule_t *s) {
+    return s->tree_window > 0 && s->tree_tag == tree_window_tag(s) ? s->tree_window : 0;
+}
+
 // Nothing may throw across the C ABI: host-side containers and `new` can (std::bad_alloc).
 // Every extern "C" entry point that reaches such code wraps its body in these.
 #define JITDB_ABI_TRY try {

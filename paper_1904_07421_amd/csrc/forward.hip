@@ -1300,12 +1300,13 @@ int run_forward(const void *x, const void *W, const void *U, const float *b, con
     // A forest of small trees filed one after another: its levels below the chain levels in one launch
     TreesArgs ta = {};
     bool trees = false;
-    if (!slots && !any_nary && w.Z && s->tree_window > 0 && s->tree_window <= kTreesMaxSpan && s->inv_perm && chain_from <= kTreesMaxLevels && s->n_nodes <= kTreesMaxNodes) {
+    const int32_t tree_window = known_tree_window(s);
+    if (!slots && !any_nary && w.Z && tree_window > 0 && tree_window <= kTreesMaxSpan && s->inv_perm && chain_from <= kTreesMaxLevels && s->n_nodes <= kTreesMaxNodes) {
         ta.x = x; ta.Bp = w.Bp; ta.bp = w.bp;
         ta.height = s->height; ta.perm = s->perm; ta.inv_perm = s->inv_perm; ta.child_ptr = s->child_ptr; ta.child_idx = s->child_idx;
         ta.h_out = h_out; ta.hs = w.hs ? w.hs : h_out; ta.FC = w.FC; ta.gates = gates; ta.fgate = fgate;
         ta.c_out = c_out; ta.cs = chain_from < L ? w.cs : nullptr; ta.Z = w.Z;
-        ta.n = (int)s->n_nodes; ta.n_leaves = sp[1]; ta.tree_window = s->tree_window; ta.l_end = chain_from;
+        ta.n = (int)s->n_nodes; ta.n_leaves = sp[1]; ta.tree_window = tree_window; ta.l_end = chain_from;
         ta.D = d.D; ta.H = d.H; ta.Hp = d.Hp; ta.Hq = d.Hq; ta.NPU = d.NPU; ta.sx_packed = (int)(d.Dp * d.esz / 64);
         trees = plan_trees(ta, d.esz);
     }

@@ -654,7 +654,7 @@ int schedule_local(const int32_t *parent, const int32_t *sig, jitdb_slots_t *slo
     const int32_t L = rep->n_levels;
     s->n_levels = L;
     s->n_edges = rep->n_edges;
-    s->tree_window = n_sig == 1 ? rep->tree_window : 0;      // (by signature, a tree's nodes of one level are not neighbours)
+    set_tree_window(s, n_sig == 1 ? rep->tree_window : 0);      // (by signature, a tree's nodes of one level are not neighbours)
     memcpy(s->host_level_ptr, rep->level_ptr, sizeof(int32_t) * ((size_t)L + 1));
     if (s->host_level_kids) memcpy(s->host_level_kids, rep->kids, sizeof(int32_t) * (size_t)L);
     if (slots) memcpy(slots->host_slot_ptr, rep->slot_ptr, sizeof(int32_t) * ((size_t)L * n_sig * n_sig + 1));
@@ -680,7 +680,7 @@ int schedule_impl(const int32_t *parent, const int32_t *sig, jitdb_slots_t *slot
     if (!s->host_level_ptr) return JITDB_E_NULL;
     s->n_levels = 0;
     s->n_edges = 0;
-    s->tree_window = 0;
+    set_tree_window(s, 0);
     if (n64 == 0) {
         s->host_level_ptr[0] = 0;
         if (s->host_level_kids) s->host_level_kids[0] = 0;
@@ -884,7 +884,7 @@ extern "C" int jitdb_schedule_append(const jitdb_schedule_t *base, const int32_t
     // children per level add up like the level sizes; known only if both parts know theirs
     const bool kids_known = out->host_level_kids && (na == 0 || base->host_level_kids);
     fresh.host_level_kids = kids_known ? out->host_level_kids + na : nullptr;
-    fresh.n_levels = 0; fresh.n_edges = 0; fresh.tree_window = 0;
+    fresh.n_levels = 0; fresh.n_edges = 0; set_tree_window(&fresh, 0);
     if (n_new > 0) {
         const int rc = jitdb_schedule(parent_new, &fresh, w.sched_ws, w.sched_ws_bytes, hip_stream);
         if (rc != JITDB_OK) return rc;
@@ -904,8 +904,8 @@ extern "C" int jitdb_schedule_append(const jitdb_schedule_t *base, const int32_t
     }
     out->n_levels = l_out;
     out->n_edges = ea + en;
-    const int32_t wa = na > 0 ? base->tree_window : fresh.tree_window, wn = n_new > 0 ? fresh.tree_window : wa;
-    out->tree_window = wa > 0 && wn > 0 ? (wa > wn ? wa : wn) : 0;
+    const int32_t wa = na > 0 ? known_tree_window(base) : fresh.tree_window, wn = n_new > 0 ? fresh.tree_window : wa;
+    set_tree_window(out, wa > 0 && wn > 0 ? (wa > wn ? wa : wn) : 0);
     if (n_out == 0) return JITDB_OK;
 
     const int64_t span = (na > n_new ? na : n_new) + 1;

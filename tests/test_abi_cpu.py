@@ -39,6 +39,24 @@ def test_strerror_and_version(lib):
     assert re.fullmatch(r"\d+\.\d+", J.jitdb_version())
 
 
+def test_structs_follow_the_header(lib, tmp_path):
+    """The binding's structs and version are those of the header that the library was built from."""
+    import subprocess
+    import paper_1904_07421_amd as J
+    from paper_1904_07421_amd import binding
+    src = tmp_path / "sizes.c"
+    src.write_text('#include <stddef.h>\n#include <stdio.h>\n#include "jitdb.h"\nint main(void) { printf("%s %zu %zu %zu %zu %zu %zu", '
+                   'JITDB_VERSION, sizeof(jitdb_schedule_t), offsetof(jitdb_schedule_t, tree_window), offsetof(jitdb_schedule_t, tree_tag), '
+                   'sizeof(jitdb_slots_t), sizeof(jitdb_cell_t), sizeof(jitdb_profile_t)); return 0; }\n')
+    exe = tmp_path / "sizes"
+    subprocess.run(["gcc", "-I", os.path.dirname(HEADER), str(src), "-o", str(exe)], check=True)
+    got = subprocess.run([str(exe)], check=True, capture_output=True, text=True).stdout.split()
+    S = binding._ScheduleStruct
+    assert got[0] == binding._VERSION == J.jitdb_version()
+    assert [int(v) for v in got[1:]] == [ctypes.sizeof(S), S.tree_window.offset, S.tree_tag.offset, ctypes.sizeof(binding._SlotsStruct),
+                                         ctypes.sizeof(binding._CellStruct), ctypes.sizeof(binding._ProfileStruct)]
+
+
 def test_workspace_queries(lib):
     import paper_1904_07421_amd as J
     assert J.jitdb_schedule_workspace_bytes(-1) == 0

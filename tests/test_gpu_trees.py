@@ -117,3 +117,52 @@ def test_infinite_weights_saturate_gates(dtype):
     print(f"infinite weights {dtype} N={p.shape[0]}", flush=True)
     assert bool(torch.isfinite(h).all()) and bool(torch.isfinite(c).all())
     assert bool((h[:, 5] == 0).all()) and bool((c[:, 5] == 0).all())
+
+
+def _forward_of(s, p, D=40, H=48):
+    """(h, c, inputs, launches of the one-block form) of a forward on s."""
+    import torch
+    import paper_1904_07421_amd as J
+    x, W, U, b = make_values(1, p.shape[0], "random", D=D, H=H)
+    J.jitdb_profile_start(4096)
+    try:
+        h, c = J.jitdb_treelstm_forward(*(torch.from_numpy(v).cuda() for v in (x, W, U, b)), s)
+        torch.cuda.synchronize()
+    finally:
+        prof = J.jitdb_profile_stop()
+    return h.cpu().numpy(), c.cpu().numpy(), (x, W, U, b), prof["trees"]["launches"]
+
+
+@pytest.mark.parametrize("how", ["by-hand", "stale", "kept"])
+def test_a_tree_window_counts_with_its_tag_only(c_oracle, how):
+    """A schedule without a window is not one with whatever its struct holds there; one that is kept takes both along."""
+    import torch
+    import paper_1904_07421_amd as J
+    p = FORESTS["word-order"]()
+    filed = J.jitdb_schedule(torch.from_numpy(p).cuda())
+    assert 0 < filed.struct.tree_window <= 256
+    if how == "kept":
+        s = J.Schedule(p.shape[0], "cuda")
+        for k in ("height", "level_ptr", "perm", "inv_perm", "child_ptr", "child_idx"):
+            getattr(s, k).copy_(getattr(filed, k))
+        s.host_level_ptr[:], s.host_level_kids[:] = filed.host_level_ptr, filed.host_level_kids
+        s.n_levels, s.n_edges = filed.n_levels, filed.n_edges
+        for k in ("n_levels", "n_edges", "tree_window", "tree_tag"):
+            setattr(s.struct, k, getattr(filed.struct, k))
+    else:
+        p = relabel(p, 9)[0]
+        if how == "stale":
+            p = np.append(p, np.int32(-1))
+        s = J.jitdb_schedule(torch.from_numpy(p).cuda())
+        if how == "by-hand":                          # (a scrambled forest small enough for one block is all one run of trees)
+            s.struct.tree_window = 40
+        else:
+            s.struct.tree_window, s.struct.tree_tag = filed.struct.tree_window, filed.struct.tree_tag
+    print(f"tree window {how} N={p.shape[0]} window={s.struct.tree_window}", flush=True)
+    h, c, seen, launches = _forward_of(s, p)
+    ho, co, _ = c_oracle(p, *seen)
+    assert launches == (1 if how == "kept" else 0)
+    assert np.abs(h - ho).max() <= 1e-4 and np.abs(c - co).max() <= 1e-4 * max(1.0, np.abs(co).max() / 50.0)
+    if how != "kept":
+        more = torch.from_numpy(perfect_kary_tree(2, 3)).cuda()
+        assert J.jitdb_schedule_append(s, more).struct.tree_window == 0
