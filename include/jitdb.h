@@ -117,9 +117,9 @@ size_t jitdb_schedule_workspace_bytes(int64_t n_nodes);
  *   parent  dev [N] int32, -1 = root.
  *   s       in/out, see jitdb_schedule_t.
  *
- * Runs on `hip_stream` and synchronises that stream: once where the trees' ids lie
- * close together (or the forest is small), else twice (to learn the number of levels, then to
- * hand back level_ptr).  On JITDB_E_PARENT_RANGE or
+ * Runs on `hip_stream` and waits for it: once where the trees' ids lie
+ * close together (or the forest is small), else three times (to learn that they do not, which stops at the
+ * first sight of it, to learn the number of levels, and to hand back level_ptr).  On JITDB_E_PARENT_RANGE or
  * JITDB_E_CYCLE the output arrays hold unspecified values; no kernel reads or
  * writes out of bounds for any input.  N == 0 succeeds with n_levels = 0.
  * The schedule depends only on `parent` and may be reused for any number of

@@ -643,10 +643,15 @@ int schedule_local(const int32_t *parent, const int32_t *sig, jitdb_slots_t *slo
     a.slot_ptr = slots ? slots->slot_ptr : nullptr;
     a.slot_capacity = slots ? slots->slot_capacity : 0;
     a.report = rep;
+    static std::atomic<int32_t> calls{0};
+    a.call = calls.fetch_add(1, std::memory_order_relaxed);      // (by chance equal to what the workspace held: the host hears at the end)
     __atomic_store_n(&rep->done, 0, __ATOMIC_RELEASE);
+    __atomic_store_n(&rep->misfit, 0, __ATOMIC_RELEASE);
     const int rc = launch_local_schedule(a, st);
     if (rc != JITDB_OK) return rc;
-    JITDB_HIP_CHECK(wait_for_report(rep, st));
+    auto done = [&] { return __atomic_load_n(&rep->done, __ATOMIC_ACQUIRE) != 0; };
+    JITDB_HIP_CHECK(wait_for_report(st, [&] { return done() || __atomic_load_n(&rep->misfit, __ATOMIC_ACQUIRE); }));
+    if (!done()) return kTakeGeneralPath;        // (the rest of the report is still being written)
     if (rep->flags & LF_RANGE) return JITDB_E_PARENT_RANGE;
     if (rep->flags & LF_GENERAL) return kTakeGeneralPath;
     if (rep->flags & LF_SIG) return JITDB_E_SIGNATURE;
@@ -660,6 +665,9 @@ int schedule_local(const int32_t *parent, const int32_t *sig, jitdb_slots_t *slo
     if (slots) memcpy(slots->host_slot_ptr, rep->slot_ptr, sizeof(int32_t) * ((size_t)L * n_sig * n_sig + 1));
     return JITDB_OK;
 }
+
+int schedule_general(const int32_t *parent, const int32_t *sig, jitdb_slots_t *slots, jitdb_schedule_t *s, void *workspace,
+                     LocalReport *rep, hipStream_t st);
 
 // The analysis, plain (sig == nullptr: one slot per level) or filed by (depth, signature).
 int schedule_impl(const int32_t *parent, const int32_t *sig, jitdb_slots_t *slots, jitdb_schedule_t *s,
@@ -703,16 +711,26 @@ int schedule_impl(const int32_t *parent, const int32_t *sig, jitdb_slots_t *slot
         return JITDB_E_NULL;
     if (slots && (!sig || !slots->key || !slots->slot_ptr)) return JITDB_E_NULL;
     if ((reinterpret_cast<uintptr_t>(workspace) & 255) != 0) return JITDB_E_BADARG;
-    ScheduleWs w = carve_schedule_ws(n64, workspace, n_keys);
     if (workspace_bytes < schedule_ws_bytes(n64, n_keys)) return JITDB_E_WORKSPACE;
 
     hipStream_t st = (hipStream_t)hip_stream;
-    const int32_t n = (int32_t)n64;
-    if (LocalReport *rep = report_pool().take()) {
-        const int code = schedule_local(parent, sig, slots, s, workspace, rep, st);
-        if (code != JITDB_E_HIP) report_pool().give(rep);      // (after a failed launch its kernels may still write it)
-        if (code != kTakeGeneralPath) return code;
-    }
+    LocalReport *rep = report_pool().take();
+    // (two levels of keys are the least a table with an edge has)
+    const bool may_fit = rep && (n_sig == 1 || 2 * n_keys <= kKeysTyped);
+    int code = may_fit ? schedule_local(parent, sig, slots, s, workspace, rep, st) : kTakeGeneralPath;
+    if (code == kTakeGeneralPath) code = schedule_general(parent, sig, slots, s, workspace, rep, st);
+    if (rep && code != JITDB_E_HIP) report_pool().give(rep);      // (after a failed launch its kernels may still write it)
+    return code;
+}
+
+// Any forest: counts, pointer jumping and sorts over all nodes.  rep: the report of the try before it, or nullptr; its step and
+// meta words are this path's own, and its other arrays are no longer written once these kernels run.
+int schedule_general(const int32_t *parent, const int32_t *sig, jitdb_slots_t *slots, jitdb_schedule_t *s, void *workspace,
+                     LocalReport *rep, hipStream_t st) {
+    const int64_t n64 = s->n_nodes;
+    const int32_t n = (int32_t)n64, n_sig = slots ? slots->n_sig : 1;
+    const int64_t n_keys = (int64_t)n_sig * n_sig;
+    ScheduleWs w = carve_schedule_ws(n64, workspace, n_keys);
     const unsigned grid = (unsigned)ceil_div(n64, kThreads);
     int rc;
 
@@ -752,9 +770,23 @@ int schedule_impl(const int32_t *parent, const int32_t *sig, jitdb_slots_t *slot
         JITDB_LAUNCH_CHECK();
     }
 
+    // The host is told through the report where there is one: a copy to pageable memory and a synchronisation cost 15 us more,
+    // about what the try before this path costs.
+    auto report = [&](int step, const int32_t *from0, int n0, int32_t *to0, const int32_t *from1, int n1, int32_t *to1) -> int {
+        report_words_kernel<<<1, kLocThreads, 0, st>>>(from0, n0, to0, from1, n1, to1, &rep->step, step);
+        JITDB_LAUNCH_CHECK();
+        JITDB_HIP_CHECK(wait_for_report(st, [&] { return __atomic_load_n(&rep->step, __ATOMIC_ACQUIRE) == step; }));
+        return JITDB_OK;
+    };
     int32_t meta[META_WORDS];
-    JITDB_HIP_CHECK(hipMemcpyAsync(meta, w.meta, sizeof(meta), hipMemcpyDeviceToHost, st));
-    JITDB_HIP_CHECK(hipStreamSynchronize(st));
+    if (rep) {
+        __atomic_store_n(&rep->step, 0, __ATOMIC_RELEASE);
+        if ((rc = report(1, w.meta, META_WORDS, rep->meta, nullptr, 0, nullptr)) != JITDB_OK) return rc;
+        memcpy(meta, rep->meta, sizeof(meta));
+    } else {
+        JITDB_HIP_CHECK(hipMemcpyAsync(meta, w.meta, sizeof(meta), hipMemcpyDeviceToHost, st));
+        JITDB_HIP_CHECK(hipStreamSynchronize(st));
+    }
     if (meta[META_ERR] != 0) return JITDB_E_PARENT_RANGE;
     if (meta[META_SIG] != 0) return JITDB_E_SIGNATURE;
     if (rounds > 0 && meta[META_LIVE + rounds - 1] != 0) return JITDB_E_CYCLE;
@@ -806,9 +838,17 @@ int schedule_impl(const int32_t *parent, const int32_t *sig, jitdb_slots_t *slot
         const unsigned g = (unsigned)(ceil_div(n64, kThreads) < 1024 ? ceil_div(n64, kThreads) : 1024);
         level_kids_kernel<<<g, kThreads, 0, st>>>(parent, s->height, n, L, w.cnt);
         JITDB_LAUNCH_CHECK();
-        JITDB_HIP_CHECK(hipMemcpyAsync(s->host_level_kids, w.cnt, sizeof(int32_t) * (size_t)L, hipMemcpyDeviceToHost, st));
     }
 
+    if (rep && S <= kReportKeys) {
+        if ((rc = report(2, bounds, (int)S + 1, rep->slot_ptr, w.cnt, s->host_level_kids ? L : 0, rep->kids)) != JITDB_OK) return rc;
+        if (slots) memcpy(slots->host_slot_ptr, rep->slot_ptr, sizeof(int32_t) * ((size_t)S + 1));
+        for (int l = 0; l <= L; ++l) s->host_level_ptr[l] = rep->slot_ptr[(int64_t)l * n_keys];
+        if (s->host_level_kids) memcpy(s->host_level_kids, rep->kids, sizeof(int32_t) * (size_t)L);
+        return s->host_level_ptr[0] != 0 || s->host_level_ptr[L] != n ? JITDB_E_CYCLE : JITDB_OK;
+    }
+    if (s->host_level_kids)
+        JITDB_HIP_CHECK(hipMemcpyAsync(s->host_level_kids, w.cnt, sizeof(int32_t) * (size_t)L, hipMemcpyDeviceToHost, st));
     if (slots) {
         JITDB_HIP_CHECK(hipMemcpyAsync(slots->host_slot_ptr, slots->slot_ptr, sizeof(int32_t) * ((size_t)S + 1),
                                        hipMemcpyDeviceToHost, st));

@@ -12,17 +12,26 @@
 //   prefix_kernel   per key: exclusive scan of the histogram over the blocks (and the sums the host is told)
 //   place_kernel    per block: key starts + prefix + rank = position; perm, inv_perm, child_ptr, child_idx
 //
-// Three launches and one host synchronisation instead of about sixty launches and two; a forest of up to
-// kWholeNodes nodes is ONE launch of one block (window_kernel with WHOLE: no cuts needed, so any order of ids
-// will do).  What does not fit (an edge longer than M ids, no cut within M ids, more than kMaxArity children,
-// more keys than the tables hold) sets a flag, the kernels after it return at once, and the host runs the
-// general path; nothing here reads or writes out of bounds for any parent array.
+// Four launches (report_done_kernel, one store, is the last) and one wait of the host instead of about sixty launches
+// and two; a forest of up to kWholeNodes nodes is ONE launch of one block (window_kernel with WHOLE: no cuts needed, so
+// any order of ids will do).  What does not fit (an edge longer than M ids, no cut within M ids, more than kMaxArity
+// children, more keys than the tables hold) takes the general path; nothing here reads or writes out of bounds for any
+// parent array.
+//
+// The try must cost such a forest little.  A window that sees a misfit stops there and sets a word in pinned memory, and the
+// host, which watches that word too, enqueues the general path behind the kernels that are still draining.  A table of so
+// many signatures that two levels of it have more keys than the tables hold is not tried.  Call to return, us, general path
+// alone / behind a try that runs to its end / as it is (the general path's own waits take 15 us each off): scrambled ids,
+// 10.8 k nodes 210 / 230 / 165, 108 k 305 / 329 / 255, 2.36 M 746 / 818 / 727; 200 k nodes in trees of 1000 389 / 418 / 344;
+// stars of 350 and chains of 350, 105 k nodes, 290 / 315 / 244 and 416 / 445 / 376; chains of 2000, 8 k nodes, 251 / 284 / 243;
+// 108 k nodes under 24 and 64 signatures 375 / 403 / 304 and 383 / 404 / 353.
 //
 // Every step is bound by LDS latency and barriers, not by memory: the parent array is read (W + 3 M) / W times
 // (W = 2048 for large forests: 1.75), each output is written once.  Measured, call to return, general path ->
 // here: 74 nodes 131 -> 21 us, 4.7 k 162 -> 40, 106 k 313 -> 33, 192 k (128 levels) 374 -> 55, 2.36 M 560 -> 123.
 #pragma once
 
+#include <atomic>
 #include <mutex>
 #include <string.h>
 #include <vector>
@@ -37,6 +46,7 @@ constexpr int kMaxArity = 256;           // siblings are ranked by counting: qua
 constexpr int kKeysPlain = 256;          // levels a forest over several windows may have
 constexpr int kKeysTyped = 1024;         // (height, signature, parent's signature) keys; also the levels of a one-block forest
 constexpr int kWholeNodes = 8192;
+constexpr int kReportKeys = kWholeNodes; // what a report has room for: every level of a forest of one block, chains too
 constexpr uint16_t kNoParent = 0xFFFF;
 
 enum : int { LF_RANGE = 1, LF_SIG = 2, LF_CYCLE = 4, LF_GENERAL = 8 };
@@ -44,10 +54,13 @@ enum : int { LF_RANGE = 1, LF_SIG = 2, LF_CYCLE = 4, LF_GENERAL = 8 };
 // Words the host reads, in pinned memory: written by the last kernel, valid once the stream is done.
 struct LocalReport {
     int32_t done;                            // set last (report_done_kernel, or the one block of a small forest)
+    int32_t misfit;                          // set by any window whose ids do not fit, long before `done`
+    int32_t step;                            // general path: how many of its two reports are there (report_words_kernel)
+    int32_t meta[META_WORDS];                // ... the first
     int32_t flags, n_levels, n_edges, tree_window;
     int32_t level_ptr[kKeysTyped + 1];
-    int32_t kids[kKeysTyped];
-    int32_t slot_ptr[kKeysTyped + 1];
+    int32_t kids[kReportKeys];
+    int32_t slot_ptr[kReportKeys + 1];
 };
 
 struct LocalArgs {
@@ -62,7 +75,8 @@ struct LocalArgs {
     int32_t *first, *count, *edges, *maxh, *flags, *gap;   // [nb] per window
     int32_t *edge_base;                      // [nb] exclusive prefix of edges
     int32_t *key_total, *kid_total;          // [n_keys_max], [kKeysPlain]
-    int32_t *meta;                           // flags, max height, edges, largest distance between cuts
+    int32_t *meta;                           // flags, max height, edges, largest distance between cuts; `call` once a window misfits
+    int32_t call;                            // differs from call to call: what meta[4] holds from before is another number
     uint16_t *rank;                          // [n] rank among the window's nodes of equal key
     int32_t *child_tmp;                      // [n] child lists, window after window
     LocalReport *report;                     // pinned host memory
@@ -145,6 +159,24 @@ window_kernel(const LocalArgs a) {
     const int64_t i0 = WHOLE ? 0 : (int64_t)b * W;                          // this window's start and the next one's
     const int64_t i1 = WHOLE ? n : (i0 + W < n ? i0 + W : n);
     const int64_t base = WHOLE ? 0 : i0 - M;                                // id of scan position 0
+    const int ns2 = a.n_sig * a.n_sig;
+    // The first window to come here tells the host (a thousand stores to one word of its memory hold up the kernel's end)
+    auto tell_misfit = [&]() __attribute__((always_inline)) {
+        if (atomicExch(&a.meta[4], a.call) != a.call) __hip_atomic_store(&a.report->misfit, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    };
+    // The whole block leaves: its ids do not fit (the general path looks for faults anew).
+    auto leave = [&]() __attribute__((always_inline)) {
+        if (t != 0) return;
+        if constexpr (WHOLE) {
+            a.report->flags = LF_GENERAL;
+            __hip_atomic_store(&a.report->done, 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+        } else {
+            a.first[b] = a.count[b] = a.edges[b] = a.gap[b] = 0;
+            a.flags[b] = LF_GENERAL;
+            a.maxh[b] = -1;
+            tell_misfit();
+        }
+    };
     if (t == 0) { s_lo = INT32_MAX; s_hi = INT32_MAX; s_gap = 0; s_flags = 0; s_maxh = 0; }
 #pragma unroll
     for (int r = 0; r < RIT; ++r) cover[r * kLocThreads + t] = 0;
@@ -200,7 +232,8 @@ window_kernel(const LocalArgs a) {
                 last = (int)i;
             }
         }
-        if (lo != INT32_MAX) atomicMin(&s_lo, lo);
+        if (flags & LF_GENERAL) s_lo = INT32_MIN;          // an edge too long (a store: no atomicMin beside it undoes it)
+        else if (lo != INT32_MAX) atomicMin(&s_lo, lo);
         if (hi != INT32_MAX) atomicMin(&s_hi, hi);
         int prev = loc_block_excl_max(last, s_scan);      // (its barriers also publish s_lo, s_hi)
         int gap = 0;
@@ -215,12 +248,13 @@ window_kernel(const LocalArgs a) {
         if (gap) atomicMax(&s_gap, gap);
     }
     __syncthreads();
-    int lo = s_lo, hi = s_hi;
-    if (lo == INT32_MAX || hi == INT32_MAX || lo >= i0 + M || hi > i1 + M || hi - lo > CAP) {
-        if (!WHOLE) flags |= LF_GENERAL;
-        lo = hi = 0;
+    int lo = __builtin_amdgcn_readfirstlane(s_lo), hi = __builtin_amdgcn_readfirstlane(s_hi);
+    if constexpr (WHOLE) {
+        lo = 0; hi = n;
+    } else if (lo == INT32_MIN || lo == INT32_MAX || hi == INT32_MAX || lo >= i0 + M || hi > i1 + M || hi - lo > CAP) {
+        leave();
+        return;
     }
-    if (WHOLE) { lo = 0; hi = n; }
     const int own = hi - lo;
 
     // ---- the block's own nodes by local id
@@ -279,7 +313,7 @@ window_kernel(const LocalArgs a) {
             live |= next[r] != kNoParent;
             out[r * kLocThreads + t] = next[r];
         }
-        live = __syncthreads_or(live);
+        live = __builtin_amdgcn_readfirstlane(__syncthreads_or(live));
         if (!live) break;
     }
     if (live) flags |= LF_CYCLE;
@@ -314,7 +348,6 @@ window_kernel(const LocalArgs a) {
     if (flags) atomicOr(&s_flags, flags);
     __syncthreads();
     flags = s_flags;
-    const int ns2 = a.n_sig * a.n_sig;
     const int maxh = s_maxh;
     if (own > 0 && ((int64_t)(maxh + 1) * ns2 > KEYS || (!WHOLE && maxh >= kKeysPlain))) flags |= LF_GENERAL;
     const int n_keys = own > 0 && flags == 0 ? (maxh + 1) * ns2 : 0;
@@ -414,6 +447,7 @@ window_kernel(const LocalArgs a) {
         if (t == 0) {
             a.first[b] = lo; a.count[b] = own; a.edges[b] = n_edges; a.flags[b] = flags; a.gap[b] = s_gap;
             a.maxh[b] = own > 0 && flags == 0 ? maxh : -1;
+            if (flags & LF_GENERAL) tell_misfit();
         }
         if (flags == 0) {
 #pragma unroll
@@ -466,6 +500,16 @@ window_kernel(const LocalArgs a) {
 // Behind the last kernel of an analysis: the kernels before it are complete when it runs.
 __global__ void report_done_kernel(LocalReport *rep) {
     if (threadIdx.x == 0) __hip_atomic_store(&rep->done, 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// One block: up to two arrays of the general path's into a report, then its step.
+__global__ void __launch_bounds__(kLocThreads)
+report_words_kernel(const int32_t *from0, int n0, int32_t *to0, const int32_t *from1, int n1, int32_t *to1, int32_t *step, int value) {
+    for (int i = threadIdx.x; i < n0; i += kLocThreads) to0[i] = from0[i];
+    for (int i = threadIdx.x; i < n1; i += kLocThreads) to1[i] = from1[i];
+    __threadfence_system();
+    __syncthreads();
+    if (threadIdx.x == 0) __hip_atomic_store(step, value, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // Blocks [0, n_keys_max): exclusive scan of one key's row over the windows.  Blocks [n_keys_max, + kKeysPlain): sum of one
@@ -625,7 +669,7 @@ inline LocalWs carve_local_ws(int64_t n, void *base, int64_t n_keys) {
     for (int32_t **p : per_window) *p = c.take<int32_t>(nb);
     w.a.key_total = c.take<int32_t>(w.a.n_keys_max);
     w.a.kid_total = c.take<int32_t>(kKeysPlain);
-    w.a.meta = c.take<int32_t>(4);
+    w.a.meta = c.take<int32_t>(8);
     w.a.rank = c.take<uint16_t>(n);
     w.a.child_tmp = c.take<int32_t>(n);
     w.bytes = c.off;
@@ -663,12 +707,13 @@ inline int launch_local_schedule(const LocalArgs &a, hipStream_t st) {
     return JITDB_OK;
 }
 
-// Waits for the report.  A word in pinned memory is seen about 4 us sooner than hipStreamSynchronize returns (8.3
+// Waits until ready() sees its word of the report.  A word in pinned memory is seen about 4 us sooner than hipStreamSynchronize returns (8.3
 // against 12 us for an empty kernel), which is a large part of a small forest's analysis; work that takes longer
 // than the spin is waited for in the ordinary way, which also reports a failed kernel.
-inline hipError_t wait_for_report(LocalReport *rep, hipStream_t st) {
+template <typename Ready>
+inline hipError_t wait_for_report(hipStream_t st, Ready &&ready) {
     for (int i = 0; i < 20000; ++i) {
-        if (__atomic_load_n(&rep->done, __ATOMIC_ACQUIRE)) return hipSuccess;
+        if (ready()) return hipSuccess;
         __builtin_ia32_pause();
     }
     return hipStreamSynchronize(st);

@@ -211,3 +211,35 @@ def test_trees_filed_one_after_another(name, n_sig):
         want = S.schedule_typed_fast(p, sig, n_sig)
         for k in ("height", "level_ptr", "perm", "inv_perm", "child_ptr", "child_idx", "key", "slot_ptr"):
             assert np.array_equal(got[k], want[k]), k
+
+
+def test_threads_whose_forests_take_different_paths():
+    """Four threads, each on a stream of its own: forests that fit the analysis in LDS beside ones that leave it early, and
+    one of more levels than a report holds.  What one call reports must not reach another."""
+    import threading
+    import torch
+    import paper_1904_07421_amd as J
+    filed = make_forest(3)
+    forests = [filed, relabel(filed, 4)[0], _lay_out([chain_forest(300)] * 40), relabel(chain_forest(9000), 6)[0]]
+    want = [S.schedule_fast(p) for p in forests]
+    dev = [dev_parent(p) for p in forests]
+    torch.cuda.synchronize()
+    wrong = []
+
+    def work(t):
+        stream = torch.cuda.Stream()
+        with torch.cuda.stream(stream):
+            for r in range(12):
+                k = (t + r) % len(forests)
+                try:
+                    assert_schedule_equal(J.jitdb_schedule(dev[k]).to_numpy(), want[k])
+                except Exception as e:                       # noqa: BLE001 - reported by the main thread
+                    wrong.append((t, r, k, repr(e)))
+
+    print("schedule from four threads", flush=True)
+    threads = [threading.Thread(target=work, args=(t,)) for t in range(4)]
+    for th in threads:
+        th.start()
+    for th in threads:
+        th.join()
+    assert not wrong, wrong

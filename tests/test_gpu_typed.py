@@ -109,6 +109,16 @@ def test_typed_schedule_errors():
     assert s.n_levels == 0 and s.host_slot_ptr[0] == 0
 
 
+@pytest.mark.parametrize("n_sig", [22, 23, 33, 64])
+@pytest.mark.parametrize("kind", ["small", "large", "no-edges"])
+def test_tables_of_many_signatures(kind, n_sig):
+    """Where two levels have more keys than the analysis in LDS has room for, and one signature less."""
+    p = {"small": lambda: make_forest(2), "large": lambda: make_forest(3), "no-edges": lambda: np.full(9000, -1, np.int32)}[kind]()
+    sig = np.random.default_rng(n_sig).integers(0, n_sig, size=p.shape[0]).astype(np.int32)
+    print(f"typed schedule many signatures {kind} n_sig={n_sig} N={p.shape[0]}", flush=True)
+    _typed_equal(_sched(p, sig, n_sig).to_numpy(), S.schedule_typed_fast(p, sig, n_sig))
+
+
 @pytest.mark.parametrize("n_sig", [1, 2])
 @pytest.mark.parametrize("trees", [12, 40, 2000])
 def test_a_bad_signature_is_reported_before_a_cycle(trees, n_sig):
