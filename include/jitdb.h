@@ -297,7 +297,9 @@ int jitdb_treelstm_forward_cells(const void *x, const jitdb_cell_t *cells, int32
                                  void *h_out, float *c_out,
                                  void *workspace, size_t workspace_bytes, void *hip_stream);
 
-/* Bytes of device workspace jitdb_treelstm_forward needs (0 if an argument is invalid). */
+/* Bytes of device workspace jitdb_treelstm_forward needs (0 if an argument is invalid).  Up to 262144 nodes that includes
+ * room to run small trees whole; jitdb_treelstm_typed_workspace_bytes of two signatures is enough as well, and such a
+ * smaller workspace makes the call run level by level, with results that agree within rounding. */
 size_t jitdb_treelstm_workspace_bytes(int64_t n_nodes, int64_t n_edges,
                                       int32_t D, int32_t H, jitdb_dtype dtype);
 
@@ -351,7 +353,7 @@ int jitdb_treelstm_forward(const void *x, const void *W, const void *U, const fl
  * from the moment the library's code is loaded on that GPU until the process ends.  The call
  * allocates and frees nothing on the device (no hipMalloc, no hipFree, no library that does).
  *
- *   - Forests whose jitdb_treelstm_workspace_bytes exceeds JITDB_STATIC_SCRATCH_BYTES are refused
+ *   - Forests that need more than JITDB_STATIC_SCRATCH_BYTES even level by level are refused
  *     with JITDB_E_WORKSPACE and nothing is launched (64 MiB: e.g. 25 000 nodes at D = 300, H = 150
  *     in bf16; use jitdb_treelstm_forward with a workspace of your own beyond that).
  *   - All calls on one GPU share that GPU's array: two calls that overlap in time on one GPU

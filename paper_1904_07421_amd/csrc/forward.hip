@@ -1144,8 +1144,7 @@ struct ScopedLaunchTimer {
     }
 };
 
-// Forests of up to this many nodes, filed tree after tree, run in one launch (trees.hip) up to kTreesMaxLevels levels.
-constexpr int64_t kTreesMaxNodes = 262144;
+// Forests filed tree after tree run as whole trees (trees.hip) up to kTreesMaxLevels levels below the chain levels.
 constexpr int kTreesMaxLevels = 32;
 constexpr int kTreesMaxSpan = 256;         // ... of trees of up to this many ids: one block runs a tree alone
 
@@ -1201,20 +1200,20 @@ ForwardWs carve_forward_ws(int64_t n, int64_t e, const Dims &d, void *base, int 
     w.bp = c.take<float>((size_t)d.NP * n_sig);
     // one level at a time; whole row tiles are read, hence the 256 spare rows
     size_t stack_bytes = (size_t)(n + kRowPad) * (d.Dp + d.Hp) * d.esz;
-    // the same sizes for tables of more than one signature: what they ask for grows with n_sig from there; and larger forests
-    // ask for no less than the largest that runs in one launch, so that their workspace holds any smaller one
-    with_z = with_z && d.H <= kTreesMaxWidth;
-    const int64_t n_z = n < kTreesMaxNodes ? n : kTreesMaxNodes;
+    // Room for the whole-tree form where it can run: one cell, at most n_trees nodes.  (Larger forests ask for no less than
+    // those, so that their workspace holds any smaller one.)
+    const int64_t n_trees = with_z && n_sig == 1 && !cells ? trees_max_nodes(d.D, d.H, d.esz) : 0;
+    const int64_t n_z = n < n_trees ? n : n_trees;
     const size_t z_bytes = (size_t)n_z * 4 * round_up(d.H, 16) * 4;
-    if (with_z && z_bytes > stack_bytes) stack_bytes = z_bytes;
+    if (z_bytes > stack_bytes) stack_bytes = z_bytes;
     w.stack = c.take<char>(stack_bytes);
-    const bool z_used = with_z && n_sig == 1 && n <= kTreesMaxNodes;
+    const bool z_used = n <= n_trees;
     w.Z = z_used ? static_cast<float *>(w.stack) : nullptr;
     w.row_rec = c.take<int4>((size_t)2 * (n + kRowPad));   // every level position
     w.hs = (d.H == d.Hp) ? nullptr : c.take<char>((size_t)n * d.Hp * d.esz);
     size_t p_bytes = (size_t)n * d.Hq * d.esz;
     const size_t fc_bytes = (size_t)n_z * round_up(d.H, 16) * 4;
-    if (with_z && fc_bytes > p_bytes) p_bytes = fc_bytes;
+    if (fc_bytes > p_bytes) p_bytes = fc_bytes;
     w.P = c.take<char>(p_bytes);
     w.FC = z_used ? static_cast<float *>(w.P) : nullptr;
     w.cs = (d.H == d.Hq) ? nullptr : c.take<float>((size_t)n * d.Hq);
@@ -1301,7 +1300,7 @@ int run_forward(const void *x, const void *W, const void *U, const float *b, con
     TreesArgs ta = {};
     bool trees = false;
     const int32_t tree_window = known_tree_window(s);
-    if (!slots && !any_nary && w.Z && tree_window > 0 && tree_window <= kTreesMaxSpan && s->inv_perm && chain_from <= kTreesMaxLevels && s->n_nodes <= kTreesMaxNodes) {
+    if (!slots && !any_nary && w.Z && tree_window > 0 && tree_window <= kTreesMaxSpan && s->inv_perm && chain_from <= kTreesMaxLevels) {
         ta.x = x; ta.Bp = w.Bp; ta.bp = w.bp;
         ta.height = s->height; ta.perm = s->perm; ta.inv_perm = s->inv_perm; ta.child_ptr = s->child_ptr; ta.child_idx = s->child_idx;
         ta.h_out = h_out; ta.hs = w.hs ? w.hs : h_out; ta.FC = w.FC; ta.gates = gates; ta.fgate = fgate;
@@ -1772,7 +1771,7 @@ int forward_entry(const void *x, const void *W, const void *U, const float *b, i
                   jitdb_dtype dtype, const jitdb_schedule_t *s, const jitdb_slots_t *slots,
                   void *h_out, float *c_out, void *gates, void *fgate, bool save,
                   void *workspace, size_t workspace_bytes, void *hip_stream, const void *packed = nullptr,
-                  const jitdb_cell_t *cells = nullptr, bool fixed_scratch = false) {
+                  const jitdb_cell_t *cells = nullptr) {
     if (!s) return JITDB_E_NULL;
     const int n_sig = slots ? slots->n_sig : 1;
     if (n_sig < 1 || n_sig > JITDB_MAX_SIGNATURES) return JITDB_E_BADARG;
@@ -1812,7 +1811,7 @@ int forward_entry(const void *x, const void *W, const void *U, const float *b, i
 
     const Dims d = make_dims(D, H, dtype);
     ForwardWs w = carve_forward_ws(n, s->n_edges, d, workspace, n_sig, cells);
-    if (fixed_scratch && workspace_bytes < w.bytes)     // the fixed array: without the room for the one-launch form
+    if (workspace_bytes < w.bytes)     // without the room for whole trees: the fixed array, a workspace of a table's size
         w = carve_forward_ws(n, s->n_edges, d, workspace, n_sig, cells, false);
     if (workspace_bytes < w.bytes) return JITDB_E_WORKSPACE;
     // a table with one child-sum cell is the plain forward (but keeps the general launches for chain levels)
@@ -1991,5 +1990,5 @@ extern "C" int jitdb_treelstm_forward_static(const void *x, const void *W, const
     // Nothing in the workspace has to start at zero: every region is written in full by this call
     // before anything reads it (packed weights, row records, the stacked level, P, padded copies).
     return forward_entry(x, W, U, b, D, H, dtype, s, nullptr, h_out, c_out, nullptr, nullptr, false,
-                         ws, (size_t)JITDB_STATIC_SCRATCH_BYTES, hip_stream, nullptr, nullptr, true);
+                         ws, (size_t)JITDB_STATIC_SCRATCH_BYTES, hip_stream);
 }

@@ -569,6 +569,7 @@ struct TreesArgs {
     int sx, sh, Hz, n_ut, pitch_h, group_rows, G, cap, n_waves, n_blocks, x_slabs, x_chunks;
     size_t lds_bytes;
 };
+int64_t trees_max_nodes(int D, int H, size_t esz);      // largest forest that plan_trees accepts (0: none)
 bool plan_trees(TreesArgs &a, size_t esz);
 int launch_trees(jitdb_dtype dtype, bool save, const TreesArgs &a, hipStream_t st);
 

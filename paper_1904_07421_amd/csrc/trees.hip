@@ -610,14 +610,20 @@ constexpr int kTreeLdsStatic = 1024;               // trees_kernel's static LDS,
 
 }  // namespace
 
-// Fills the launch geometry of `a`; false if the forest is better run level by level.
-bool plan_trees(TreesArgs &a, size_t esz) {
+// The largest forest that runs as whole trees; workspaces have room for no larger one.
+int64_t trees_max_nodes(int D, int H, size_t esz) {
     // Every block reads the recurrent weights once per level, so the gain shrinks with their size and, where the level kernels
     // fill the chip, with the number of nodes.  Forward alone, 32 to 8192 trees of 4 - 48 nodes, D = 300, level by level ->
     // here: H = 64 fp32 201 -> 67 us (949 nodes), 1115 -> 522 (214 k), bf16 149 -> 58, 541 -> 242; H = 150 fp32 244 -> 126,
     // 1937 -> 1428, bf16 163 -> 83, 887 -> 637; H = 256 fp32 275 -> 217, 2438 -> 2437, bf16 169 -> 146 (949), 272 -> 209 (26 k),
     // 532 -> 552 (106 k); H = 384 slower throughout.
-    if (a.H > kTreesMaxWidth || (esz == 2 && a.H > 160 && a.n > 65536)) return false;
+    if (H > kTreesMaxWidth || ceil_div((int64_t)D * (int64_t)esz, 64) > kXSlabs[sizeof(kXSlabs) / sizeof(int) - 1]) return 0;
+    return esz == 2 && H > 160 ? 65536 : 262144;
+}
+
+// Fills the launch geometry of `a`; false if the forest is better run level by level.
+bool plan_trees(TreesArgs &a, size_t esz) {
+    if (a.n > trees_max_nodes(a.D, a.H, esz)) return false;
     a.sx = (int)ceil_div((int64_t)a.D * (int64_t)esz, 64);
     a.sh = (int)ceil_div((int64_t)a.H * (int64_t)esz, 64);
     a.Hz = (int)round_up(a.H, 16);
@@ -643,7 +649,6 @@ bool plan_trees(TreesArgs &a, size_t esz) {
     if (a.lds_bytes > (size_t)kTreeLdsMax || a.cap >= kNoLocal) return false;
     a.n_blocks = (int)ceil_div(a.n, a.G);
     // x part: one wave per unit tile and run of node tiles; as many waves as the chip holds at a time
-    if (a.sx > kXSlabs[sizeof(kXSlabs) / sizeof(int) - 1]) return false;
     a.x_slabs = 0;
     for (int ns : kXSlabs)
         if (a.x_slabs == 0 && ns >= a.sx) a.x_slabs = ns;

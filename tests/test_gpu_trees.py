@@ -166,3 +166,32 @@ def test_a_tree_window_counts_with_its_tag_only(c_oracle, how):
     if how != "kept":
         more = torch.from_numpy(perfect_kary_tree(2, 3)).cuda()
         assert J.jitdb_schedule_append(s, more).struct.tree_window == 0
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_a_workspace_without_room_for_whole_trees(c_oracle, dtype):
+    """A table's workspace serves a plain forest of its size, level by level; less than that is refused."""
+    import torch
+    import paper_1904_07421_amd as J
+    p, D, H = FORESTS["word-order"](), 40, 150
+    n = p.shape[0]
+    x, W, U, b = make_values(1, n, "random", D=D, H=H)
+    s, h1, c1, seen = run_gpu_forward(p, x, W, U, b, dtype)
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    code = J.JITDB_F32 if dtype == "f32" else J.JITDB_BF16
+    sizes = [J.jitdb_treelstm_typed_workspace_bytes(n, s.n_edges, D, H, code, k) for k in (2, 3)]
+    least = 2 * sizes[0] - sizes[1]                       # less the second cell's weights
+    dev = [torch.from_numpy(v).cuda().to(dt) for v in (x, W, U)] + [torch.from_numpy(b).cuda()]
+    assert least < J.jitdb_treelstm_workspace_bytes(n, s.n_edges, D, H, code)
+    ho, co, _ = c_oracle(p, *seen)
+    for size in (sizes[0], least):
+        print(f"workspace without room for whole trees {dtype} N={n} {size}", flush=True)
+        ws = torch.empty(size + 4096, dtype=torch.uint8, device="cuda").fill_(0xA5)
+        h, c = J.jitdb_treelstm_forward(*dev, s, workspace=ws[:size])
+        torch.cuda.synchronize()
+        assert bool((ws[size:] == 0xA5).all())
+        assert np.abs(h.float().cpu().numpy() - ho).max() <= TOL[dtype]
+        assert np.abs(c.cpu().numpy() - co).max() <= TOL[dtype] * max(1.0, np.abs(co).max() / (8.0 if dtype == "bf16" else 50.0))
+    with pytest.raises(J.JitdbError) as e:
+        J.jitdb_treelstm_forward(*dev, s, workspace=ws[:least - 256])
+    assert e.value.code == -5

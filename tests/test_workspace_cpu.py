@@ -54,3 +54,18 @@ def test_a_larger_forests_workspace_holds_a_smaller_ones(D, H, dtype):
     assert cells == sorted(cells)
     backward = [_bytes(n, max(1, n // 2), D, H, dtype) for n in sizes[1:]]
     assert backward == sorted(backward)
+
+
+@pytest.mark.parametrize("D,H,dtype,n,plain", [(300, 256, J.JITDB_BF16, 300000, True), (300, 150, J.JITDB_F32, 200000, False),
+                                               (700, 256, J.JITDB_BF16, 60000, True)])
+def test_no_room_for_whole_trees_where_they_do_not_run(D, H, dtype, n, plain):
+    """Past the largest forest that runs as whole trees, in tables of several cells and where D or H rule them out, a
+    workspace is what its nodes and its weights take.  The nodes' part is what it grows by from there."""
+    asks = [lambda m: J.jitdb_treelstm_typed_workspace_bytes(m, m - 1, D, H, dtype, 3),
+            lambda m: J.jitdb_treelstm_cells_workspace_bytes(m, m - 1, D, H, dtype, [(J.JITDB_CELL_NARY, 2)])]
+    if plain:
+        asks.append(lambda m: J.jitdb_treelstm_workspace_bytes(m, m - 1, D, H, dtype))
+    for ask in asks:
+        per_node = (ask(9 * n) - ask(8 * n)) / n
+        weights = 8 * 4 * 512 * (_up(D, 64) + 3 * 256 + 64) * 4           # generous: every cell padded to 512 units, fp32
+        assert ask(n) <= n * per_node + weights + (1 << 20), (ask(n), n * per_node)
