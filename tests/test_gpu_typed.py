@@ -316,3 +316,23 @@ def test_grouped_ranges_at_tile_edges(n_sig, sizes, dtype):
     eh, ec = float(np.abs(h - ho).max()), float(np.abs(c - co).max())
     # c of the wide root is a sum over its children: its bound grows with max |c| as elsewhere in this file
     assert eh <= TOL[dtype] and ec <= TOL[dtype] * max(1.0, float(np.abs(co).max()) / 8.0)
+
+
+@pytest.mark.parametrize("n_sig", [8, 9, 16, 17, 23, 64])
+@pytest.mark.parametrize("nodes", [900, 30000])
+def test_grouped_ranges_of_many_cells(nodes, n_sig):
+    """64 sub-slots are searched at a time, more than 256 of them by runs, which end inside, at and past the last sub-slot.
+    The larger forest's leaves are in excess of the thin kernel's rows."""
+    rng = np.random.default_rng(n_sig)
+    p = np.full(nodes, -1, np.int32)
+    inner = nodes // 3
+    p[inner:] = rng.integers(0, inner, size=nodes - inner)           # leaves under one of a third of the nodes
+    p[1:inner:2] = 0
+    sig = rng.integers(0, n_sig, size=nodes).astype(np.int32)
+    sig[rng.random(nodes) < 0.3] = n_sig - 1                          # the last sub-slots are the largest
+    x, W, U, b = make_values_typed(1, nodes, n_sig, D=20, H=24)
+    print(f"typed ranges of many cells n_sig={n_sig} N={nodes}", flush=True)
+    _, h, c, seen = _gpu_forward_typed(p, sig, n_sig, x, W, U, b, "f32")
+    ho, co = TT.forward_typed(p, sig, *seen)
+    eh, ec = float(np.abs(h - ho).max()), float(np.abs(c - co).max())
+    assert eh <= TOL["f32"] and ec <= TOL["f32"] * max(1.0, float(np.abs(co).max()) / 8.0)
