@@ -13,7 +13,6 @@ import os
 from typing import Optional, Tuple
 
 import numpy as np
-import torch as _torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "libjitdb.so")
@@ -280,8 +279,10 @@ def _check(code: int):
 def _stream_ptr(stream) -> int:
     if stream is not None:
         return int(stream.cuda_stream)
-    # the handle alone: torch.cuda.current_stream() builds a Stream object around it on every call
-    return int(_torch._C._cuda_getCurrentRawStream(_torch.cuda.current_device()))
+    import torch
+    # the handle alone where torch hands it out: torch.cuda.current_stream() builds a Stream object around it on every call
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    return int(raw(torch.cuda.current_device()) if raw else torch.cuda.current_stream().cuda_stream)
 
 
 _NO_SWITCH = contextlib.nullcontext()
@@ -289,8 +290,9 @@ _NO_SWITCH = contextlib.nullcontext()
 
 def _on_device(device):
     """Context in which `device` is current; nothing is switched where it is already."""
+    import torch
     i = device.index
-    return _NO_SWITCH if i is None or i == _torch.cuda.current_device() else _torch.cuda.device(device)
+    return _NO_SWITCH if i is None or i == torch.cuda.current_device() else torch.cuda.device(device)
 
 
 def _empty(stream, *args, **kw):
@@ -309,7 +311,10 @@ def _on_stream(stream):
     """Context in which default buffers are allocated: the stream the launches go to.  Memory the
     caching allocator hands out belongs to the stream that is current at that moment; allocated under
     another stream it could be given to other work while these kernels still use it."""
-    return _NO_SWITCH if stream is None else _torch.cuda.stream(stream)
+    if stream is None:
+        return _NO_SWITCH
+    import torch
+    return torch.cuda.stream(stream)
 
 
 class Schedule:

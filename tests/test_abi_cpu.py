@@ -96,3 +96,16 @@ def test_argument_errors_before_any_gpu_work(lib):
     assert lib.jitdb_schedule(None, ctypes.byref(s), None, 0, None) == -1
     assert lib.jitdb_treelstm_forward(None, None, None, None, 300, 150, 0, None, None, None,
                                       None, 0, None) == -1
+
+
+def test_the_package_needs_torch_only_for_tensors():
+    """Sizes, the cache's table and the launch counts are there without torch, which the calls on tensors import."""
+    import subprocess
+    import sys
+    code = ("import sys; sys.modules['torch'] = None\n"
+            "import paper_1904_07421_amd as J\n"
+            "from paper_1904_07421_amd import granularity\n"
+            "assert J.jitdb_version() and J.jitdb_schedule_workspace_bytes(1000) > 0\n"
+            "assert granularity.launch_counts([-1, 0, 0])['cells'] == 3\n"
+            "assert J.CacheTable(2).lookup((1, 2), 3) == -1\n")
+    subprocess.run([sys.executable, "-c", code], check=True, cwd=ROOT)

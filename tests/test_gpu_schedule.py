@@ -243,3 +243,17 @@ def test_threads_whose_forests_take_different_paths():
     for th in threads:
         th.join()
     assert not wrong, wrong
+
+
+def test_calls_go_to_torchs_current_stream(monkeypatch):
+    """With and without the shortcut that hands out the stream's handle alone."""
+    import torch
+    from paper_1904_07421_amd import binding
+    side = torch.cuda.Stream()
+    for shortcut in (True, False):
+        if not shortcut:
+            monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream")
+        with torch.cuda.stream(side):
+            assert binding._stream_ptr(None) == side.cuda_stream
+        assert binding._stream_ptr(None) == torch.cuda.current_stream().cuda_stream
+        assert binding._stream_ptr(side) == side.cuda_stream
