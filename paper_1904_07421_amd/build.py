@@ -61,15 +61,8 @@ def _join(a, b):
     return tuple(x | y for x, y in zip(a, b))
 
 
-def check_lds_read_waits(asm_text: str, kernel_substr: str = "level_kernel") -> int:
-    """Static check of the generated code of the level kernel, whose LDS fragment reads are
-    inline asm the compiler knows nothing about: between a ds_read and the s_waitcnt
-    lgkmcnt that covers it, no other instruction may touch the registers it will write (a
-    compiler-made copy or spill there would move data that has not arrived).  LDS and
-    scalar-memory operations of a wave are counted by one in-order counter, modelled as a
-    FIFO of destination-register sets; the states are propagated over the control-flow
-    graph of each kernel to a fixed point.  Returns the number of ds_read instructions seen."""
-    # split into kernels, then basic blocks
+def _kernel_bodies(asm_text: str, kernel_substr: str) -> list:
+    """The instructions and labels of every kernel whose name holds kernel_substr."""
     kernels, cur = [], None
     for raw in asm_text.splitlines():
         line = raw.split(";")[0].strip()
@@ -83,31 +76,48 @@ def check_lds_read_waits(asm_text: str, kernel_substr: str = "level_kernel") -> 
         if cur is None or (line.startswith(".") and not line.endswith(":")):
             continue
         cur.append(line)
-    seen = 0
-    for body in kernels:
-        blocks, names = [[]], {}
-        for line in body:
-            if line.endswith(":"):
-                if blocks[-1]:
-                    blocks.append([])
-                names[line[:-1]] = len(blocks) - 1
-                continue
-            blocks[-1].append(line)
-            op = line.split(" ")[0]
-            if op.startswith("s_cbranch") or op in ("s_branch", "s_endpgm"):
+    return kernels
+
+
+def _control_flow(body):
+    """(basic blocks, the blocks that may follow each)."""
+    blocks, names = [[]], {}
+    for line in body:
+        if line.endswith(":"):
+            if blocks[-1]:
                 blocks.append([])
-        succ = []
-        for bi, blk in enumerate(blocks):
-            last = blk[-1].split() if blk else []
-            nxt = [bi + 1] if bi + 1 < len(blocks) else []
-            if last and last[0] == "s_branch":
-                succ.append([names[last[1]]])
-            elif last and last[0].startswith("s_cbranch"):
-                succ.append([names[last[1]]] + nxt)
-            elif last and last[0] == "s_endpgm":
-                succ.append([])
-            else:
-                succ.append(nxt)
+            names[line[:-1]] = len(blocks) - 1
+            continue
+        blocks[-1].append(line)
+        op = line.split(" ")[0]
+        if op.startswith("s_cbranch") or op in ("s_branch", "s_endpgm"):
+            blocks.append([])
+    succ = []
+    for bi, blk in enumerate(blocks):
+        last = blk[-1].split() if blk else []
+        nxt = [bi + 1] if bi + 1 < len(blocks) else []
+        if last and last[0] == "s_branch":
+            succ.append([names[last[1]]])
+        elif last and last[0].startswith("s_cbranch"):
+            succ.append([names[last[1]]] + nxt)
+        elif last and last[0] == "s_endpgm":
+            succ.append([])
+        else:
+            succ.append(nxt)
+    return blocks, succ
+
+
+def check_lds_read_waits(asm_text: str, kernel_substr: str = "level_kernel") -> int:
+    """Static check of the generated code of the level kernel, whose LDS fragment reads are
+    inline asm the compiler knows nothing about: between a ds_read and the s_waitcnt
+    lgkmcnt that covers it, no other instruction may touch the registers it will write (a
+    compiler-made copy or spill there would move data that has not arrived).  LDS and
+    scalar-memory operations of a wave are counted by one in-order counter, modelled as a
+    FIFO of destination-register sets; the states are propagated over the control-flow
+    graph of each kernel to a fixed point.  Returns the number of ds_read instructions seen."""
+    seen = 0
+    for body in _kernel_bodies(asm_text, kernel_substr):
+        blocks, succ = _control_flow(body)
         state_in = [None] * len(blocks)
         state_in[0] = ()
         work = [0]
@@ -140,6 +150,70 @@ def check_lds_read_waits(asm_text: str, kernel_substr: str = "level_kernel") -> 
                     state_in[t] = joined
                     work.append(t)
         seen += sum(1 for line in body if line.startswith("ds_read"))
+    return seen
+
+
+_ANY_REG = re.compile(r"\b([va])(\d+)\b|\b([va])\[(\d+):(\d+)\]")
+# Passes of the MFMAs in use.  Between one and whoever reads its result stand at least passes + 2 other instructions (s_nop n
+# counts as n + 1), for the bf16 forms passes + 3 and one more from four passes on.
+_MFMA_PASSES = {"32x32x16_bf16": 8, "16x16x32_bf16": 4, "4x4x4_16b_bf16": 2, "32x32x2_f32": 16, "16x16x4_f32": 8, "4x4x1_16b_f32": 2}
+
+
+def _any_regs(text: str) -> set:
+    out = set()
+    for m in _ANY_REG.finditer(text):
+        if m.group(1):
+            out.add((m.group(1), int(m.group(2))))
+        else:
+            out.update((m.group(3), r) for r in range(int(m.group(4)), int(m.group(5)) + 1))
+    return out
+
+
+def check_mfma_results(asm_text: str, kernel_substr: str = "kernel") -> int:
+    """Static check that nothing reads an MFMA's result before it is there.  The hardware does not wait by itself: the
+    compiler keeps the distance with other instructions and s_nop, and has been seen to lose it at the target of a branch
+    that skips the instructions in between (reads of accumulation registers, wrong and varying results).  For every register
+    an MFMA writes, the instructions still needed before it may be read are propagated over the control-flow graph, the
+    largest number winning where paths meet.  Another MFMA may take the register as its addend.  Returns the MFMAs seen."""
+    seen = 0
+    for body in _kernel_bodies(asm_text, kernel_substr):
+        blocks, succ = _control_flow(body)
+        state_in = [None] * len(blocks)
+        state_in[0] = {}
+        work = [0]
+        while work:
+            bi = work.pop()
+            left = dict(state_in[bi])
+            for line in blocks[bi]:
+                op, _, rest = line.partition(" ")
+                args = re.split(r",(?![^\[]*\])", rest)
+                mfma = re.match(r"v_mfma_f32_(\w+)", op)
+                is_v = op.startswith("v_")
+                if left and (is_v or re.match(r"(global|buffer|flat|scratch|ds)_", op)):
+                    reads = args[1:3] if mfma else args[1:] if is_v or "load" in op or op.startswith("ds_read") else args
+                    if any(r in left for r in _any_regs(",".join(reads))):
+                        raise RuntimeError("an MFMA's result is read before it is there: " + line)
+                step = int(rest, 0) + 1 if op == "s_nop" else 1
+                left = {r: n - step for r, n in left.items() if n > step}
+                if mfma:
+                    if mfma.group(1) not in _MFMA_PASSES:
+                        raise RuntimeError("the passes of this MFMA are not known: " + op)
+                    passes = _MFMA_PASSES[mfma.group(1)]
+                    need = passes + 2 if op.endswith("_f32") else passes + 3 + (passes > 2)
+                    left.update((r, need) for r in _any_regs(args[0]))
+                elif is_v and not op.startswith("v_cmp"):
+                    for r in _any_regs(args[0]):
+                        left.pop(r, None)
+            for t in succ[bi]:
+                if state_in[t] is None:
+                    state_in[t] = dict(left)
+                    work.append(t)
+                    continue
+                more = {r: n for r, n in left.items() if n > state_in[t].get(r, 0)}
+                if more:
+                    state_in[t].update(more)
+                    work.append(t)
+        seen += sum(1 for line in body if line.startswith("v_mfma"))
     return seen
 
 
@@ -208,7 +282,7 @@ def build(verbose: bool = False) -> str:
     try:
         res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, cwd=tmp)
         asm_texts = {}
-        for stem in ("forward", "backward"):
+        for stem in ("forward", "backward", "trees", "probe"):
             asm_path = os.path.join(tmp, stem + "-hip-amdgcn-amd-amdhsa-gfx950.s")
             asm_texts[stem] = open(asm_path).read() if os.path.exists(asm_path) else None
     finally:
@@ -219,12 +293,15 @@ def build(verbose: bool = False) -> str:
     if res.returncode != 0:
         raise RuntimeError("hipcc failed:\n" + out)
     _check_no_scratch(lines)
+    for stem, text in asm_texts.items():
+        if text is None:
+            raise RuntimeError(f"the device assembly of {stem}.hip was not produced; cannot check it")
+        if check_mfma_results(text) == 0:
+            raise RuntimeError(f"no MFMAs found in the assembly of {stem}.hip: the check is not looking at it")
     # the kernels whose LDS reads are inline asm
     # (names with their length prefix, as they are mangled: "level_kernel" alone would also match fused_level_kernel)
     for stem, name in (("forward", "12level_kernel"), ("forward", "14gemm_kb_kernel"), ("forward", "17nary_level_kernel"),
                        ("backward", "16rows_tile_kernel"), ("backward", "9tn_kernel")):
-        if asm_texts.get(stem) is None:
-            raise RuntimeError(f"the device assembly of {stem}.hip was not produced; cannot check it")
         if check_lds_read_waits(asm_texts[stem], name) == 0:
             raise RuntimeError(f"no LDS reads found in the assembly of {name}: the check is not looking at it")
     # the K loops whose waits for direct-to-LDS stage loads are hand-counted

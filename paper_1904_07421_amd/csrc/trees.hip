@@ -194,6 +194,11 @@ constexpr int slabs_below(int ns) {                // the instance before: slabs
     return below;
 }
 
+// Leaves have no forget gate.  Its products are left out of their tiles by a branch between the other MFMAs, except in the wide
+// bf16 instances: with the accumulators in accumulation registers the compiler reads an MFMA's result there two instructions
+// behind it where the branch is taken, eight too few, and every tile of leaves came out wrong.  (The build looks for such reads.)
+template <typename T, int NS> constexpr bool kLeavesSkip = sizeof(T) == 4 || NS <= 10;
+
 template <typename T, bool SAVE, int NS>
 __global__ void __launch_bounds__(256, (kXWavesPerSimd<T, NS>))
 tree_x_kernel(const TreesArgs a) {
@@ -256,7 +261,7 @@ tree_x_kernel(const TreesArgs a) {
         for (int s = 0; s < NS; ++s) {
 #pragma unroll
             for (int g = 0; g < 3; ++g) mfma16<T>(fa[s], fb[s][g], acc[g]);
-            if (!leaf) mfma16<T>(fa[s], fb[s][3], acc[3]);          // (leaves have no forget gate)
+            if (!kLeavesSkip<T, NS> || !leaf) mfma16<T>(fa[s], fb[s][3], acc[3]);
             if (s < PF) fa[s] = load_slab(row, s);
         }
         const int unit = ut * 16 + (fresh_lane(lane) & 15);       // (nothing derived from it stays in registers meanwhile)

@@ -86,3 +86,39 @@ def test_foreign_vector_memory_instruction_in_a_k_loop_is_refused():
         B.check_stage_loads(_k_loop(1, 6, extra="\tglobal_store_dword v[2:3], v40, off\n"))
     # the same instructions outside the loop are none of its business
     assert B.check_stage_loads(_k_loop(1, 6)) == 1
+
+
+# ---- distance between an MFMA and who reads its result -----------------------------------------
+BRANCHY = """
+_ZN5jitdb13tree_x_kernelEv:
+\tv_mfma_f32_16x16x32_bf16 a[4:7], a[20:23], v[2:5], a[4:7]
+\tv_mfma_f32_16x16x32_bf16 a[4:7], a[24:27], v[2:5], a[4:7]
+\ts_cbranch_vccnz .LBB0_1
+\ts_nop 5
+.LBB0_1:
+\tglobal_load_dwordx4 a[20:23], v[8:9], off
+\ts_nop 5
+\tv_accvgpr_read_b32 v10, a7
+\tv_accvgpr_read_b32 v11, a6
+\ts_endpgm
+"""
+
+
+def test_an_mfma_result_read_in_time_passes_and_mfmas_are_counted():
+    assert B.check_mfma_results(BRANCHY) == 2
+
+
+@pytest.mark.parametrize("bad", [
+    BRANCHY.replace("off\n\ts_nop 5", "off\n\ts_nop 4"),                                  # one short where the branch is taken
+    BRANCHY.replace("\ts_nop 5\n\tv_accvgpr_read_b32 v10, a7", "\tv_accvgpr_read_b32 v10, a7"),
+    BRANCHY.replace("global_load_dwordx4 a[20:23], v[8:9], off", "global_store_dwordx4 v[8:9], a[4:7], off"),
+    BRANCHY.replace("a[24:27], v[2:5], a[4:7]", "a[4:7], v[2:5], a[8:11]"),                  # as an operand, not an addend
+])
+def test_an_mfma_result_read_too_early_is_refused(bad):
+    with pytest.raises(RuntimeError, match="before it is there"):
+        B.check_mfma_results(bad)
+
+
+def test_an_mfma_of_unknown_length_is_refused():
+    with pytest.raises(RuntimeError, match="not known"):
+        B.check_mfma_results(BRANCHY.replace("16x16x32_bf16", "16x16x128_f8f6f4"))

@@ -65,6 +65,28 @@ def test_trees_in_one_block_each(c_oracle, forest, D, H, dtype):
     torch.cuda.synchronize()
 
 
+@pytest.mark.parametrize("save", [False, True])
+@pytest.mark.parametrize("dtype,D", [("f32", D) for D in (64, 65, 112, 113, 160, 161, 200, 256, 257, 320)] +
+                         [("bf16", D) for D in (128, 129, 224, 225, 320, 321, 393, 512, 513, 600, 640)])
+def test_every_width_of_the_x_part(c_oracle, dtype, D, save):
+    """Each instance of the x part at both ends of its widths, leaves and inner nodes, with and without saved gates."""
+    import torch
+    import paper_1904_07421_amd as J
+    p, H = FORESTS["word-order"](), 100
+    x, W, U, b = make_values(1, p.shape[0], "random", D=D, H=H)
+    print(f"x part {dtype} D={D} save={save} N={p.shape[0]}", flush=True)
+    s, h, c, seen = run_gpu_forward(p, x, W, U, b, dtype)
+    assert 0 < s.struct.tree_window <= 256
+    if save:
+        dt = torch.float32 if dtype == "f32" else torch.bfloat16
+        dev = [torch.from_numpy(v).cuda().to(dt) for v in seen[:3]] + [torch.from_numpy(b).cuda()]
+        h2, c2, _, _ = J.jitdb_treelstm_forward_train(*dev, s)
+        h, c = h2.float().cpu().numpy(), c2.cpu().numpy()
+    ho, co, _ = c_oracle(p, *seen)
+    assert np.abs(h - ho).max() <= TOL[dtype]
+    assert np.abs(c - co).max() <= TOL[dtype] * max(1.0, np.abs(co).max() / (8.0 if dtype == "bf16" else 50.0))
+
+
 @pytest.mark.parametrize("what", ["wide-x", "wide-h", "long-tree", "scrambled"])
 def test_what_does_not_fit_runs_level_by_level(c_oracle, what):
     """D past the largest instance, a tree longer than one block should take, ids all over the forest."""
