@@ -50,6 +50,14 @@ __device__ __forceinline__ void load_units(const E *__restrict__ p, int left, fl
                 else v[q * PER + e] = __uint_as_float(e & 1 ? w[e / 2] & 0xFFFF0000u : w[e / 2] << 16);
             }
         }
+    } else if (VEC && sizeof(E) == 2) {        // an even number of units: pairs (106 k nodes, H 150: 1.07 -> 0.86 ms of the pass)
+#pragma unroll
+        for (int q = 0; q < N / 2; ++q) {
+            uint32_t w = 0;
+            if (2 * q < left) w = reinterpret_cast<const uint32_t *>(p)[q];
+            v[2 * q] = __uint_as_float(w << 16);
+            v[2 * q + 1] = __uint_as_float(w & 0xFFFF0000u);
+        }
     } else {
 #pragma unroll
         for (int e = 0; e < N; ++e) v[e] = e < left ? to_f32<E>(p[e]) : 0.0f;
@@ -178,7 +186,9 @@ bwd_prepare_kernel(const PrepArgs a) {
 // it (zero_forget).  dc_j stays in dc[j] for the children's level.
 // Bound by memory: 36 bytes a unit of the node (bf16, with gh) and 8 per child, read and written in 16-byte pieces: 591 k
 // leaves, H = 512: 1.96 ms (4.6 TB/s), all 15 levels of 1.18 M nodes 5.9 ms (8.0 one unit a lane and dZ written twice).
-// Few rows: bound by the chain node -> children -> their rows, so several children's rows are in flight.
+// Few rows: bound by the chain node -> children -> their rows, so four children's rows are in flight and the next four's ids.
+// Whole backward pass, two children at a time and ids on demand (four in fp32) -> so: one node with 40 k children, H 512, bf16
+// 59.6 -> 45.0 ms, 60 nodes with 400, H 256, bf16 1.24 -> 0.88; 4.7 k nodes of trees, H 150, fp32 0.239 -> 0.229.
 struct CellArgs {
     const int32_t *perm, *inv_perm, *child_ptr, *child_idx;
     int32_t *parent_of;
@@ -189,7 +199,7 @@ struct CellArgs {
     int64_t rows_alloc;
     int row0, n_rows, H, Hk, zero_forget;      // the level's rows are positions row0 .. row0 + n_rows
 };
-template <typename T> constexpr int kKidsAhead = sizeof(T) == 4 ? 4 : 2;
+constexpr int kKidsAhead = 4;
 template <typename T, bool VEC, bool LEAVES>
 __global__ void __launch_bounds__(kT)
 bwd_cell_kernel(const CellArgs a) {
@@ -260,22 +270,25 @@ bwd_cell_kernel(const CellArgs a) {
         for (int g = 0; g < 3; ++g) store16(a.dZ, r, g * gate_kb + kb, a.rows_alloc, zero);
     }
     if (!LEAVES) {
-        // kKidsAhead children at a time: their ids, then their rows, then their arithmetic (the last one's again past the end)
-        constexpr int K = kKidsAhead<T>;
+        // kKidsAhead children at a time: their rows and the next ones' ids, then their arithmetic (the last one's again past the end)
+        constexpr int K = kKidsAhead;
+        int kid[K];
+#pragma unroll
+        for (int q = 0; q < K; ++q) kid[q] = a.child_idx[kid0 + q < kid1 ? kid0 + q : kid1 - 1];
         for (int ce = kid0; ce < kid1; ce += K) {
-            int64_t kid[K];
+            int next[K];
             float fk[K][PER], ck[K][PER];
             int pos[K];
 #pragma unroll
-            for (int q = 0; q < K; ++q) kid[q] = a.child_idx[ce + q < kid1 ? ce + q : kid1 - 1];
+            for (int q = 0; q < K; ++q) next[q] = a.child_idx[ce + K + q < kid1 ? ce + K + q : kid1 - 1];
 #pragma unroll
             for (int q = 0; q < K; ++q) {
                 pos[q] = a.inv_perm[kid[q]];
 #pragma unroll
                 for (int e = 0; e < PER; ++e) fk[q][e] = ck[q][e] = 0.0f;
                 if (left > 0) {
-                    load_units<T, PER, VEC>(static_cast<const T *>(a.fgate) + kid[q] * a.H + m0, left, fk[q]);
-                    load_units<float, PER, true>(a.c + kid[q] * a.H + m0, left, ck[q]);
+                    load_units<T, PER, VEC>(static_cast<const T *>(a.fgate) + (int64_t)kid[q] * a.H + m0, left, fk[q]);
+                    load_units<float, PER, true>(a.c + (int64_t)kid[q] * a.H + m0, left, ck[q]);
                 }
             }
 #pragma unroll
@@ -289,6 +302,8 @@ bwd_cell_kernel(const CellArgs a) {
                 store16(a.G, pos[q], kb, a.rows_alloc, pack_units<T>(ck[q]));
                 if (m0 == 0) a.parent_of[kid[q]] = (int32_t)j;
             }
+#pragma unroll
+            for (int q = 0; q < K; ++q) kid[q] = next[q];
         }
     }
     if (!LEAVES || a.zero_forget) store16(a.dZ, r, 3 * gate_kb + kb, a.rows_alloc, pack_units<T>(dzf));

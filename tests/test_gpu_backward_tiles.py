@@ -108,3 +108,28 @@ def test_an_infinite_cotangent_of_a_leaf_stays_out_of_the_inner_nodes_sums(lone,
     assert torch.equal(dx[:n - 1], want[0][:n - 1])
     assert torch.equal(dU, want[2])
     assert torch.equal(dW[3 * H:], want[1][3 * H:]) and torch.equal(db[3 * H:], want[3][3 * H:])
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("D,H", [(41, 66), (42, 68), (44, 70), (46, 72), (63, 65)])
+def test_rows_that_end_inside_a_piece(D, H, dtype):
+    """Rows are read in pieces of 16 bytes; the last one ends after one, two, three or four pairs, or odd."""
+    parent = _stars(60, 6)
+    n = len(parent)
+    x, W, U, b = make_values(1, n, "random", D=D, H=H)
+    gh = np.random.default_rng(H).standard_normal((n, H)).astype(np.float32)
+    print(f"backward row ends D={D} H={H} dtype={dtype} N={n}", flush=True)
+    if dtype == "bf16":
+        bits = [to_bf16_bits(a) for a in (x, W, U)]
+        dev = [torch.from_numpy(t.view(np.int16)).view(torch.bfloat16).cuda() for t in bits]
+        seen = [bf16_bits_to_f32(t) for t in bits]
+    else:
+        dev = [torch.from_numpy(a).cuda() for a in (x, W, U)]
+        seen = [x, W, U]
+    s = J.jitdb_schedule(torch.from_numpy(parent).cuda())
+    h, c, gates, fgate = J.jitdb_treelstm_forward_train(*dev, torch.from_numpy(b).cuda(), s)
+    got = J.jitdb_treelstm_backward(dev[0], dev[1], dev[2], s, h, c, gates, fgate, torch.from_numpy(gh).cuda(), None)
+    want = B.forward_backward(parent, *seen, b, gh, np.zeros_like(gh))[2:]
+    for name, a, r in zip(("dx", "dW", "dU", "db"), got, want):
+        err = float(np.abs(a.cpu().numpy() - r).max() / max(1.0, np.abs(r).max()))
+        assert err <= TOL[dtype], (name, err)
