@@ -1307,7 +1307,13 @@ int run_forward(const void *x, const void *W, const void *U, const float *b, con
         ta.c_out = c_out; ta.cs = chain_from < L ? w.cs : nullptr; ta.Z = w.Z;
         ta.n = (int)s->n_nodes; ta.n_leaves = sp[1]; ta.tree_window = tree_window; ta.l_end = chain_from;
         ta.D = d.D; ta.H = d.H; ta.Hp = d.Hp; ta.Hq = d.Hq; ta.NPU = d.NPU; ta.sx_packed = (int)(d.Dp * d.esz / 64);
-        trees = plan_trees(ta, d.esz);
+        TreesShape shape = {L, sp[chain_from], 0.0, 0.0};
+        for (int l = 1; l < chain_from; ++l) {
+            const double per_node = (double)(sp[l] - sp[l - 1]) / (sp[l + 1] - sp[l]);
+            shape.fan += per_node > 1.0 ? per_node : 1.0;
+            shape.wide += per_node < 2.5 ? 0.0 : per_node < 18.5 ? per_node - 2.5 : 16.0;
+        }
+        trees = plan_trees(ta, d.esz, shape);
     }
 
     {   // row records and packed weights (one launch; further cells' weights one launch each)

@@ -607,7 +607,12 @@ struct TreesArgs {
     size_t lds_bytes;
 };
 int64_t trees_max_nodes(int D, int H, size_t esz);      // largest forest that plan_trees accepts (0: none)
-bool plan_trees(TreesArgs &a, size_t esz);
+struct TreesShape {                        // of the forest, for the choice of the form
+    int n_levels, n_below;                 // levels with the chain levels; nodes below the chain levels
+    double fan, wide;                      // sums over the levels above the leaves of the nodes of the level below per node, at
+                                           // least 1, and of what that is beyond 2.5, at most 16
+};
+bool plan_trees(TreesArgs &a, size_t esz, const TreesShape &s);
 int launch_trees(jitdb_dtype dtype, bool save, const TreesArgs &a, hipStream_t st);
 
 }  // namespace jitdb

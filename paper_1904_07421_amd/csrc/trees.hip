@@ -626,8 +626,29 @@ int64_t trees_max_nodes(int D, int H, size_t esz) {
     return esz == 2 && H > 160 ? 65536 : 262144;
 }
 
+// Microseconds by which whole trees take longer than the level kernels (less than zero: they are faster).  What speaks against
+// them: the longest run of trees keeps one block busy while the others are done (a.tree_window nodes past its share, more the
+// wider the cells), and every level costs each block the latency of its weights.  For them: a level costs no launches, and
+// less the wider x is; the level kernels walk a node's children one by one (the widest node of a level that averages more than
+// two or three has several times that); the chain levels above multiply no x.
+// Fitted to 1400 measured forwards: D 16 - 300, H 40 - 256, one tree of 16 - 250 nodes, interleaved trees of 1 - 10 nodes, stars,
+// trees of 1 - 250 nodes filed one after another up to 225 k nodes, chains.  The time over that of the faster form, mean and
+// worst: always whole trees 1.18 and 4.3 in fp32, 1.13 and 3.1 in bf16; by this rule 1.005 and 1.3, 1.006 and 1.4.
+double trees_excess_us(const TreesArgs &a, size_t esz, const TreesShape &s) {
+    const bool f32 = esz == 4;
+    const double h = a.H / 100.0, d = a.D / 100.0, below = s.n_below / 1000.0, chain = (a.n - s.n_below) / 1000.0;
+    const int levels = a.l_end, chain_levels = s.n_levels - a.l_end;
+    const int longest = a.n - a.G < a.tree_window ? a.n - a.G : a.tree_window;
+    double us = levels * (f32 ? -11.0 + 3.0 * h - 1.2 * d : -8.9 + 2.6 * h - 0.35 * d) +
+                below * (f32 ? -0.80 - 0.37 * d : -0.067 - 0.097 * d) + (below + chain) * h * (f32 ? 0.16 : 0.025) +
+                chain_levels * (f32 ? 0.06 - 1.26 * d : 0.15 - 0.37 * d) + chain * (f32 ? 0.47 - 0.085 * d : 0.41 - 0.053 * d);
+    if (levels > 1)
+        us += 20.0 - (f32 ? 3.8 : 5.5) * h + longest * h * (f32 ? 0.29 : 0.137) - s.fan * (f32 ? 0.75 : 0.49) - s.wide * (f32 ? 2.5 : 1.2);
+    return us;
+}
+
 // Fills the launch geometry of `a`; false if the forest is better run level by level.
-bool plan_trees(TreesArgs &a, size_t esz) {
+bool plan_trees(TreesArgs &a, size_t esz, const TreesShape &s) {
     if (a.n > trees_max_nodes(a.D, a.H, esz)) return false;
     a.sx = (int)ceil_div((int64_t)a.D * (int64_t)esz, 64);
     a.sh = (int)ceil_div((int64_t)a.H * (int64_t)esz, 64);
@@ -653,6 +674,7 @@ bool plan_trees(TreesArgs &a, size_t esz) {
     }
     if (a.lds_bytes > (size_t)kTreeLdsMax || a.cap >= kNoLocal) return false;
     a.n_blocks = (int)ceil_div(a.n, a.G);
+    if (trees_excess_us(a, esz, s) > 0.0) return false;
     // x part: one wave per unit tile and run of node tiles; as many waves as the chip holds at a time
     a.x_slabs = 0;
     for (int ns : kXSlabs)

@@ -217,3 +217,33 @@ def test_a_workspace_without_room_for_whole_trees(c_oracle, dtype):
     with pytest.raises(J.JitdbError) as e:
         J.jitdb_treelstm_forward(*dev, s, workspace=ws[:least - 256])
     assert e.value.code == -5
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("what,H,whole", [
+    ("one tree of 250 nodes", 240, False), ("one tree of 250 nodes", 40, True),        # one block for all of it, wide cells
+    ("interleaved", 150, False), ("filed", 150, True),                                 # the same trees, ids over each other or not
+    ("chains, narrow x", 150, False), ("chains", 150, True),
+])
+def test_whole_trees_where_they_are_the_faster_form(c_oracle, what, H, whole, dtype):
+    """Both forms give the oracle's states; which one runs goes by the estimate of their times."""
+    import paper_1904_07421_amd as J
+    rng = np.random.default_rng(3)
+    small = _lay_out([perfect_kary_tree(2, 3)] * 16)
+    p = {"one tree of 250 nodes": lambda: np.array([-1] + [int(rng.integers(v)) for v in range(1, 250)], np.int32),
+         "interleaved": lambda: relabel(small, 5)[0], "filed": lambda: small,
+         "chains, narrow x": lambda: _lay_out([chain_forest(10 + k % 50) for k in range(4000)]),
+         "chains": lambda: _lay_out([chain_forest(10 + k % 50) for k in range(400)])}[what]()
+    D = {"chains, narrow x": 16, "chains": 300}.get(what, 100)
+    x, W, U, b = make_values(1, p.shape[0], "random", D=D, H=H)
+    J.jitdb_profile_start(8192)
+    try:
+        s, h, c, seen = run_gpu_forward(p, x, W, U, b, dtype)
+    finally:
+        prof = J.jitdb_profile_stop()
+    print(f"form {what} H={H} {dtype} N={p.shape[0]} whole={prof['trees']['launches']}", flush=True)
+    assert 0 < s.struct.tree_window <= 256
+    assert (prof["trees"]["launches"] == 1) == whole
+    ho, co, _ = c_oracle(p, *seen)
+    assert np.abs(h - ho).max() <= TOL[dtype]
+    assert np.abs(c - co).max() <= TOL[dtype] * max(1.0, np.abs(co).max() / (8.0 if dtype == "bf16" else 50.0))
