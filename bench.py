@@ -504,11 +504,12 @@ def main():
     if prof is not None:
         proj_rows = (prof["proj"]["rows"] + prof["thin_proj"]["rows"]) / args.steps   # includes roots, whose P nobody reads
         chain_rows = prof["chain"]["edges"] / args.steps     # edges projected inside the chain launches (one per row)
-        if prof["trees"]["launches"]:       # every level below the chain levels in one launch: all of the forward's work but theirs
+        if prof["trees"]["launches"]:       # every level below the chain levels: all of the forward's work but theirs
             ms, rows = prof["trees"]["ms"] / args.steps, prof["trees"]["rows"] / args.steps
             fl = sum(flops_total.values()) - chain_rows * flops_row["chain"]
             by = bytes_min - chain_rows * bytes_row["chain"]
-            kernels["trees"] = {"ms_per_step": ms, "launches_per_step": prof["trees"]["launches"] / args.steps, "rows_per_step": rows,
+            kernels["trees"] = {"ms_per_step": ms, "launches_per_step": 2 * prof["trees"]["launches"] / args.steps,     # tree_x_kernel and trees_kernel
+                                "rows_per_step": rows,
                                 "flops_per_step": fl, "tflops": fl / (ms * 1e-3) / 1e12, "frac_mfma_peak": fl / (ms * 1e-3) / 1e12 / peak_tflops,
                                 "bytes_per_step": by, "gbs": by / (ms * 1e-3) / 1e9, "frac_hbm_peak": by / (ms * 1e-3) / 1e9 / PEAK_HBM_GBS,
                                 "flop_per_byte": fl / by, "bound": "mfma" if fl / by >= ridge else "hbm"}

@@ -462,13 +462,13 @@ typedef enum {
     JITDB_K_THIN_PROJ = 7,      /* includes the next slot's stack step when the two share a launch */
     JITDB_K_CHAIN = 8,          /* a level whose nodes all have one child: gather, all four gates and the cell
                                    update in one launch (no stack step, no projection) */
-    JITDB_K_TREES = 9,          /* a forest of small trees: every level below the chain levels in one launch */
+    JITDB_K_TREES = 9,          /* a forest of small trees: every level below the chain levels, two kernels timed as one */
     JITDB_K_CLASSES = 10
 } jitdb_kernel_class;
 
 typedef struct {
     double ms[JITDB_K_CLASSES];        /* summed event time per class, milliseconds */
-    int64_t launches[JITDB_K_CLASSES]; /* recorded launches per class */
+    int64_t launches[JITDB_K_CLASSES]; /* recorded launches per class (TREES: pairs of them) */
     int64_t rows[JITDB_K_CLASSES];     /* level rows (nodes) those launches covered; 0 for PACK */
     int64_t edges[JITDB_K_CLASSES];    /* children whose forget projections those launches computed themselves
                                           (CHAIN); 0 for the classes that read them from the projection step */

@@ -578,7 +578,9 @@ struct BwdWs {
 
 // How the sums over nodes are cut: as many ranges as give every compute unit two blocks, but no range under kMinSplitRows rows
 // (each costs 128 KB of partial sums a tile).  Long sums are cut eight times finer: the ranges, dealt whole to the XCDs, then
-// come out even (13 ranges of 90 k rows: 5.4 ms, two on five of the XCDs and one on the others).
+// come out even (13 ranges of 90 k rows: 5.4 ms, two on five of the XCDs and one on the others).  Long from 4 x 4096 rows on;
+// backward pass, ms, with 2048 / 4096 / 8192 there: 577 k nodes H 300 fp32 20.2 / 20.2 / 25.5, bf16 5.84 / 5.83 / 6.11; 286 k
+// nodes H 512 fp32 16.8 / 16.7 / 21.0.
 constexpr int kMinSplitRows = 128, kLongSplitRows = 4096;
 // Sums over the inner nodes alone (dU_iou, dW_f) start at the first of them, not at the 64 rows it lies in: a leaf has no part
 // in them, but its zero child sum times an infinite dz would be NaN.  Their ranges are those of all nodes, moved up by less
@@ -643,6 +645,8 @@ BwdWs carve_bwd_ws(int64_t n, const BwdDims &d, void *base) {
     return w;
 }
 
+// Half the compute units.  Backward pass, us, from 64 / 128 / 256 tiles on: 26 k nodes H 150 fp32 810 / 767 / 737, bf16 408 / 409 /
+// 392; 72 k nodes H 512 fp32 5933 / 5686 / 5717, bf16 1267 / 1257 / 1297; 143 k nodes H 256 fp32 4428 / 4308 / 4312.
 constexpr int kTileMinBlocks = 128;
 template <typename T>
 int launch_rows(const RowProduct *g, int n_products, int64_t rows_alloc, hipStream_t st) {

@@ -21,7 +21,7 @@
 //   chain_kernel       a thin level whose nodes all have exactly one child (sequences, the long
 //                      tail of a deep forest) as ONE launch: x and the child's h read in place,
 //                      all four gates over the full K, no stack step and no projection
-//   trees_kernel       (trees.hip) a forest of small trees filed one after another: all of the above in one launch
+//   tree_x_kernel, trees_kernel   (trees.hip) a forest of small trees filed one after another: all of the above in two launches
 //
 // With cells of different type in the table (jitdb_treelstm_forward_cells) a slot of N-ary cells
 // runs nary_level_kernel below: the same GEMM core with the N-ary cell update as its epilogue.

@@ -14,14 +14,15 @@
 //                      (barrier) i, o, u = Z + U hs;  c = i u + sum f c,  h = o tanh c; h goes out and into LDS
 //                      (barrier) P = U_f h from LDS; f = sigmoid(Z_f of the PARENT + P), f c goes out for the parent
 //                    A child's forget gate needs nothing of its parent but Z_f, which is there already: no P row and no
-//                    c row is fetched by a parent, child sums are the only gather, in 16-byte pieces with four
+//                    c row is fetched by a parent, child sums are the only gather, in 16-byte pieces with eight
 //                    children in flight.
 //                      (barrier, at the end of a level)
 //
 // A wave multiplies the gates of 16 hidden units (v_mfma_f32_16x16x32_bf16 / 16x16x4_f32), so the cell update finds a unit's
 // gates in one lane.  A comes from LDS, the weights from L2 in 1 KB pieces (64-byte slabs of 16 packed rows), kTreeAhead
 // slabs ahead.  What bounds it: the chain of three barriers and four memory latencies per level (bf16), the fp32
-// matrix rate on 16-row tiles (fp32).  Two blocks share a compute unit, so one's latencies hide behind the other.
+// matrix rate on 16-row tiles (fp32).  Up to H = 128 (8 waves) two blocks share a compute unit, so one's latencies hide behind
+// the other; wider cells take 12 or 16 waves and run one block a compute unit.
 #include "level_common.h"
 
 namespace jitdb {
@@ -186,7 +187,9 @@ __device__ __forceinline__ void save_gates(const TreesArgs &a, int64_t node, int
 // come straight from memory in operand layout, the next tile's slab requested as soon as this one's is used.  No LDS, no
 // barrier: waves of a block take different units of the same nodes, which meet in L1.
 template <typename T, int NS> constexpr int kXWavesPerSimd = NS <= 10 ? 2 : 1;
-constexpr int kXSlabs[] = {4, 7, 10, 16, 20};      // its instances: D up to 640 in bf16, 320 in fp32
+// Its instances: D up to 128, 224, 320, 512 and 640 in bf16, half of that in fp32.  Ten slabs are the most with which two waves
+// share a SIMD, twenty the most that 512 registers hold; the others bound the slabs multiplied as zeros to five.
+constexpr int kXSlabs[] = {4, 7, 10, 16, 20};
 constexpr int slabs_below(int ns) {                // the instance before: slabs up to there lie inside D whenever ns is chosen
     int below = 0;
     for (int k : kXSlabs)
@@ -621,7 +624,8 @@ int64_t trees_max_nodes(int D, int H, size_t esz) {
     // fill the chip, with the number of nodes.  Forward alone, 32 to 8192 trees of 4 - 48 nodes, D = 300, level by level ->
     // here: H = 64 fp32 201 -> 67 us (949 nodes), 1115 -> 522 (214 k), bf16 149 -> 58, 541 -> 242; H = 150 fp32 244 -> 126,
     // 1937 -> 1428, bf16 163 -> 83, 887 -> 637; H = 256 fp32 275 -> 217, 2438 -> 2437, bf16 169 -> 146 (949), 272 -> 209 (26 k),
-    // 532 -> 552 (106 k); H = 384 slower throughout.
+    // 532 -> 552 (106 k); H = 384 slower throughout.  The lines lie inside what was measured, not where the gain ends: no forest
+    // beyond 225 k nodes, and in bf16 at 106 k nodes H = 176 455 -> 381, 224 511 -> 455, 240 531 -> 531, 256 503 -> 532.
     if (H > kTreesMaxWidth || ceil_div((int64_t)D * (int64_t)esz, 64) > kXSlabs[sizeof(kXSlabs) / sizeof(int) - 1]) return 0;
     return esz == 2 && H > 160 ? 65536 : 262144;
 }
