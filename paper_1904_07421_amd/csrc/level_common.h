@@ -146,8 +146,10 @@ __device__ __forceinline__ void mfma16(const u32x4 &a, const u32x4 &b, floatx4 &
 // lane whose sum passes `tile` holds the range: two loads and six shuffles a step, one step for a level's slots and for
 // the n_sig^2 sub-slots of up to eight cells.  Each step waits for the one before it, so more than kRangeSteps of them are
 // first counted in 64 runs, one per lane, and the walk starts at the tile's run.  Forward, us, 296 k nodes, H 512, bf16,
-// leaves under one cell and the others under any, step by step / by runs: 16 cells 2146 / 2130, 32 cells 2734 / 2666,
-// 64 cells 5393 / 4335.  (A table written by a launch of its own cost 5 us twice per level and memory in the workspace.)
+// every node under any cell, step by step / by runs: 16 cells 2177 / 2173, 32 cells 2787 / 2696, 64 cells 5494 / 4511.  The
+// counting is compiled small and out of the way: four loads at a time took 64 cells to 4304 and four cells, which never get
+// there, from 1877 to 1882 (step with its schedule).  (A table written by a launch of its own cost 5 us twice per level and
+// memory in the workspace.)
 // False: past the last tile.
 constexpr int kRangeSteps = 4;
 __device__ __forceinline__ int wave_prefix(int v) {
@@ -163,13 +165,13 @@ __device__ __forceinline__ bool enter_range(LevelArgs &a, int tile, int &row0) {
     const int lane = threadIdx.x & 63;
     const int base = a.ranges[0];
     int start = 0, before = 0;
-    if (a.n_ranges > 64 * kRangeSteps) {                         // (sub-slots: range_stride is 1)
+    if (__builtin_expect(a.n_ranges > 64 * kRangeSteps, 0)) {    // (sub-slots: range_stride is 1)
         typedef u32x4 __attribute__((aligned(4))) u32x4a;
         const int per = ((a.n_ranges + 255) >> 8) * 4;           // a whole number of 16-byte loads, at most 64 ranges
         const int begin = lane * per;
         int n_t = 0, lo = a.ranges[begin < a.n_ranges ? begin : a.n_ranges];
         if (begin + per <= a.n_ranges) {
-#pragma unroll 4
+#pragma unroll 1
             for (int q = 1; q <= per; q += 4) {
                 const u32x4 hi = *reinterpret_cast<const u32x4a *>(a.ranges + begin + q);
 #pragma unroll
