@@ -606,6 +606,7 @@ struct TreesArgs {
     int D, H, Hp, Hq, NPU, sx_packed;      // sx_packed: slab of the packed weights at which the h part begins
     // by plan_trees
     int sx, sh, Hz, n_ut, pitch_h, group_rows, G, cap, n_waves, n_blocks, x_slabs, x_chunks;
+    int res_slabs, near_rows, f_lds;       // weights in registers: slabs of the instance (0: from L2); h and f c in LDS; slabs of f's in LDS
     size_t lds_bytes;
 };
 int64_t trees_max_nodes(int D, int H, size_t esz);      // largest forest that plan_trees accepts (0: none)

@@ -21,8 +21,8 @@
 // A wave multiplies the gates of 16 hidden units (v_mfma_f32_16x16x32_bf16 / 16x16x4_f32), so the cell update finds a unit's
 // gates in one lane.  A comes from LDS, the weights from L2 in 1 KB pieces (64-byte slabs of 16 packed rows), kTreeAhead
 // slabs ahead.  What bounds it: the chain of three barriers and four memory latencies per level (bf16), the fp32
-// matrix rate on 16-row tiles (fp32).  Up to H = 128 (8 waves) two blocks share a compute unit, so one's latencies hide behind
-// the other; wider cells take 12 or 16 waves and run one block a compute unit.
+// matrix rate on 16-row tiles (fp32).  Wide cells take up to 16 waves and run one block a compute unit.  Where the weights of 16
+// units fit a wave's registers, trees_resident_kernel runs instead.
 #include "level_common.h"
 
 namespace jitdb {
@@ -65,9 +65,8 @@ __device__ __forceinline__ float quarter_sum(const floatx4 &acc, int lane) {
 // acc[rt][g] += A rows (16 rt ..; NRT == 0: at most four rows) x packed rows of gate g, over n_slabs slabs of 64 bytes of K.
 // a_lane: this lane's bytes of slab 0 (row lane & 15 or lane & 3, piece lane >> 4) in LDS or memory; b_lane likewise in the
 // packed weights, the gates 2048 bytes apart.  A_AHEAD: A comes from memory and is requested with the weights.
-template <typename T, int NRT, int NG, bool A_AHEAD = false, typename ALoad>
+template <typename T, int NRT, int NG, bool A_AHEAD = false, int AHEAD = kTreeAhead<NRT, NG>, typename ALoad>
 __device__ __forceinline__ void tree_gemm(floatx4 (&acc)[NRT ? NRT : 1][NG], ALoad &&load_a, const char *b_lane, int64_t b_slab, int n_slabs) {
-    constexpr int AHEAD = kTreeAhead<NRT, NG>;
     constexpr int NA = NRT ? NRT : 1;
     u32x4 fb[AHEAD][NG], fr[A_AHEAD ? AHEAD : 1][NA];
     auto request = [&](int s, int slot) __attribute__((always_inline)) {
@@ -294,67 +293,105 @@ tree_x_kernel(const TreesArgs a) {
 struct TreeBlock {
     char *A, *Ht;                          // LDS: child sums and h of the group's rows, [group_rows][pitch_h]
     float *Fs;                             // LDS: sums of the children's f c, [group_rows][Hz]
-    const uint16_t *order, *cstart, *kids, *par;   // local ids by row; child list starts, children, parents by local id
+    uint16_t *order, *cstart, *kids, *par;         // local ids by row; child list starts, children, parents by local id
     int lo, own;
     int lane, wave, n_waves;
 };
 
-// Child sums of rows [r0, r_end) into A and Fs.  A wave takes 64 of a row's 16-byte pieces at a time, eight children in flight.
-template <typename T>
-__device__ __forceinline__ void gather_sums(const TreesArgs &a, const TreeBlock &b, int r0, int r_end) {
+// All of the block's LDS writes are visible after it; stores to memory are not waited for (__syncthreads would).
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+// The arrays of a block's view behind `at`: 4 cap + 8 entries.
+__device__ __forceinline__ void place_view(const TreesArgs &a, TreeBlock &b, char *at) {
+    b.order = reinterpret_cast<uint16_t *>(at);
+    b.cstart = b.order + a.cap;
+    b.kids = b.cstart + a.cap + 2;
+    b.par = b.kids + a.cap;
+    b.lane = threadIdx.x & 63;
+    b.wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    b.n_waves = blockDim.x >> 6;
+}
+
+// Child sums of rows [r0, r_end) into A and Fs.  A wave takes 64 of a row's 16-byte pieces at a time, of ROWS rows side by side,
+// KIDS children of each in flight.
+template <typename T, int ROWS, int KIDS>
+__device__ __forceinline__ void gather_sums(const TreesArgs &a, const TreeBlock &b, int r0, int r_end, int ph) {
     constexpr int VEC = Traits<T>::VEC;
-    const int ph = a.sh * 4, pf = a.Hz / 4;      // 16-byte pieces of an h row and of an f c row
+    const int pf = a.Hz / 4;                     // 16-byte pieces of an f c row (ph: of an h row)
     const int per_row = (ph + pf + 63) >> 6, n_tasks = (r_end - r0) * per_row;
-    for (int q = b.wave; q < n_tasks; q += b.n_waves) {
-        const int rr = q / per_row, k = (q - rr * per_row) * 64 + fresh_lane(b.lane);
-        if (k >= ph + pf) continue;
-        const int i = __builtin_amdgcn_readfirstlane((int)b.order[r0 + rr]);
-        const int c0 = b.cstart[i], c1 = b.cstart[i + 1];
-        const bool is_h = k < ph;
-        if (is_h && k * VEC >= a.Hz) {           // the slab's pieces past the last unit tile
-            *reinterpret_cast<u32x4 *>(b.A + rr * a.pitch_h + k * 16) = u32x4{0, 0, 0, 0};
-            continue;
-        }
-        // an h row or an f c row: the same loads, summed as what they are
-        const char *col = is_h ? static_cast<const char *>(a.hs) + (int64_t)b.lo * a.Hp * (int)sizeof(T) + k * 16
-                               : reinterpret_cast<const char *>(a.FC) + (int64_t)b.lo * a.Hz * 4 + (k - ph) * 16;
-        const int pitch = is_h ? a.Hp * (int)sizeof(T) : a.Hz * 4;
-        float s[VEC];
+    for (int q0 = b.wave; q0 < n_tasks; q0 += ROWS * b.n_waves) {
+        const char *col[ROWS];
+        u32x4 w[ROWS][KIDS];
+        int c0[ROWS], c1[ROWS];
+        auto piece = [&](int q, int &rr, int &k) __attribute__((always_inline)) {
+            rr = q / per_row;
+            k = (q - rr * per_row) * 64 + fresh_lane(b.lane);
+            return k < ph + pf;
+        };
+        const int pitch_f = a.Hz * 4, pitch_h = a.Hp * (int)sizeof(T);
 #pragma unroll
-        for (int j = 0; j < VEC; ++j) s[j] = 0.0f;
-        for (int c = c0; c < c1; c += 8) {       // ascending ids
-            u32x4 w[8];
+        for (int j = 0; j < ROWS; ++j) {
+            const int q = q0 + j * b.n_waves;
+            c0[j] = c1[j] = 0;
+            if (q >= n_tasks) continue;
+            int rr, k;
+            if (!piece(q, rr, k)) continue;
+            const int i = __builtin_amdgcn_readfirstlane((int)b.order[r0 + rr]);
+            c0[j] = b.cstart[i];
+            c1[j] = b.cstart[i + 1];
+            const bool is_h = k < ph;
+            if (is_h && k * VEC >= a.Hz) c1[j] = c0[j];      // the slab's pieces past the last unit tile are zero
+            // an h row or an f c row: the same loads, summed as what they are
+            col[j] = is_h ? static_cast<const char *>(a.hs) + (int64_t)b.lo * pitch_h + k * 16
+                          : reinterpret_cast<const char *>(a.FC) + (int64_t)b.lo * pitch_f + (k - ph) * 16;
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                w[e] = u32x4{0, 0, 0, 0};
-                if (c + e < c1) w[e] = *reinterpret_cast<const u32x4 *>(col + (int64_t)b.kids[c + e] * pitch);
+            for (int e = 0; e < KIDS; ++e) {
+                w[j][e] = u32x4{0, 0, 0, 0};
+                if (c0[j] + e < c1[j]) w[j][e] = *reinterpret_cast<const u32x4 *>(col[j] + (int64_t)b.kids[c0[j] + e] * (is_h ? pitch_h : pitch_f));
             }
+        }
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                if (c + e >= c1) break;
-                if (sizeof(T) == 4 || is_h) {
-                    add_h_piece<T>(s, w[e]);
-                } else {
+        for (int j = 0; j < ROWS; ++j) {
+            const int q = q0 + j * b.n_waves;
+            if (q >= n_tasks) continue;
+            int rr, k;
+            if (!piece(q, rr, k)) continue;
+            const bool is_h = k < ph;
+            float s[VEC];
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) s[j] += __uint_as_float(w[e][j]);
+            for (int e = 0; e < VEC; ++e) s[e] = 0.0f;
+            for (int c = c0[j]; c < c1[j]; c += KIDS) {      // ascending ids
+                if (c > c0[j]) {
+#pragma unroll
+                    for (int e = 0; e < KIDS; ++e) {
+                        w[j][e] = u32x4{0, 0, 0, 0};
+                        if (c + e < c1[j]) w[j][e] = *reinterpret_cast<const u32x4 *>(col[j] + (int64_t)b.kids[c + e] * (is_h ? pitch_h : pitch_f));
+                    }
+                }
+#pragma unroll
+                for (int e = 0; e < KIDS; ++e) {
+                    if (c + e >= c1[j]) break;
+                    if (sizeof(T) == 4 || is_h) {
+                        add_h_piece<T>(s, w[j][e]);
+                    } else {
+#pragma unroll
+                        for (int u = 0; u < 4; ++u) s[u] += __uint_as_float(w[j][e][u]);
+                    }
                 }
             }
-        }
-        if (is_h) {
-            T e[VEC];
+            if (is_h) {
+                T e[VEC];
 #pragma unroll
-            for (int j = 0; j < VEC; ++j) e[j] = from_f32<T>(s[j]);
-            u32x4 v;
-            __builtin_memcpy(&v, e, 16);
-            *reinterpret_cast<u32x4 *>(b.A + rr * a.pitch_h + k * 16) = v;
-        } else {
-            *reinterpret_cast<float4 *>(b.Fs + rr * a.Hz + (k - ph) * 4) = make_float4(s[0], s[1], s[2], s[3]);
+                for (int u = 0; u < VEC; ++u) e[u] = from_f32<T>(s[u]);
+                u32x4 v;
+                __builtin_memcpy(&v, e, 16);
+                *reinterpret_cast<u32x4 *>(b.A + rr * a.pitch_h + k * 16) = v;
+            } else {
+                *reinterpret_cast<float4 *>(b.Fs + rr * a.Hz + (k - ph) * 4) = make_float4(s[0], s[1], s[2], s[3]);
+            }
         }
     }
 }
-
-// All of the block's LDS writes are visible after it; stores to memory are not waited for (__syncthreads would).
-__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 // The cells of rows [r0, r_end): at most 16 NRT, NRT == 0: at most four, one per lane quarter.
 template <typename T, bool SAVE, int NRT>
@@ -456,33 +493,22 @@ __device__ __forceinline__ void forget_tile(const TreesArgs &a, const TreeBlock 
         }
 }
 
-template <typename T, bool SAVE>
-__global__ void __launch_bounds__(kTreeMaxWaves * 64, 4)
-trees_kernel(const TreesArgs a) {
-    extern __shared__ __attribute__((aligned(16))) char lds[];
-    __shared__ int s_cut[2];
-    __shared__ int s_min[kTreeMaxLevels];
-    __shared__ int s_cnt[kTreeMaxLevels];
-    __shared__ int s_start[kTreeMaxLevels + 1];
-    const int t = threadIdx.x, nt = blockDim.x;
-    TreeBlock b;
-    b.A = lds;
-    b.Ht = b.A + a.group_rows * a.pitch_h;
-    b.Fs = reinterpret_cast<float *>(b.Ht + a.group_rows * a.pitch_h);
-    uint16_t *order = reinterpret_cast<uint16_t *>(b.Fs + a.group_rows * a.Hz);
-    uint16_t *cstart = order + a.cap, *kids = cstart + a.cap + 2, *par = kids + a.cap;
-    b.order = order; b.cstart = cstart; b.kids = kids; b.par = par;
-    b.lane = t & 63;
-    b.wave = __builtin_amdgcn_readfirstlane(t >> 6);
-    b.n_waves = nt >> 6;
+struct TreeMeta {                          // LDS of a block for the view of its trees
+    int cut[2];
+    int min[kTreeMaxLevels], cnt[kTreeMaxLevels], start[kTreeMaxLevels + 1];
+};
 
+// Which trees are this block's, and its rows: fills `b` and `m`; false if there are none.  A barrier still has to follow.
+// `lds` is scratch in front of the arrays of `b` (its barriers wait for LDS alone: weights on their way to registers stay so).
+__device__ __forceinline__ bool view_trees(const TreesArgs &a, char *lds, TreeBlock &b, TreeMeta &m) {
+    const int t = threadIdx.x, nt = blockDim.x;
     // ---- where the block's trees begin and end: for both places, how many parent-child intervals cross every position
     //      from i0 - tw on (the first and the last child bound a node's interval: child lists ascend)
     const int tw = a.tree_window, span = 2 * tw + 1;
     int *cover = reinterpret_cast<int *>(lds);                 // [2][span + 1]
     for (int i = t; i < 2 * (span + 1); i += nt) cover[i] = 0;
-    if (t < kTreeMaxLevels) { s_min[t] = INT32_MAX; s_cnt[t] = 0; }
-    __syncthreads();
+    if (t < kTreeMaxLevels) { m.min[t] = INT32_MAX; m.cnt[t] = 0; }
+    lds_barrier();
     for (int side = 0; side < 2; ++side) {
         const int64_t i0 = ((int64_t)blockIdx.x + side) * a.G;
         if (i0 == 0 || i0 >= a.n) continue;
@@ -499,7 +525,7 @@ trees_kernel(const TreesArgs a) {
             if (p1 <= span) atomicAdd(&cover[side * (span + 1) + p1], -1);
         }
     }
-    __syncthreads();
+    lds_barrier();
     if (b.wave < 2) {
         const int64_t i0 = ((int64_t)blockIdx.x + b.wave) * a.G;
         int cut;
@@ -526,61 +552,76 @@ trees_kernel(const TreesArgs a) {
             for (int d = 32; d > 0; d >>= 1) cut = min(cut, __shfl_xor(cut, d, 64));
             if (cut > a.n) cut = a.n;                          // (past the last node, or no cut: not a schedule of jitdb_schedule)
         }
-        if (b.lane == 0) s_cut[b.wave] = cut;
+        if (b.lane == 0) m.cut[b.wave] = cut;
     }
-    __syncthreads();
-    b.lo = s_cut[0];
-    b.own = s_cut[1] - b.lo;
+    lds_barrier();
+    b.lo = m.cut[0];
+    b.own = m.cut[1] - b.lo;
     if (b.own > a.cap) b.own = a.cap;
-    if (b.own <= 0) return;
+    if (b.own <= 0) return false;
 
     // ---- rows: a level's nodes of this block are consecutive positions of the schedule
     const int e0 = a.child_ptr[b.lo], n_edges = min(a.child_ptr[b.lo + b.own] - e0, b.own);
     for (int i = t; i < b.own; i += nt) {
         const int h = a.height[b.lo + i];
         if (h < kTreeMaxLevels) {
-            atomicMin(&s_min[h], a.inv_perm[b.lo + i]);
-            atomicAdd(&s_cnt[h], 1);
+            atomicMin(&m.min[h], a.inv_perm[b.lo + i]);
+            atomicAdd(&m.cnt[h], 1);
         }
-        order[i] = 0;
-        par[i] = kNoLocal;
+        b.order[i] = 0;
+        b.par[i] = kNoLocal;
     }
-    for (int i = t; i <= b.own; i += nt) cstart[i] = (uint16_t)min(max(a.child_ptr[b.lo + i] - e0, 0), n_edges);
+    for (int i = t; i <= b.own; i += nt) b.cstart[i] = (uint16_t)min(max(a.child_ptr[b.lo + i] - e0, 0), n_edges);
     for (int e = t; e < n_edges; e += nt) {
         const int k = a.child_idx[e0 + e] - b.lo;
-        kids[e] = (uint16_t)(k >= 0 && k < b.own ? k : 0);
+        b.kids[e] = (uint16_t)(k >= 0 && k < b.own ? k : 0);
     }
-    __syncthreads();
+    lds_barrier();
     if (b.wave == 0) {
-        const int c = b.lane < kTreeMaxLevels ? s_cnt[b.lane] : 0;
+        const int c = b.lane < kTreeMaxLevels ? m.cnt[b.lane] : 0;
         int inc = c;
 #pragma unroll
         for (int d = 1; d < 64; d <<= 1) {
             const int v = __shfl_up(inc, d, 64);
             if (b.lane >= d) inc += v;
         }
-        if (b.lane < kTreeMaxLevels) s_start[b.lane] = inc - c;
-        if (b.lane == kTreeMaxLevels - 1) s_start[kTreeMaxLevels] = inc;
+        if (b.lane < kTreeMaxLevels) m.start[b.lane] = inc - c;
+        if (b.lane == kTreeMaxLevels - 1) m.start[kTreeMaxLevels] = inc;
     }
-    __syncthreads();
+    lds_barrier();
     for (int i = t; i < b.own; i += nt) {
         const int h = a.height[b.lo + i];
         if (h < kTreeMaxLevels) {
-            const int r = s_start[h] + a.inv_perm[b.lo + i] - s_min[h];
-            if (r >= 0 && r < b.own) order[r] = (uint16_t)i;
+            const int r = m.start[h] + a.inv_perm[b.lo + i] - m.min[h];
+            if (r >= 0 && r < b.own) b.order[r] = (uint16_t)i;
         }
-        for (int e = cstart[i]; e < cstart[i + 1]; ++e) par[kids[e]] = (uint16_t)i;
+        for (int e = b.cstart[i]; e < b.cstart[i + 1]; ++e) b.par[b.kids[e]] = (uint16_t)i;
     }
+    return true;
+}
+
+template <typename T, bool SAVE>
+__global__ void __launch_bounds__(kTreeMaxWaves * 64, 4)
+trees_kernel(const TreesArgs a) {
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    __shared__ TreeMeta m;
+    const int t = threadIdx.x, nt = blockDim.x;
+    TreeBlock b;
+    b.A = lds;
+    b.Ht = b.A + a.group_rows * a.pitch_h;
+    b.Fs = reinterpret_cast<float *>(b.Ht + a.group_rows * a.pitch_h);
+    place_view(a, b, reinterpret_cast<char *>(b.Fs + a.group_rows * a.Hz));
+    if (!view_trees(a, lds, b, m)) return;
     for (int i = t * 16; i < a.group_rows * a.pitch_h; i += nt * 16)      // pad columns of the h rows stay zero
         *reinterpret_cast<u32x4 *>(b.Ht + i) = u32x4{0, 0, 0, 0};
     // levels of this block that run here: [0, n_lvl)
     int n_lvl = 0;
-    while (n_lvl < a.l_end && s_cnt[n_lvl] > 0) ++n_lvl;
+    while (n_lvl < a.l_end && m.cnt[n_lvl] > 0) ++n_lvl;
     __syncthreads();
 
     if (n_lvl < 2) return;
     {   // the leaves: every wave for itself, 16 or 32 rows of 16 units at a time (waves side by side share the rows' lines in L1)
-        const int n_leaf = s_cnt[0], n32 = n_leaf >> 5, rest = n_leaf & 31, n_tasks = (n32 + (rest > 0)) * a.n_ut;
+        const int n_leaf = m.cnt[0], n32 = n_leaf >> 5, rest = n_leaf & 31, n_tasks = (n32 + (rest > 0)) * a.n_ut;
         for (int q = b.wave; q < n_tasks; q += b.n_waves) {
             const int tile = q / a.n_ut, ut = q - tile * a.n_ut;
             if (tile < n32) forget_tile<T, SAVE, 2, true>(a, b, ut, tile * 32, tile * 32 + 32);
@@ -591,11 +632,11 @@ trees_kernel(const TreesArgs a) {
         __syncthreads();
     }
     for (int l = 1; l < n_lvl; ++l) {
-        const int l0 = s_start[l], l1 = s_start[l + 1];
+        const int l0 = m.start[l], l1 = m.start[l + 1];
         for (int r0 = l0; r0 < l1; r0 += a.group_rows) {
             const int r_end = r0 + a.group_rows < l1 ? r0 + a.group_rows : l1, rows = r_end - r0;
             if (r0 > l0) lds_barrier();               // the group before is done with Fs
-            gather_sums<T>(a, b, r0, r_end);
+            gather_sums<T, 1, 8>(a, b, r0, r_end, a.sh * 4);
             lds_barrier();
             if (rows > 16) level_group<T, SAVE, 2>(a, b, r0, r_end);
             else if (rows > 4) level_group<T, SAVE, 1>(a, b, r0, r_end);
@@ -609,6 +650,419 @@ trees_kernel(const TreesArgs a) {
             }
         }
         __syncthreads();                              // the next level's sums read what this one left in memory
+    }
+}
+
+// ---- the levels with the recurrent weights in registers ----------------------------------------
+// trees_kernel reads U from L2 once per level, and at 50 KB a microsecond and compute unit (measured: clock stamps) that is most of
+// a level.  Where the four gates' weights of 16 units fit the registers of one wave, a wave loads them once, while the block works
+// out its trees, and keeps them over all levels; bf16 wider than 160 and fp32 wider than 128 have room for i, o and u, and
+// for f's first slabs in what LDS has left.
+// Schedule + forward, from L2 -> so: 71 nodes H 150 fp32 99 -> 89 us, 4.7 k nodes H 150 fp32 156 -> 141, 21 k nodes H 99 bf16
+// 150 -> 125, 54 k nodes H 180 bf16 314 -> 258, 106 k nodes H 150 bf16 368 -> 316, 216 k nodes H 64 fp32 372 -> 367.  What bounds it:
+// the 4x4 MFMAs of three waves on a SIMD and the barriers (few rows), memory traffic of Z, h and f c (many rows).
+// NEAR: h and f c of all of the block's nodes stay in LDS (rows by local id), so that a level's sums wait for no memory;
+// otherwise they go through memory as in trees_kernel, and Ht and C hold the rows of one group.
+// Waves: unit tile wave % n_ut, rows in tiles of 16 (bf16) or 4 (fp32, whose 4x4 MFMAs have the rate of the 16x16 ones),
+// dealt to the n_waves / n_ut sets of waves.
+template <typename T, int NS> constexpr int kResTiles = NS * 4 / (int)sizeof(T);       // most unit tiles
+template <typename T, int NS> constexpr int kResWaves = kResTiles<T, NS> <= 8 ? 8 : 12;
+template <typename T, int NS> constexpr bool kResForget = NS * 16 <= (kResTiles<T, NS> <= 8 ? 128 : 80);   // f's weights in registers, too
+template <typename T, int NS> constexpr int kResWeights = NS * (kResForget<T, NS> ? 16 : 12);   // registers
+template <typename T, int NS> constexpr int kResPerSimd = kResWaves<T, NS> == 12 ? 3 : kResWeights<T, NS> <= (sizeof(T) == 4 ? 64 : 32) ? 4 : 2;
+template <typename T> constexpr int kResRows = sizeof(T) == 4 ? 4 : 16;                 // rows of a tile
+constexpr int kResGroup = 64;                      // most rows of a group (not NEAR)
+constexpr int kResAhead = 2;                       // slabs of f's weights on their way from L2, of those that LDS does not hold
+template <typename T, int NS> constexpr bool kResNearOnly = kResForget<T, NS> == false && sizeof(T) == 4;
+
+template <typename T, int NS>
+struct ResWeights {
+    u32x4 iou[NS][3];
+    u32x4 f[kResForget<T, NS> ? NS : 1][1];
+};
+// What one lane adds to a tile's products: four rows (16-row tiles: row hf * 4 + v) or one (4-row tiles: row hf).
+template <int NG> struct ResPre { float z[NG][4]; };
+
+struct ResBlock : TreeBlock {
+    float *C;                 // LDS [slot][Hz]: sum of the children's f c, then c, then (NEAR) f c
+    int ut, set, n_sets;
+    int piece, piece_row, piece_rows;      // res_gather: this thread's 16-byte piece, first row and rows a step
+    char *F; int f_lds;       // LDS: the first f_lds slabs of f's weights, a wave's tile after the other, in lane order
+};
+// Row r's place in Ht and C.
+template <bool NEAR>
+__device__ __forceinline__ int res_slot(const ResBlock &b, int r, int r0) { return NEAR ? (int)b.order[r] : r - r0; }
+template <typename T>
+__device__ __forceinline__ bool res_quad(int row, int r_end) { return sizeof(T) == 4 || r_end - row <= 4; }
+__device__ __forceinline__ int res_row(bool quad, int row, int r_end, int hf, int v) {
+    const int r = row + (quad ? hf : hf * 4 + v);
+    return r < r_end ? r : r_end - 1;
+}
+template <typename T>
+__device__ __forceinline__ void res_load_z(const TreesArgs &a, const ResBlock &b, int row, int r_end, ResPre<3> &p) {
+    if (row >= r_end) return;
+    const int lane = fresh_lane(b.lane), unit = b.ut * 16 + (lane & 15);
+    const bool quad = res_quad<T>(row, r_end);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        if (v > 0 && quad) break;
+        const float *zp = a.Z + (int64_t)(b.lo + b.order[res_row(quad, row, r_end, lane >> 4, v)]) * 4 * a.Hz + unit;
+#pragma unroll
+        for (int g = 0; g < 3; ++g) p.z[g][v] = zp[g * a.Hz];
+    }
+}
+template <typename T>
+__device__ __forceinline__ void res_load_zf(const TreesArgs &a, const ResBlock &b, int row, int r_end, ResPre<1> &p) {
+    if (row >= r_end) return;
+    const int lane = fresh_lane(b.lane), unit = b.ut * 16 + (lane & 15);
+    const bool quad = res_quad<T>(row, r_end);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        if (v > 0 && quad) break;
+        const int i = b.order[res_row(quad, row, r_end, lane >> 4, v)], q = b.par[i];
+        p.z[0][v] = a.Z[((int64_t)(b.lo + (q != kNoLocal ? q : i)) * 4 + 3) * a.Hz + unit];
+    }
+}
+
+// acc[g] = A rows x the weights w[s][g]; a_lane: this lane's bytes of slab 0 (row lane & 15 or lane & 3, piece lane >> 4) in LDS.
+template <typename T, int NS, int NG, bool QUAD>
+__device__ __forceinline__ void res_gemm(floatx4 (&acc)[NG], const char *a_lane, const u32x4 (&w)[NS][NG]) {
+#pragma unroll
+    for (int g = 0; g < NG; ++g) acc[g] = floatx4{0, 0, 0, 0};
+    u32x4 fa[2];
+    fa[0] = *reinterpret_cast<const u32x4 *>(a_lane);
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+        if (s + 1 < NS) fa[(s + 1) & 1] = *reinterpret_cast<const u32x4 *>(a_lane + (s + 1) * 64);
+        const u32x4 &f = fa[s & 1];
+        if constexpr (!QUAD) {
+#pragma unroll
+            for (int g = 0; g < NG; ++g) mfma16<T>(f, w[s][g], acc[g]);
+        } else if constexpr (sizeof(T) == 2) {
+#pragma unroll
+            for (int g = 0; g < NG; ++g) mfma4<T>(f, w[s][g], acc[g]);
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int g = 0; g < NG; ++g)
+                    acc[g] = __builtin_amdgcn_mfma_f32_4x4x1f32(__uint_as_float(f[j]), __uint_as_float(w[s][g][j]), acc[g], 0, 0, 0);
+        }
+    }
+}
+
+// The cells of the tile of rows from `row` on.
+template <typename T, bool SAVE, int NS, bool NEAR, bool QUAD>
+__device__ __forceinline__ void res_cells(const TreesArgs &a, const ResBlock &b, const u32x4 (&w)[NS][3], const ResPre<3> &p, int row,
+                                          int r0, int r_end) {
+    constexpr int PITCH = NS * 64 + 16;
+    const int lane = fresh_lane(b.lane), hf = lane >> 4, n = lane & 15, unit = b.ut * 16 + n;
+    floatx4 acc[3];
+    res_gemm<T, NS, 3, QUAD>(acc, b.A + (row - r0 + (QUAD ? lane & 3 : n)) * PITCH + hf * 16, w);
+#pragma unroll
+    for (int v = 0; v < (QUAD ? 1 : 4); ++v) {
+        float z[3];
+#pragma unroll
+        for (int g = 0; g < 3; ++g) z[g] = p.z[g][v] + (QUAD ? quarter_sum(acc[g], lane) : acc[g][v]);
+        const int r = row + (QUAD ? hf : hf * 4 + v);
+        if (r >= r_end) continue;
+        const int i = b.order[r], slot = NEAR ? i : r - r0;
+        const float gi = sigmoid_t<T>(z[0]), go = sigmoid_t<T>(z[1]), gu = tanh_t<T>(z[2]);
+        float *cp = b.C + slot * a.Hz + unit;
+        const float c = gi * gu + *cp;
+        *cp = c;                                 // for the forget gates' step
+        const T hv = unit < a.H ? from_f32<T>(go * tanh_t<T>(c)) : T(0);
+        *reinterpret_cast<T *>(b.Ht + slot * PITCH + unit * (int)sizeof(T)) = hv;
+        store_unit<T>(a, b.lo + i, unit, c, hv);
+        if constexpr (SAVE) {
+            if (unit < a.H) save_gates<T>(a, b.lo + i, unit, gi, go, gu);
+        }
+    }
+}
+
+// f c of the tile's rows from P = U_f h, f with the parent's Z_f (in p).  FAR_LEAF: c comes from memory, in cm.
+template <typename T, bool SAVE, int NS, bool NEAR, bool QUAD, bool FAR_LEAF>
+__device__ __forceinline__ void res_forget(const TreesArgs &a, const ResBlock &b, const ResWeights<T, NS> &w, const ResPre<1> &p,
+                                           const ResPre<1> &cm, const char *rows, int row, int r0, int r_end) {
+    constexpr int PITCH = NS * 64 + 16;
+    const int lane = fresh_lane(b.lane), hf = lane >> 4, n = lane & 15, unit = b.ut * 16 + n;
+    const int ra = row + (QUAD ? lane & 3 : n);
+    const char *a_lane = rows + (NEAR ? (int)b.order[ra < r_end ? ra : r_end - 1] : ra - r0) * PITCH + hf * 16;
+    floatx4 acc[1];
+    if constexpr (kResForget<T, NS>) {
+        res_gemm<T, NS, 1, QUAD>(acc, a_lane, w.f);
+    } else {
+        // the slabs in LDS while the others are on their way
+        const char *wp = tree_weights(a, lane, b.ut, a.sx_packed, 3), *fl = b.F + (b.ut * b.f_lds * 64 + lane) * 16;
+        const int64_t slab = (int64_t)a.NPU * 64;
+        const int rest = a.sh - b.f_lds;
+        u32x4 ahead[kResAhead];
+#pragma unroll
+        for (int e = 0; e < kResAhead; ++e)
+            if (e < rest) ahead[e] = *reinterpret_cast<const u32x4 *>(wp + (b.f_lds + e) * slab);
+        floatx4 part[1][1] = {{floatx4{0, 0, 0, 0}}};
+        auto multiply = [&](const u32x4 &fb, int s) __attribute__((always_inline)) {
+            const u32x4 fa = *reinterpret_cast<const u32x4 *>(a_lane + s * 64);
+            if constexpr (QUAD) mfma4<T>(fa, fb, part[0][0]);
+            else mfma16<T>(fa, fb, part[0][0]);
+        };
+        for (int s = 0; s < b.f_lds; ++s) multiply(*reinterpret_cast<const u32x4 *>(fl + s * 1024), s);
+#pragma unroll
+        for (int e = 0; e < kResAhead; ++e)
+            if (e < rest) multiply(ahead[e], b.f_lds + e);
+        const int done = b.f_lds + kResAhead;
+        if (done < a.sh)
+            tree_gemm<T, QUAD ? 0 : 1, 1, false, kResAhead>(part, [&](int, int s) { return *reinterpret_cast<const u32x4 *>(a_lane + (done + s) * 64); },
+                                                            wp + done * slab, slab, a.sh - done);
+        acc[0] = part[0][0];
+    }
+#pragma unroll
+    for (int v = 0; v < (QUAD ? 1 : 4); ++v) {
+        const float pf = QUAD ? quarter_sum(acc[0], lane) : acc[0][v];
+        const int r = row + (QUAD ? hf : hf * 4 + v);
+        if (r >= r_end) continue;
+        const int i = b.order[r];
+        if (b.par[i] == kNoLocal) continue;
+        const float f = sigmoid_t<T>(pf + p.z[0][v]);
+        float *cp = b.C + (NEAR ? i : r - r0) * a.Hz + unit;
+        const float fc = unit < a.H ? f * (FAR_LEAF ? cm.z[0][v] : *cp) : 0.0f;
+        if constexpr (NEAR) *cp = fc;
+        else a.FC[(int64_t)(b.lo + i) * a.Hz + unit] = fc;
+        if constexpr (SAVE) {
+            if (unit < a.H) static_cast<T *>(a.fgate)[(int64_t)(b.lo + i) * a.H + unit] = from_f32<T>(f);
+        }
+    }
+}
+
+// NEAR: child sums of rows [r0, r_end) from LDS into A and, of f c, into the rows' own places in C.  A thread sums one 16-byte
+// piece of one row.
+template <typename T, int NS>
+__device__ __forceinline__ void res_gather(const TreesArgs &a, const ResBlock &b, int r0, int r_end) {
+    constexpr int PITCH = NS * 64 + 16, VEC = Traits<T>::VEC, PH = NS * 4;
+    const int k = b.piece;
+    for (int r = r0 + b.piece_row; r < r_end; r += b.piece_rows) {
+        const int i = b.order[r], rr = r - r0;
+        const int c0 = b.cstart[i], c1 = b.cstart[i + 1];
+        float s[VEC];
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) s[e] = 0.0f;
+        if (k < PH) {
+            for (int c = c0; c < c1; ++c)        // ascending ids; pieces past the last unit tile are zero in every row
+                add_h_piece<T>(s, *reinterpret_cast<const u32x4 *>(b.Ht + (int)b.kids[c] * PITCH + k * 16));
+            T e[VEC];
+#pragma unroll
+            for (int j = 0; j < VEC; ++j) e[j] = from_f32<T>(s[j]);
+            u32x4 v;
+            __builtin_memcpy(&v, e, 16);
+            *reinterpret_cast<u32x4 *>(b.A + rr * PITCH + k * 16) = v;
+        } else {
+            const int u = (k - PH) * 4;
+            float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
+            for (int c = c0; c < c1; ++c) {
+                const float4 w = *reinterpret_cast<const float4 *>(b.C + (int)b.kids[c] * a.Hz + u);
+                o.x += w.x; o.y += w.y; o.z += w.z; o.w += w.w;
+            }
+            *reinterpret_cast<float4 *>(b.C + i * a.Hz + u) = o;
+        }
+    }
+}
+
+// 16 bytes, piece k, of the h row of local node i; zero past the last unit tile.
+template <typename T>
+__device__ __forceinline__ u32x4 res_h_piece(const TreesArgs &a, const ResBlock &b, int i, int k) {
+    u32x4 v = {0, 0, 0, 0};
+    if (k * Traits<T>::VEC < a.Hz)
+        v = *reinterpret_cast<const u32x4 *>(static_cast<const char *>(a.hs) + (int64_t)(b.lo + i) * a.Hp * (int)sizeof(T) + k * 16);
+    return v;
+}
+
+template <typename T, bool SAVE, int NS, bool NEAR>
+__global__ void __launch_bounds__((kResWaves<T, NS> * 64), (kResPerSimd<T, NS>))
+trees_resident_kernel(const TreesArgs a) {
+    constexpr int PITCH = NS * 64 + 16, STEP = kResRows<T>, NT = kResWaves<T, NS> * 64, PH = NS * 4;
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    __shared__ TreeMeta m;
+    const int t = threadIdx.x;
+    ResBlock b;
+    b.A = lds;
+    b.Ht = b.A + a.group_rows * PITCH;
+    b.C = reinterpret_cast<float *>(b.Ht + (NEAR ? a.cap : a.group_rows) * PITCH);
+    b.Fs = b.C;
+    place_view(a, b, reinterpret_cast<char *>(b.C + (NEAR ? a.cap : a.group_rows) * a.Hz));
+    b.F = lds + a.lds_bytes - (size_t)a.f_lds * a.n_ut * 1024;
+    b.f_lds = a.f_lds;
+    b.n_sets = kResWaves<T, NS> / a.n_ut;
+    b.set = b.wave / a.n_ut;
+    b.ut = b.wave - b.set * a.n_ut;
+    {
+        const int per = PH + a.Hz / 4;
+        b.piece_rows = NT / per;
+        b.piece_row = t / per;
+        b.piece = t - b.piece_row * per;
+        if (b.piece_row >= b.piece_rows) b.piece_row = 1 << 20;
+    }
+    if (b.set >= b.n_sets) b.set = 1 << 20;               // a wave without a tile: no row is ever its own
+
+    ResWeights<T, NS> w;
+    {   // slabs past the packed h part meet zeros, but 0 times an infinite weight would be NaN
+        const char *wp = tree_weights(a, b.lane, b.ut, a.sx_packed, 0);
+        u32x4 wf[kResForget<T, NS> ? 1 : NS];
+        if constexpr (!kResForget<T, NS>) {
+#pragma unroll
+            for (int s = 0; s < NS; ++s)
+                if (s < a.f_lds) wf[s] = *reinterpret_cast<const u32x4 *>(wp + (int64_t)s * a.NPU * 64 + 3 * 2048);
+        }
+#pragma unroll
+        for (int s = 0; s < NS; ++s)
+#pragma unroll
+            for (int g = 0; g < (kResForget<T, NS> ? 4 : 3); ++g) {
+                u32x4 v = {0, 0, 0, 0};
+                if (s < a.sh) v = *reinterpret_cast<const u32x4 *>(wp + (int64_t)s * a.NPU * 64 + g * 2048);
+                if (g < 3) w.iou[s][g] = v;
+                else w.f[kResForget<T, NS> ? s : 0][0] = v;
+            }
+        if constexpr (!kResForget<T, NS>) {
+#pragma unroll
+            for (int s = 0; s < NS; ++s)
+                if (s < a.f_lds) *reinterpret_cast<u32x4 *>(b.F + ((b.ut * a.f_lds + s) * 64 + b.lane) * 16) = wf[s];
+        }
+    }
+    if (!view_trees(a, lds, b, m)) return;
+    int n_lvl = 0;                                        // levels of this block that run here: [0, n_lvl)
+    lds_barrier();
+    while (n_lvl < a.l_end && m.cnt[n_lvl] > 0) ++n_lvl;
+    if (n_lvl < 2) return;
+
+    const ResPre<1> none = {};
+    const int n_leaf = m.cnt[0];
+    ResPre<1> zf;
+    // ---- the leaves, whose cells are done: their f c
+    if constexpr (NEAR) {
+        res_load_zf<T>(a, b, b.set * STEP, n_leaf, zf);
+        const int per = PH + a.Hz / 4;
+        for (int q = t; q < b.own * per; q += NT) {       // rows of h and c (other nodes: zero pads) side by side
+            const int r = q / per, k = q - r * per, i = b.order[r];
+            if (k < PH) {
+                if (r < n_leaf) *reinterpret_cast<u32x4 *>(b.Ht + i * PITCH + k * 16) = res_h_piece<T>(a, b, i, k);
+                else if (k * Traits<T>::VEC >= a.Hz) *reinterpret_cast<u32x4 *>(b.Ht + i * PITCH + k * 16) = u32x4{0, 0, 0, 0};
+            } else if (r < n_leaf) {
+                const int u = (k - PH) * 4;
+                const float *c = a.c_out + (int64_t)(b.lo + i) * a.H;
+                float4 o;
+                o.x = u < a.H ? c[u] : 0.0f; o.y = u + 1 < a.H ? c[u + 1] : 0.0f;
+                o.z = u + 2 < a.H ? c[u + 2] : 0.0f; o.w = u + 3 < a.H ? c[u + 3] : 0.0f;
+                *reinterpret_cast<float4 *>(b.C + i * a.Hz + u) = o;
+            }
+        }
+        lds_barrier();
+        for (int row = b.set * STEP; row < n_leaf; row += b.n_sets * STEP) {
+            ResPre<1> cur = zf;
+            res_load_zf<T>(a, b, row + b.n_sets * STEP, n_leaf, zf);
+            if (res_quad<T>(row, n_leaf)) res_forget<T, SAVE, NS, true, true, false>(a, b, w, cur, none, b.Ht, row, 0, n_leaf);
+            else res_forget<T, SAVE, NS, true, sizeof(T) == 4, false>(a, b, w, cur, none, b.Ht, row, 0, n_leaf);
+        }
+    } else {
+        // group_rows of them at a time through LDS (Ht and A in turn), the next ones' rows on their way meanwhile
+        constexpr int MOST = (kResGroup * PH + NT - 1) / NT;
+        u32x4 ahead[MOST];
+        auto request = [&](int r0) __attribute__((always_inline)) {
+#pragma unroll
+            for (int e = 0; e < MOST; ++e) {
+                const int q = t + e * NT, r = r0 + q / PH;
+                if (q < a.group_rows * PH && r < n_leaf) ahead[e] = res_h_piece<T>(a, b, b.order[r], q % PH);
+            }
+        };
+        auto load_c = [&](int row, int r_end, ResPre<1> &p) __attribute__((always_inline)) {
+            if (row >= r_end) return;
+            const int lane = fresh_lane(b.lane), unit = b.ut * 16 + (lane & 15);
+            const bool quad = res_quad<T>(row, r_end);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                if (v > 0 && quad) break;
+                p.z[0][v] = a.c_out[(int64_t)(b.lo + b.order[res_row(quad, row, r_end, lane >> 4, v)]) * a.H + (unit < a.H ? unit : 0)];
+            }
+        };
+        // this wave's tiles, one group after the other; what a tile adds is requested two tiles ahead
+        auto group_end = [&](int row) __attribute__((always_inline)) {
+            const int e = row / a.group_rows * a.group_rows + a.group_rows;
+            return e < n_leaf ? e : n_leaf;
+        };
+        auto tile_after = [&](int row) __attribute__((always_inline)) {
+            const int e = group_end(row), next = row + b.n_sets * STEP;
+            return row >= n_leaf ? n_leaf : next < e ? next : e + b.set * STEP;
+        };
+        auto load_tile = [&](int row, ResPre<1> &zp, ResPre<1> &cp) __attribute__((always_inline)) {
+            if (row >= n_leaf) return;
+            res_load_zf<T>(a, b, row, group_end(row), zp);
+            load_c(row, group_end(row), cp);
+        };
+        request(0);
+        char *buf = b.Ht;
+        ResPre<1> zf1, cm, cm1;
+        int row = b.set * STEP < a.group_rows ? b.set * STEP : n_leaf, row1 = tile_after(row);
+        load_tile(row, zf, cm);
+        load_tile(row1, zf1, cm1);
+        for (int r0 = 0; r0 < n_leaf; r0 += a.group_rows) {
+            const int r_end = r0 + a.group_rows < n_leaf ? r0 + a.group_rows : n_leaf;
+#pragma unroll
+            for (int e = 0; e < MOST; ++e) {
+                const int q = t + e * NT;
+                if (q < a.group_rows * PH) *reinterpret_cast<u32x4 *>(buf + (q / PH) * PITCH + (q % PH) * 16) = ahead[e];
+            }
+            request(r0 + a.group_rows);
+            lds_barrier();
+            while (row < r_end) {
+                const int at = row;
+                const ResPre<1> cur = zf, cc = cm;
+                zf = zf1; cm = cm1;
+                row = row1;
+                row1 = tile_after(row);
+                load_tile(row1, zf1, cm1);
+                if (res_quad<T>(at, r_end)) res_forget<T, SAVE, NS, false, true, true>(a, b, w, cur, cc, buf, at, r0, r_end);
+                else res_forget<T, SAVE, NS, false, sizeof(T) == 4, true>(a, b, w, cur, cc, buf, at, r0, r_end);
+            }
+            buf = buf == b.Ht ? b.A : b.Ht;
+        }
+        lds_barrier();
+        for (int i = t * 16; i < a.group_rows * PITCH; i += NT * 16)      // pad columns of the h rows stay zero
+            *reinterpret_cast<u32x4 *>(b.Ht + i) = u32x4{0, 0, 0, 0};
+    }
+    ResPre<3> z;
+    res_load_z<T>(a, b, m.start[1] + b.set * STEP, m.start[1] + a.group_rows < m.start[2] ? m.start[1] + a.group_rows : m.start[2], z);
+    if constexpr (NEAR) lds_barrier();
+    else __syncthreads();
+
+    for (int l = 1; l < n_lvl; ++l) {
+        const int l1 = m.start[l + 1];
+        for (int r0 = m.start[l]; r0 < l1; r0 += a.group_rows) {
+            const int r_end = r0 + a.group_rows < l1 ? r0 + a.group_rows : l1;
+            if (r0 > m.start[l]) lds_barrier();           // the group before is done with A and C
+            if constexpr (NEAR) res_gather<T, NS>(a, b, r0, r_end);
+            else if constexpr (kResPerSimd<T, NS> == 4) gather_sums<T, 1, 8>(a, b, r0, r_end, PH);
+            else gather_sums<T, 2, 4>(a, b, r0, r_end, PH);
+            lds_barrier();
+            if (l + 1 < n_lvl) res_load_zf<T>(a, b, r0 + b.set * STEP, r_end, zf);
+            for (int row = r0 + b.set * STEP; row < r_end; row += b.n_sets * STEP) {
+                ResPre<3> cur = z;
+                res_load_z<T>(a, b, row + b.n_sets * STEP, r_end, z);
+                if (res_quad<T>(row, r_end)) res_cells<T, SAVE, NS, NEAR, true>(a, b, w.iou, cur, row, r0, r_end);
+                else res_cells<T, SAVE, NS, NEAR, sizeof(T) == 4>(a, b, w.iou, cur, row, r0, r_end);
+            }
+            {   // the next group's
+                const int e1 = r_end < l1 ? l1 : l + 1 < n_lvl ? m.start[l + 2] : r_end;
+                res_load_z<T>(a, b, r_end + b.set * STEP, r_end + a.group_rows < e1 ? r_end + a.group_rows : e1, z);
+            }
+            if (l + 1 >= n_lvl) continue;
+            lds_barrier();
+            for (int row = r0 + b.set * STEP; row < r_end; row += b.n_sets * STEP) {
+                ResPre<1> cur = zf;
+                res_load_zf<T>(a, b, row + b.n_sets * STEP, r_end, zf);
+                if (res_quad<T>(row, r_end)) res_forget<T, SAVE, NS, NEAR, true, false>(a, b, w, cur, none, b.Ht, row, r0, r_end);
+                else res_forget<T, SAVE, NS, NEAR, sizeof(T) == 4, false>(a, b, w, cur, none, b.Ht, row, r0, r_end);
+            }
+        }
+        if constexpr (NEAR) lds_barrier();                // the next level's sums read what this one left
+        else __syncthreads();
     }
 }
 
@@ -651,6 +1105,15 @@ double trees_excess_us(const TreesArgs &a, size_t esz, const TreesShape &s) {
     return us;
 }
 
+// Weight slabs of the resident form's instances (0 waves: not for this type).
+constexpr int kResSlabs[] = {2, 4, 5, 6, 8, 10};
+static int resident_waves(int ns, size_t esz) {
+    if (esz == 2) return ns == 2 || ns == 4 ? 8 : ns == 5 || ns == 6 ? 12 : 0;
+    return ns == 4 || ns == 8 ? 8 : ns == 10 ? 12 : 0;
+}
+static bool resident_forget(int ns, size_t esz) { return esz == 4 ? ns <= 8 : ns <= 5; }
+static bool resident_shares_cu(int ns, size_t esz) { return ns * (int)esz * 4 <= (esz == 4 ? 64 : 16); }
+
 // Fills the launch geometry of `a`; false if the forest is better run level by level.
 bool plan_trees(TreesArgs &a, size_t esz, const TreesShape &s) {
     if (a.n > trees_max_nodes(a.D, a.H, esz)) return false;
@@ -658,23 +1121,65 @@ bool plan_trees(TreesArgs &a, size_t esz, const TreesShape &s) {
     a.sh = (int)ceil_div((int64_t)a.H * (int64_t)esz, 64);
     a.Hz = (int)round_up(a.H, 16);
     a.n_ut = a.Hz / 16;
-    a.pitch_h = a.sh * 64 + 16;
-    const int passes = (int)ceil_div(a.n_ut, kTreeMaxWaves);
-    a.n_waves = (int)round_up(ceil_div(a.n_ut, passes), 4);  // whole rounds of the four SIMDs, so that blocks share them evenly
-    if (a.n_waves < 8) a.n_waves = 8;                       // for the gathers
-    const size_t row_bytes = (size_t)2 * a.pitch_h + 4 * a.Hz;
-    a.group_rows = kTreeRows * row_bytes <= (size_t)kTreeLdsMax * 9 / 10 ? kTreeRows : kTreeRows / 2;
-    const size_t tiles = a.group_rows * row_bytes, cuts = (size_t)2 * (2 * a.tree_window + 2) * 4;
-    // one block per compute unit up to kTreeNodesPerBlock nodes each, then as many as registers and LDS let it hold (two blocks
-    // hide each other's latencies, but a small forest's blocks should not share a compute unit while others idle)
-    int per_cu = (int)ceil_div(a.n, (int64_t)kTreeCus * kTreeNodesPerBlock);
-    if (per_cu > kTreeMaxWaves / a.n_waves) per_cu = kTreeMaxWaves / a.n_waves;
-    for (;; --per_cu) {
-        a.G = (int)ceil_div(a.n, kTreeCus * per_cu);
-        a.cap = a.G + a.tree_window;
-        if (a.cap > a.n) a.cap = a.n;
-        a.lds_bytes = (tiles > cuts ? tiles : cuts) + (size_t)(4 * a.cap + 8) * 2;
-        if (per_cu == 1 || (a.lds_bytes + kTreeLdsStatic) * per_cu <= (size_t)kTreeLdsMax) break;
+    const size_t cuts = (size_t)2 * (2 * a.tree_window + 2) * 4;
+    a.res_slabs = 0;
+    for (int ns : kResSlabs)
+        if (a.res_slabs == 0 && ns >= a.sh && resident_waves(ns, esz) > 0) a.res_slabs = ns;
+    if (a.res_slabs > 0) {
+        a.n_waves = resident_waves(a.res_slabs, esz);
+        a.pitch_h = a.res_slabs * 64 + 16;
+        const int most = resident_shares_cu(a.res_slabs, esz) ? 2 : 1;      // blocks of a compute unit
+        const size_t row = (size_t)a.pitch_h + 4 * a.Hz;
+        a.group_rows = kTreeRows;
+        a.near_rows = 0;
+        for (int per_cu = 1; per_cu <= most && !a.near_rows; ++per_cu) {
+            a.G = (int)ceil_div(a.n, kTreeCus * per_cu);
+            a.cap = a.G + a.tree_window < a.n ? a.G + a.tree_window : a.n;
+            const size_t tiles = (size_t)a.group_rows * a.pitch_h + a.cap * row;
+            a.lds_bytes = (tiles > cuts ? tiles : cuts) + (size_t)(4 * a.cap + 8) * 2;
+            a.near_rows = (a.lds_bytes + kTreeLdsStatic) * per_cu <= (size_t)kTreeLdsMax;
+        }
+        if (!a.near_rows && a.res_slabs == 10) a.res_slabs = 0;       // (fp32 wider than 128 has no other form)
+        for (int rows = kResGroup; !a.near_rows && a.res_slabs > 0; rows /= 2) {
+            a.group_rows = rows;
+            int per_cu = (int)ceil_div(a.n, (int64_t)kTreeCus * kTreeNodesPerBlock);
+            if (per_cu > most) per_cu = most;
+            for (;; --per_cu) {
+                a.G = (int)ceil_div(a.n, kTreeCus * per_cu);
+                a.cap = a.G + a.tree_window < a.n ? a.G + a.tree_window : a.n;
+                const size_t tiles = (size_t)rows * (a.pitch_h + row);
+                a.lds_bytes = (tiles > cuts ? tiles : cuts) + (size_t)(4 * a.cap + 8) * 2;
+                if (per_cu == 1 || (a.lds_bytes + kTreeLdsStatic) * per_cu <= (size_t)kTreeLdsMax) break;
+            }
+            if (a.lds_bytes + kTreeLdsStatic <= (size_t)kTreeLdsMax || rows <= 16) break;
+        }
+    }
+    a.f_lds = 0;
+    if (a.res_slabs > 0 && !resident_forget(a.res_slabs, esz)) {      // what LDS has left holds f's weights
+        const int64_t left = (int64_t)kTreeLdsMax - kTreeLdsStatic - 16 - (int64_t)a.lds_bytes;
+        a.f_lds = left > 0 ? (int)(left / (a.n_ut * 1024)) : 0;
+        if (a.f_lds > a.sh) a.f_lds = a.sh;
+        a.lds_bytes = (size_t)round_up((int64_t)a.lds_bytes, 16) + (size_t)a.f_lds * a.n_ut * 1024;
+    }
+    if (a.res_slabs == 0) {
+        a.pitch_h = a.sh * 64 + 16;
+        const int passes = (int)ceil_div(a.n_ut, kTreeMaxWaves);
+        a.n_waves = (int)round_up(ceil_div(a.n_ut, passes), 4);  // whole rounds of the four SIMDs, so that blocks share them evenly
+        if (a.n_waves < 8) a.n_waves = 8;                       // for the gathers
+        const size_t row_bytes = (size_t)2 * a.pitch_h + 4 * a.Hz;
+        a.group_rows = kTreeRows * row_bytes <= (size_t)kTreeLdsMax * 9 / 10 ? kTreeRows : kTreeRows / 2;
+        const size_t tiles = a.group_rows * row_bytes;
+        // one block per compute unit up to kTreeNodesPerBlock nodes each, then as many as registers and LDS let it hold (two blocks
+        // hide each other's latencies, but a small forest's blocks should not share a compute unit while others idle)
+        int per_cu = (int)ceil_div(a.n, (int64_t)kTreeCus * kTreeNodesPerBlock);
+        if (per_cu > kTreeMaxWaves / a.n_waves) per_cu = kTreeMaxWaves / a.n_waves;
+        for (;; --per_cu) {
+            a.G = (int)ceil_div(a.n, kTreeCus * per_cu);
+            a.cap = a.G + a.tree_window;
+            if (a.cap > a.n) a.cap = a.n;
+            a.lds_bytes = (tiles > cuts ? tiles : cuts) + (size_t)(4 * a.cap + 8) * 2;
+            if (per_cu == 1 || (a.lds_bytes + kTreeLdsStatic) * per_cu <= (size_t)kTreeLdsMax) break;
+        }
     }
     if (a.lds_bytes > (size_t)kTreeLdsMax || a.cap >= kNoLocal) return false;
     a.n_blocks = (int)ceil_div(a.n, a.G);
@@ -697,6 +1202,17 @@ int launch_tree_x(const TreesArgs &a, hipStream_t st) {
     JITDB_LAUNCH_CHECK();
     return JITDB_OK;
 }
+template <typename T, bool SAVE, int NS>
+int launch_resident(const TreesArgs &a, hipStream_t st) {
+    auto fn = &trees_resident_kernel<T, SAVE, NS, true>;
+    if constexpr (!kResNearOnly<T, NS>)
+        if (!a.near_rows) fn = &trees_resident_kernel<T, SAVE, NS, false>;
+    if (a.lds_bytes > 64 * 1024)
+        JITDB_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void *>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, kTreeLdsMax));
+    fn<<<a.n_blocks, kResWaves<T, NS> * 64, a.lds_bytes, st>>>(a);
+    JITDB_LAUNCH_CHECK();
+    return JITDB_OK;
+}
 template <typename T, bool SAVE>
 int launch_trees_t(const TreesArgs &a, hipStream_t st) {
     int rc = JITDB_E_BADARG;
@@ -708,6 +1224,14 @@ int launch_trees_t(const TreesArgs &a, hipStream_t st) {
         case 20: rc = launch_tree_x<T, SAVE, 20>(a, st); break;
     }
     if (rc != JITDB_OK || a.l_end < 2) return rc;
+    switch (a.res_slabs) {
+        case 2: if constexpr (sizeof(T) == 2) return launch_resident<T, SAVE, 2>(a, st); break;
+        case 4: return launch_resident<T, SAVE, 4>(a, st);
+        case 5: if constexpr (sizeof(T) == 2) return launch_resident<T, SAVE, 5>(a, st); break;
+        case 6: if constexpr (sizeof(T) == 2) return launch_resident<T, SAVE, 6>(a, st); break;
+        case 8: if constexpr (sizeof(T) == 4) return launch_resident<T, SAVE, 8>(a, st); break;
+        case 10: if constexpr (sizeof(T) == 4) return launch_resident<T, SAVE, 10>(a, st); break;
+    }
     if (a.lds_bytes > 64 * 1024)
         JITDB_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void *>(&trees_kernel<T, SAVE>), hipFuncAttributeMaxDynamicSharedMemorySize, kTreeLdsMax));
     trees_kernel<T, SAVE><<<a.n_blocks, a.n_waves * 64, a.lds_bytes, st>>>(a);

@@ -37,6 +37,8 @@ FORESTS = {
     # 32 levels, two trees wide; sequences of up to 12 nodes leave chain levels on top
     "deep": lambda: _lay_out([chain_forest(31), star_forest(4)] * 5 + [_lay_out([perfect_kary_tree(2, 2)])]),
     "many": lambda: _lay_out([make_forest(1)] * 700),
+    # blocks of many nodes (h and f c go through memory from H of about 50 on), every remainder of a group of 64 rows
+    "far": lambda: _lay_out([make_forest(1)] * 600 + [_broom(k) for k in (4, 5, 15, 16, 17, 36, 64, 65, 68, 120)]),
 }
 
 
@@ -81,6 +83,33 @@ def test_every_width_of_the_x_part(c_oracle, dtype, D, save):
         dt = torch.float32 if dtype == "f32" else torch.bfloat16
         dev = [torch.from_numpy(v).cuda().to(dt) for v in seen[:3]] + [torch.from_numpy(b).cuda()]
         h2, c2, _, _ = J.jitdb_treelstm_forward_train(*dev, s)
+        h, c = h2.float().cpu().numpy(), c2.cpu().numpy()
+    ho, co, _ = c_oracle(p, *seen)
+    assert np.abs(h - ho).max() <= TOL[dtype]
+    assert np.abs(c - co).max() <= TOL[dtype] * max(1.0, np.abs(co).max() / (8.0 if dtype == "bf16" else 50.0))
+
+
+@pytest.mark.parametrize("save", [False, True])
+@pytest.mark.parametrize("forest", ["row-groups", "far"])
+@pytest.mark.parametrize("dtype,H", [("f32", H) for H in (16, 17, 64, 65, 127, 128, 129, 160, 161)] +
+                         [("bf16", H) for H in (16, 50, 64, 65, 128, 129, 160, 161, 192, 193)])
+def test_every_width_of_the_recurrent_part(c_oracle, dtype, H, forest, save):
+    """Each instance that keeps the recurrent weights in registers at both ends of its widths, child sums through LDS and
+    through memory; the bounds are the forward's."""
+    import torch
+    import paper_1904_07421_amd as J
+    p, D = FORESTS[forest](), 24
+    x, W, U, b = make_values(1, p.shape[0], "random", D=D, H=H)
+    print(f"recurrent part {dtype} H={H} {forest} save={save} N={p.shape[0]}", flush=True)
+    s, h, c, seen = run_gpu_forward(p, x, W, U, b, dtype)
+    assert 0 < s.struct.tree_window <= 256
+    if save:
+        dt = torch.float32 if dtype == "f32" else torch.bfloat16
+        dev = [torch.from_numpy(v).cuda().to(dt) for v in seen[:3]] + [torch.from_numpy(b).cuda()]
+        h2, c2, gates, fgate = J.jitdb_treelstm_forward_train(*dev, s)
+        assert torch.isfinite(gates.float()).all()
+        has = torch.from_numpy(p >= 0).cuda()
+        assert ((fgate.float()[has] >= 0) & (fgate.float()[has] <= 1)).all()
         h, c = h2.float().cpu().numpy(), c2.cpu().numpy()
     ho, co, _ = c_oracle(p, *seen)
     assert np.abs(h - ho).max() <= TOL[dtype]
