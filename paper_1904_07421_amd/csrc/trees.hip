@@ -657,7 +657,8 @@ trees_kernel(const TreesArgs a) {
 // trees_kernel reads U from L2 once per level, and at 50 KB a microsecond and compute unit (measured: clock stamps) that is most of
 // a level.  Where the four gates' weights of 16 units fit the registers of one wave, a wave loads them once, while the block works
 // out its trees, and keeps them over all levels; bf16 wider than 160 and fp32 wider than 128 have room for i, o and u, and
-// for f's first slabs in what LDS has left.
+// for f's first slabs in what LDS has left.  bf16 wider than 192 takes eight waves of two unit tiles each: 16 waves would
+// have 32 registers beside the weights, eight have 64 (groups of 32 rows then, so that LDS holds most of f's weights).
 // Schedule + forward, from L2 -> so: 71 nodes H 150 fp32 99 -> 89 us, 4.7 k nodes H 150 fp32 156 -> 141, 21 k nodes H 99 bf16
 // 150 -> 125, 54 k nodes H 180 bf16 314 -> 258, 106 k nodes H 150 bf16 368 -> 316, 216 k nodes H 64 fp32 372 -> 367.  What bounds it:
 // the 4x4 MFMAs of three waves on a SIMD and the barriers (few rows), memory traffic of Z, h and f c (many rows).
@@ -666,18 +667,20 @@ trees_kernel(const TreesArgs a) {
 // Waves: unit tile wave % n_ut, rows in tiles of 16 (bf16) or 4 (fp32, whose 4x4 MFMAs have the rate of the 16x16 ones),
 // dealt to the n_waves / n_ut sets of waves.
 template <typename T, int NS> constexpr int kResTiles = NS * 4 / (int)sizeof(T);       // most unit tiles
-template <typename T, int NS> constexpr int kResWaves = kResTiles<T, NS> <= 8 ? 8 : 12;
+template <typename T, int NS> constexpr int kResPerWave = kResTiles<T, NS> <= 12 ? 1 : 2;      // unit tiles of a wave
+template <typename T, int NS> constexpr int kResWaves = kResTiles<T, NS> / kResPerWave<T, NS> <= 8 ? 8 : 12;
 template <typename T, int NS> constexpr bool kResForget = NS * 16 <= (kResTiles<T, NS> <= 8 ? 128 : 80);   // f's weights in registers, too
-template <typename T, int NS> constexpr int kResWeights = NS * (kResForget<T, NS> ? 16 : 12);   // registers
+template <typename T, int NS> constexpr int kResWeights = kResPerWave<T, NS> * NS * (kResForget<T, NS> ? 16 : 12);   // registers
 template <typename T, int NS> constexpr int kResPerSimd = kResWaves<T, NS> == 12 ? 3 : kResWeights<T, NS> <= (sizeof(T) == 4 ? 64 : 32) ? 4 : 2;
 template <typename T> constexpr int kResRows = sizeof(T) == 4 ? 4 : 16;                 // rows of a tile
-constexpr int kResGroup = 64;                      // most rows of a group (not NEAR)
+template <typename T, int NS> constexpr int kResGroup = kResPerWave<T, NS> == 1 ? 64 : 32;      // most rows of a group (not NEAR)
 constexpr int kResAhead = 2;                       // slabs of f's weights on their way from L2, of those that LDS does not hold
 template <typename T, int NS> constexpr bool kResNearOnly = kResForget<T, NS> == false && sizeof(T) == 4;
+template <typename T, int NS> constexpr bool kResFarOnly = kResPerWave<T, NS> > 1;
 
 template <typename T, int NS>
 struct ResWeights {
-    u32x4 iou[NS][3];
+    u32x4 iou[kResPerWave<T, NS>][NS][3];
     u32x4 f[kResForget<T, NS> ? NS : 1][1];
 };
 // What one lane adds to a tile's products: four rows (16-row tiles: row hf * 4 + v) or one (4-row tiles: row hf).
@@ -685,7 +688,8 @@ template <int NG> struct ResPre { float z[NG][4]; };
 
 struct ResBlock : TreeBlock {
     float *C;                 // LDS [slot][Hz]: sum of the children's f c, then c, then (NEAR) f c
-    int ut, set, n_sets;
+    int ut, set, n_sets;      // the wave's unit tiles: ut, ut + n_waves, ... (n_tiles of them)
+    int n_tiles;
     int piece, piece_row, piece_rows;      // res_gather: this thread's 16-byte piece, first row and rows a step
     char *F; int f_lds;       // LDS: the first f_lds slabs of f's weights, a wave's tile after the other, in lane order
 };
@@ -699,9 +703,9 @@ __device__ __forceinline__ int res_row(bool quad, int row, int r_end, int hf, in
     return r < r_end ? r : r_end - 1;
 }
 template <typename T>
-__device__ __forceinline__ void res_load_z(const TreesArgs &a, const ResBlock &b, int row, int r_end, ResPre<3> &p) {
+__device__ __forceinline__ void res_load_z(const TreesArgs &a, const ResBlock &b, int ut, int row, int r_end, ResPre<3> &p) {
     if (row >= r_end) return;
-    const int lane = fresh_lane(b.lane), unit = b.ut * 16 + (lane & 15);
+    const int lane = fresh_lane(b.lane), unit = ut * 16 + (lane & 15);
     const bool quad = res_quad<T>(row, r_end);
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
@@ -712,9 +716,9 @@ __device__ __forceinline__ void res_load_z(const TreesArgs &a, const ResBlock &b
     }
 }
 template <typename T>
-__device__ __forceinline__ void res_load_zf(const TreesArgs &a, const ResBlock &b, int row, int r_end, ResPre<1> &p) {
+__device__ __forceinline__ void res_load_zf(const TreesArgs &a, const ResBlock &b, int ut, int row, int r_end, ResPre<1> &p) {
     if (row >= r_end) return;
-    const int lane = fresh_lane(b.lane), unit = b.ut * 16 + (lane & 15);
+    const int lane = fresh_lane(b.lane), unit = ut * 16 + (lane & 15);
     const bool quad = res_quad<T>(row, r_end);
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
@@ -724,11 +728,9 @@ __device__ __forceinline__ void res_load_zf(const TreesArgs &a, const ResBlock &
     }
 }
 
-// acc[g] = A rows x the weights w[s][g]; a_lane: this lane's bytes of slab 0 (row lane & 15 or lane & 3, piece lane >> 4) in LDS.
+// acc[g] += A rows x the weights w[s][g]; a_lane: this lane's bytes of slab 0 (row lane & 15 or lane & 3, piece lane >> 4) in LDS.
 template <typename T, int NS, int NG, bool QUAD>
 __device__ __forceinline__ void res_gemm(floatx4 (&acc)[NG], const char *a_lane, const u32x4 (&w)[NS][NG]) {
-#pragma unroll
-    for (int g = 0; g < NG; ++g) acc[g] = floatx4{0, 0, 0, 0};
     u32x4 fa[2];
     fa[0] = *reinterpret_cast<const u32x4 *>(a_lane);
 #pragma unroll
@@ -753,17 +755,23 @@ __device__ __forceinline__ void res_gemm(floatx4 (&acc)[NG], const char *a_lane,
 
 // The cells of the tile of rows from `row` on.
 template <typename T, bool SAVE, int NS, bool NEAR, bool QUAD>
-__device__ __forceinline__ void res_cells(const TreesArgs &a, const ResBlock &b, const u32x4 (&w)[NS][3], const ResPre<3> &p, int row,
-                                          int r0, int r_end) {
+__device__ __forceinline__ void res_cells(const TreesArgs &a, const ResBlock &b, int ut, const u32x4 (&w)[NS][3], const ResPre<3> &p,
+                                          int row, int r0, int r_end) {
     constexpr int PITCH = NS * 64 + 16;
-    const int lane = fresh_lane(b.lane), hf = lane >> 4, n = lane & 15, unit = b.ut * 16 + n;
+    const int lane = fresh_lane(b.lane), hf = lane >> 4, n = lane & 15, unit = ut * 16 + n;
+    constexpr bool FROM_Z = kResPerWave<T, NS> > 1 && !QUAD;       // (fewer registers)
     floatx4 acc[3];
+#pragma unroll
+    for (int g = 0; g < 3; ++g)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) acc[g][v] = FROM_Z ? p.z[g][v] : 0.0f;
     res_gemm<T, NS, 3, QUAD>(acc, b.A + (row - r0 + (QUAD ? lane & 3 : n)) * PITCH + hf * 16, w);
 #pragma unroll
     for (int v = 0; v < (QUAD ? 1 : 4); ++v) {
+        if constexpr (FROM_Z) __builtin_amdgcn_sched_barrier(0);
         float z[3];
 #pragma unroll
-        for (int g = 0; g < 3; ++g) z[g] = p.z[g][v] + (QUAD ? quarter_sum(acc[g], lane) : acc[g][v]);
+        for (int g = 0; g < 3; ++g) z[g] = FROM_Z ? acc[g][v] : p.z[g][v] + (QUAD ? quarter_sum(acc[g], lane) : acc[g][v]);
         const int r = row + (QUAD ? hf : hf * 4 + v);
         if (r >= r_end) continue;
         const int i = b.order[r], slot = NEAR ? i : r - r0;
@@ -782,18 +790,18 @@ __device__ __forceinline__ void res_cells(const TreesArgs &a, const ResBlock &b,
 
 // f c of the tile's rows from P = U_f h, f with the parent's Z_f (in p).  FAR_LEAF: c comes from memory, in cm.
 template <typename T, bool SAVE, int NS, bool NEAR, bool QUAD, bool FAR_LEAF>
-__device__ __forceinline__ void res_forget(const TreesArgs &a, const ResBlock &b, const ResWeights<T, NS> &w, const ResPre<1> &p,
+__device__ __forceinline__ void res_forget(const TreesArgs &a, const ResBlock &b, int ut, const ResWeights<T, NS> &w, const ResPre<1> &p,
                                            const ResPre<1> &cm, const char *rows, int row, int r0, int r_end) {
     constexpr int PITCH = NS * 64 + 16;
-    const int lane = fresh_lane(b.lane), hf = lane >> 4, n = lane & 15, unit = b.ut * 16 + n;
+    const int lane = fresh_lane(b.lane), hf = lane >> 4, n = lane & 15, unit = ut * 16 + n;
     const int ra = row + (QUAD ? lane & 3 : n);
     const char *a_lane = rows + (NEAR ? (int)b.order[ra < r_end ? ra : r_end - 1] : ra - r0) * PITCH + hf * 16;
-    floatx4 acc[1];
+    floatx4 acc[1] = {floatx4{0, 0, 0, 0}};
     if constexpr (kResForget<T, NS>) {
         res_gemm<T, NS, 1, QUAD>(acc, a_lane, w.f);
     } else {
         // the slabs in LDS while the others are on their way
-        const char *wp = tree_weights(a, lane, b.ut, a.sx_packed, 3), *fl = b.F + (b.ut * b.f_lds * 64 + lane) * 16;
+        const char *wp = tree_weights(a, lane, ut, a.sx_packed, 3), *fl = b.F + (ut * b.f_lds * 64 + lane) * 16;
         const int64_t slab = (int64_t)a.NPU * 64;
         const int rest = a.sh - b.f_lds;
         u32x4 ahead[kResAhead];
@@ -879,7 +887,7 @@ __device__ __forceinline__ u32x4 res_h_piece(const TreesArgs &a, const ResBlock 
 template <typename T, bool SAVE, int NS, bool NEAR>
 __global__ void __launch_bounds__((kResWaves<T, NS> * 64), (kResPerSimd<T, NS>))
 trees_resident_kernel(const TreesArgs a) {
-    constexpr int PITCH = NS * 64 + 16, STEP = kResRows<T>, NT = kResWaves<T, NS> * 64, PH = NS * 4;
+    constexpr int PITCH = NS * 64 + 16, STEP = kResRows<T>, NW = kResWaves<T, NS>, NT = NW * 64, PH = NS * 4, TW = kResPerWave<T, NS>;
     extern __shared__ __attribute__((aligned(16))) char lds[];
     __shared__ TreeMeta m;
     const int t = threadIdx.x;
@@ -891,9 +899,10 @@ trees_resident_kernel(const TreesArgs a) {
     place_view(a, b, reinterpret_cast<char *>(b.C + (NEAR ? a.cap : a.group_rows) * a.Hz));
     b.F = lds + a.lds_bytes - (size_t)a.f_lds * a.n_ut * 1024;
     b.f_lds = a.f_lds;
-    b.n_sets = kResWaves<T, NS> / a.n_ut;
-    b.set = b.wave / a.n_ut;
+    b.n_sets = TW > 1 ? 1 : NW / a.n_ut;
+    b.set = TW > 1 ? 0 : b.wave / a.n_ut;
     b.ut = b.wave - b.set * a.n_ut;
+    b.n_tiles = TW > 1 && b.ut + NW < a.n_ut ? 2 : 1;
     {
         const int per = PH + a.Hz / 4;
         b.piece_rows = NT / per;
@@ -904,8 +913,11 @@ trees_resident_kernel(const TreesArgs a) {
     if (b.set >= b.n_sets) b.set = 1 << 20;               // a wave without a tile: no row is ever its own
 
     ResWeights<T, NS> w;
-    {   // slabs past the packed h part meet zeros, but 0 times an infinite weight would be NaN
-        const char *wp = tree_weights(a, b.lane, b.ut, a.sx_packed, 0);
+#pragma unroll
+    for (int j = 0; j < TW; ++j) {   // slabs past the packed h part meet zeros, but 0 times an infinite weight would be NaN
+        if (j >= b.n_tiles) break;
+        const int ut = b.ut + j * NW;
+        const char *wp = tree_weights(a, b.lane, ut, a.sx_packed, 0);
         u32x4 wf[kResForget<T, NS> ? 1 : NS];
         if constexpr (!kResForget<T, NS>) {
 #pragma unroll
@@ -918,13 +930,13 @@ trees_resident_kernel(const TreesArgs a) {
             for (int g = 0; g < (kResForget<T, NS> ? 4 : 3); ++g) {
                 u32x4 v = {0, 0, 0, 0};
                 if (s < a.sh) v = *reinterpret_cast<const u32x4 *>(wp + (int64_t)s * a.NPU * 64 + g * 2048);
-                if (g < 3) w.iou[s][g] = v;
+                if (g < 3) w.iou[j][s][g] = v;
                 else w.f[kResForget<T, NS> ? s : 0][0] = v;
             }
         if constexpr (!kResForget<T, NS>) {
 #pragma unroll
             for (int s = 0; s < NS; ++s)
-                if (s < a.f_lds) *reinterpret_cast<u32x4 *>(b.F + ((b.ut * a.f_lds + s) * 64 + b.lane) * 16) = wf[s];
+                if (s < a.f_lds) *reinterpret_cast<u32x4 *>(b.F + ((ut * a.f_lds + s) * 64 + b.lane) * 16) = wf[s];
         }
     }
     if (!view_trees(a, lds, b, m)) return;
@@ -936,9 +948,24 @@ trees_resident_kernel(const TreesArgs a) {
     const ResPre<1> none = {};
     const int n_leaf = m.cnt[0];
     ResPre<1> zf;
+    // a wave's tiles of rows and units: at % TW counts the units', at / TW is the first row
+    auto ut_of = [&](int at) __attribute__((always_inline)) { return TW > 1 ? b.ut + (at % TW) * NW : b.ut; };
+    auto after = [&](int at) __attribute__((always_inline)) {
+        return TW > 1 && at % TW + 1 < b.n_tiles ? at + 1 : (at / TW + b.n_sets * STEP) * TW;
+    };
+    auto forget_rows = [&](int r0, int r_end) __attribute__((always_inline)) {      // (zf: the first tile's)
+        for (int at = (r0 + b.set * STEP) * TW; at / TW < r_end;) {
+            const int row = at / TW, ut = ut_of(at);
+            const ResPre<1> cur = zf;
+            at = after(at);
+            res_load_zf<T>(a, b, ut_of(at), at / TW, r_end, zf);
+            if (res_quad<T>(row, r_end)) res_forget<T, SAVE, NS, NEAR, true, false>(a, b, ut, w, cur, none, b.Ht, row, r0, r_end);
+            else res_forget<T, SAVE, NS, NEAR, sizeof(T) == 4, false>(a, b, ut, w, cur, none, b.Ht, row, r0, r_end);
+        }
+    };
     // ---- the leaves, whose cells are done: their f c
     if constexpr (NEAR) {
-        res_load_zf<T>(a, b, b.set * STEP, n_leaf, zf);
+        res_load_zf<T>(a, b, b.ut, b.set * STEP, n_leaf, zf);
         const int per = PH + a.Hz / 4;
         for (int q = t; q < b.own * per; q += NT) {       // rows of h and c (other nodes: zero pads) side by side
             const int r = q / per, k = q - r * per, i = b.order[r];
@@ -955,15 +982,10 @@ trees_resident_kernel(const TreesArgs a) {
             }
         }
         lds_barrier();
-        for (int row = b.set * STEP; row < n_leaf; row += b.n_sets * STEP) {
-            ResPre<1> cur = zf;
-            res_load_zf<T>(a, b, row + b.n_sets * STEP, n_leaf, zf);
-            if (res_quad<T>(row, n_leaf)) res_forget<T, SAVE, NS, true, true, false>(a, b, w, cur, none, b.Ht, row, 0, n_leaf);
-            else res_forget<T, SAVE, NS, true, sizeof(T) == 4, false>(a, b, w, cur, none, b.Ht, row, 0, n_leaf);
-        }
+        forget_rows(0, n_leaf);
     } else {
         // group_rows of them at a time through LDS (Ht and A in turn), the next ones' rows on their way meanwhile
-        constexpr int MOST = (kResGroup * PH + NT - 1) / NT;
+        constexpr int MOST = (kResGroup<T, NS> * PH + NT - 1) / NT;
         u32x4 ahead[MOST];
         auto request = [&](int r0) __attribute__((always_inline)) {
 #pragma unroll
@@ -972,9 +994,9 @@ trees_resident_kernel(const TreesArgs a) {
                 if (q < a.group_rows * PH && r < n_leaf) ahead[e] = res_h_piece<T>(a, b, b.order[r], q % PH);
             }
         };
-        auto load_c = [&](int row, int r_end, ResPre<1> &p) __attribute__((always_inline)) {
+        auto load_c = [&](int ut, int row, int r_end, ResPre<1> &p) __attribute__((always_inline)) {
             if (row >= r_end) return;
-            const int lane = fresh_lane(b.lane), unit = b.ut * 16 + (lane & 15);
+            const int lane = fresh_lane(b.lane), unit = ut * 16 + (lane & 15);
             const bool quad = res_quad<T>(row, r_end);
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
@@ -982,44 +1004,51 @@ trees_resident_kernel(const TreesArgs a) {
                 p.z[0][v] = a.c_out[(int64_t)(b.lo + b.order[res_row(quad, row, r_end, lane >> 4, v)]) * a.H + (unit < a.H ? unit : 0)];
             }
         };
-        // this wave's tiles, one group after the other; what a tile adds is requested two tiles ahead
+        // this wave's tiles, one group after the other; what a tile adds is requested two tiles ahead (TW > 1: one)
         auto group_end = [&](int row) __attribute__((always_inline)) {
             const int e = row / a.group_rows * a.group_rows + a.group_rows;
             return e < n_leaf ? e : n_leaf;
         };
-        auto tile_after = [&](int row) __attribute__((always_inline)) {
-            const int e = group_end(row), next = row + b.n_sets * STEP;
-            return row >= n_leaf ? n_leaf : next < e ? next : e + b.set * STEP;
+        auto leaves_after = [&](int at) __attribute__((always_inline)) {
+            if (TW > 1 && at % TW + 1 < b.n_tiles) return at + 1;
+            const int row = at / TW, e = group_end(row), next = row + b.n_sets * STEP;
+            return TW * (row >= n_leaf ? n_leaf : next < e ? next : e + b.set * STEP);
         };
-        auto load_tile = [&](int row, ResPre<1> &zp, ResPre<1> &cp) __attribute__((always_inline)) {
+        auto load_tile = [&](int at, ResPre<1> &zp, ResPre<1> &cp) __attribute__((always_inline)) {
+            const int row = at / TW;
             if (row >= n_leaf) return;
-            res_load_zf<T>(a, b, row, group_end(row), zp);
-            load_c(row, group_end(row), cp);
+            res_load_zf<T>(a, b, ut_of(at), row, group_end(row), zp);
+            load_c(ut_of(at), row, group_end(row), cp);
         };
-        request(0);
+        if (TW == 1) request(0);
         char *buf = b.Ht;
         ResPre<1> zf1, cm, cm1;
-        int row = b.set * STEP < a.group_rows ? b.set * STEP : n_leaf, row1 = tile_after(row);
-        load_tile(row, zf, cm);
-        load_tile(row1, zf1, cm1);
+        int at0 = TW * (b.set * STEP < a.group_rows ? b.set * STEP : n_leaf), at1 = leaves_after(at0);
+        load_tile(at0, zf, cm);
+        if (TW == 1) load_tile(at1, zf1, cm1);
         for (int r0 = 0; r0 < n_leaf; r0 += a.group_rows) {
             const int r_end = r0 + a.group_rows < n_leaf ? r0 + a.group_rows : n_leaf;
+            if (TW > 1) request(r0);             // (no registers for the next group's rows)
 #pragma unroll
             for (int e = 0; e < MOST; ++e) {
                 const int q = t + e * NT;
                 if (q < a.group_rows * PH) *reinterpret_cast<u32x4 *>(buf + (q / PH) * PITCH + (q % PH) * 16) = ahead[e];
             }
-            request(r0 + a.group_rows);
+            if (TW == 1) request(r0 + a.group_rows);
             lds_barrier();
-            while (row < r_end) {
-                const int at = row;
+            while (at0 / TW < r_end) {
+                const int row = at0 / TW, ut = ut_of(at0);
                 const ResPre<1> cur = zf, cc = cm;
-                zf = zf1; cm = cm1;
-                row = row1;
-                row1 = tile_after(row);
-                load_tile(row1, zf1, cm1);
-                if (res_quad<T>(at, r_end)) res_forget<T, SAVE, NS, false, true, true>(a, b, w, cur, cc, buf, at, r0, r_end);
-                else res_forget<T, SAVE, NS, false, sizeof(T) == 4, true>(a, b, w, cur, cc, buf, at, r0, r_end);
+                at0 = at1;
+                at1 = leaves_after(at0);
+                if constexpr (TW == 1) {
+                    zf = zf1; cm = cm1;
+                    load_tile(at1, zf1, cm1);
+                } else {
+                    load_tile(at0, zf, cm);
+                }
+                if (res_quad<T>(row, r_end)) res_forget<T, SAVE, NS, false, true, true>(a, b, ut, w, cur, cc, buf, row, r0, r_end);
+                else res_forget<T, SAVE, NS, false, sizeof(T) == 4, true>(a, b, ut, w, cur, cc, buf, row, r0, r_end);
             }
             buf = buf == b.Ht ? b.A : b.Ht;
         }
@@ -1028,7 +1057,7 @@ trees_resident_kernel(const TreesArgs a) {
             *reinterpret_cast<u32x4 *>(b.Ht + i) = u32x4{0, 0, 0, 0};
     }
     ResPre<3> z;
-    res_load_z<T>(a, b, m.start[1] + b.set * STEP, m.start[1] + a.group_rows < m.start[2] ? m.start[1] + a.group_rows : m.start[2], z);
+    res_load_z<T>(a, b, b.ut, m.start[1] + b.set * STEP, m.start[1] + a.group_rows < m.start[2] ? m.start[1] + a.group_rows : m.start[2], z);
     if constexpr (NEAR) lds_barrier();
     else __syncthreads();
 
@@ -1039,27 +1068,29 @@ trees_resident_kernel(const TreesArgs a) {
             if (r0 > m.start[l]) lds_barrier();           // the group before is done with A and C
             if constexpr (NEAR) res_gather<T, NS>(a, b, r0, r_end);
             else if constexpr (kResPerSimd<T, NS> == 4) gather_sums<T, 1, 8>(a, b, r0, r_end, PH);
+            else if constexpr (TW > 1) gather_sums<T, 2, 2>(a, b, r0, r_end, PH);
             else gather_sums<T, 2, 4>(a, b, r0, r_end, PH);
             lds_barrier();
-            if (l + 1 < n_lvl) res_load_zf<T>(a, b, r0 + b.set * STEP, r_end, zf);
+            if (TW == 1 && l + 1 < n_lvl) res_load_zf<T>(a, b, b.ut, r0 + b.set * STEP, r_end, zf);
             for (int row = r0 + b.set * STEP; row < r_end; row += b.n_sets * STEP) {
-                ResPre<3> cur = z;
-                res_load_z<T>(a, b, row + b.n_sets * STEP, r_end, z);
-                if (res_quad<T>(row, r_end)) res_cells<T, SAVE, NS, NEAR, true>(a, b, w.iou, cur, row, r0, r_end);
-                else res_cells<T, SAVE, NS, NEAR, sizeof(T) == 4>(a, b, w.iou, cur, row, r0, r_end);
+#pragma unroll
+                for (int j = 0; j < TW; ++j) {
+                    if (j >= b.n_tiles) break;
+                    const ResPre<3> cur = z;
+                    if (j + 1 < b.n_tiles) res_load_z<T>(a, b, b.ut + (j + 1) * NW, row, r_end, z);
+                    else res_load_z<T>(a, b, b.ut, row + b.n_sets * STEP, r_end, z);
+                    if (res_quad<T>(row, r_end)) res_cells<T, SAVE, NS, NEAR, true>(a, b, b.ut + j * NW, w.iou[j], cur, row, r0, r_end);
+                    else res_cells<T, SAVE, NS, NEAR, sizeof(T) == 4>(a, b, b.ut + j * NW, w.iou[j], cur, row, r0, r_end);
+                }
             }
+            if (TW > 1 && l + 1 < n_lvl) res_load_zf<T>(a, b, b.ut, r0, r_end, zf);      // (no registers for it before)
             {   // the next group's
                 const int e1 = r_end < l1 ? l1 : l + 1 < n_lvl ? m.start[l + 2] : r_end;
-                res_load_z<T>(a, b, r_end + b.set * STEP, r_end + a.group_rows < e1 ? r_end + a.group_rows : e1, z);
+                res_load_z<T>(a, b, b.ut, r_end + b.set * STEP, r_end + a.group_rows < e1 ? r_end + a.group_rows : e1, z);
             }
             if (l + 1 >= n_lvl) continue;
             lds_barrier();
-            for (int row = r0 + b.set * STEP; row < r_end; row += b.n_sets * STEP) {
-                ResPre<1> cur = zf;
-                res_load_zf<T>(a, b, row + b.n_sets * STEP, r_end, zf);
-                if (res_quad<T>(row, r_end)) res_forget<T, SAVE, NS, NEAR, true, false>(a, b, w, cur, none, b.Ht, row, r0, r_end);
-                else res_forget<T, SAVE, NS, NEAR, sizeof(T) == 4, false>(a, b, w, cur, none, b.Ht, row, r0, r_end);
-            }
+            forget_rows(r0, r_end);
         }
         if constexpr (NEAR) lds_barrier();                // the next level's sums read what this one left
         else __syncthreads();
@@ -1108,7 +1139,7 @@ double trees_excess_us(const TreesArgs &a, size_t esz, const TreesShape &s) {
 // Weight slabs of the resident form's instances (0 waves: not for this type).
 constexpr int kResSlabs[] = {2, 4, 5, 6, 8, 10};
 static int resident_waves(int ns, size_t esz) {
-    if (esz == 2) return ns == 2 || ns == 4 ? 8 : ns == 5 || ns == 6 ? 12 : 0;
+    if (esz == 2) return ns == 2 || ns == 4 || ns == 8 ? 8 : ns == 5 || ns == 6 ? 12 : 0;
     return ns == 4 || ns == 8 ? 8 : ns == 10 ? 12 : 0;
 }
 static bool resident_forget(int ns, size_t esz) { return esz == 4 ? ns <= 8 : ns <= 5; }
@@ -1132,7 +1163,8 @@ bool plan_trees(TreesArgs &a, size_t esz, const TreesShape &s) {
         const size_t row = (size_t)a.pitch_h + 4 * a.Hz;
         a.group_rows = kTreeRows;
         a.near_rows = 0;
-        for (int per_cu = 1; per_cu <= most && !a.near_rows; ++per_cu) {
+        const bool two_tiles = esz == 2 && a.res_slabs == 8;              // (through memory only)
+        for (int per_cu = 1; per_cu <= most && !a.near_rows && !two_tiles; ++per_cu) {
             a.G = (int)ceil_div(a.n, kTreeCus * per_cu);
             a.cap = a.G + a.tree_window < a.n ? a.G + a.tree_window : a.n;
             const size_t tiles = (size_t)a.group_rows * a.pitch_h + a.cap * row;
@@ -1140,7 +1172,7 @@ bool plan_trees(TreesArgs &a, size_t esz, const TreesShape &s) {
             a.near_rows = (a.lds_bytes + kTreeLdsStatic) * per_cu <= (size_t)kTreeLdsMax;
         }
         if (!a.near_rows && a.res_slabs == 10) a.res_slabs = 0;       // (fp32 wider than 128 has no other form)
-        for (int rows = kResGroup; !a.near_rows && a.res_slabs > 0; rows /= 2) {
+        for (int rows = two_tiles ? kResGroup<bf16_t, 8> : kResGroup<bf16_t, 4>; !a.near_rows && a.res_slabs > 0; rows /= 2) {
             a.group_rows = rows;
             int per_cu = (int)ceil_div(a.n, (int64_t)kTreeCus * kTreeNodesPerBlock);
             if (per_cu > most) per_cu = most;
@@ -1204,7 +1236,7 @@ int launch_tree_x(const TreesArgs &a, hipStream_t st) {
 }
 template <typename T, bool SAVE, int NS>
 int launch_resident(const TreesArgs &a, hipStream_t st) {
-    auto fn = &trees_resident_kernel<T, SAVE, NS, true>;
+    auto fn = &trees_resident_kernel<T, SAVE, NS, !kResFarOnly<T, NS>>;
     if constexpr (!kResNearOnly<T, NS>)
         if (!a.near_rows) fn = &trees_resident_kernel<T, SAVE, NS, false>;
     if (a.lds_bytes > 64 * 1024)
@@ -1229,7 +1261,7 @@ int launch_trees_t(const TreesArgs &a, hipStream_t st) {
         case 4: return launch_resident<T, SAVE, 4>(a, st);
         case 5: if constexpr (sizeof(T) == 2) return launch_resident<T, SAVE, 5>(a, st); break;
         case 6: if constexpr (sizeof(T) == 2) return launch_resident<T, SAVE, 6>(a, st); break;
-        case 8: if constexpr (sizeof(T) == 4) return launch_resident<T, SAVE, 8>(a, st); break;
+        case 8: return launch_resident<T, SAVE, 8>(a, st);
         case 10: if constexpr (sizeof(T) == 4) return launch_resident<T, SAVE, 10>(a, st); break;
     }
     if (a.lds_bytes > 64 * 1024)

@@ -92,7 +92,7 @@ def test_every_width_of_the_x_part(c_oracle, dtype, D, save):
 @pytest.mark.parametrize("save", [False, True])
 @pytest.mark.parametrize("forest", ["row-groups", "far"])
 @pytest.mark.parametrize("dtype,H", [("f32", H) for H in (16, 17, 64, 65, 127, 128, 129, 160, 161)] +
-                         [("bf16", H) for H in (16, 50, 64, 65, 128, 129, 160, 161, 192, 193)])
+                         [("bf16", H) for H in (16, 50, 64, 65, 128, 129, 160, 161, 192, 193, 208, 209, 240, 256)])
 def test_every_width_of_the_recurrent_part(c_oracle, dtype, H, forest, save):
     """Each instance that keeps the recurrent weights in registers at both ends of its widths, child sums through LDS and
     through memory; the bounds are the forward's."""
