@@ -673,7 +673,7 @@ template <typename T, int NS> constexpr bool kResForget = NS * 16 <= (kResTiles<
 template <typename T, int NS> constexpr int kResWeights = kResPerWave<T, NS> * NS * (kResForget<T, NS> ? 16 : 12);   // registers
 template <typename T, int NS> constexpr int kResPerSimd = kResWaves<T, NS> == 12 ? 3 : kResWeights<T, NS> <= (sizeof(T) == 4 ? 64 : 32) ? 4 : 2;
 template <typename T> constexpr int kResRows = sizeof(T) == 4 ? 4 : 16;                 // rows of a tile
-template <typename T, int NS> constexpr int kResGroup = kResPerWave<T, NS> == 1 ? 64 : 32;      // most rows of a group (not NEAR)
+template <typename T, int NS> constexpr int kResGroup = kResPerWave<T, NS> == 1 ? 64 : 16;      // most rows of a group (not NEAR)
 constexpr int kResAhead = 2;                       // slabs of f's weights on their way from L2, of those that LDS does not hold
 template <typename T, int NS> constexpr bool kResNearOnly = kResForget<T, NS> == false && sizeof(T) == 4;
 template <typename T, int NS> constexpr bool kResFarOnly = kResPerWave<T, NS> > 1;
@@ -896,7 +896,11 @@ trees_resident_kernel(const TreesArgs a) {
     b.Ht = b.A + a.group_rows * PITCH;
     b.C = reinterpret_cast<float *>(b.Ht + (NEAR ? a.cap : a.group_rows) * PITCH);
     b.Fs = b.C;
-    place_view(a, b, reinterpret_cast<char *>(b.C + (NEAR ? a.cap : a.group_rows) * a.Hz));
+    {
+        char *end = reinterpret_cast<char *>(b.C + (NEAR ? a.cap : a.group_rows) * a.Hz);
+        if (TW > 1 && end < lds + 2 * TW * a.group_rows * PITCH) end = lds + 2 * TW * a.group_rows * PITCH;      // the leaves' buffers
+        place_view(a, b, end);
+    }
     b.F = lds + a.lds_bytes - (size_t)a.f_lds * a.n_ut * 1024;
     b.f_lds = a.f_lds;
     b.n_sets = TW > 1 ? 1 : NW / a.n_ut;
@@ -913,17 +917,9 @@ trees_resident_kernel(const TreesArgs a) {
     if (b.set >= b.n_sets) b.set = 1 << 20;               // a wave without a tile: no row is ever its own
 
     ResWeights<T, NS> w;
-#pragma unroll
-    for (int j = 0; j < TW; ++j) {   // slabs past the packed h part meet zeros, but 0 times an infinite weight would be NaN
-        if (j >= b.n_tiles) break;
-        const int ut = b.ut + j * NW;
-        const char *wp = tree_weights(a, b.lane, ut, a.sx_packed, 0);
-        u32x4 wf[kResForget<T, NS> ? 1 : NS];
-        if constexpr (!kResForget<T, NS>) {
-#pragma unroll
-            for (int s = 0; s < NS; ++s)
-                if (s < a.f_lds) wf[s] = *reinterpret_cast<const u32x4 *>(wp + (int64_t)s * a.NPU * 64 + 3 * 2048);
-        }
+    auto load_cells_weights = [&](int j) __attribute__((always_inline)) {
+        // slabs past the packed h part meet zeros, but 0 times an infinite weight would be NaN
+        const char *wp = tree_weights(a, b.lane, b.ut + j * NW, a.sx_packed, 0);
 #pragma unroll
         for (int s = 0; s < NS; ++s)
 #pragma unroll
@@ -933,10 +929,25 @@ trees_resident_kernel(const TreesArgs a) {
                 if (g < 3) w.iou[j][s][g] = v;
                 else w.f[kResForget<T, NS> ? s : 0][0] = v;
             }
+    };
+    {
+        u32x4 wf[TW][kResForget<T, NS> ? 1 : NS];
         if constexpr (!kResForget<T, NS>) {
 #pragma unroll
-            for (int s = 0; s < NS; ++s)
-                if (s < a.f_lds) *reinterpret_cast<u32x4 *>(b.F + ((ut * a.f_lds + s) * 64 + b.lane) * 16) = wf[s];
+            for (int j = 0; j < TW; ++j)
+#pragma unroll
+                for (int s = 0; s < NS; ++s)
+                    if (j < b.n_tiles && s < a.f_lds)
+                        wf[j][s] = *reinterpret_cast<const u32x4 *>(tree_weights(a, b.lane, b.ut + j * NW, a.sx_packed, 3) + (int64_t)s * a.NPU * 64);
+        }
+        load_cells_weights(0);
+        if constexpr (!kResForget<T, NS>) {
+#pragma unroll
+            for (int j = 0; j < TW; ++j)
+#pragma unroll
+                for (int s = 0; s < NS; ++s)
+                    if (j < b.n_tiles && s < a.f_lds)
+                        *reinterpret_cast<u32x4 *>(b.F + (((b.ut + j * NW) * a.f_lds + s) * 64 + b.lane) * 16) = wf[j][s];
         }
     }
     if (!view_trees(a, lds, b, m)) return;
@@ -984,14 +995,15 @@ trees_resident_kernel(const TreesArgs a) {
         lds_barrier();
         forget_rows(0, n_leaf);
     } else {
-        // group_rows of them at a time through LDS (Ht and A in turn), the next ones' rows on their way meanwhile
-        constexpr int MOST = (kResGroup<T, NS> * PH + NT - 1) / NT;
+        // leaf_rows of them at a time through LDS (two buffers in turn), the next ones' rows on their way meanwhile
+        const int leaf_rows = a.group_rows * TW;
+        constexpr int MOST = (kResGroup<T, NS> * TW * PH + NT - 1) / NT;
         u32x4 ahead[MOST];
         auto request = [&](int r0) __attribute__((always_inline)) {
 #pragma unroll
             for (int e = 0; e < MOST; ++e) {
                 const int q = t + e * NT, r = r0 + q / PH;
-                if (q < a.group_rows * PH && r < n_leaf) ahead[e] = res_h_piece<T>(a, b, b.order[r], q % PH);
+                if (q < leaf_rows * PH && r < n_leaf) ahead[e] = res_h_piece<T>(a, b, b.order[r], q % PH);
             }
         };
         auto load_c = [&](int ut, int row, int r_end, ResPre<1> &p) __attribute__((always_inline)) {
@@ -1004,9 +1016,9 @@ trees_resident_kernel(const TreesArgs a) {
                 p.z[0][v] = a.c_out[(int64_t)(b.lo + b.order[res_row(quad, row, r_end, lane >> 4, v)]) * a.H + (unit < a.H ? unit : 0)];
             }
         };
-        // this wave's tiles, one group after the other; what a tile adds is requested two tiles ahead (TW > 1: one)
+        // this wave's tiles, one group after the other; what a tile adds is requested two tiles ahead
         auto group_end = [&](int row) __attribute__((always_inline)) {
-            const int e = row / a.group_rows * a.group_rows + a.group_rows;
+            const int e = row / leaf_rows * leaf_rows + leaf_rows;
             return e < n_leaf ? e : n_leaf;
         };
         auto leaves_after = [&](int at) __attribute__((always_inline)) {
@@ -1020,41 +1032,39 @@ trees_resident_kernel(const TreesArgs a) {
             res_load_zf<T>(a, b, ut_of(at), row, group_end(row), zp);
             load_c(ut_of(at), row, group_end(row), cp);
         };
-        if (TW == 1) request(0);
-        char *buf = b.Ht;
+        request(0);
+        char *const buf1 = lds + leaf_rows * PITCH, *buf = buf1;
         ResPre<1> zf1, cm, cm1;
-        int at0 = TW * (b.set * STEP < a.group_rows ? b.set * STEP : n_leaf), at1 = leaves_after(at0);
+        int at0 = TW * (b.set * STEP < leaf_rows ? b.set * STEP : n_leaf), at1 = leaves_after(at0);
         load_tile(at0, zf, cm);
-        if (TW == 1) load_tile(at1, zf1, cm1);
-        for (int r0 = 0; r0 < n_leaf; r0 += a.group_rows) {
-            const int r_end = r0 + a.group_rows < n_leaf ? r0 + a.group_rows : n_leaf;
-            if (TW > 1) request(r0);             // (no registers for the next group's rows)
+        load_tile(at1, zf1, cm1);
+        for (int r0 = 0; r0 < n_leaf; r0 += leaf_rows) {
+            const int r_end = r0 + leaf_rows < n_leaf ? r0 + leaf_rows : n_leaf;
 #pragma unroll
             for (int e = 0; e < MOST; ++e) {
                 const int q = t + e * NT;
-                if (q < a.group_rows * PH) *reinterpret_cast<u32x4 *>(buf + (q / PH) * PITCH + (q % PH) * 16) = ahead[e];
+                if (q < leaf_rows * PH) *reinterpret_cast<u32x4 *>(buf + (q / PH) * PITCH + (q % PH) * 16) = ahead[e];
             }
-            if (TW == 1) request(r0 + a.group_rows);
+            request(r0 + leaf_rows);
             lds_barrier();
             while (at0 / TW < r_end) {
                 const int row = at0 / TW, ut = ut_of(at0);
                 const ResPre<1> cur = zf, cc = cm;
                 at0 = at1;
                 at1 = leaves_after(at0);
-                if constexpr (TW == 1) {
-                    zf = zf1; cm = cm1;
-                    load_tile(at1, zf1, cm1);
-                } else {
-                    load_tile(at0, zf, cm);
-                }
+                zf = zf1; cm = cm1;
+                load_tile(at1, zf1, cm1);
                 if (res_quad<T>(row, r_end)) res_forget<T, SAVE, NS, false, true, true>(a, b, ut, w, cur, cc, buf, row, r0, r_end);
                 else res_forget<T, SAVE, NS, false, sizeof(T) == 4, true>(a, b, ut, w, cur, cc, buf, row, r0, r_end);
             }
-            buf = buf == b.Ht ? b.A : b.Ht;
+            buf = buf == buf1 ? lds : buf1;
         }
         lds_barrier();
         for (int i = t * 16; i < a.group_rows * PITCH; i += NT * 16)      // pad columns of the h rows stay zero
             *reinterpret_cast<u32x4 *>(b.Ht + i) = u32x4{0, 0, 0, 0};
+        // (the leaves' steps need the registers)
+        if constexpr (TW > 1)
+            if (b.n_tiles > 1) load_cells_weights(1);
     }
     ResPre<3> z;
     res_load_z<T>(a, b, b.ut, m.start[1] + b.set * STEP, m.start[1] + a.group_rows < m.start[2] ? m.start[1] + a.group_rows : m.start[2], z);
@@ -1179,7 +1189,8 @@ bool plan_trees(TreesArgs &a, size_t esz, const TreesShape &s) {
             for (;; --per_cu) {
                 a.G = (int)ceil_div(a.n, kTreeCus * per_cu);
                 a.cap = a.G + a.tree_window < a.n ? a.G + a.tree_window : a.n;
-                const size_t tiles = (size_t)rows * (a.pitch_h + row);
+                const size_t leaves = (size_t)rows * a.pitch_h * (two_tiles ? 4 : 2);      // two buffers
+                const size_t tiles = leaves > rows * (a.pitch_h + row) ? leaves : rows * (a.pitch_h + row);
                 a.lds_bytes = (tiles > cuts ? tiles : cuts) + (size_t)(4 * a.cap + 8) * 2;
                 if (per_cu == 1 || (a.lds_bytes + kTreeLdsStatic) * per_cu <= (size_t)kTreeLdsMax) break;
             }
