@@ -605,7 +605,7 @@ struct TreesArgs {
     int n, n_leaves, tree_window, l_end;   // levels [0, l_end) run here
     int D, H, Hp, Hq, NPU, sx_packed;      // sx_packed: slab of the packed weights at which the h part begins
     // by plan_trees
-    int sx, sh, Hz, n_ut, pitch_h, group_rows, G, cap, n_waves, n_blocks, x_slabs, x_chunks;
+    int sx, sh, Hz, n_ut, pitch_h, group_rows, G, cap, n_waves, n_blocks, x_slabs, x_chunks, x_rt;
     int res_slabs, near_rows, f_lds;       // weights in registers: slabs of the instance (0: from L2); h and f c in LDS; slabs of f's in LDS
     size_t lds_bytes;
 };

@@ -180,12 +180,15 @@ __device__ __forceinline__ void save_gates(const TreesArgs &a, int64_t node, int
     g[2 * a.H] = from_f32<T>(gu);
 }
 
+// All of the block's LDS writes are visible after it; stores to memory are not waited for (__syncthreads would).
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
 // ---- the x part ----------------------------------------------------------------------------
 // A wave keeps the weights of its 16 units' four gates in registers (NS slabs: 16 NS registers, which is what decides how
-// many waves share a SIMD: two up to ten slabs, one beyond) and multiplies one tile of 16 nodes after another; their x rows
-// come straight from memory in operand layout, the next tile's slab requested as soon as this one's is used.  No LDS, no
-// barrier: waves of a block take different units of the same nodes, which meet in L1.
-template <typename T, int NS> constexpr int kXWavesPerSimd = NS <= 10 ? 2 : 1;
+// many waves share a SIMD: two up to ten slabs, one beyond) and multiplies one tile of 16 nodes after another.  Tiles run in
+// the schedule's order: first the leaves', then the others', so that a tile's nodes all go the same way.  Blocks of neighbouring
+// units run on one XCD: they read the same rows and fill the same lines.
+constexpr int kXWavesPerSimd(int ns) { return ns <= 10 ? 2 : 1; }
 // Its instances: D up to 128, 224, 320, 512 and 640 in bf16, half of that in fp32.  Ten slabs are the most with which two waves
 // share a SIMD, twenty the most that 512 registers hold; the others bound the slabs multiplied as zeros to five.
 constexpr int kXSlabs[] = {4, 7, 10, 16, 20};
@@ -196,44 +199,89 @@ constexpr int slabs_below(int ns) {                // the instance before: slabs
     return below;
 }
 
+struct XTiles {
+    const int32_t *perm;
+    int n_leaves, n, leaf_tiles, n_tiles;
+    __device__ __forceinline__ explicit XTiles(const TreesArgs &a)
+        : perm(a.perm), n_leaves(a.n_leaves), n(a.n), leaf_tiles((a.n_leaves + 15) >> 4), n_tiles(leaf_tiles + ((a.n - a.n_leaves + 15) >> 4)) {}
+    __device__ __forceinline__ int node(int tile, int i) const {      // (past the end: the last one again)
+        const bool leaf = tile < leaf_tiles;
+        const int p = (leaf ? 0 : n_leaves - leaf_tiles * 16) + tile * 16 + i, last = (leaf ? n_leaves : n) - 1;
+        return perm[p < last ? p : last];
+    }
+};
+
+template <int NS>
+__device__ __forceinline__ void load_x_weights(const TreesArgs &a, int lane, int ut, u32x4 (&fb)[NS][4]) {
+    const char *w = tree_weights(a, lane, ut, 0, 0);
+#pragma unroll
+    for (int s = 0; s < NS; ++s)
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+            fb[s][g] = *reinterpret_cast<const u32x4 *>(w + (int64_t)(s < a.sx_packed ? s : 0) * a.NPU * 64 + g * 2048);
+    // slabs past the packed x part meet zeros, but 0 times an infinite weight would be NaN
+#pragma unroll
+    for (int s = slabs_below(NS); s < NS; ++s)
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+            if (s >= a.sx_packed) fb[s][g] = u32x4{0, 0, 0, 0};
+}
+
+// The biases of a wave's units, [gate][unit], in LDS: a load from memory behind the next rows' requests and the last tile's
+// stores would wait for all of them.
+__device__ __forceinline__ void keep_x_bias(const TreesArgs &a, int lane, int ut, float *bias) {
+    bias[lane] = a.bp[(ut >> 1) * kGateTile + (lane >> 4) * kUnit + (ut & 1) * 16 + (lane & 15)];
+}
+
+// Leaves finish, the others leave Z.  node_of(i): node of row i of the tile.
+template <typename T, bool SAVE, typename NodeOf>
+__device__ __forceinline__ void finish_x_tile(const TreesArgs &a, int lane, int ut, bool leaf, const floatx4 (&acc)[4], const float *bias, NodeOf &&node_of) {
+    lane = fresh_lane(lane);                     // (nothing derived from it stays in registers meanwhile)
+    const int unit = ut * 16 + (lane & 15);
+    const float *b = bias + (lane & 15), bi = b[0], bo = b[16], bu = b[32], bf = b[48];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        __builtin_amdgcn_sched_barrier(0);
+        const float zi = acc[0][v] + bi, zo = acc[1][v] + bo, zu = acc[2][v] + bu;
+        const int64_t node = node_of((lane >> 4) * 4 + v);
+        if (leaf) {
+            const float gi = sigmoid_t<T>(zi), go = sigmoid_t<T>(zo), gu = tanh_t<T>(zu);
+            const float c = gi * gu;
+            store_unit<T>(a, node, unit, c, unit < a.H ? from_f32<T>(go * tanh_t<T>(c)) : T(0));
+            if constexpr (SAVE) {
+                if (unit < a.H) save_gates<T>(a, node, unit, gi, go, gu);
+            }
+        } else {
+            float *z = a.Z + node * 4 * a.Hz + unit;
+            z[0] = zi; z[a.Hz] = zo; z[2 * a.Hz] = zu; z[3 * a.Hz] = acc[3][v] + bf;
+        }
+    }
+}
+
+// fp32, which the matrix rate bounds, and bf16 from ten slabs on: x rows come straight from memory in operand layout, the next tile's slab requested as soon as
+// this one's is used, its node ids a tile earlier.  No LDS, no barrier: waves of a block take different units of the same nodes,
+// which meet in L1.  (No load may be waited for behind a tile's stores, which it would drain first: 278 k nodes, D 300, H 256, fp32
+// 1110 us with the biases loaded there, 1040 now.)
 // Leaves have no forget gate.  Its products are left out of their tiles by a branch between the other MFMAs, except in the wide
-// bf16 instances: with the accumulators in accumulation registers the compiler reads an MFMA's result there two instructions
+// bf16 instances: with the accumulators in accumulation registers the compiler once read an MFMA's result there two instructions
 // behind it where the branch is taken, eight too few, and every tile of leaves came out wrong.  (The build looks for such reads.)
 template <typename T, int NS> constexpr bool kLeavesSkip = sizeof(T) == 4 || NS <= 10;
-
 template <typename T, bool SAVE, int NS>
-__global__ void __launch_bounds__(256, (kXWavesPerSimd<T, NS>))
+__global__ void __launch_bounds__(256, kXWavesPerSimd(NS))
 tree_x_kernel(const TreesArgs a) {
     constexpr int VEC = Traits<T>::VEC;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int gw = blockIdx.x * 4 + wave;
+    const int gw = ((blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3)) * 4 + wave;
     const int ut = gw % a.n_ut, chunk = gw / a.n_ut;
     if (chunk >= a.x_chunks) return;
     const int hf = lane >> 4, n = lane & 15;
+    __shared__ float bias[4][64];
+    keep_x_bias(a, lane, ut, bias[wave]);
     u32x4 fb[NS][4];
-    {
-        const char *w = tree_weights(a, lane, ut, 0, 0);
-#pragma unroll
-        for (int s = 0; s < NS; ++s)
-#pragma unroll
-            for (int g = 0; g < 4; ++g)
-                fb[s][g] = *reinterpret_cast<const u32x4 *>(w + (int64_t)(s < a.sx_packed ? s : 0) * a.NPU * 64 + g * 2048);
-        // slabs past the packed x part meet zeros, but 0 times an infinite weight would be NaN
-#pragma unroll
-        for (int s = slabs_below(NS); s < NS; ++s)
-#pragma unroll
-            for (int g = 0; g < 4; ++g)
-                if (s >= a.sx_packed) fb[s][g] = u32x4{0, 0, 0, 0};
-    }
+    load_x_weights<NS>(a, lane, ut, fb);
     const T *x = static_cast<const T *>(a.x);
-    // tiles in the schedule's order: first the leaves', then the others', so that a tile's nodes all go the same way
-    const int leaf_tiles = (a.n_leaves + 15) >> 4, n_tiles = leaf_tiles + ((a.n - a.n_leaves + 15) >> 4);
-    auto node_of = [&](int tile, int i) __attribute__((always_inline)) {      // (past the end: the last one again)
-        const bool leaf = tile < leaf_tiles;
-        const int p = (leaf ? 0 : a.n_leaves - leaf_tiles * 16) + tile * 16 + i, last = (leaf ? a.n_leaves : a.n) - 1;
-        return (int64_t)a.perm[p < last ? p : last];
-    };
-    auto row_of = [&](int tile) __attribute__((always_inline)) { return x + node_of(tile, n) * a.D + hf * VEC; };
+    const XTiles tiles(a);
+    auto row_of = [&](int node) __attribute__((always_inline)) { return x + (int64_t)node * a.D + hf * VEC; };
     // slab s of a row: whole 16 bytes where all four pieces lie inside D; the slab that straddles D, and those past it,
     // piece by piece
     auto load_slab = [&](const T *row, int s) __attribute__((always_inline)) {
@@ -242,23 +290,23 @@ tree_x_kernel(const TreesArgs a) {
         else v = load_x_piece<T>(row - hf * VEC, (s * 4 + hf) * VEC, a.D);
         return v;
     };
-    // (ten slabs leave no registers for the last ones across the cell update: those come at the tile's start)
-    constexpr int PF = NS == 10 ? (SAVE || sizeof(T) == 2 ? 6 : 8) : NS;
+    // (where gates are saved, ten bf16 slabs leave no registers for the last two across the cell update: those come at the tile's start)
+    constexpr int PF = NS == 10 && SAVE && sizeof(T) == 2 ? 8 : NS;
     u32x4 fa[NS];
-    const T *row = row_of(chunk);
+    auto nodes_of = [&](int tile) __attribute__((always_inline)) { return tiles.node(tile < tiles.n_tiles ? tile : chunk, n); };
+    int id = nodes_of(chunk), id_next = nodes_of(chunk + a.x_chunks);
+    const T *row = row_of(id);
 #pragma unroll
     for (int s = 0; s < PF; ++s) fa[s] = load_slab(row, s);
-    for (int tile = chunk; tile < n_tiles; tile += a.x_chunks) {
-        int64_t node[4];
-#pragma unroll
-        for (int v = 0; v < 4; ++v) node[v] = node_of(tile, hf * 4 + v);
-        const bool leaf = tile < leaf_tiles;
+    for (int tile = chunk; tile < tiles.n_tiles; tile += a.x_chunks) {
+        const bool leaf = tile < tiles.leaf_tiles;
+        const int id_after = nodes_of(tile + 2 * a.x_chunks);
         floatx4 acc[4];
 #pragma unroll
         for (int g = 0; g < 4; ++g) acc[g] = floatx4{0, 0, 0, 0};
 #pragma unroll
         for (int s = PF; s < NS; ++s) fa[s] = load_slab(row, s);
-        row = row_of(tile + a.x_chunks < n_tiles ? tile + a.x_chunks : tile);
+        row = row_of(id_next);
 #pragma unroll
         for (int s = 0; s < NS; ++s) {
 #pragma unroll
@@ -266,25 +314,119 @@ tree_x_kernel(const TreesArgs a) {
             if (!kLeavesSkip<T, NS> || !leaf) mfma16<T>(fa[s], fb[s][3], acc[3]);
             if (s < PF) fa[s] = load_slab(row, s);
         }
-        const int unit = ut * 16 + (fresh_lane(lane) & 15);       // (nothing derived from it stays in registers meanwhile)
-        const float *bias = a.bp + (ut >> 1) * kGateTile + (ut & 1) * 16 + (unit & 15);
-        const float bi = bias[0], bo = bias[kUnit], bu = bias[2 * kUnit], bf = bias[3 * kUnit];
+        finish_x_tile<T, SAVE>(a, lane, ut, leaf, acc, bias[wave], [&](int i) { return __shfl(id, i, 64); });
+        id = id_next;
+        id_next = id_after;
+    }
+}
+
+// Elements [k0, k0 + 8) of a row of D >= 8 from one 16-byte load inside it, zero past D.
+__device__ __forceinline__ u32x4 load_x_piece_inside(const bf16_t *row, int k0, int D) {
+    u32x4 v = {0, 0, 0, 0};
+    if (k0 >= D) return v;
+    __builtin_memcpy(&v, row + (k0 + 8 <= D ? k0 : D - 8), 16);
+    const int bits = ((8 - D) & 7) * 16;                      // what the piece that straddles D has to come down by
+    if (k0 + 8 > D) {
+        const uint64_t lo = v[0] | (uint64_t)v[1] << 32, hi = v[2] | (uint64_t)v[3] << 32;
+        const uint64_t l = bits >= 64 ? hi >> (bits - 64) : lo >> bits | hi << (64 - bits), h = bits >= 64 ? 0 : hi >> bits;
+        v = u32x4{(uint32_t)l, (uint32_t)(l >> 32), (uint32_t)h, (uint32_t)(h >> 32)};
+    }
+    return v;
+}
+
+// bf16 up to seven slabs: a wave's own loads in operand layout touch 64 lines for 1 KB, and every unit tile's wave repeats
+// them.  A block of four unit tiles fetches its rows once, 16 consecutive bytes a lane, and multiplies from LDS (two buffers, one
+// barrier a group of 16 x_rt rows, the next group's rows in flight meanwhile).  21 k nodes, D 203, H 99: 31.7 -> 25.2 us.  It hides
+// one round trip of a group's rows, so with ten slabs, whose registers hold 16 rows of products and no more, it is slower: 106 k
+// nodes, D 300, H 150 111 -> 162.
+constexpr int kXLdsWaves = 4, kXLdsSlabs = 7, kXLdsRows = 32;
+template <bool SAVE, int NS>
+__global__ void __launch_bounds__(kXLdsWaves * 64, kXWavesPerSimd(NS))
+tree_x_lds_kernel(const TreesArgs a) {
+    using T = bf16_t;
+    constexpr int NT = kXLdsWaves * 64, ROWS = kXLdsRows, PX = NS * 4, PITCH = NS * 64 + 16, E = (ROWS * PX + NT - 1) / NT;
+    __shared__ __attribute__((aligned(16))) char xs[2][ROWS * PITCH];
+    __shared__ int ids[4][ROWS];
+    __shared__ float bias[kXLdsWaves][64];
+    const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int block = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+    const int n_ug = (a.n_ut + kXLdsWaves - 1) / kXLdsWaves;
+    const int chunk = block / n_ug, first_ut = block % n_ug * kXLdsWaves;
+    if (chunk >= a.x_chunks) return;
+    const bool mine = first_ut + wave < a.n_ut;               // (the others only fetch)
+    const int ut = mine ? first_ut + wave : first_ut;
+    const XTiles tiles(a);
+    const int rows = 16 * a.x_rt, n_groups = (tiles.n_tiles + a.x_rt - 1) / a.x_rt;
+    auto id_of = [&](int group) __attribute__((always_inline)) {          // of row t (past the end: some row again)
+        const int tile = (group < n_groups ? group : chunk) * a.x_rt + (t >> 4);
+        return tiles.node(tile < tiles.n_tiles ? tile : tiles.n_tiles - 1, t & 15);
+    };
+    if (t < rows) {
+        ids[0][t] = id_of(chunk);
+        ids[1][t] = id_of(chunk + a.x_chunks);
+        ids[2][t] = id_of(chunk + 2 * a.x_chunks);
+    }
+    keep_x_bias(a, lane, ut, bias[wave]);
+    u32x4 fb[NS][4];
+    load_x_weights<NS>(a, lane, ut, fb);
+    lds_barrier();
+    u32x4 xr[E];
+    auto request = [&](const int *id) __attribute__((always_inline)) {
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            __builtin_amdgcn_sched_barrier(0);
-            const float zi = acc[0][v] + bi, zo = acc[1][v] + bo, zu = acc[2][v] + bu;
-            if (leaf) {
-                const float gi = sigmoid_t<T>(zi), go = sigmoid_t<T>(zo), gu = tanh_t<T>(zu);
-                const float c = gi * gu;
-                store_unit<T>(a, node[v], unit, c, unit < a.H ? from_f32<T>(go * tanh_t<T>(c)) : T(0));
-                if constexpr (SAVE) {
-                    if (unit < a.H) save_gates<T>(a, node[v], unit, gi, go, gu);
-                }
-            } else {
-                float *z = a.Z + node[v] * 4 * a.Hz + unit;
-                z[0] = zi; z[a.Hz] = zo; z[2 * a.Hz] = zu; z[3 * a.Hz] = acc[3][v] + bf;
+        for (int e = 0; e < E; ++e) {
+            const int q = t + e * NT;
+            xr[e] = u32x4{0, 0, 0, 0};
+            if (q >= rows * PX) continue;
+            const T *row = static_cast<const T *>(a.x) + (int64_t)id[q / PX] * a.D;
+            xr[e] = a.D >= 8 ? load_x_piece_inside(row, q % PX * 8, a.D) : load_x_piece<T>(row, q % PX * 8, a.D);
+        }
+    };
+    auto write = [&](char *buf) __attribute__((always_inline)) {
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            const int q = t + e * NT;
+            if (q < rows * PX) *reinterpret_cast<u32x4 *>(buf + q / PX * PITCH + q % PX * 16) = xr[e];
+        }
+    };
+    request(ids[0]);
+    write(xs[0]);
+    request(ids[1]);
+    lds_barrier();
+    int cur = 0, k = 0;
+    for (int group = chunk; group < n_groups; group += a.x_chunks, cur ^= 1, k = (k + 1) & 3) {
+        int id_after = 0;
+        if (t < rows) id_after = id_of(group + 3 * a.x_chunks);
+        floatx4 acc[ROWS / 16][4];
+#pragma unroll
+        for (int j = 0; j < ROWS / 16; ++j) {
+#pragma unroll
+            for (int g = 0; g < 4; ++g) acc[j][g] = floatx4{0, 0, 0, 0};
+            const int tile = group * a.x_rt + j;
+            if (!mine || j >= a.x_rt) continue;
+            const bool leaf = tile < tiles.leaf_tiles;
+            const char *a_lane = xs[cur] + (j * 16 + (lane & 15)) * PITCH + (lane >> 4) * 16;
+#pragma unroll
+            for (int s = 0; s < NS; ++s) {
+                const u32x4 fa = *reinterpret_cast<const u32x4 *>(a_lane + s * 64);
+#pragma unroll
+                for (int g = 0; g < 3; ++g) mfma16<T>(fa, fb[s][g], acc[j][g]);
+                if (!leaf) mfma16<T>(fa, fb[s][3], acc[j][3]);
             }
         }
+        // The next group's rows are here and the ones after them asked for before this group's stores: the wait for loads waits
+        // for every older store, and those then have a group's time too.
+        write(xs[cur ^ 1]);
+        if (t < rows) ids[(k + 3) & 3][t] = id_after;
+        __builtin_amdgcn_sched_barrier(0);
+        request(ids[(k + 2) & 3]);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int j = 0; j < ROWS / 16; ++j) {
+            const int tile = group * a.x_rt + j;
+            if (!mine || j >= a.x_rt || tile >= tiles.n_tiles) continue;
+            finish_x_tile<T, SAVE>(a, lane, ut, tile < tiles.leaf_tiles, acc[j], bias[wave], [&](int i) { return ids[k][j * 16 + i]; });
+        }
+        lds_barrier();
     }
 }
 
@@ -297,9 +439,6 @@ struct TreeBlock {
     int lo, own;
     int lane, wave, n_waves;
 };
-
-// All of the block's LDS writes are visible after it; stores to memory are not waited for (__syncthreads would).
-__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 // The arrays of a block's view behind `at`: 4 cap + 8 entries.
 __device__ __forceinline__ void place_view(const TreesArgs &a, TreeBlock &b, char *at) {
@@ -1155,6 +1294,8 @@ static int resident_waves(int ns, size_t esz) {
 static bool resident_forget(int ns, size_t esz) { return esz == 4 ? ns <= 8 : ns <= 5; }
 static bool resident_shares_cu(int ns, size_t esz) { return ns * (int)esz * 4 <= (esz == 4 ? 64 : 16); }
 
+static bool x_through_lds(const TreesArgs &a, size_t esz) { return esz == 2 && a.x_slabs <= kXLdsSlabs; }
+
 // Fills the launch geometry of `a`; false if the forest is better run level by level.
 bool plan_trees(TreesArgs &a, size_t esz, const TreesShape &s) {
     if (a.n > trees_max_nodes(a.D, a.H, esz)) return false;
@@ -1231,9 +1372,15 @@ bool plan_trees(TreesArgs &a, size_t esz, const TreesShape &s) {
     a.x_slabs = 0;
     for (int ns : kXSlabs)
         if (a.x_slabs == 0 && ns >= a.sx) a.x_slabs = ns;
-    const int64_t waves = (int64_t)kTreeCus * 4 * (a.x_slabs <= 10 ? 2 : 1), tiles16 = ceil_div(a.n_leaves, 16) + ceil_div(a.n - a.n_leaves, 16);
-    a.x_chunks = (int)(waves / a.n_ut);
-    if (a.x_chunks > tiles16) a.x_chunks = (int)tiles16;
+    const int64_t waves = (int64_t)kTreeCus * 4 * kXWavesPerSimd(a.x_slabs), tiles16 = ceil_div(a.n_leaves, 16) + ceil_div(a.n - a.n_leaves, 16);
+    a.x_rt = 1;
+    if (!x_through_lds(a, esz)) {
+        a.x_chunks = (int)(waves / a.n_ut);
+    } else {      // a block fetches for four unit tiles, 32 rows a time where that leaves no block without work
+        a.x_chunks = (int)(waves / (kXLdsWaves * ceil_div(a.n_ut, kXLdsWaves)));
+        if (tiles16 >= 2 * (int64_t)a.x_chunks) a.x_rt = kXLdsRows / 16;
+    }
+    if (a.x_chunks > ceil_div(tiles16, a.x_rt)) a.x_chunks = (int)ceil_div(tiles16, a.x_rt);
     if (a.x_chunks < 1) a.x_chunks = 1;
     return true;
 }
@@ -1241,7 +1388,10 @@ bool plan_trees(TreesArgs &a, size_t esz, const TreesShape &s) {
 namespace {
 template <typename T, bool SAVE, int NS>
 int launch_tree_x(const TreesArgs &a, hipStream_t st) {
-    tree_x_kernel<T, SAVE, NS><<<(unsigned)ceil_div((int64_t)a.x_chunks * a.n_ut, 4), 256, 0, st>>>(a);
+    if constexpr (sizeof(T) == 2 && NS <= kXLdsSlabs)
+        tree_x_lds_kernel<SAVE, NS><<<(unsigned)(8 * ceil_div(a.x_chunks * ceil_div(a.n_ut, kXLdsWaves), 8)), kXLdsWaves * 64, 0, st>>>(a);
+    else
+        tree_x_kernel<T, SAVE, NS><<<(unsigned)(8 * ceil_div((int64_t)a.x_chunks * a.n_ut, 32)), 256, 0, st>>>(a);
     JITDB_LAUNCH_CHECK();
     return JITDB_OK;
 }

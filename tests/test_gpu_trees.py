@@ -89,6 +89,20 @@ def test_every_width_of_the_x_part(c_oracle, dtype, D, save):
     assert np.abs(c - co).max() <= TOL[dtype] * max(1.0, np.abs(co).max() / (8.0 if dtype == "bf16" else 50.0))
 
 
+@pytest.mark.parametrize("D,H", [(3, 150), (7, 64), (8, 65), (9, 150), (127, 130), (129, 80), (203, 150), (224, 200)])
+def test_x_part_over_several_groups(c_oracle, D, H):
+    """bf16 rows through LDS: blocks that take several groups of 32 rows (one unit tile to fetch for in the last block of some
+    H), last pieces of every length, D below one piece; the bounds are the forward's."""
+    p = _lay_out([make_forest(1)] * 350)
+    x, W, U, b = make_values(1, p.shape[0], "random", D=D, H=H)
+    print(f"x part D={D} H={H} N={p.shape[0]}", flush=True)
+    s, h, c, seen = run_gpu_forward(p, x, W, U, b, "bf16")
+    assert 0 < s.struct.tree_window <= 256
+    ho, co, _ = c_oracle(p, *seen)
+    assert np.abs(h - ho).max() <= TOL["bf16"]
+    assert np.abs(c - co).max() <= TOL["bf16"] * max(1.0, np.abs(co).max() / 8.0)
+
+
 @pytest.mark.parametrize("save", [False, True])
 @pytest.mark.parametrize("forest", ["row-groups", "far"])
 @pytest.mark.parametrize("dtype,H", [("f32", H) for H in (16, 17, 64, 65, 127, 128, 129, 160, 161)] +
