@@ -1254,14 +1254,16 @@ constexpr int kTreeLdsStatic = 1024;               // trees_kernel's static LDS,
 
 // The largest forest that runs as whole trees; workspaces have room for no larger one.
 int64_t trees_max_nodes(int D, int H, size_t esz) {
-    // Every block reads the recurrent weights once per level, so the gain shrinks with their size and, where the level kernels
-    // fill the chip, with the number of nodes.  Forward alone, 32 to 8192 trees of 4 - 48 nodes, D = 300, level by level ->
-    // here: H = 64 fp32 201 -> 67 us (949 nodes), 1115 -> 522 (214 k), bf16 149 -> 58, 541 -> 242; H = 150 fp32 244 -> 126,
-    // 1937 -> 1428, bf16 163 -> 83, 887 -> 637; H = 256 fp32 275 -> 217, 2438 -> 2437, bf16 169 -> 146 (949), 272 -> 209 (26 k),
-    // 532 -> 552 (106 k); H = 384 slower throughout.  The lines lie inside what was measured, not where the gain ends: no forest
-    // beyond 225 k nodes, and in bf16 at 106 k nodes H = 176 455 -> 381, 224 511 -> 455, 240 531 -> 531, 256 503 -> 532.
+    // The gain shrinks with the number of nodes, where the level kernels fill the chip, and with what they spend on x.  Schedule +
+    // forward in bf16, level by level -> here: H = 168 and 192, D = 300 384, 377 -> 258, 250 us (73 k nodes), 868, 845 -> 675, 653
+    // (214 k), D = 64 337, 332 -> 261, 256 (73 k), 358, 346 -> 352, 344 (106 k), 612, 577 -> 639, 614 (214 k).  H = 200 to 256, which
+    // hold fewer weights: D = 300 414 - 429 -> 361 - 389 (73 k), 558 - 586 -> 494 - 528 (106 k), 969 - 1015 -> 950 - 994 (214 k),
+    // D = 64 364 - 374 -> 360 - 387 (73 k), 406 - 447 -> 494 - 520 (106 k).  fp32, D = 300: H = 64 234 -> 96 (4.7 k), 1198 -> 539 (214 k),
+    // H = 150 2028 -> 1406, H = 256 296 -> 228 (4.7 k), 2530 -> 2321 (214 k).  H = 384 slower throughout.  The lines lie inside what was
+    // measured, not where the gain ends: no forest beyond 225 k nodes.
     if (H > kTreesMaxWidth || ceil_div((int64_t)D * (int64_t)esz, 64) > kXSlabs[sizeof(kXSlabs) / sizeof(int) - 1]) return 0;
-    return esz == 2 && H > 160 ? 65536 : 262144;
+    if (esz == 4 || H <= 160) return 262144;
+    return H <= 192 ? (D >= 128 ? 262144 : 106496) : (D >= 256 ? 131072 : 65536);
 }
 
 // Microseconds by which whole trees take longer than the level kernels (less than zero: they are faster).  What speaks against
