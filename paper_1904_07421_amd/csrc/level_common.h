@@ -285,6 +285,30 @@ __device__ __forceinline__ void store_state(const LevelArgs &a, int64_t nd, int 
     }
 }
 
+// Four units of a gate row; `vec`: one store.
+template <typename T>
+__device__ __forceinline__ void save_units(T *dst, const float (&v)[4], int left, bool vec) {
+    if (vec) {
+        T e[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) e[j] = from_f32<T>(v[j]);
+        __builtin_memcpy(__builtin_assume_aligned(dst, 4 * sizeof(T)), e, 4 * sizeof(T));
+    } else {
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            if (j < left) dst[j] = from_f32<T>(v[j]);
+    }
+}
+
+__device__ __forceinline__ void wave_lds_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// A wait for loads waits for every older store, so gates are saved behind the children's rows, four units a store (i and u pass
+// through LDS one by one, o in i's place): 524 k inner rows of H 512 in bf16 with saves 1302 -> 1209 us.  (Without saves a pass's
+// own stores, held back until the next pass has its children's rows, gain nothing: 1993 against 2004 us at 1 M rows.)
 template <typename T, int MODE, bool SAVE = false>
 __device__ __forceinline__ void cell_pass(const LevelArgs &a, const floatx16 (&acc)[4], float *region,
                                           const int *rn, const int *rar, const int *rcb,
@@ -302,37 +326,41 @@ __device__ __forceinline__ void cell_pass(const LevelArgs &a, const floatx16 (&a
     for (int v = 0; v < 16; ++v) {
         const int rl = (v >> 2) * 8 + hf * 4 + (v & 3);   // 0..31
         const float gi = sigmoid_t<T>(acc[0][v] + bi);
-        const float go = sigmoid_t<T>(acc[1][v] + bo);
         const float gu = tanh_t<T>(acc[2][v] + bu);
-        s_iu[rl * kEpiStride + l32] = gi * gu;
-        s_o[rl * kEpiStride + l32] = go;
+        s_iu[rl * kEpiStride + l32] = SAVE ? gi : gi * gu;
+        s_o[rl * kEpiStride + l32] = SAVE ? gu : sigmoid_t<T>(acc[1][v] + bo);
         if constexpr (KIDS) s_fx[rl * kEpiStride + l32] = acc[3][v] + bf;
-        if constexpr (SAVE) {
-            const int nd = rn[rl];
-            const int unit = unit_tile * kUnit + l32;
-            if (nd >= 0 && unit < a.H) {
-                T *g = static_cast<T *>(a.gates) + (int64_t)nd * 3 * a.H + unit;
-                g[0] = from_f32<T>(gi);
-                g[a.H] = from_f32<T>(go);
-                g[2 * a.H] = from_f32<T>(gu);
-            }
-        }
     }
     // the wave's own LDS writes are ordered before its reads; nothing else touches the region
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    float4 cc[4], go4[4], fx4[4];
+    wave_lds_fence();
+    float4 cc[4], go4[4], fx4[4], gi4[4], gu4[4];
     int node[4], tr[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         tr[q] = (lane >> 3) + 8 * q;
         node[q] = rn[tr[q]];
         const int so = tr[q] * kEpiStride + (lane & 7) * 4;
-        cc[q] = *reinterpret_cast<const float4 *>(s_iu + so);
-        go4[q] = *reinterpret_cast<const float4 *>(s_o + so);
+        const float4 first = *reinterpret_cast<const float4 *>(s_iu + so), second = *reinterpret_cast<const float4 *>(s_o + so);
+        if constexpr (SAVE) {
+            gi4[q] = first;
+            gu4[q] = second;
+            cc[q] = make_float4(first.x * second.x, first.y * second.y, first.z * second.z, first.w * second.w);
+        } else {
+            cc[q] = first;
+            go4[q] = second;
+        }
         if constexpr (KIDS) fx4[q] = *reinterpret_cast<const float4 *>(s_fx + so);
     }
+    if constexpr (SAVE) {
+        wave_lds_fence();
+#pragma unroll
+        for (int v = 0; v < 16; ++v) s_iu[((v >> 2) * 8 + hf * 4 + (v & 3)) * kEpiStride + l32] = sigmoid_t<T>(acc[1][v] + bo);
+        wave_lds_fence();
+#pragma unroll
+        for (int q = 0; q < 4; ++q) go4[q] = *reinterpret_cast<const float4 *>(s_iu + tr[q] * kEpiStride + (lane & 7) * 4);
+    }
+    const bool vec = SAVE && (a.H & 3) == 0 &&
+                     ((reinterpret_cast<uintptr_t>(a.gates) | reinterpret_cast<uintptr_t>(a.fgate)) & (4 * sizeof(T) - 1)) == 0;
     if constexpr (KIDS) {
         // Children are taken one per row and round, for four rows at once: eight independent loads in
         // flight per thread (two per row and round measured no faster: half of all parents have one
@@ -392,13 +420,8 @@ __device__ __forceinline__ void cell_pass(const LevelArgs &a, const floatx16 (&a
                 cc[q].z += wgt[q] * f2 * ck[q].z;
                 cc[q].w += wgt[q] * f3 * ck[q].w;
                 if constexpr (SAVE) {
-                    if (kidv[q] >= 0) {
-                        const float fv[4] = {f0, f1, f2, f3};
-                        T *dst = static_cast<T *>(a.fgate) + (int64_t)kidv[q] * a.H + unit0;
-#pragma unroll
-                        for (int e = 0; e < 4; ++e)
-                            if (unit0 + e < a.H) dst[e] = from_f32<T>(fv[e]);
-                    }
+                    const float fv[4] = {f0, f1, f2, f3};
+                    if (kidv[q] >= 0 && unit0 < a.H) save_units(static_cast<T *>(a.fgate) + (int64_t)kidv[q] * a.H + unit0, fv, a.H - unit0, vec);
                 }
             }
         }
@@ -407,6 +430,15 @@ __device__ __forceinline__ void cell_pass(const LevelArgs &a, const floatx16 (&a
     for (int q = 0; q < 4; ++q) {
         if (node[q] < 0) continue;
         store_state<T>(a, node[q], unit0, cc[q], go4[q]);
+        if constexpr (SAVE) {
+            if (unit0 >= a.H) continue;
+            T *g = static_cast<T *>(a.gates) + (int64_t)node[q] * 3 * a.H + unit0;
+            const float vi[4] = {gi4[q].x, gi4[q].y, gi4[q].z, gi4[q].w}, vo[4] = {go4[q].x, go4[q].y, go4[q].z, go4[q].w};
+            const float vu[4] = {gu4[q].x, gu4[q].y, gu4[q].z, gu4[q].w};
+            save_units(g, vi, a.H - unit0, vec);
+            save_units(g + a.H, vo, a.H - unit0, vec);
+            save_units(g + 2 * a.H, vu, a.H - unit0, vec);
+        }
     }
 }
 

@@ -62,6 +62,27 @@ def test_training_forward_keeps_the_gate_activations(kind, D, H, dtype):
     assert not fgate.float().cpu().numpy()[~has_parent].any()          # rows of roots stay as handed in (zeros)
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("H,shift", [(99, 0), (100, 0), (100, 1), (150, 0)])
+def test_tiled_levels_save_gates(H, shift, dtype):
+    """Levels wide enough for the tiled kernel, leaves and inner nodes, whose ids lie all over the forest: gates in stores of four
+    units, one by one where H is no multiple of four or the buffers do not lie on one (`shift` elements)."""
+    k, D = 4100, 20
+    parent = np.concatenate([np.full(k, -1), np.repeat(np.arange(k), 2), k + np.arange(2 * k)]).astype(np.int32)
+    n = parent.shape[0]
+    x, W, U, b = make_values(1, n, "random", D=D, H=H)
+    print(f"tiled forward_train H={H} shift={shift} dtype={dtype} N={n}", flush=True)
+    dev, seen = _upload(x, W, U, b, dtype)
+    s = J.jitdb_schedule(torch.from_numpy(parent).cuda())
+    gates = torch.zeros(n * 3 * H + shift, dtype=dev[0].dtype, device="cuda")[shift:].view(n, 3 * H)
+    fgate = torch.zeros(n * H + shift, dtype=dev[0].dtype, device="cuda")[shift:].view(n, H)
+    out = (torch.empty((n, H), dtype=dev[0].dtype, device="cuda"), torch.empty((n, H), device="cuda"), gates, fgate)
+    h, c, _, _ = J.jitdb_treelstm_forward_train(*dev, s, out=out)
+    ho, co, go, fo = B.forward_saved(parent, *seen)
+    for got, want in ((h, ho), (c, co), (gates, go), (fgate, np.where((parent >= 0)[:, None], fo, 0.0))):
+        assert np.abs(got.float().cpu().numpy() - want).max() <= TOL[dtype]
+
+
 def _rel(got, want):
     return float(np.abs(got - want).max() / max(1.0, np.abs(want).max()))
 
