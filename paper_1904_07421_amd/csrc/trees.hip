@@ -1260,10 +1260,11 @@ int64_t trees_max_nodes(int D, int H, size_t esz) {
     // hold fewer weights: D = 300 414 - 429 -> 361 - 389 (73 k), 558 - 586 -> 494 - 528 (106 k), 969 - 1015 -> 950 - 994 (214 k),
     // D = 64 364 - 374 -> 360 - 387 (73 k), 406 - 447 -> 494 - 520 (106 k).  fp32, D = 300: H = 64 234 -> 96 (4.7 k), 1198 -> 539 (214 k),
     // H = 150 2028 -> 1406, H = 256 296 -> 228 (4.7 k), 2530 -> 2321 (214 k).  H = 384 slower throughout.  The lines lie inside what was
-    // measured, not where the gain ends: no forest beyond 225 k nodes.
+    // measured, not where the gain ends: no forest beyond 225 k nodes, and for H > 192 no more room than the levels of a forest a few
+    // times larger take anyway (larger forests ask for this room too).
     if (H > kTreesMaxWidth || ceil_div((int64_t)D * (int64_t)esz, 64) > kXSlabs[sizeof(kXSlabs) / sizeof(int) - 1]) return 0;
     if (esz == 4 || H <= 160) return 262144;
-    return H <= 192 ? (D >= 128 ? 262144 : 106496) : (D >= 256 ? 131072 : 65536);
+    return H <= 192 ? (D >= 128 ? 262144 : 106496) : (D >= 256 ? 81920 : 65536);
 }
 
 // Microseconds by which whole trees take longer than the level kernels (less than zero: they are faster).  What speaks against
