@@ -6,7 +6,7 @@
 // nothing from other blocks, so its levels may follow one another behind block barriers.
 //
 //   tree_x_kernel    Z = W x + b for all nodes, spread evenly over the chip; leaves finish their cells right there, the
-//                    other nodes leave Z [node][i | o | u | f] in fp32
+//                    other nodes leave Z [node][i | o | u | f] in fp32 (bf16 rows up to 224 wide: tree_x_lds_kernel)
 //   trees_kernel     block b takes the trees from the first cut at or after id b G to the first at or after (b + 1) G (a
 //                    cut is a place between ids that no edge crosses; jitdb_schedule_t::tree_window says that they are
 //                    close together).  Rows are the block's nodes in (height, id) order, in groups of 16 or 32:
