@@ -1152,8 +1152,8 @@ struct ForwardWs {
     void *Bp;
     float *bp;
     void *stack;  // the current level's stacked input, (N + 256) rows of Dp + Hp
-    float *Z;     // trees.hip: x parts of the gates [N][4][H rounded up to 16], in the same memory; nullptr: no room
-    float *FC;    // trees.hip: every node's f c, [N, H rounded up to 16], in the memory of P
+    float *Z;     // trees.hip: x parts of the gates [N][4][H rounded up to 16], in the memory of stack and P; nullptr: no room
+    float *FC;    // trees.hip: every node's f c, [N, H rounded up to 16], behind Z
     int4 *row_rec; // row records of all level positions, two int4 each
     void *hs;     // nullptr when h_out can serve (H == Hp)
     void *P;
@@ -1198,24 +1198,23 @@ ForwardWs carve_forward_ws(int64_t n, int64_t e, const Dims &d, void *base, int 
     (void)e;
     w.Bp = c.take<char>(packed_w_bytes(d) * n_sig);
     w.bp = c.take<float>((size_t)d.NP * n_sig);
-    // one level at a time; whole row tiles are read, hence the 256 spare rows
-    size_t stack_bytes = (size_t)(n + kRowPad) * (d.Dp + d.Hp) * d.esz;
-    // Room for the whole-tree form where it can run: one cell, at most n_trees nodes.  (Larger forests ask for no less than
-    // those, so that their workspace holds any smaller one.)
-    const int64_t n_trees = with_z && n_sig == 1 && !cells ? trees_max_nodes(d.D, d.H, d.esz) : 0;
-    const int64_t n_z = n < n_trees ? n : n_trees;
-    const size_t z_bytes = (size_t)n_z * 4 * round_up(d.H, 16) * 4;
-    if (z_bytes > stack_bytes) stack_bytes = z_bytes;
-    w.stack = c.take<char>(stack_bytes);
-    const bool z_used = n <= n_trees;
-    w.Z = z_used ? static_cast<float *>(w.stack) : nullptr;
     w.row_rec = c.take<int4>((size_t)2 * (n + kRowPad));   // every level position
     w.hs = (d.H == d.Hp) ? nullptr : c.take<char>((size_t)n * d.Hp * d.esz);
-    size_t p_bytes = (size_t)n * d.Hq * d.esz;
-    const size_t fc_bytes = (size_t)n_z * round_up(d.H, 16) * 4;
-    if (fc_bytes > p_bytes) p_bytes = fc_bytes;
-    w.P = c.take<char>(p_bytes);
-    w.FC = z_used ? static_cast<float *>(w.P) : nullptr;
+    // The stacked input of one level at a time (whole row tiles are read, hence the 256 spare rows) and P, or, where whole trees
+    // can run (one cell, at most n_trees nodes), Z and f c.  (Larger forests ask for no less than those, so that their
+    // workspace holds any smaller one.)
+    const int64_t n_trees = with_z && n_sig == 1 && !cells ? trees_max_nodes(d.D, d.H, d.esz) : 0;
+    const int64_t n_z = n < n_trees ? n : n_trees;
+    const size_t stack_bytes = (size_t)round_up((n + kRowPad) * (d.Dp + d.Hp) * (int64_t)d.esz, 256);
+    const size_t level_bytes = stack_bytes + (size_t)n * d.Hq * d.esz;
+    const size_t z_bytes = (size_t)n_z * 4 * round_up(d.H, 16) * 4, tree_bytes = z_bytes + z_bytes / 4;
+    char *shared = c.take<char>(level_bytes > tree_bytes ? level_bytes : tree_bytes);
+    w.stack = shared;
+    if (shared) w.P = shared + stack_bytes;
+    if (shared && n <= n_trees) {
+        w.Z = reinterpret_cast<float *>(shared);
+        w.FC = reinterpret_cast<float *>(shared + z_bytes);
+    }
     w.cs = (d.H == d.Hq) ? nullptr : c.take<float>((size_t)n * d.Hq);
     int n_max = 0;
     for (int t = 0; cells && t < n_sig; ++t)

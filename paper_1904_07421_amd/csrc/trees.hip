@@ -1259,12 +1259,19 @@ int64_t trees_max_nodes(int D, int H, size_t esz) {
     // (214 k), D = 64 337, 332 -> 261, 256 (73 k), 358, 346 -> 352, 344 (106 k), 612, 577 -> 639, 614 (214 k).  H = 200 to 256, which
     // hold fewer weights: D = 300 414 - 429 -> 361 - 389 (73 k), 558 - 586 -> 494 - 528 (106 k), 969 - 1015 -> 950 - 994 (214 k),
     // D = 64 364 - 374 -> 360 - 387 (73 k), 406 - 447 -> 494 - 520 (106 k).  fp32, D = 300: H = 64 234 -> 96 (4.7 k), 1198 -> 539 (214 k),
-    // H = 150 2028 -> 1406, H = 256 296 -> 228 (4.7 k), 2530 -> 2321 (214 k).  H = 384 slower throughout.  The lines lie inside what was
-    // measured, not where the gain ends: no forest beyond 225 k nodes, and for H > 192 no more room than the levels of a forest a few
-    // times larger take anyway (larger forests ask for this room too).
+    // H = 150 2028 -> 1406, H = 256 296 -> 228 (4.7 k), 2530 -> 2321 (214 k).  H = 384 slower throughout.
+    // fp32 and up to 160 units: the largest forest measured, rounded up.  (Its room, 20 bytes a node and unit, is more than the levels
+    // take up to 0.3 - 1 M nodes.)  Wider bf16 cells stop where whole trees gain little or where a forest of kTreesRoomNodes, and
+    // with it every larger one, would be asked for more than its levels take: at D = 300 that is 110 k nodes for H = 192 (262 144
+    // nodes would make its 0.41 GB 0.97).
     if (H > kTreesMaxWidth || ceil_div((int64_t)D * (int64_t)esz, 64) > kXSlabs[sizeof(kXSlabs) / sizeof(int) - 1]) return 0;
     if (esz == 4 || H <= 160) return 262144;
-    return H <= 192 ? (D >= 128 ? 262144 : 106496) : (D >= 256 ? 81920 : 65536);
+    if (H > 192) return D >= 256 ? 81920 : 65536;       // (within that room, too)
+    constexpr int64_t kTreesRoomNodes = 300000;
+    const int kpad = Traits<bf16_t>::BK;
+    const int64_t level_bytes = 2 * (round_up(D, kpad) + round_up(H, kpad) + round_up(H, 8));     // a row of the stacked input, one of P
+    const int64_t room = kTreesRoomNodes * level_bytes / (20 * round_up(H, 16)), gains = D >= 128 ? 262144 : 106496;
+    return room < gains ? room : gains;
 }
 
 // Microseconds by which whole trees take longer than the level kernels (less than zero: they are faster).  What speaks against

@@ -69,3 +69,16 @@ def test_no_room_for_whole_trees_where_they_do_not_run(D, H, dtype, n, plain):
         per_node = (ask(9 * n) - ask(8 * n)) / n
         weights = 8 * 4 * 512 * (_up(D, 64) + 3 * 256 + 64) * 4           # generous: every cell padded to 512 units, fp32
         assert ask(n) <= n * per_node + weights + (1 << 20), (ask(n), n * per_node)
+
+
+@pytest.mark.parametrize("H", [161, 168, 176, 177, 192, 193, 208, 224, 240, 256])
+@pytest.mark.parametrize("D", [1, 64, 65, 127, 128, 192, 255, 256, 300, 512, 640])
+def test_wide_cells_ask_300_000_nodes_for_their_levels_alone(D, H):
+    """bf16 cells of more than 160 units: from there on the plain forward asks for what a table of one such cell takes (that of
+    two cells without the second cell's weights), which never has room for whole trees."""
+    for n in (300000, 450000, 1000000):
+        two, three = (J.jitdb_treelstm_typed_workspace_bytes(n, n - 1, D, H, J.JITDB_BF16, k) for k in (2, 3))
+        assert J.jitdb_treelstm_workspace_bytes(n, n - 1, D, H, J.JITDB_BF16) <= 2 * two - three + 256, (n, D, H)
+    sizes = [1, 1000, 65536, 65537, 81920, 81921, 100000, 110000, 120000, 262144, 262145, 300000, 600000]
+    asked = [J.jitdb_treelstm_workspace_bytes(n, n - 1, D, H, J.JITDB_BF16) for n in sizes]
+    assert asked == sorted(asked)
