@@ -6,7 +6,7 @@
 // nothing from other blocks, so its levels may follow one another behind block barriers.
 //
 //   tree_x_kernel    Z = W x + b for all nodes, spread evenly over the chip; leaves finish their cells right there, the
-//                    other nodes leave Z [node][i | o | u | f] in fp32 (bf16 rows up to 224 wide: tree_x_lds_kernel)
+//                    other nodes leave Z [node][i | o | u | f] in fp32 (narrow bf16 rows: tree_x_lds_kernel)
 //   trees_kernel     block b takes the trees from the first cut at or after id b G to the first at or after (b + 1) G (a
 //                    cut is a place between ids that no edge crosses; jitdb_schedule_t::tree_window says that they are
 //                    close together).  Rows are the block's nodes in (height, id) order, in groups of 16 or 32:
@@ -258,10 +258,10 @@ __device__ __forceinline__ void finish_x_tile(const TreesArgs &a, int lane, int 
     }
 }
 
-// fp32, which the matrix rate bounds, and bf16 from ten slabs on: x rows come straight from memory in operand layout, the next tile's slab requested as soon as
-// this one's is used, its node ids a tile earlier.  No LDS, no barrier: waves of a block take different units of the same nodes,
-// which meet in L1.  (No load may be waited for behind a tile's stores, which it would drain first: 278 k nodes, D 300, H 256, fp32
-// 1110 us with the biases loaded there, 1040 now.)
+// fp32, which the matrix rate bounds, bf16 from ten slabs on, and below as x_through_lds says: x rows come straight from memory in
+// operand layout, the next tile's slab requested as soon as this one's is used, its node ids a tile earlier.  No LDS, no barrier:
+// waves of a block take different units of the same nodes, which meet in L1.  (No load may be waited for behind a tile's stores,
+// which it would drain first: 278 k nodes, D 300, H 256, fp32 1110 us with the biases loaded there, 1040 now.)
 // Leaves have no forget gate.  Its products are left out of their tiles by a branch between the other MFMAs, except in the wide
 // bf16 instances: with the accumulators in accumulation registers the compiler once read an MFMA's result there two instructions
 // behind it where the branch is taken, eight too few, and every tile of leaves came out wrong.  (The build looks for such reads.)
@@ -334,12 +334,13 @@ __device__ __forceinline__ u32x4 load_x_piece_inside(const bf16_t *row, int k0, 
     return v;
 }
 
-// bf16 up to seven slabs: a wave's own loads in operand layout touch 64 lines for 1 KB, and every unit tile's wave repeats
-// them.  A block of four unit tiles fetches its rows once, 16 consecutive bytes a lane, and multiplies from LDS (two buffers, one
-// barrier a group of 16 x_rt rows, the next group's rows in flight meanwhile).  21 k nodes, D 203, H 99: 31.7 -> 25.2 us.  It hides
-// one round trip of a group's rows, so with ten slabs, whose registers hold 16 rows of products and no more, it is slower: 106 k
-// nodes, D 300, H 150 111 -> 162.
+// bf16 up to seven slabs, as x_through_lds says: a wave's own loads in operand layout touch 64 lines for 1 KB, more where rows
+// start on odd elements, and every unit tile's wave repeats them.  A block of four unit tiles fetches its rows once, 16 consecutive
+// bytes a lane, and multiplies from LDS (two buffers, one barrier a group of 16 x_rt rows, the next group's rows in flight
+// meanwhile).  21 k nodes, D 203, H 99: 31.7 -> 25.2 us.  It hides one round trip of a group's rows, so with ten slabs, whose
+// registers hold 16 rows of products and no more, it is slower: 106 k nodes, D 300, H 150 111 -> 162.
 constexpr int kXLdsWaves = 4, kXLdsSlabs = 7, kXLdsRows = 32;
+constexpr int kXLdsAlways = 4, kXLdsManyNodes = 160000;        // slabs, nodes: x_through_lds
 template <bool SAVE, int NS>
 __global__ void __launch_bounds__(kXLdsWaves * 64, kXWavesPerSimd(NS))
 tree_x_lds_kernel(const TreesArgs a) {
@@ -1304,7 +1305,15 @@ static int resident_waves(int ns, size_t esz) {
 static bool resident_forget(int ns, size_t esz) { return esz == 4 ? ns <= 8 : ns <= 5; }
 static bool resident_shares_cu(int ns, size_t esz) { return ns * (int)esz * 4 <= (esz == 4 ? 64 : 16); }
 
-static bool x_through_lds(const TreesArgs &a, size_t esz) { return esz == 2 && a.x_slabs <= kXLdsSlabs; }
+// Which of the two x kernels runs in bf16.  Whole forward, loads in operand layout -> through LDS, H 150 unless stated: up to four
+// slabs D 127 93 -> 84 us (20 k nodes), D 64 80 -> 82 (20 k), 238 -> 228 (106 k), 452 -> 423 (214 k); seven slabs with odd D, D 203
+// 64 -> 59 (5 k), 98 -> 89 (20 k), 297 -> 272 (106 k); rows of whole 128-byte lines, D 192, 1.00 - 1.06 times the time up to 52 k nodes,
+// 0.97 - 1.02 from 106 k on; with other even D, 224 66 -> 69 (10 k), 80 -> 87 (20 k), 127 -> 140 (52 k), 250 -> 258 (106 k), D 200
+// 344 -> 353 (150 k), of all of them 1.03 times the time up to there (H 64 - 160), 1.01 - 1.02 from 180 k on, where D 224 gains up to 5 %.
+static bool x_through_lds(const TreesArgs &a, size_t esz) {
+    if (esz != 2 || a.x_slabs > kXLdsSlabs) return false;
+    return a.x_slabs <= kXLdsAlways || (a.D & 1) != 0 || a.D % 64 == 0 || a.n >= kXLdsManyNodes;
+}
 
 // Fills the launch geometry of `a`; false if the forest is better run level by level.
 bool plan_trees(TreesArgs &a, size_t esz, const TreesShape &s) {
@@ -1398,10 +1407,14 @@ bool plan_trees(TreesArgs &a, size_t esz, const TreesShape &s) {
 namespace {
 template <typename T, bool SAVE, int NS>
 int launch_tree_x(const TreesArgs &a, hipStream_t st) {
-    if constexpr (sizeof(T) == 2 && NS <= kXLdsSlabs)
-        tree_x_lds_kernel<SAVE, NS><<<(unsigned)(8 * ceil_div(a.x_chunks * ceil_div(a.n_ut, kXLdsWaves), 8)), kXLdsWaves * 64, 0, st>>>(a);
-    else
-        tree_x_kernel<T, SAVE, NS><<<(unsigned)(8 * ceil_div((int64_t)a.x_chunks * a.n_ut, 32)), 256, 0, st>>>(a);
+    if constexpr (sizeof(T) == 2 && NS <= kXLdsSlabs) {
+        if (NS <= kXLdsAlways || x_through_lds(a, sizeof(T))) {
+            tree_x_lds_kernel<SAVE, NS><<<(unsigned)(8 * ceil_div(a.x_chunks * ceil_div(a.n_ut, kXLdsWaves), 8)), kXLdsWaves * 64, 0, st>>>(a);
+            JITDB_LAUNCH_CHECK();
+            return JITDB_OK;
+        }
+    }
+    if constexpr (sizeof(T) == 4 || NS > kXLdsAlways) tree_x_kernel<T, SAVE, NS><<<(unsigned)(8 * ceil_div((int64_t)a.x_chunks * a.n_ut, 32)), 256, 0, st>>>(a);
     JITDB_LAUNCH_CHECK();
     return JITDB_OK;
 }

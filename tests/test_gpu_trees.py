@@ -158,6 +158,17 @@ def test_x_part_over_several_groups(c_oracle, D, H):
     _check_whole(c_oracle, p, D, H, "bf16")
 
 
+@pytest.mark.parametrize("trees,D,H,save", [(350, 130, 150, False), (350, 160, 99, True), (350, 192, 200, True), (350, 222, 65, False), (2440, 130, 16, True),
+                                            (2440, 222, 16, False)])
+def test_x_part_of_even_widths_past_128(c_oracle, trees, D, H, save):
+    """bf16 rows of more than 128 and at most 224 columns, an even number: in operand layout, from 160 000 nodes on through LDS (odd
+    ones and rows of whole lines always)."""
+    p = _lay_out([make_forest(1)] * trees)
+    print(f"x part D={D} H={H} N={p.shape[0]} save={save}", flush=True)
+    assert (p.shape[0] >= 160000) == (trees > 2000)
+    _check_whole(c_oracle, p, D, H, "bf16", save)
+
+
 RECURRENT = [("near", "f32", (16, 17, 64, 65, 127, 128, 129, 160, 161)),
              ("near", "bf16", (16, 50, 64, 65, 128, 129, 160, 161, 192, 193, 208, 209, 240, 256)),
              ("near-full", "f32", (129, 160)), ("near-full", "bf16", (161, 192)),
