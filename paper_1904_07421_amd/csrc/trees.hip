@@ -7,22 +7,24 @@
 //
 //   tree_x_kernel    Z = W x + b for all nodes, spread evenly over the chip; leaves finish their cells right there, the
 //                    other nodes leave Z [node][i | o | u | f] in fp32 (narrow bf16 rows: tree_x_lds_kernel)
-//   trees_kernel     block b takes the trees from the first cut at or after id b G to the first at or after (b + 1) G (a
+//   trees_resident_kernel, trees_kernel
+//                    block b takes the trees from the first cut at or after id b G to the first at or after (b + 1) G (a
 //                    cut is a place between ids that no edge crosses; jitdb_schedule_t::tree_window says that they are
-//                    close together).  Rows are the block's nodes in (height, id) order, in groups of 16 or 32:
+//                    close together).  Rows are the block's nodes in (height, id) order, in groups of 16 to 64:
 //                      gather    for a row of level l: sum of the children's h (operand, LDS) and of their f c (fp32, LDS)
 //                      (barrier) i, o, u = Z + U hs;  c = i u + sum f c,  h = o tanh c; h goes out and into LDS
 //                      (barrier) P = U_f h from LDS; f = sigmoid(Z_f of the PARENT + P), f c goes out for the parent
 //                    A child's forget gate needs nothing of its parent but Z_f, which is there already: no P row and no
-//                    c row is fetched by a parent, child sums are the only gather, in 16-byte pieces with eight
+//                    c row is fetched by a parent, child sums are the only gather, in 16-byte pieces with several
 //                    children in flight.
 //                      (barrier, at the end of a level)
 //
 // A wave multiplies the gates of 16 hidden units (v_mfma_f32_16x16x32_bf16 / 16x16x4_f32), so the cell update finds a unit's
-// gates in one lane.  A comes from LDS, the weights from L2 in 1 KB pieces (64-byte slabs of 16 packed rows), kTreeAhead
-// slabs ahead.  What bounds it: the chain of three barriers and four memory latencies per level (bf16), the fp32
-// matrix rate on 16-row tiles (fp32).  Wide cells take up to 16 waves and run one block a compute unit.  Where the weights of 16
-// units fit a wave's registers, trees_resident_kernel runs instead.
+// gates in one lane.  A comes from LDS.  Where the weights of a wave's units fit its registers (bf16, and fp32 up to 128 units, or
+// 160 with the block's h and f c in LDS) trees_resident_kernel loads them once: what bounds it are the barriers and memory
+// latencies of each level.  Otherwise (fp32) trees_kernel reads them from L2 every level, in 1 KB pieces (64-byte slabs of 16
+// packed rows), kTreeAhead slabs ahead, and is bound by that and by the fp32 matrix rate on 16-row tiles; its wide cells
+// take up to 16 waves and run one block a compute unit.
 #include "level_common.h"
 
 namespace jitdb {
@@ -534,7 +536,7 @@ __device__ __forceinline__ void gather_sums(const TreesArgs &a, const TreeBlock 
 }
 
 // The cells of rows [r0, r_end): at most 16 NRT, NRT == 0: at most four, one per lane quarter.
-template <typename T, bool SAVE, int NRT>
+template <bool SAVE, int NRT>
 __device__ __forceinline__ void level_group(const TreesArgs &a, const TreeBlock &b, int r0, int r_end) {
     constexpr int NA = NRT ? NRT : 1, NV = NRT ? 4 : 1;
     for (int ut = b.wave; ut < a.n_ut; ut += b.n_waves) {
@@ -555,7 +557,7 @@ __device__ __forceinline__ void level_group(const TreesArgs &a, const TreeBlock 
                 }
             }
         const char *a_lane = b.A + (NRT ? n : lane & 3) * a.pitch_h + hf * 16;
-        tree_gemm<T, NRT, 3>(acc, [&](int rt, int s) { return *reinterpret_cast<const u32x4 *>(a_lane + rt * 16 * a.pitch_h + s * 64); },
+        tree_gemm<float, NRT, 3>(acc, [&](int rt, int s) { return *reinterpret_cast<const u32x4 *>(a_lane + rt * 16 * a.pitch_h + s * 64); },
                              tree_weights(a, lane, ut, a.sx_packed, 0), (int64_t)a.NPU * 64, a.sh);
 #pragma unroll
         for (int rt = 0; rt < NA; ++rt) {
@@ -566,16 +568,16 @@ __device__ __forceinline__ void level_group(const TreesArgs &a, const TreeBlock 
                 float z[3];
 #pragma unroll
                 for (int g = 0; g < 3; ++g) z[g] = NRT ? acc[rt][g][v] : z4[g] + quarter_sum(acc[0][g], lane);
-                const float gi = sigmoid_t<T>(z[0]), go = sigmoid_t<T>(z[1]), gu = tanh_t<T>(z[2]);
+                const float gi = sigmoid_t<float>(z[0]), go = sigmoid_t<float>(z[1]), gu = tanh_t<float>(z[2]);
                 const float c = gi * gu + b.Fs[rr * a.Hz + unit];
                 b.Fs[rr * a.Hz + unit] = c;          // for the forget gates' step
-                const T hv = unit < a.H ? from_f32<T>(go * tanh_t<T>(c)) : T(0);
-                *reinterpret_cast<T *>(b.Ht + rr * a.pitch_h + unit * (int)sizeof(T)) = hv;
+                const float hv = unit < a.H ? go * tanh_t<float>(c) : 0.0f;
+                *reinterpret_cast<float *>(b.Ht + rr * a.pitch_h + unit * 4) = hv;
                 if (r >= r_end) continue;
                 const int64_t node = b.lo + b.order[r];
-                store_unit<T>(a, node, unit, c, hv);
+                store_unit<float>(a, node, unit, c, hv);
                 if constexpr (SAVE) {
-                    if (unit < a.H) save_gates<T>(a, node, unit, gi, go, gu);
+                    if (unit < a.H) save_gates<float>(a, node, unit, gi, go, gu);
                 }
             }
         }
@@ -584,7 +586,7 @@ __device__ __forceinline__ void level_group(const TreesArgs &a, const TreeBlock 
 
 // f c of rows [r0, r_end) from P = U_f h, f with the parent's Z_f.  LEAF: h and c come from memory (tree_x_kernel has
 // finished the leaves' cells), else from LDS.
-template <typename T, bool SAVE, int NRT, bool LEAF>
+template <bool SAVE, int NRT, bool LEAF>
 __device__ __forceinline__ void forget_tile(const TreesArgs &a, const TreeBlock &b, int ut, int r0, int r_end) {
     constexpr int NA = NRT ? NRT : 1, NV = NRT ? 4 : 1;
     const int lane = fresh_lane(b.lane), hf = lane >> 4, n = lane & 15;
@@ -608,12 +610,12 @@ __device__ __forceinline__ void forget_tile(const TreesArgs &a, const TreeBlock 
 #pragma unroll
         for (int rt = 0; rt < NA; ++rt) {
             const int r = r0 + (NRT ? rt * 16 + n : lane & 3);
-            row[rt] = static_cast<const char *>(a.hs) + (int64_t)(b.lo + b.order[r < r_end ? r : r_end - 1]) * a.Hp * (int)sizeof(T) + hf * 16;
+            row[rt] = static_cast<const char *>(a.hs) + (int64_t)(b.lo + b.order[r < r_end ? r : r_end - 1]) * a.Hp * 4 + hf * 16;
         }
-        tree_gemm<T, NRT, 1, true>(acc, [&](int rt, int s) { return *reinterpret_cast<const u32x4 *>(row[rt] + s * 64); }, w, (int64_t)a.NPU * 64, a.sh);
+        tree_gemm<float, NRT, 1, true>(acc, [&](int rt, int s) { return *reinterpret_cast<const u32x4 *>(row[rt] + s * 64); }, w, (int64_t)a.NPU * 64, a.sh);
     } else {
         const char *a_lane = b.Ht + (NRT ? n : lane & 3) * a.pitch_h + hf * 16;
-        tree_gemm<T, NRT, 1>(acc, [&](int rt, int s) { return *reinterpret_cast<const u32x4 *>(a_lane + rt * 16 * a.pitch_h + s * 64); }, w,
+        tree_gemm<float, NRT, 1>(acc, [&](int rt, int s) { return *reinterpret_cast<const u32x4 *>(a_lane + rt * 16 * a.pitch_h + s * 64); }, w,
                              (int64_t)a.NPU * 64, a.sh);
     }
 #pragma unroll
@@ -625,10 +627,10 @@ __device__ __forceinline__ void forget_tile(const TreesArgs &a, const TreeBlock 
             if (r >= r_end) continue;
             const int i = b.order[r];
             if (b.par[i] == kNoLocal) continue;
-            const float f = sigmoid_t<T>(pf + zf[rt][v]);
+            const float f = sigmoid_t<float>(pf + zf[rt][v]);
             a.FC[(int64_t)(b.lo + i) * a.Hz + unit] = unit < a.H ? f * c[rt][v] : 0.0f;
             if constexpr (SAVE) {
-                if (unit < a.H) static_cast<T *>(a.fgate)[(int64_t)(b.lo + i) * a.H + unit] = from_f32<T>(f);
+                if (unit < a.H) static_cast<float *>(a.fgate)[(int64_t)(b.lo + i) * a.H + unit] = f;
             }
         }
 }
@@ -740,7 +742,7 @@ __device__ __forceinline__ bool view_trees(const TreesArgs &a, char *lds, TreeBl
     return true;
 }
 
-template <typename T, bool SAVE>
+template <bool SAVE>
 __global__ void __launch_bounds__(kTreeMaxWaves * 64, 4)
 trees_kernel(const TreesArgs a) {
     extern __shared__ __attribute__((aligned(16))) char lds[];
@@ -764,10 +766,10 @@ trees_kernel(const TreesArgs a) {
         const int n_leaf = m.cnt[0], n32 = n_leaf >> 5, rest = n_leaf & 31, n_tasks = (n32 + (rest > 0)) * a.n_ut;
         for (int q = b.wave; q < n_tasks; q += b.n_waves) {
             const int tile = q / a.n_ut, ut = q - tile * a.n_ut;
-            if (tile < n32) forget_tile<T, SAVE, 2, true>(a, b, ut, tile * 32, tile * 32 + 32);
-            else if (rest > 16) forget_tile<T, SAVE, 2, true>(a, b, ut, tile * 32, n_leaf);
-            else if (rest > 4) forget_tile<T, SAVE, 1, true>(a, b, ut, tile * 32, n_leaf);
-            else forget_tile<T, SAVE, 0, true>(a, b, ut, tile * 32, n_leaf);
+            if (tile < n32) forget_tile<SAVE, 2, true>(a, b, ut, tile * 32, tile * 32 + 32);
+            else if (rest > 16) forget_tile<SAVE, 2, true>(a, b, ut, tile * 32, n_leaf);
+            else if (rest > 4) forget_tile<SAVE, 1, true>(a, b, ut, tile * 32, n_leaf);
+            else forget_tile<SAVE, 0, true>(a, b, ut, tile * 32, n_leaf);
         }
         __syncthreads();
     }
@@ -776,17 +778,17 @@ trees_kernel(const TreesArgs a) {
         for (int r0 = l0; r0 < l1; r0 += a.group_rows) {
             const int r_end = r0 + a.group_rows < l1 ? r0 + a.group_rows : l1, rows = r_end - r0;
             if (r0 > l0) lds_barrier();               // the group before is done with Fs
-            gather_sums<T, 1, 8>(a, b, r0, r_end, a.sh * 4);
+            gather_sums<float, 1, 8>(a, b, r0, r_end, a.sh * 4);
             lds_barrier();
-            if (rows > 16) level_group<T, SAVE, 2>(a, b, r0, r_end);
-            else if (rows > 4) level_group<T, SAVE, 1>(a, b, r0, r_end);
-            else level_group<T, SAVE, 0>(a, b, r0, r_end);
+            if (rows > 16) level_group<SAVE, 2>(a, b, r0, r_end);
+            else if (rows > 4) level_group<SAVE, 1>(a, b, r0, r_end);
+            else level_group<SAVE, 0>(a, b, r0, r_end);
             if (l + 1 >= n_lvl) continue;
             lds_barrier();
             for (int ut = b.wave; ut < a.n_ut; ut += b.n_waves) {
-                if (rows > 16) forget_tile<T, SAVE, 2, false>(a, b, ut, r0, r_end);
-                else if (rows > 4) forget_tile<T, SAVE, 1, false>(a, b, ut, r0, r_end);
-                else forget_tile<T, SAVE, 0, false>(a, b, ut, r0, r_end);
+                if (rows > 16) forget_tile<SAVE, 2, false>(a, b, ut, r0, r_end);
+                else if (rows > 4) forget_tile<SAVE, 1, false>(a, b, ut, r0, r_end);
+                else forget_tile<SAVE, 0, false>(a, b, ut, r0, r_end);
             }
         }
         __syncthreads();                              // the next level's sums read what this one left in memory
@@ -798,7 +800,8 @@ trees_kernel(const TreesArgs a) {
 // a level.  Where the four gates' weights of 16 units fit the registers of one wave, a wave loads them once, while the block works
 // out its trees, and keeps them over all levels; bf16 wider than 160 and fp32 wider than 128 have room for i, o and u, and
 // for f's first slabs in what LDS has left.  bf16 wider than 192 takes eight waves of two unit tiles each: 16 waves would
-// have 32 registers beside the weights, eight have 64 (groups of 32 rows then, so that LDS holds most of f's weights).
+// have 32 registers beside the weights, eight have 64 (inner levels in groups of 16 rows, leaves 32 at a time, so that LDS holds
+// all or all but a slab of f's weights).
 // Schedule + forward, from L2 -> so: 71 nodes H 150 fp32 99 -> 89 us, 4.7 k nodes H 150 fp32 156 -> 141, 21 k nodes H 99 bf16
 // 150 -> 125, 54 k nodes H 180 bf16 314 -> 258, 106 k nodes H 150 bf16 368 -> 316, 216 k nodes H 64 fp32 372 -> 367.  What bounds it:
 // the 4x4 MFMAs of three waves on a SIMD and the barriers (few rows), memory traffic of Z, h and f c (many rows).
@@ -1282,7 +1285,11 @@ int64_t trees_max_nodes(int D, int H, size_t esz) {
 // two or three has several times that); the chain levels above multiply no x.
 // Fitted to 1400 measured forwards: D 16 - 300, H 40 - 256, one tree of 16 - 250 nodes, interleaved trees of 1 - 10 nodes, stars,
 // trees of 1 - 250 nodes filed one after another up to 225 k nodes, chains.  The time over that of the faster form, mean and
-// worst: always whole trees 1.18 and 4.3 in fp32, 1.13 and 3.1 in bf16; by this rule 1.005 and 1.3, 1.006 and 1.4.
+// worst: always whole trees 1.18 and 4.3 in fp32, 1.13 and 3.1 in bf16; by this rule 1.005 and 1.3, 1.006 and 1.4.  Those forwards
+// ran on trees_kernel, which read the weights once a level, in bf16 too.  Timed both ways since most run on
+// trees_resident_kernel, the chosen form takes in 120 forwards of filed trees 1.01 of the faster one's time in the mean and 1.13 at
+// worst, in 45 of interleaved trees of 1 - 10 nodes and single trees 1.03 and 1.45; the worst are 154 k nodes in trees of 1 - 3, D 32,
+// H 100, which run whole: bf16, ids over each other in runs of 120, 238 us against 164, fp32, runs of 250, 501 against 386.
 double trees_excess_us(const TreesArgs &a, size_t esz, const TreesShape &s) {
     const bool f32 = esz == 4;
     const double h = a.H / 100.0, d = a.D / 100.0, below = s.n_below / 1000.0, chain = (a.n - s.n_below) / 1000.0;
@@ -1298,12 +1305,12 @@ double trees_excess_us(const TreesArgs &a, size_t esz, const TreesShape &s) {
 
 // Weight slabs of the resident form's instances (0 waves: not for this type).
 constexpr int kResSlabs[] = {2, 4, 5, 6, 8, 10};
-static int resident_waves(int ns, size_t esz) {
+static constexpr int resident_waves(int ns, size_t esz) {
     if (esz == 2) return ns == 2 || ns == 4 || ns == 8 ? 8 : ns == 5 || ns == 6 ? 12 : 0;
     return ns == 4 || ns == 8 ? 8 : ns == 10 ? 12 : 0;
 }
-static bool resident_forget(int ns, size_t esz) { return esz == 4 ? ns <= 8 : ns <= 5; }
-static bool resident_shares_cu(int ns, size_t esz) { return ns * (int)esz * 4 <= (esz == 4 ? 64 : 16); }
+static constexpr bool resident_forget(int ns, size_t esz) { return esz == 4 ? ns <= 8 : ns <= 5; }
+static constexpr bool resident_shares_cu(int ns, size_t esz) { return ns * (int)esz * 4 <= (esz == 4 ? 64 : 16); }
 
 // Which of the two x kernels runs in bf16.  Whole forward, loads in operand layout -> through LDS, H 150 unless stated: up to four
 // slabs D 127 93 -> 84 us (20 k nodes), D 64 80 -> 82 (20 k), 238 -> 228 (106 k), 452 -> 423 (214 k); seven slabs with odd D, D 203
@@ -1420,6 +1427,8 @@ int launch_tree_x(const TreesArgs &a, hipStream_t st) {
 }
 template <typename T, bool SAVE, int NS>
 int launch_resident(const TreesArgs &a, hipStream_t st) {
+    static_assert(resident_waves(NS, sizeof(T)) == kResWaves<T, NS> && resident_forget(NS, sizeof(T)) == kResForget<T, NS> &&
+                  resident_shares_cu(NS, sizeof(T)) == (kResPerSimd<T, NS> * 4 >= 2 * kResWaves<T, NS>), "plan_trees sizes LDS and blocks by these");
     auto fn = &trees_resident_kernel<T, SAVE, NS, !kResFarOnly<T, NS>>;
     if constexpr (!kResNearOnly<T, NS>)
         if (!a.near_rows) fn = &trees_resident_kernel<T, SAVE, NS, false>;
@@ -1448,11 +1457,14 @@ int launch_trees_t(const TreesArgs &a, hipStream_t st) {
         case 8: return launch_resident<T, SAVE, 8>(a, st);
         case 10: if constexpr (sizeof(T) == 4) return launch_resident<T, SAVE, 10>(a, st); break;
     }
-    if (a.lds_bytes > 64 * 1024)
-        JITDB_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void *>(&trees_kernel<T, SAVE>), hipFuncAttributeMaxDynamicSharedMemorySize, kTreeLdsMax));
-    trees_kernel<T, SAVE><<<a.n_blocks, a.n_waves * 64, a.lds_bytes, st>>>(a);
-    JITDB_LAUNCH_CHECK();
-    return JITDB_OK;
+    if constexpr (sizeof(T) == 4) {
+        if (a.lds_bytes > 64 * 1024)
+            JITDB_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void *>(&trees_kernel<SAVE>), hipFuncAttributeMaxDynamicSharedMemorySize, kTreeLdsMax));
+        trees_kernel<SAVE><<<a.n_blocks, a.n_waves * 64, a.lds_bytes, st>>>(a);
+        JITDB_LAUNCH_CHECK();
+        return JITDB_OK;
+    }
+    return JITDB_E_BADARG;                      // (every bf16 width has its instance)
 }
 }  // namespace
 
