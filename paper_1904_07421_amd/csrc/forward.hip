@@ -104,13 +104,17 @@ pack_weights_kernel(const PackArgs p) {
 // more levels is left in position order: its levels are too small for the order to matter.
 // The longer the runs of equal arity, the fewer passes of the cell update mix child lists of different length: a
 // large forest takes windows of 16384 positions (blocks of 1024 threads, a launch of their own); measured on
-// 2.36 M nodes, windows of 4096 -> 8192 -> 16384 rows take the internal levels from 5.26 to 5.17 to 5.10 ms
-// (32768: 5.13) for 0.04 / 0.085 ms more in this step.
+// 2.36 M nodes, windows of 4096 -> 8192 -> 16384 rows take the internal levels from 5.26 to 5.17 to 5.10 ms (32768: 5.13).
+// What bounds the step is what one compute unit can ask for: every record touches scattered lines, so the loads of a record
+// are as few and as wide as they can be (child_ptr's two entries in one, the first four child ids in one: 2.36 M nodes
+// 117 -> 86 us), and a forest whose large windows are fewer than 32 blocks leaves the chip idle and takes the small ones.  Schedule
+// and forward with large / small windows, us: 296 k nodes H 512 bf16 1720 / 1696, H 256 1037 / 1001, four cells 1851 / 1792, N-ary
+// 1506 / 1479; 432 k nodes H 300 fp32 6298 / 6269; 595 k H 512 2993 / 2997; 1.18 M 5561 / 5631; 2.36 M 10 651 / 10 767.
 constexpr int kRecPerThread = 16;
 constexpr int kRecWindow = kRecPerThread * kThreads;          // 4096
 constexpr int kRecThreadsLarge = 1024;
 constexpr int kRecWindowLarge = kRecPerThread * kRecThreadsLarge;   // 16384
-constexpr int64_t kRecLargeMinNodes = 262144;      // forests of at least this many nodes take the large windows
+constexpr int64_t kRecLargeMinNodes = 524288;      // forests of at least this many nodes take the large windows
 
 // window `window` of the records (NT threads, kRecPerThread records each)
 template <int NT>
@@ -119,6 +123,8 @@ __device__ __forceinline__ void row_record_body(const int32_t *__restrict__ perm
                                                 const int32_t *__restrict__ child_idx,
                                                 int4 *__restrict__ row_rec, int n, int window) {
     constexpr int kWin = kRecPerThread * NT;
+    typedef u32x2 __attribute__((aligned(4))) u32x2a;
+    typedef u32x4 __attribute__((aligned(4))) u32x4a;
     __shared__ int s_count[256];   // per key: count, then the next free slot
     __shared__ int s_scan[256];
     const int t = threadIdx.x;
@@ -143,8 +149,9 @@ __device__ __forceinline__ void row_record_body(const int32_t *__restrict__ perm
     int hgt[kRecPerThread];
 #pragma unroll
     for (int i = 0; i < kRecPerThread; ++i) {
-        cb[i] = child_ptr[node[i]];
-        ar[i] = child_ptr[node[i] + 1] - cb[i];
+        const u32x2a q = *reinterpret_cast<const u32x2a *>(child_ptr + node[i]);
+        cb[i] = (int)q[0];
+        ar[i] = (int)(q[1] - q[0]);
         hgt[i] = sorted ? height[node[i]] : 0;
     }
 #pragma unroll
@@ -170,26 +177,34 @@ __device__ __forceinline__ void row_record_body(const int32_t *__restrict__ perm
     }
     if (t < 256) s_count[t] = s_scan[t] - v;
     __syncthreads();
-    // the first four child ids of every record, again all loads of the thread side by side (a child position the
-    // node does not have reads the node's first position, or, for a leaf, whatever stands at its CSR start, which
-    // lies inside the array: child_ptr <= E < N; the value is replaced by -1)
+    // The first four child ids of every record, again all loads of the thread side by side: sixteen bytes from its CSR start on,
+    // from the array's last four entries where it starts behind those (child_ptr <= E < N, and the array has N entries).  Ids that
+    // are not the node's are replaced by -1.
     // (in two halves: eight records' ids are in flight at a time, which keeps the large-window form in its registers)
 #pragma unroll
     for (int half = 0; half < 2; ++half) {
         constexpr int HB = kRecPerThread / 2;
-        int kid[HB][4];
+        u32x4 kid[HB];
 #pragma unroll
-        for (int i = 0; i < HB; ++i)
+        for (int i = 0; i < HB; ++i) {
+            const int c = cb[half * HB + i];
+            if (n >= 4) {
+                kid[i] = *reinterpret_cast<const u32x4a *>(child_idx + (c < n - 4 ? c : n - 4));
+            } else {
 #pragma unroll
-            for (int j = 0; j < 4; ++j) kid[i][j] = child_idx[cb[half * HB + i] + (j < ar[half * HB + i] ? j : 0)];
+                for (int j = 0; j < 4; ++j) kid[i][j] = (uint32_t)child_idx[j < ar[half * HB + i] ? c + j : 0];
+            }
+        }
 #pragma unroll
         for (int k = 0; k < HB; ++k) {
             const int i = half * HB + k;
             if (node[i] < 0) continue;
             const int64_t q = sorted ? (int64_t)w0 + atomicAdd(&s_count[key[i]], 1) : (int64_t)w0 + i * NT + t;
+            u32x4 v = kid[k];
+            for (int up = n >= 4 ? cb[i] - (n - 4) : 0; up > 0; --up) v = u32x4{v[1], v[2], v[3], 0u};
             row_rec[2 * q] = make_int4(node[i], ar[i], cb[i], 0);
-            row_rec[2 * q + 1] = make_int4(0 < ar[i] ? kid[k][0] : -1, 1 < ar[i] ? kid[k][1] : -1,
-                                           2 < ar[i] ? kid[k][2] : -1, 3 < ar[i] ? kid[k][3] : -1);
+            row_rec[2 * q + 1] = make_int4(0 < ar[i] ? (int)v[0] : -1, 1 < ar[i] ? (int)v[1] : -1,
+                                           2 < ar[i] ? (int)v[2] : -1, 3 < ar[i] ? (int)v[3] : -1);
         }
     }
 }
