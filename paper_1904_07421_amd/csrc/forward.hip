@@ -51,42 +51,50 @@ namespace {
 // Packed row r = tile*128 + gate*32 + uu holds gate `gate` of hidden unit tile*32 + uu as
 // [ W row (D values, zero padded to Dp) | U row (H values, zero padded to Hp) ].  There are
 // NPU >= NP rows; rows of units >= H are zero.
+// Several cells that lie one behind the other (a typed table's) are packed in one launch.
 struct PackArgs {
     const void *W, *U; const float *b;
-    int D, H, Dp, Hp, NP, NPU;
+    int D, H, Dp, Hp, NP, NPU, n_cells;
     void *Bp; float *bp;
 };
+__host__ __device__ __forceinline__ int64_t pack_pieces(int NPU, int Dp, int Hp, size_t esz) { return (int64_t)NPU * (Dp + Hp) * (int64_t)esz / 16; }
 
-// block `block` of `n_blocks` (NT threads each, stride loop)
+// block `block` of `n_blocks` (NT threads each, stride loop).  A thread writes sixteen bytes, in the order of the packed memory;
+// their source is sixteen bytes of one row of W or U, on any element boundary.
 template <typename T, int NT = kThreads>
-__device__ __forceinline__ void pack_weights_body(const T *__restrict__ W, const T *__restrict__ U,
-                                                  const float *__restrict__ b, int D, int H, int Dp, int Hp,
-                                                  int NP, int NPU, T *__restrict__ Bp, float *__restrict__ bp,
-                                                  int64_t block, int64_t n_blocks) {
-    const int Kp = Dp + Hp;
-    const int64_t total = (int64_t)NPU * Kp;
+__device__ __forceinline__ void pack_weights_body(const PackArgs &p, int64_t block, int64_t n_blocks) {
+    constexpr int VEC = Traits<T>::VEC;
+    const int64_t per_cell = pack_pieces(p.NPU, p.Dp, p.Hp, sizeof(T)), total = per_cell * p.n_cells;
     for (int64_t idx = block * NT + threadIdx.x; idx < total; idx += n_blocks * NT) {
-        const int r = (int)(idx / Kp), k = (int)(idx % Kp);
-        const int tile = r / kGateTile, gate = (r % kGateTile) / kUnit, uu = r % kUnit;
-        const int unit = tile * kUnit + uu;
-        const bool row_ok = unit < H;
-        const int64_t src = (int64_t)gate * H + unit;
-        T v = T(0);
-        if (row_ok) {
-            if (k < D) v = W[src * D + k];
-            else if (k >= Dp && k - Dp < H) v = U[src * H + (k - Dp)];
+        int cell = 0;
+        uint32_t i = (uint32_t)idx;                          // (a cell has at most 2^31 pieces)
+        if (p.n_cells > 1) { cell = (int)(idx / per_cell); i = (uint32_t)(idx - cell * per_cell); }
+        const uint32_t row_slab = i >> 2;
+        const int s = (int)(row_slab / (uint32_t)p.NPU), r = (int)(row_slab - (uint32_t)s * p.NPU), q = (int)(i & 3);
+        const int tile = r / kGateTile, gate = (r % kGateTile) / kUnit, unit = tile * kUnit + r % kUnit;
+        const int64_t src = (int64_t)cell * 4 * p.H + (int64_t)gate * p.H + unit;
+        const int k = (s * 4 + q) * VEC, of = k < p.Dp ? p.D : p.H, at = k < p.Dp ? k : k - p.Dp;
+        u32x4 v = {0u, 0u, 0u, 0u};
+        if (unit < p.H && at < of) {
+            const T *row = static_cast<const T *>(k < p.Dp ? p.W : p.U) + src * of + at;
+            if (at + VEC <= of) {
+                __builtin_memcpy(&v, row, 16);
+            } else {
+                T e[VEC];
+#pragma unroll
+                for (int j = 0; j < VEC; ++j) e[j] = at + j < of ? row[j] : T(0);
+                __builtin_memcpy(&v, e, 16);
+            }
         }
-        *reinterpret_cast<T *>(reinterpret_cast<char *>(Bp) +
-                               operand_offset(r, (int64_t)k * sizeof(T), NPU)) = v;
-        if (k == 0 && r < NP) bp[r] = row_ok ? b[src] : 0.0f;
+        *reinterpret_cast<u32x4 *>(static_cast<char *>(p.Bp) + (cell * per_cell + i) * 16) = v;
+        if (k == 0 && r < p.NP) p.bp[(int64_t)cell * p.NP + r] = unit < p.H ? p.b[src] : 0.0f;
     }
 }
 
 template <typename T>
 __global__ void __launch_bounds__(kThreads)
 pack_weights_kernel(const PackArgs p) {
-    pack_weights_body<T>(static_cast<const T *>(p.W), static_cast<const T *>(p.U), p.b, p.D, p.H, p.Dp, p.Hp, p.NP,
-                         p.NPU, static_cast<T *>(p.Bp), p.bp, blockIdx.x, gridDim.x);
+    pack_weights_body<T>(p, blockIdx.x, gridDim.x);
 }
 
 // ---- row records -------------------------------------------------------------------
@@ -220,9 +228,7 @@ prepare_kernel(const int32_t *__restrict__ perm, const int32_t *__restrict__ key
     if ((int)blockIdx.x < n_windows)
         row_record_body<kThreads>(perm, key, child_ptr, child_idx, row_rec, n, first_window + (int)blockIdx.x);
     else
-        pack_weights_body<T>(static_cast<const T *>(p.W), static_cast<const T *>(p.U), p.b, p.D, p.H, p.Dp, p.Hp,
-                             p.NP, p.NPU, static_cast<T *>(p.Bp), p.bp,
-                             (int64_t)blockIdx.x - n_windows, (int64_t)gridDim.x - n_windows);
+        pack_weights_body<T>(p, (int64_t)blockIdx.x - n_windows, (int64_t)gridDim.x - n_windows);
 }
 
 // The same launch for large forests: row records in windows of kRecWindowLarge positions, blocks of 1024 threads.
@@ -234,9 +240,7 @@ prepare_large_kernel(const int32_t *__restrict__ perm, const int32_t *__restrict
     if ((int)blockIdx.x < n_windows)
         row_record_body<kRecThreadsLarge>(perm, key, child_ptr, child_idx, row_rec, n, blockIdx.x);
     else
-        pack_weights_body<T, kRecThreadsLarge>(static_cast<const T *>(p.W), static_cast<const T *>(p.U), p.b, p.D, p.H,
-                                               p.Dp, p.Hp, p.NP, p.NPU, static_cast<T *>(p.Bp), p.bp,
-                                               (int64_t)blockIdx.x - n_windows, (int64_t)gridDim.x - n_windows);
+        pack_weights_body<T, kRecThreadsLarge>(p, (int64_t)blockIdx.x - n_windows, (int64_t)gridDim.x - n_windows);
 }
 
 // ---- stack -------------------------------------------------------------------------
@@ -1330,9 +1334,10 @@ int run_forward(const void *x, const void *W, const void *U, const float *b, con
         trees = plan_trees(ta, d.esz, shape);
     }
 
-    {   // row records and packed weights (one launch; further cells' weights one launch each)
-        const int64_t total = (int64_t)d.NPU * (d.Dp + d.Hp);
-        const unsigned pack_grid = (unsigned)(ceil_div(total, kThreads) < 4096 ? ceil_div(total, kThreads) : 4096);
+    {   // row records and packed weights (one launch; cells named one by one: the further ones' weights one launch each)
+        const bool one_behind_other = !cells;                       // the cells' weights: packed with the first one's
+        const int64_t pieces = pack_pieces(d.NPU, d.Dp, d.Hp, d.esz) * (one_behind_other ? n_sig : 1);
+        const unsigned pack_grid = (unsigned)(ceil_div(pieces, kThreads) < 4096 ? ceil_div(pieces, kThreads) : 4096);
         auto pack_args = [&](int t) {
             PackArgs p;
             if (cells) {
@@ -1342,7 +1347,7 @@ int run_forward(const void *x, const void *W, const void *U, const float *b, con
                 p.U = static_cast<const T *>(U) + (size_t)t * 4 * d.H * d.H;
                 p.b = b + (size_t)t * 4 * d.H;
             }
-            p.D = d.D; p.H = d.H; p.Dp = d.Dp; p.Hp = d.Hp; p.NP = d.NP; p.NPU = d.NPU;
+            p.D = d.D; p.H = d.H; p.Dp = d.Dp; p.Hp = d.Hp; p.NP = d.NP; p.NPU = d.NPU; p.n_cells = one_behind_other ? n_sig : 1;
             p.Bp = static_cast<char *>(w.Bp) + packed_w_bytes(d) * t;
             p.bp = w.bp + (size_t)d.NP * t;
             return p;
@@ -1363,7 +1368,7 @@ int run_forward(const void *x, const void *W, const void *U, const float *b, con
             ScopedLaunchTimer tm(JITDB_K_PACK, 0, st);
             if (large) {
                 const int n_windows = (int)ceil_div(s->n_nodes, kRecWindowLarge);
-                const unsigned pg = pack_here ? (unsigned)(ceil_div(total, kRecThreadsLarge) < 1024 ? ceil_div(total, kRecThreadsLarge) : 1024) : 0u;
+                const unsigned pg = pack_here ? (unsigned)(ceil_div(pieces, kRecThreadsLarge) < 1024 ? ceil_div(pieces, kRecThreadsLarge) : 1024) : 0u;
                 prepare_large_kernel<T><<<(unsigned)n_windows + pg, kRecThreadsLarge, 0, st>>>(
                     s->perm, slots ? slots->key : s->height, s->child_ptr, s->child_idx, w.row_rec, (int)s->n_nodes,
                     n_windows, pack_args(0));
@@ -1375,7 +1380,7 @@ int run_forward(const void *x, const void *W, const void *U, const float *b, con
             }
             JITDB_LAUNCH_CHECK();
         }
-        for (int t = 1; t < n_sig && !packed; ++t) {
+        for (int t = 1; t < n_sig && !packed && !one_behind_other; ++t) {
             if (is_nary(t)) continue;
             ScopedLaunchTimer tm(JITDB_K_PACK, 0, st);
             pack_weights_kernel<T><<<pack_grid, kThreads, 0, st>>>(pack_args(t));
@@ -1869,22 +1874,16 @@ extern "C" int jitdb_treelstm_pack(const void *W, const void *U, const float *b,
     const Dims d = make_dims(D, H, dtype);
     if (packed_bytes < packed_total_bytes(d, n_sig)) return JITDB_E_WORKSPACE;
     hipStream_t st = (hipStream_t)hip_stream;
-    const int64_t total = (int64_t)d.NPU * (d.Dp + d.Hp);
-    const unsigned grid = (unsigned)(ceil_div(total, kThreads) < 4096 ? ceil_div(total, kThreads) : 4096);
-    float *bp0 = reinterpret_cast<float *>(static_cast<char *>(packed) + round_up(packed_w_bytes(d) * n_sig, 256));
-    for (int t = 0; t < n_sig; ++t) {
-        PackArgs p;
-        const size_t esz = d.esz;
-        p.W = static_cast<const char *>(W) + (size_t)t * 4 * d.H * d.D * esz;
-        p.U = static_cast<const char *>(U) + (size_t)t * 4 * d.H * d.H * esz;
-        p.b = b + (size_t)t * 4 * d.H;
-        p.D = d.D; p.H = d.H; p.Dp = d.Dp; p.Hp = d.Hp; p.NP = d.NP; p.NPU = d.NPU;
-        p.Bp = static_cast<char *>(packed) + packed_w_bytes(d) * t;
-        p.bp = bp0 + (size_t)d.NP * t;
-        if (dtype == JITDB_F32) pack_weights_kernel<float><<<grid, kThreads, 0, st>>>(p);
-        else pack_weights_kernel<bf16_t><<<grid, kThreads, 0, st>>>(p);
-        JITDB_LAUNCH_CHECK();
-    }
+    const int64_t pieces = pack_pieces(d.NPU, d.Dp, d.Hp, d.esz) * n_sig;
+    const unsigned grid = (unsigned)(ceil_div(pieces, kThreads) < 4096 ? ceil_div(pieces, kThreads) : 4096);
+    PackArgs p;
+    p.W = W; p.U = U; p.b = b;
+    p.D = d.D; p.H = d.H; p.Dp = d.Dp; p.Hp = d.Hp; p.NP = d.NP; p.NPU = d.NPU; p.n_cells = n_sig;
+    p.Bp = packed;
+    p.bp = reinterpret_cast<float *>(static_cast<char *>(packed) + round_up(packed_w_bytes(d) * n_sig, 256));
+    if (dtype == JITDB_F32) pack_weights_kernel<float><<<grid, kThreads, 0, st>>>(p);
+    else pack_weights_kernel<bf16_t><<<grid, kThreads, 0, st>>>(p);
+    JITDB_LAUNCH_CHECK();
     return JITDB_OK;
 }
 
