@@ -24,6 +24,7 @@
 // All atomics are integer add / max / or (order independent).
 
 #include "common.h"
+#include "pinned.h"
 
 namespace jitdb {
 namespace {

@@ -611,38 +611,8 @@ place_kernel(const LocalArgs a) {
 
 // ---- host side ---------------------------------------------------------------------------
 // Reports in pinned memory.  A call takes one, its kernels write it, the call reads it after its synchronisation and
-// gives it back; at most kReportsKept stay allocated between calls.
-constexpr size_t kReportsKept = 16;
-struct ReportPool {
-    std::mutex lock;
-    std::vector<LocalReport *> free_list;
-    LocalReport *take() {
-        {
-            std::lock_guard<std::mutex> g(lock);
-            if (!free_list.empty()) {
-                LocalReport *r = free_list.back();
-                free_list.pop_back();
-                return r;
-            }
-        }
-        void *p = nullptr;
-        if (hipHostMalloc(&p, sizeof(LocalReport), hipHostMallocPortable | hipHostMallocMapped) != hipSuccess) {
-            (void)hipGetLastError();
-            return nullptr;
-        }
-        return static_cast<LocalReport *>(p);
-    }
-    void give(LocalReport *r) {
-        {
-            std::lock_guard<std::mutex> g(lock);
-            if (free_list.size() < kReportsKept) {
-                free_list.push_back(r);
-                return;
-            }
-        }
-        (void)hipHostFree(r);
-    }
-};
+// gives it back.
+using ReportPool = PinnedPool<LocalReport>;
 inline ReportPool &report_pool() {
     static ReportPool *pool = new ReportPool();      // never destroyed: the runtime may be gone before static destructors run
     return *pool;
@@ -705,18 +675,6 @@ inline int launch_local_schedule(const LocalArgs &a, hipStream_t st) {
     report_done_kernel<<<1, 64, 0, st>>>(a.report);
     JITDB_LAUNCH_CHECK();
     return JITDB_OK;
-}
-
-// Waits until ready() sees its word of the report.  A word in pinned memory is seen about 4 us sooner than hipStreamSynchronize returns (8.3
-// against 12 us for an empty kernel), which is a large part of a small forest's analysis; work that takes longer
-// than the spin is waited for in the ordinary way, which also reports a failed kernel.
-template <typename Ready>
-inline hipError_t wait_for_report(hipStream_t st, Ready &&ready) {
-    for (int i = 0; i < 20000; ++i) {
-        if (ready()) return hipSuccess;
-        __builtin_ia32_pause();
-    }
-    return hipStreamSynchronize(st);
 }
 
 }  // namespace
