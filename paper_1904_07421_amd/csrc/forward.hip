@@ -18,8 +18,8 @@
 //                      128 x 256 tiles: one 32 x 32-unit tile per wave, operands straight
 //                      from L2; a thin level's projection and the next level's stack
 //                      step share one launch (thin_proj_stack_kernel)
-//   chain_kernel       a thin level whose nodes all have exactly one child (sequences, the long
-//                      tail of a deep forest) as ONE launch: x and the child's h read in place,
+//   chain_kernel       the thin levels whose nodes all have exactly one child (sequences, the long
+//                      tail of a deep forest) in ONE launch: x and the child's h read in place,
 //                      all four gates over the full K, no stack step and no projection
 //   tree_x_kernel, trees_kernel   (trees.hip) a forest of small trees filed one after another: all of the above in two launches
 //
@@ -124,12 +124,12 @@ constexpr int kRecThreadsLarge = 1024;
 constexpr int kRecWindowLarge = kRecPerThread * kRecThreadsLarge;   // 16384
 constexpr int64_t kRecLargeMinNodes = 524288;      // forests of at least this many nodes take the large windows
 
-// window `window` of the records (NT threads, kRecPerThread records each)
+// window `window` of the records (NT threads, kRecPerThread records each) of the positions below `end`, in a forest of n nodes
 template <int NT>
 __device__ __forceinline__ void row_record_body(const int32_t *__restrict__ perm, const int32_t *__restrict__ height,
                                                 const int32_t *__restrict__ child_ptr,
                                                 const int32_t *__restrict__ child_idx,
-                                                int4 *__restrict__ row_rec, int n, int window) {
+                                                int4 *__restrict__ row_rec, int n, int end, int window) {
     constexpr int kWin = kRecPerThread * NT;
     typedef u32x2 __attribute__((aligned(4))) u32x2a;
     typedef u32x4 __attribute__((aligned(4))) u32x4a;
@@ -137,7 +137,7 @@ __device__ __forceinline__ void row_record_body(const int32_t *__restrict__ perm
     __shared__ int s_scan[256];
     const int t = threadIdx.x;
     const int w0 = window * kWin;
-    const int wn = (n - w0) < kWin ? (n - w0) : kWin;
+    const int wn = (end - w0) < kWin ? (end - w0) : kWin;
     const int lvl0 = height[perm[w0]];
     const int lvl1 = height[perm[w0 + wn - 1]];
     const bool sorted = (lvl1 - lvl0) < 16;
@@ -224,9 +224,10 @@ template <typename T>
 __global__ void __launch_bounds__(kThreads)
 prepare_kernel(const int32_t *__restrict__ perm, const int32_t *__restrict__ key,
                const int32_t *__restrict__ child_ptr, const int32_t *__restrict__ child_idx,
-               int4 *__restrict__ row_rec, int n, int first_window, int n_windows, const PackArgs p) {
+               int4 *__restrict__ row_rec, int n, int end, int n_windows, const PackArgs p, int *__restrict__ clear, int64_t n_clear) {
+    for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < n_clear; i += (int64_t)gridDim.x * kThreads) clear[i] = 0;
     if ((int)blockIdx.x < n_windows)
-        row_record_body<kThreads>(perm, key, child_ptr, child_idx, row_rec, n, first_window + (int)blockIdx.x);
+        row_record_body<kThreads>(perm, key, child_ptr, child_idx, row_rec, n, end, (int)blockIdx.x);
     else
         pack_weights_body<T>(p, (int64_t)blockIdx.x - n_windows, (int64_t)gridDim.x - n_windows);
 }
@@ -236,9 +237,10 @@ template <typename T>
 __global__ void __launch_bounds__(kRecThreadsLarge)
 prepare_large_kernel(const int32_t *__restrict__ perm, const int32_t *__restrict__ key,
                      const int32_t *__restrict__ child_ptr, const int32_t *__restrict__ child_idx,
-                     int4 *__restrict__ row_rec, int n, int n_windows, const PackArgs p) {
+                     int4 *__restrict__ row_rec, int n, int end, int n_windows, const PackArgs p, int *__restrict__ clear, int64_t n_clear) {
+    for (int64_t i = (int64_t)blockIdx.x * kRecThreadsLarge + threadIdx.x; i < n_clear; i += (int64_t)gridDim.x * kRecThreadsLarge) clear[i] = 0;
     if ((int)blockIdx.x < n_windows)
-        row_record_body<kRecThreadsLarge>(perm, key, child_ptr, child_idx, row_rec, n, blockIdx.x);
+        row_record_body<kRecThreadsLarge>(perm, key, child_ptr, child_idx, row_rec, n, end, blockIdx.x);
     else
         pack_weights_body<T, kRecThreadsLarge>(p, (int64_t)blockIdx.x - n_windows, (int64_t)gridDim.x - n_windows);
 }
@@ -915,134 +917,228 @@ nary_thin_kernel(const LevelArgs a, const NaryEpi e, const void *__restrict__ Bx
 }
 
 // ---- chain levels ---------------------------------------------------------------------
-// A level in which every node has exactly one child (sequences filed as chains, the long thin
-// tail of a forest) needs neither the stack step nor the projection: the child sum is the
-// child's h, read in place, and U_f h_k belongs to the same row, so the forget gate is a fourth
-// full-K product like i, o and u.  One launch per level instead of two; such a level costs its
-// chain of dependent launches and the memory latencies inside them, not its work, so the kernel
-// is arranged to meet every latency once:
+// A level in which every node has exactly one child (sequences filed as chains, the long thin tail of a forest) needs
+// neither the stack step nor the projection: the child sum is the child's h, read in place, and U_f h_k belongs to the
+// same row, so the forget gate is a fourth full-K product like i, o and u.  What such levels cost is not their work but
+// the string of dependent trips to memory inside each of them and the gap between launches, so all of them run in
+// one launch (kChainLevels of them; more take another launch) that follows each row through the levels:
 //
-//   * tiles and waves as in thin_kernel (32 rows x 32 units, wave g = gate g);
-//   * the four waves need the same A rows [x_j | h_child], so the block fetches the tile's whole
-//     A (32 rows x K) once, all loads in flight together, 32 threads per row on consecutive
-//     16-byte pieces (zero past D, past K and without a child), into LDS; one barrier;
-//   * the K loop then has no barrier: A fragments from LDS (the next one read while this one is
-//     multiplied), the wave's own weight rows from global memory / L2, kChainAhead K groups ahead,
-//     the first turn requested before anything else in the kernel;
-//   * the gates meet in LDS and each of the first four waves finishes eight of the tile's rows;
-//   * KS > 1: 4 KS waves, wave w multiplies gate w % 4 over part w / 4 of K.  A level of a few hundred rows leaves
-//     most SIMDs idle, and one wave per gate spends the level's time on its own chain of MFMAs (fp32: four
-//     64-cycle MFMAs per 32 bytes of K); KS waves per gate cut that chain, and the weight loads and fragment
-//     reads in it, KS-fold.  The parts' sums are added in the order of the parts.
+//   * a tile is 16 RT rows x 32 units, wave w multiplies gate w % 4; a block takes ONE tile and is done;
+//   * blocks draw their tiles from a counter, in the order of the levels, and a tile waits for the row tiles of
+//     the level below that hold its rows' children: each has a word that counts its finished unit tiles.  Whatever a block
+//     waits for was drawn before, by a block that runs already, so every wait ends, whichever blocks share the chip;
+//   * everything that does not depend on the child is there before the wait: the wave's weights (the first kChainAhead K
+//     groups), the row's ids, x rows in LDS or Z.  Two or more blocks of later levels sit beside the one that multiplies;
+//   * behind the wait the block fetches the children's h once, all loads in flight together, into LDS; the K loop has no
+//     barrier (A fragments from LDS, weights kChainAhead groups ahead); the gates meet in LDS and each of
+//     the first four waves finishes eight of the tile's rows;
+//   * h and c of a child may come from another XCD's block: they are written and read past the L2s (agent-scope
+//     accesses), the word is raised once the stores have arrived (vmcnt 0 in every wave, then the block's barrier);
+//   * US = 2 (fp32, whose MFMAs are a long chain for one wave): eight waves, wave w has units 16 (w / 4) .. of its gate;
+//   * RT = 1 spreads a level over more blocks and shortens each one's part of the chain; where bf16 levels have
+//     kChainWideTiles such tiles on average the chip is full and RT = 2 asks half as much of the weights and the words.
 //
-// Needs D % 4 == 0 (an 8- / 16-byte piece of an x row is inside D or outside) and an A tile that
-// fits LDS (chain_lds_bytes) beside the KS sets of pre-activations.
-constexpr int kChainAhead = 16;                         // weight K groups in flight per wave
-constexpr int kChainLdsTotal = 156 * 1024;              // LDS one block may take in all (static + dynamic)
-constexpr int kChainStatic = 1024;                      // static LDS of chain_kernel beside its pre-activations (row ids), rounded up
-__host__ __device__ constexpr int chain_zt_bytes(int ks) { return 4 * ks * 32 * kEpiStride * 4; }
-// dynamic LDS chain_kernel<T, KS> may ask for
-constexpr int chain_lds_max(int ks) { return kChainLdsTotal - kChainStatic - chain_zt_bytes(ks); }
+// Schedule + forward, chains / stars / trees in turn, us, one launch a level (13 - 20 us each) -> RT = 2 -> RT = 1:
+// 4096 trees of up to 128 nodes, D 300, H 256 fp32 3567 -> 3231 -> 3033, bf16 2052 -> 1644 -> 1691; 500 trees H 150 fp32
+// 1443 -> 1090 -> 891, bf16 981 -> 608 -> 539; 12 k trees, D 128, H 128, bf16 1978 -> 1612 -> 1786; x part not in Z: 2 k trees of
+// up to 64, H 400 fp32 2643 -> 2478 -> 2301, H 512 bf16 1506 -> 1437 -> 1484.  What is left of a level (about 5 us where it is
+// small) is the way of h from one block to the next: stores, word, look, loads.  (Words side by side in one line, all blocks
+// looking at it: 4084 instead of 3255 in the first case.)
+//
+// Needs D % 4 == 0 (an 8- / 16-byte piece of an x row is inside D or outside) and rows of A that leave room for two blocks on a CU.
+constexpr int kChainAhead = 16;                         // weight loads in flight per wave
+constexpr int kChainLevels = 256;                       // levels one launch may hold (its table travels with the arguments)
+constexpr int kChainMaxKBytes = 4304;                   // of a row, RT = 1: two blocks share a CU's LDS
+constexpr int kChainMaxKBytes2 = 1840;                  // ... RT = 2
+constexpr int kChainWideTiles = 192;                    // (330 tiles a level: 3 % for RT = 2, 500: 10 %, 31: 13 % for RT = 1)
 // LDS pitch of an A row: K bytes + 16, so that 16 lanes' 16-byte reads of one K group fall in 64 different banks
-__host__ __device__ inline int chain_row_pitch(int k_bytes) { return k_bytes + 16; }
-inline size_t chain_lds_bytes(int k_bytes) { return (size_t)32 * chain_row_pitch(k_bytes); }
+__host__ __device__ inline constexpr int chain_row_pitch(int k_bytes) { return k_bytes + 16; }
+inline constexpr int chain_lds_bytes(int k_bytes, int rt) { return 16 * rt * chain_row_pitch(k_bytes); }
+constexpr int kChainLdsMax = chain_lds_bytes(kChainMaxKBytes, 1);
+static_assert(2 * (kChainLdsMax + 4 * 16 * kEpiStride * 4 + 1024) <= 160 * 1024, "two blocks share a CU");
+static_assert(chain_lds_bytes(kChainMaxKBytes2, 2) <= kChainLdsMax && 2 * (chain_lds_bytes(kChainMaxKBytes2, 2) + 4 * 32 * kEpiStride * 4 + 1024) <= 160 * 1024, "two blocks share a CU");
 
-// Validity of the two halves of a 16-byte piece, K bytes [kb, kb + 16), of a chain row's A operand.
+struct ChainArgs {
+    const int32_t *perm, *inv_perm, *child_ptr, *child_idx;     // inv_perm may be nullptr: a tile then waits for the whole level below
+    int *ticket;                         // tiles drawn so far
+    int *done;                           // per row tile of the launch, `stride` words apart: unit tiles finished
+    int stride;
+    int n_levels;
+    int tiles[kChainLevels + 1];         // row tiles before the launch's level
+    int pos[kChainLevels + 1];           // positions of the launch's levels
+};
+
+__device__ __forceinline__ void store_shared(void *p, const u32x2 &v) {
+    __hip_atomic_store(static_cast<uint64_t *>(p), __builtin_bit_cast(uint64_t, v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ u32x2 load_shared(const void *p) {
+    return __builtin_bit_cast(u32x2, __hip_atomic_load(static_cast<const uint64_t *>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+}
+
+// store_state for rows that a later tile of the same launch reads: the copies it reads (hs_out and cs) leave past the L2.
 template <typename T>
-__device__ __forceinline__ void chain_piece_ok(bool kid_ok, int kb, int x_bytes, int k_bytes, int D, bool &ok0, bool &ok1) {
-    constexpr int ESZ = (int)sizeof(T);
-    const bool in_x = kb < x_bytes;
-    const int k0 = kb / ESZ;
-    ok0 = in_x ? (k0 < D) : (kb < k_bytes && kid_ok);
-    ok1 = (ESZ == 2 && in_x) ? (k0 + 4 < D) : ok0;       // bf16: the second four elements of the piece
+__device__ __forceinline__ void store_state_shared(const LevelArgs &a, int64_t nd, int unit0, const float4 &cc, const float4 &go) {
+    const float c4[4] = {cc.x, cc.y, cc.z, cc.w};
+    const float o4[4] = {go.x, go.y, go.z, go.w};
+    T hv[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) hv[j] = unit0 + j < a.H ? from_f32<T>(o4[j] * tanh_t<T>(c4[j])) : T(0);
+    if (unit0 < a.Hp) {                  // (H != Hp: pad columns of the padded copy are zeroed)
+        T *dst = static_cast<T *>(a.hs_out) + nd * a.Hp + unit0;
+        if constexpr (sizeof(T) == 4) {
+            store_shared(dst, u32x2{__float_as_uint(hv[0]), __float_as_uint(hv[1])});
+            store_shared(dst + 2, u32x2{__float_as_uint(hv[2]), __float_as_uint(hv[3])});
+        } else {
+            store_shared(dst, u32x2{(uint32_t)hv[0] | ((uint32_t)hv[1] << 16), (uint32_t)hv[2] | ((uint32_t)hv[3] << 16)});
+        }
+    }
+    if (unit0 < a.Hq) {
+        float *dst = a.cs + nd * a.Hq + unit0;
+        store_shared(dst, u32x2{__float_as_uint(c4[0]), __float_as_uint(c4[1])});
+        store_shared(dst + 2, u32x2{__float_as_uint(c4[2]), __float_as_uint(c4[3])});
+    }
+    if (a.hs_out != a.h_out) {
+        T *dst = static_cast<T *>(a.h_out) + nd * a.H + unit0;
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            if (unit0 + j < a.H) dst[j] = hv[j];
+    }
+    if (a.cs != a.c_out) {
+        float *dst = a.c_out + nd * a.H + unit0;
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            if (unit0 + j < a.H) dst[j] = c4[j];
+    }
 }
 
 //
 // HAS_Z: the x part of the pre-activations (and the bias) is in Z already (tree_x_kernel has been over all nodes): A is the
 // child's h alone and K is H.
-template <typename T, int KS, bool HAS_Z = false>
-__global__ void __launch_bounds__(kThinWaves * 64 * KS, KS == 1 ? 2 : 1)
-chain_kernel(const LevelArgs a) {
+template <typename T, int US, int RT, bool HAS_Z>
+__global__ void __launch_bounds__(kThinWaves * 64 * US, 4)
+chain_kernel(const LevelArgs a, const ChainArgs lv) {
     constexpr int ESZ = (int)sizeof(T);
-    extern __shared__ __attribute__((aligned(16))) char a_lds[];          // [32][chain_row_pitch]
-    __shared__ __attribute__((aligned(16))) float zt[4 * KS][32 * kEpiStride];  // pre-activations, [part][gate][row][unit]
-    __shared__ int s_node[32];
-    __shared__ int s_kid[32];
-    static_assert(sizeof(zt) == chain_zt_bytes(KS) && 2 * 32 * 4 <= kChainStatic, "chain_lds_max counts these");
+    constexpr int ROWS = 16 * RT;
+    constexpr int NB = 2 / US;                                            // tiles of 16 units per wave
+    constexpr int RING = kChainAhead / NB;                                // slabs of weights in flight
+    extern __shared__ __attribute__((aligned(16))) char a_lds[];          // [16 RT][chain_row_pitch]
+    __shared__ __attribute__((aligned(16))) float zt[4][ROWS * kEpiStride];   // pre-activations, [gate][row][unit]
+    __shared__ int s_node[ROWS];
+    __shared__ int s_kid[ROWS];
+    __shared__ int s_tile, s_level;
+    __shared__ __attribute__((aligned(16))) float s_bias[HAS_Z ? 4 : kGateTile];
+    static_assert(kChainLevels <= kThinWaves * 64, "a thread per level");
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int gate = wave & 3, part = wave >> 2;
-    const int hf = lane >> 5, l32 = lane & 31;
-    const int tile = blockIdx.x;
-    const int row0 = (tile / a.n_col_tiles) * 32;
-    const int col = tile % a.n_col_tiles;     // unit tile
+    const int gate = wave & 3, half = wave >> 2;
+    const int q4 = lane >> 4, l16 = lane & 15;
+    if (tid == 0) s_tile = __hip_atomic_fetch_add(lv.ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const int t_lo = lv.tiles[tid < lv.n_levels ? tid : lv.n_levels], t_hi = lv.tiles[tid < lv.n_levels ? tid + 1 : lv.n_levels];
+    __syncthreads();
+    const int tile = __builtin_amdgcn_readfirstlane(s_tile);     // (the grid has as many blocks as there are tiles)
+    const int row_tile = tile / a.n_col_tiles;
+    const int col = tile - row_tile * a.n_col_tiles;             // unit tile
+    if (t_lo <= row_tile && row_tile < t_hi) s_level = tid;
 
-    // ---- weights: lane (l32, hf) supplies row l32 of the wave's gate, bytes [hf*16, +16) of each 32-byte K
-    //      group.  Every load of the ring is unconditional (a group index past the end is clamped to the
-    //      last group, whose data is then not used): the number of loads between a request and its use is
-    //      the same on every path, so the waits the compiler places are counted, not "all".
+    // ---- weights: lane (l16, q4) supplies row l16 of a tile of the wave's gate, bytes [q4*16, +16) of each slab (64 bytes of K).
+    //      Every load of the ring is unconditional (a slab past the end is clamped to the last one, whose data is
+    //      then not used): the number of loads between a request and its use is the same on every path, so the waits
+    //      the compiler places are counted, not "all".
     const int x_bytes = HAS_Z ? 0 : a.Dp * ESZ;          // K bytes of the x part
-    const int k_bytes = x_bytes + a.Hp * ESZ;
+    const int h_bytes = a.Hp * ESZ;
+    const int k_bytes = x_bytes + h_bytes;
     const int pitch = chain_row_pitch(k_bytes);
-    const int n_all = k_bytes / 32;                      // K groups of a row (a multiple of four)
-    // this wave's part of them, [g_begin, g_begin + n_groups): whole slabs (pairs of groups)
-    const int per_part = ((n_all + KS - 1) / KS + 1) & ~1;
-    const int g_begin = part * per_part < n_all ? part * per_part : n_all;
-    const int n_groups = n_all - g_begin < per_part ? n_all - g_begin : per_part;
-    const int last_group = n_groups > 0 ? g_begin + n_groups - 1 : n_all - 1;   // (a part without groups loads the row's last one, unused)
-    const int64_t brow = (int64_t)col * kGateTile + gate * kUnit + l32;
-    const char *bp = static_cast<const char *>(a.Bp) + operand_offset(brow, HAS_Z ? (int64_t)a.Dp * ESZ : 0, a.NPU) + hf * 16;
-    const int64_t b_pair = (int64_t)a.NPU * 64;
-    u32x4 fb[kChainAhead];
-    auto request = [&](int g, int slot) __attribute__((always_inline)) {
-        fb[slot] = *reinterpret_cast<const u32x4 *>(bp + (int64_t)(g >> 1) * b_pair + (g & 1) * 32);
+    const int n_slabs = k_bytes / 64;
+    const int64_t brow = (int64_t)col * kGateTile + gate * kUnit + half * 16 + l16;
+    const char *bp = static_cast<const char *>(a.Bp) + operand_offset(brow, HAS_Z ? (int64_t)a.Dp * ESZ : 0, a.NPU) + q4 * 16;
+    const int64_t b_slab = (int64_t)a.NPU * 64;
+    u32x4 fb[RING][NB];
+    auto request = [&](int s, int slot) __attribute__((always_inline)) {
+        const char *p = bp + (int64_t)(s < n_slabs ? s : n_slabs - 1) * b_slab;
+#pragma unroll
+        for (int q = 0; q < NB; ++q) fb[slot][q] = *reinterpret_cast<const u32x4 *>(p + q * 16 * 64);
     };
 #pragma unroll
-    for (int s = 0; s < kChainAhead; ++s) request(g_begin + s < last_group ? g_begin + s : last_group, s);
-    __builtin_amdgcn_sched_barrier(0);
+    for (int s = 0; s < RING; ++s) request(s, s);
+    __syncthreads();
 
-    // ---- the tile's A: thread t moves pieces (t & 31) + 32 i of rows (t >> 5) + RPP j
-    {
-        constexpr int RPP = 8 * KS;           // rows per pass of the block's threads
-        constexpr int NJ = 32 / RPP;
-        const char *src_x[NJ], *src_h[NJ];
-        bool kid_ok[NJ];
+    // ---- the rows: node, child, and, in wave 0, the row tiles below that hold the children
+    const int l = __builtin_amdgcn_readfirstlane(s_level);
+    const int rt_level = row_tile - lv.tiles[l];                 // row tile within the level
+    const int row0 = lv.pos[l] + rt_level * ROWS;
+    const int n_rows = lv.pos[l + 1] - row0 < ROWS ? lv.pos[l + 1] - row0 : ROWS;
+    const int rt_below = l > 0 ? lv.tiles[l - 1] : 0;
+    int wait_lo = 0, wait_hi = -1;                               // row tiles of the launch
+    if (wave == 0) {
+        const int mine = lane & (ROWS - 1), r = mine < n_rows ? mine : n_rows - 1;   // past the end: computed twice, stored never
+        const int node = lv.perm[row0 + r];
+        typedef u32x2 __attribute__((aligned(4))) u32x2a;
+        const u32x2a cp = *reinterpret_cast<const u32x2a *>(lv.child_ptr + node);
+        const int kid = (int)cp[1] > (int)cp[0] ? lv.child_idx[(int)cp[0]] : -1;   // (always one, in a level this kernel is launched for)
+        if (lane < ROWS) {
+            s_node[mine] = mine < n_rows ? node : -1;
+            s_kid[mine] = kid;
+        }
+        if (l > 0) {
+            const int last = lv.tiles[l] - 1 - rt_below;         // (the bounds hold whatever the schedule's arrays say)
+            int lo = 0, hi = last;
+            if (lv.inv_perm) {
+                int q = (lv.inv_perm[kid < 0 ? 0 : kid] - lv.pos[l - 1]) / ROWS;
+                q = q < 0 ? 0 : q > last ? last : q;
+                lo = hi = q;
+#pragma unroll
+                for (int d = 1; d < ROWS; d <<= 1) {
+                    const int lo2 = __shfl_xor(lo, d, 64), hi2 = __shfl_xor(hi, d, 64);
+                    lo = lo2 < lo ? lo2 : lo;
+                    hi = hi2 > hi ? hi2 : hi;
+                }
+            }
+            wait_lo = rt_below + lo;
+            wait_hi = rt_below + hi;
+        }
+    }
+    __syncthreads();
+
+    // ---- what does not depend on the child.  A: thread t moves pieces (t & 31) + 32 i of rows (t >> 5) + RPP j
+    constexpr int RPP = 8 * US;           // rows per pass of the block's threads
+    constexpr int NJ = ROWS / RPP;
+    constexpr int kUpdateWaves = ROWS / 8;
+    const int tr = (wave & (kUpdateWaves - 1)) * 8 + (lane >> 3);   // the cell update's row and units
+    const int u4 = (lane & 7) * 4;
+    const int unit0 = col * kUnit + u4;
+    const int node = s_node[tr];
+    float4 bq[4];
+    if constexpr (HAS_Z) {
+        if (wave < kUpdateWaves) {      // Z with the bias in it (unit groups past its width read the first)
+            const float *z = a.Z + (int64_t)(node < 0 ? 0 : node) * 4 * a.Hz + (unit0 < a.Hz ? unit0 : 0);
+#pragma unroll
+            for (int g = 0; g < 4; ++g) bq[g] = *reinterpret_cast<const float4 *>(z + g * a.Hz);
+        }
+    } else {
+        if (tid < kGateTile) s_bias[tid] = a.bp[col * kGateTile + tid];
+        const int n_rounds = (x_bytes / 16 + 31) / 32;
+        const char *src[NJ];
 #pragma unroll
         for (int j = 0; j < NJ; ++j) {
-            const int rl = (tid >> 5) + RPP * j;
-            int r = row0 + rl;
-            const bool ok = r < a.n_rows;
-            if (!ok) r = a.n_rows - 1;                // computed twice, stored never
-            const int4 r0 = a.row_rec[2 * (int64_t)r];
-            const int4 r1 = a.row_rec[2 * (int64_t)r + 1];
-            kid_ok[j] = r0.y >= 1;                    // always, in a level this kernel is launched for
-            src_x[j] = static_cast<const char *>(a.x) + (int64_t)r0.x * a.D * ESZ;
-            src_h[j] = static_cast<const char *>(a.hs) + (int64_t)(kid_ok[j] ? r1.x : 0) * a.Hp * ESZ;
-            if ((tid & 31) == 0) {                    // the rows as the cell update wants them
-                s_node[rl] = ok ? r0.x : -1;
-                s_kid[rl] = (ok && kid_ok[j]) ? r1.x : -1;
-            }
+            const int nd = s_node[(tid >> 5) + RPP * j];
+            src[j] = static_cast<const char *>(a.x) + (int64_t)(nd < 0 ? 0 : nd) * a.D * ESZ;
         }
-        const int n_rounds = (k_bytes / 16 + 31) / 32;
-#pragma unroll 4
+#pragma unroll 2
         for (int i = 0; i < n_rounds; ++i) {
             const int kb = ((tid & 31) + 32 * i) * 16;
-            if (kb >= k_bytes) break;
+            if (kb >= x_bytes) break;
+            // a piece past D comes from the start of the row (always valid: D >= 4) and is replaced by zero
+            const bool ok0 = kb / ESZ < a.D, ok1 = ESZ == 4 ? ok0 : kb / ESZ + 4 < a.D;
 #pragma unroll
             for (int j = 0; j < NJ; ++j) {
-                bool ok0, ok1;
-                chain_piece_ok<T>(kid_ok[j], kb, x_bytes, k_bytes, a.D, ok0, ok1);
-                // a piece that is not to be read comes from the start of the x row (always valid: D >= 4)
-                // and is replaced by zero
-                const char *p = kb < x_bytes ? src_x[j] + kb : src_h[j] + (kb - x_bytes);
                 u32x4 v;
                 if constexpr (ESZ == 4) {
-                    v = *reinterpret_cast<const u32x4 *>(ok0 ? p : src_x[j]);
+                    v = *reinterpret_cast<const u32x4 *>(ok0 ? src[j] + kb : src[j]);
                 } else {
-                    const u32x2 q0 = *reinterpret_cast<const u32x2 *>(ok0 ? p : src_x[j]);
-                    const u32x2 q1 = *reinterpret_cast<const u32x2 *>(ok1 ? p + 8 : src_x[j]);
+                    const u32x2 q0 = *reinterpret_cast<const u32x2 *>(ok0 ? src[j] + kb : src[j]);
+                    const u32x2 q1 = *reinterpret_cast<const u32x2 *>(ok1 ? src[j] + kb + 8 : src[j]);
                     v[0] = q0[0]; v[1] = q0[1]; v[2] = q1[0]; v[3] = q1[1];
                 }
                 v[0] = ok0 ? v[0] : 0u; v[1] = ok0 ? v[1] : 0u; v[2] = ok1 ? v[2] : 0u; v[3] = ok1 ? v[3] : 0u;
@@ -1050,86 +1146,128 @@ chain_kernel(const LevelArgs a) {
             }
         }
     }
-    floatx16 acc;
-#pragma unroll
-    for (int v = 0; v < 16; ++v) acc[v] = 0.0f;
+
+    // ---- wait for the children (wave 0; the others stand at the barrier)
+    for (int w = wait_lo; w <= wait_hi; w += 64) {
+        const int *word = lv.done + (int64_t)(w + lane <= wait_hi ? w + lane : wait_hi) * lv.stride;
+        while (!__all(__hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= a.n_col_tiles)) __builtin_amdgcn_s_sleep(4);
+    }
+    asm volatile("" ::: "memory");
     __syncthreads();
 
-    // ---- K loop: whole turns of the ring, then the rest (a multiple of 4 groups)
-    const char *abuf = a_lds + l32 * pitch + hf * 16;    // this lane's A fragment, K group 0
-    const int n_full = n_groups / kChainAhead;
-    const int g_end = g_begin + n_groups;
-    u32x4 fa = *reinterpret_cast<const u32x4 *>(abuf + (g_begin < n_all ? g_begin : n_all - 1) * 32);
-    for (int c = 0; c < n_full; ++c) {
-        const int g0 = g_begin + c * kChainAhead;
-#pragma unroll
-        for (int s = 0; s < kChainAhead; ++s) {
-            // the next A fragment leaves LDS while this one is multiplied
-            const int gnext = g0 + s + 1 < g_end ? g0 + s + 1 : last_group;
-            const u32x4 fa_next = *reinterpret_cast<const u32x4 *>(abuf + gnext * 32);
-            mfma_step<T>(fa, fb[s], acc);
-            const int gn = g0 + s + kChainAhead;
-            request(gn < last_group ? gn : last_group, s);
-            __builtin_amdgcn_sched_barrier(0);      // the ring is refilled slot by slot, not in a burst at the end
-            fa = fa_next;
-        }
-    }
-    {
-        const int g0 = g_begin + n_full * kChainAhead;
-        const int tail = g_end - g0;
-#pragma unroll
-        for (int s = 0; s < kChainAhead; ++s)
-            if (s < tail) {
-                const int gnext = g0 + s + 1 < g_end ? g0 + s + 1 : last_group;
-                const u32x4 fa_next = *reinterpret_cast<const u32x4 *>(abuf + gnext * 32);
-                mfma_step<T>(fa, fb[s], acc);
-                fa = fa_next;
-            }
-    }
-
-    // ---- the gates meet in LDS; wave w < 4 finishes rows 8 w .. 8 w + 7: eight lanes per row, four units per lane
-#pragma unroll
-    for (int v = 0; v < 16; ++v) {
-        const int rl = (v >> 2) * 8 + hf * 4 + (v & 3);
-        zt[wave][rl * kEpiStride + l32] = acc[v];
-    }
-    __syncthreads();
-    if (wave >= 4) return;
-    const int tr = wave * 8 + (lane >> 3);
-    const int node = s_node[tr];
-    if (node < 0) return;
-    const int u4 = (lane & 7) * 4;
-    const int unit0 = col * kUnit + u4;
-    const int kid = s_kid[tr];
-    const int unit_ld = unit0 < a.Hq ? unit0 : 0;        // unit groups past the padded width read the first group (and store nothing)
+    // ---- the children's h into LDS, c into registers
     float4 ck = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (kid >= 0) ck = *reinterpret_cast<const float4 *>(a.cs + (int64_t)kid * a.Hq + unit_ld);
-    // what is added to the products: the packed bias, or Z with the bias in it (unit groups past its width read the first)
-    const float *bias = HAS_Z ? a.Z + (int64_t)node * 4 * a.Hz + (unit0 < a.Hz ? unit0 : 0) : a.bp + col * kGateTile + u4;
-    const int bias_gate = HAS_Z ? a.Hz : kUnit;
-    float z[4][4];
+    {
+        const int n_rounds = (h_bytes / 16 + 31) / 32;
+        const char *src[NJ];
 #pragma unroll
-    for (int g = 0; g < 4; ++g) {
-        float4 q = *reinterpret_cast<const float4 *>(&zt[g][tr * kEpiStride + u4]);
-#pragma unroll
-        for (int p = 1; p < KS; ++p) {
-            const float4 qp = *reinterpret_cast<const float4 *>(&zt[4 * p + g][tr * kEpiStride + u4]);
-            q.x += qp.x; q.y += qp.y; q.z += qp.z; q.w += qp.w;
+        for (int j = 0; j < NJ; ++j) {
+            const int kid = s_kid[(tid >> 5) + RPP * j];
+            src[j] = static_cast<const char *>(a.hs) + (int64_t)(kid < 0 ? 0 : kid) * h_bytes;
         }
-        const float4 bq = *reinterpret_cast<const float4 *>(bias + g * bias_gate);
-        z[g][0] = q.x + bq.x; z[g][1] = q.y + bq.y; z[g][2] = q.z + bq.z; z[g][3] = q.w + bq.w;
-    }
-    const float ckv[4] = {ck.x, ck.y, ck.z, ck.w};
-    float cc[4], go[4];
+        constexpr int NR = 2 * US / RT;          // rounds whose loads are in flight together
+        for (int i = 0; i < n_rounds; i += NR) {
+            u32x2 v[NR][NJ][2];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        const float gi = sigmoid_t<T>(z[0][e]);
-        go[e] = sigmoid_t<T>(z[1][e]);
-        const float gu = tanh_t<T>(z[2][e]);
-        const float gf = sigmoid_t<T>(z[3][e]);
-        cc[e] = gi * gu + gf * ckv[e];
+            for (int q = 0; q < NR; ++q) {
+                int kb = ((tid & 31) + 32 * (i + q)) * 16;
+                kb = kb < h_bytes ? kb : 0;
+#pragma unroll
+                for (int j = 0; j < NJ; ++j) {
+                    v[q][j][0] = load_shared(src[j] + kb);
+                    v[q][j][1] = load_shared(src[j] + kb + 8);
+                }
+            }
+            if (i == 0 && wave < kUpdateWaves) {            // unit groups past the padded width read the first group (and store nothing)
+                const int kid = s_kid[tr];
+                const float *c = a.cs + (int64_t)(kid < 0 ? 0 : kid) * a.Hq + (unit0 < a.Hq ? unit0 : 0);
+                const u32x2 c0 = load_shared(c), c1 = load_shared(c + 2);
+                if (kid >= 0) ck = make_float4(__uint_as_float(c0[0]), __uint_as_float(c0[1]), __uint_as_float(c1[0]), __uint_as_float(c1[1]));
+            }
+#pragma unroll
+            for (int q = 0; q < NR; ++q) {
+                const int kb = ((tid & 31) + 32 * (i + q)) * 16;
+                if (kb < h_bytes) {
+#pragma unroll
+                    for (int j = 0; j < NJ; ++j)
+                        *reinterpret_cast<u32x4 *>(a_lds + ((tid >> 5) + RPP * j) * pitch + x_bytes + kb) =
+                            u32x4{v[q][j][0][0], v[q][j][0][1], v[q][j][1][0], v[q][j][1][1]};
+                }
+            }
+        }
+#pragma unroll 1
+        for (int j = 0; j < NJ; ++j)
+            if (s_kid[(tid >> 5) + RPP * j] < 0)             // (no child after all: zeros)
+                for (int kb = (tid & 31) * 16; kb < h_bytes; kb += 512)
+                    *reinterpret_cast<u32x4 *>(a_lds + ((tid >> 5) + RPP * j) * pitch + x_bytes + kb) = u32x4{0u, 0u, 0u, 0u};
     }
-    store_state<T>(a, node, unit0, make_float4(cc[0], cc[1], cc[2], cc[3]), make_float4(go[0], go[1], go[2], go[3]));
+    floatx4 acc[RT][NB];
+#pragma unroll
+    for (int i = 0; i < RT; ++i)
+#pragma unroll
+        for (int q = 0; q < NB; ++q) acc[i][q] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+    __syncthreads();
+
+    // ---- K loop: whole turns of the ring, then the last one, which requests nothing any more
+    const char *abuf = a_lds + l16 * pitch + q4 * 16;    // this lane's A fragment, slab 0
+    const int n_full = (n_slabs - 1) / RING;
+    u32x4 fa[RT];
+    auto step = [&](int s, int next) __attribute__((always_inline)) {      // the next A fragment leaves LDS while this one is multiplied
+        u32x4 fa_next[RT];
+#pragma unroll
+        for (int i = 0; i < RT; ++i) fa_next[i] = *reinterpret_cast<const u32x4 *>(abuf + i * 16 * pitch + next * 64);
+#pragma unroll
+        for (int i = 0; i < RT; ++i)
+#pragma unroll
+            for (int q = 0; q < NB; ++q) mfma16<T>(fa[i], fb[s][q], acc[i][q]);
+#pragma unroll
+        for (int i = 0; i < RT; ++i) fa[i] = fa_next[i];
+    };
+#pragma unroll
+    for (int i = 0; i < RT; ++i) fa[i] = *reinterpret_cast<const u32x4 *>(abuf + i * 16 * pitch);
+    for (int c = 0; c < n_full; ++c) {
+#pragma unroll
+        for (int s = 0; s < RING; ++s) {            // (behind these turns at least one slab is left)
+            step(s, c * RING + s + 1);
+            request(c * RING + s + RING, s);
+            __builtin_amdgcn_sched_barrier(0);      // the ring is refilled slot by slot, not in a burst at the end
+        }
+    }
+#pragma unroll
+    for (int s = 0; s < RING; ++s)
+        if (n_full * RING + s < n_slabs) step(s, n_full * RING + s + 1 < n_slabs ? n_full * RING + s + 1 : n_slabs - 1);
+
+    // ---- the gates meet in LDS; the first waves finish eight rows each: eight lanes per row, four units per lane
+#pragma unroll
+    for (int i = 0; i < RT; ++i)
+#pragma unroll
+        for (int q = 0; q < NB; ++q)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) zt[gate][(i * 16 + q4 * 4 + v) * kEpiStride + (half + q) * 16 + l16] = acc[i][q][v];
+    __syncthreads();
+    if (wave < kUpdateWaves && node >= 0) {
+        float z[4][4];
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const float4 q = *reinterpret_cast<const float4 *>(&zt[g][tr * kEpiStride + u4]);
+            if constexpr (!HAS_Z) bq[g] = *reinterpret_cast<const float4 *>(s_bias + g * kUnit + u4);
+            z[g][0] = q.x + bq[g].x; z[g][1] = q.y + bq[g].y; z[g][2] = q.z + bq[g].z; z[g][3] = q.w + bq[g].w;
+        }
+        const float ckv[4] = {ck.x, ck.y, ck.z, ck.w};
+        float cc[4], go[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const float gi = sigmoid_t<T>(z[0][e]);
+            go[e] = sigmoid_t<T>(z[1][e]);
+            const float gu = tanh_t<T>(z[2][e]);
+            const float gf = sigmoid_t<T>(z[3][e]);
+            cc[e] = gi * gu + gf * ckv[e];
+        }
+        store_state_shared<T>(a, node, unit0, make_float4(cc[0], cc[1], cc[2], cc[3]), make_float4(go[0], go[1], go[2], go[3]));
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // this wave's rows have arrived
+    __syncthreads();
+    if (tid == 0) __hip_atomic_fetch_add(lv.done + (int64_t)row_tile * lv.stride, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // ---- host side ---------------------------------------------------------------------
@@ -1293,11 +1431,8 @@ int run_forward(const void *x, const void *W, const void *U, const float *b, con
     // below skips it too.
     int chain_from = L;
     const int chain_k_bytes = (d.Dp + d.Hp) * d.esz;
-    const size_t chain_lds = chain_lds_bytes(chain_k_bytes);      // the tile's A rows live in LDS
-    // waves per gate: fp32 (long MFMA chains) two if the LDS beside the A tile allows, bf16 one.  (Four measured
-    // slower than two: blocks of 1024 threads start later than they finish earlier.)
-    const int chain_ks = (sizeof(T) == 4 && chain_lds <= (size_t)chain_lds_max(2)) ? 2 : 1;
-    if (!SAVE && !slots && chains && s->host_level_kids && (d.D & 3) == 0 && chain_lds <= (size_t)chain_lds_max(chain_ks)) {
+    constexpr int chain_us = sizeof(T) == 4 ? 2 : 1, chain_rt_max = sizeof(T) == 4 ? 1 : 2;
+    if (!SAVE && !slots && chains && s->host_level_kids && (d.D & 3) == 0 && chain_k_bytes <= kChainMaxKBytes) {
         for (int l = L - 1; l >= 1; --l) {
             const int rows = sp[l + 1] - sp[l];
             if (rows > kThinMaxRows || s->host_level_kids[l] != rows) break;
@@ -1305,15 +1440,29 @@ int run_forward(const void *x, const void *W, const void *U, const float *b, con
         }
     }
     if (chain_from < L) {    // more dynamic LDS than a launch may ask for by default
-        for (bool z : {false, true}) {
-            const void *fn = chain_ks == 2 ? (z ? reinterpret_cast<const void *>(&chain_kernel<T, 2, true>)
-                                                : reinterpret_cast<const void *>(&chain_kernel<T, 2>))
-                                           : (z ? reinterpret_cast<const void *>(&chain_kernel<T, 1, true>)
-                                                : reinterpret_cast<const void *>(&chain_kernel<T, 1>));
-            JITDB_HIP_CHECK(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, chain_lds_max(chain_ks)));
-        }
+        for (const void *fn : {reinterpret_cast<const void *>(&chain_kernel<T, chain_us, 1, false>), reinterpret_cast<const void *>(&chain_kernel<T, chain_us, 1, true>),
+                               reinterpret_cast<const void *>(&chain_kernel<T, chain_us, chain_rt_max, false>), reinterpret_cast<const void *>(&chain_kernel<T, chain_us, chain_rt_max, true>)})
+            JITDB_HIP_CHECK(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, kChainLdsMax));
     }
-    const size_t chain_z_lds = chain_lds_bytes(d.Hp * (int)d.esz);    // ... their h part alone
+    // The chain levels' words (a word per row tile, a counter per launch) stand where those levels' row records would.
+    // With the library's event pairs on, a launch holds one level, so that every level has a time of its own.
+    const int chain_per_launch = g_prof.on ? 1 : kChainLevels;
+    int *chain_words = nullptr;
+    int64_t n_chain_words = 0, n_chain_tiles = 0;
+    int chain_stride = 1, chain_rt = 1;
+    if (chain_from < L) {
+        chain_words = reinterpret_cast<int *>(w.row_rec + 2 * (int64_t)sp[chain_from]);
+        for (int l = chain_from; l < L; ++l) n_chain_tiles += ceil_div(sp[l + 1] - sp[l], 16);
+        if (chain_rt_max == 2 && chain_k_bytes <= kChainMaxKBytes2 && n_chain_tiles * (d.Hu / kUnit) >= (int64_t)kChainWideTiles * (L - chain_from)) {
+            chain_rt = 2;
+            n_chain_tiles = 0;
+            for (int l = chain_from; l < L; ++l) n_chain_tiles += ceil_div(sp[l + 1] - sp[l], 32);
+        }
+        // (blocks that look at one line wait for each other: a line per word where the records' memory has room, else a fourth)
+        const int64_t room = 8 * (s->n_nodes - sp[chain_from] + kRowPad) - (L - chain_from);
+        chain_stride = 32 * n_chain_tiles <= room ? 32 : 4;
+        n_chain_words = n_chain_tiles * chain_stride + ceil_div(L - chain_from, chain_per_launch);
+    }
     // A forest of small trees filed one after another: its levels below the chain levels in one launch
     TreesArgs ta = {};
     bool trees = false;
@@ -1354,31 +1503,33 @@ int run_forward(const void *x, const void *W, const void *U, const float *b, con
         };
         const bool large = s->n_nodes >= kRecLargeMinNodes;
         const bool pack_here = !(packed || is_nary(0));
-        if (trees) {     // records of the chain levels only
-            const int first = chain_from < L ? sp[chain_from] / kRecWindow : 0;
-            const int n_windows = chain_from < L ? (int)ceil_div(s->n_nodes, kRecWindow) - first : 0;
-            const unsigned grid = (unsigned)n_windows + (pack_here ? pack_grid : 0u);
-            if (grid > 0) {
-                ScopedLaunchTimer tm(JITDB_K_PACK, 0, st);
-                prepare_kernel<T><<<grid, kThreads, 0, st>>>(s->perm, s->height, s->child_ptr, s->child_idx, w.row_rec, (int)s->n_nodes,
-                                                             first, n_windows, pack_args(0));
-                JITDB_LAUNCH_CHECK();
-            }
-        } else {
-            ScopedLaunchTimer tm(JITDB_K_PACK, 0, st);
+        // records of the levels that run one by one; the chain levels' words are cleared in the same launch
+        const int rec_end = trees ? 0 : sp[chain_from * (slots ? n_sig * n_sig : 1)];
+        {
+            const int per_window = large ? kRecWindowLarge : kRecWindow;
+            const int n_windows = (int)ceil_div((int64_t)rec_end, per_window);
             if (large) {
-                const int n_windows = (int)ceil_div(s->n_nodes, kRecWindowLarge);
                 const unsigned pg = pack_here ? (unsigned)(ceil_div(pieces, kRecThreadsLarge) < 1024 ? ceil_div(pieces, kRecThreadsLarge) : 1024) : 0u;
+                ScopedLaunchTimer tm(JITDB_K_PACK, 0, st);
                 prepare_large_kernel<T><<<(unsigned)n_windows + pg, kRecThreadsLarge, 0, st>>>(
-                    s->perm, slots ? slots->key : s->height, s->child_ptr, s->child_idx, w.row_rec, (int)s->n_nodes,
-                    n_windows, pack_args(0));
+                    s->perm, slots ? slots->key : s->height, s->child_ptr, s->child_idx, w.row_rec, (int)s->n_nodes, rec_end,
+                    n_windows, pack_args(0), chain_words, n_chain_words);
+                JITDB_LAUNCH_CHECK();
             } else {
-                const int n_windows = (int)ceil_div(s->n_nodes, kRecWindow);
-                prepare_kernel<T><<<(unsigned)n_windows + (pack_here ? pack_grid : 0u), kThreads, 0, st>>>(
-                    s->perm, slots ? slots->key : s->height, s->child_ptr, s->child_idx, w.row_rec, (int)s->n_nodes,
-                    0, n_windows, pack_args(0));
+                PackArgs p = pack_args(0);
+                unsigned grid = (unsigned)n_windows + (pack_here ? pack_grid : 0u);
+                if (grid == 0 && n_chain_words > 0) {      // nothing but words to clear
+                    grid = (unsigned)(ceil_div(n_chain_words, kThreads) < 256 ? ceil_div(n_chain_words, kThreads) : 256);
+                    p.n_cells = 0;
+                }
+                if (grid > 0) {
+                    ScopedLaunchTimer tm(JITDB_K_PACK, 0, st);
+                    prepare_kernel<T><<<grid, kThreads, 0, st>>>(
+                        s->perm, slots ? slots->key : s->height, s->child_ptr, s->child_idx, w.row_rec, (int)s->n_nodes, rec_end,
+                        n_windows, p, chain_words, n_chain_words);
+                    JITDB_LAUNCH_CHECK();
+                }
             }
-            JITDB_LAUNCH_CHECK();
         }
         for (int t = 1; t < n_sig && !packed && !one_behind_other; ++t) {
             if (is_nary(t)) continue;
@@ -1476,7 +1627,7 @@ int run_forward(const void *x, const void *W, const void *U, const float *b, con
         if (rc != JITDB_OK) return rc;
     }
     for (size_t i = 0; i < segs.size(); ++i) {
-        if (trees && segs[i].l < chain_from) continue;
+        if (trees || segs[i].l >= chain_from) break;      // (of trees, the chain levels are all that is left)
         const int l = segs[i].l, sig = segs[i].sig, n_rows = segs[i].rows;
         const bool grouped = sig < 0;
         a.Bp = static_cast<char *>(w.Bp) + packed_w_bytes(d) * (grouped ? 0 : sig);
@@ -1488,22 +1639,6 @@ int run_forward(const void *x, const void *W, const void *U, const float *b, con
         if (grouped) {      // the level's ranges: its slots for the cell, its sub-slots for the projection
             a.ranges = slots->slot_ptr + (int64_t)l * T2;
             a.n_ranges = n_sig; a.range_stride = n_sig; a.range_cells = n_sig;
-        }
-        if (l >= chain_from) {
-            a.n_col_tiles = n_unit_tiles;
-            a.n_tiles = (int)ceil_div(n_rows, 32) * a.n_col_tiles;
-            a.n_blocks = a.n_tiles;
-            ScopedLaunchTimer tm(JITDB_K_CHAIN, n_rows, st, s->host_level_kids[l]);
-            if (trees) {
-                if (chain_ks == 2) chain_kernel<T, 2, true><<<a.n_blocks, kThinWaves * 64 * 2, chain_z_lds, st>>>(a);
-                else chain_kernel<T, 1, true><<<a.n_blocks, kThinWaves * 64, chain_z_lds, st>>>(a);
-            } else if (chain_ks == 2) {
-                chain_kernel<T, 2><<<a.n_blocks, kThinWaves * 64 * 2, chain_lds, st>>>(a);
-            } else {
-                chain_kernel<T, 1><<<a.n_blocks, kThinWaves * 64, chain_lds, st>>>(a);
-            }
-            JITDB_LAUNCH_CHECK();
-            continue;
         }
         if (is_nary(sig)) {
             // a slot of N-ary nodes: stack, one contraction for all 3 + N gates, cell update (cells.hip)
@@ -1639,6 +1774,39 @@ int run_forward(const void *x, const void *W, const void *U, const float *b, con
             }
             JITDB_LAUNCH_CHECK();
         }
+    }
+    int *done = chain_words, *ticket = chain_words ? chain_words + n_chain_tiles * chain_stride : nullptr;
+    for (int l0 = chain_from; l0 < L; l0 += chain_per_launch) {
+        ChainArgs lv;
+        lv.perm = s->perm; lv.inv_perm = s->inv_perm; lv.child_ptr = s->child_ptr; lv.child_idx = s->child_idx;
+        lv.n_levels = L - l0 < chain_per_launch ? L - l0 : chain_per_launch;
+        lv.done = done;
+        lv.ticket = ticket++;
+        lv.tiles[0] = 0;
+        lv.pos[0] = sp[l0];
+        for (int i = 0; i < lv.n_levels; ++i) {
+            lv.tiles[i + 1] = lv.tiles[i] + (int)ceil_div(sp[l0 + i + 1] - sp[l0 + i], 16 * chain_rt);
+            lv.pos[i + 1] = sp[l0 + i + 1];
+        }
+        const int n_tiles = lv.tiles[lv.n_levels];
+        lv.stride = chain_stride;
+        done += (int64_t)n_tiles * chain_stride;
+        a.Bp = w.Bp; a.bp = w.bp;
+        a.n_col_tiles = n_unit_tiles;
+        const unsigned grid = (unsigned)n_tiles * (unsigned)n_unit_tiles;
+        const int rows = lv.pos[lv.n_levels] - lv.pos[0];
+        ScopedLaunchTimer tm(JITDB_K_CHAIN, rows, st, rows);         // (one child a row)
+        // (of whole trees the x part is in Z: the h part alone)
+        const size_t lds = (size_t)chain_lds_bytes(trees ? d.Hp * (int)d.esz : chain_k_bytes, chain_rt);
+        constexpr int nt = kThinWaves * 64 * chain_us;
+        if (chain_rt == 1) {
+            if (trees) chain_kernel<T, chain_us, 1, true><<<grid, nt, lds, st>>>(a, lv);
+            else chain_kernel<T, chain_us, 1, false><<<grid, nt, lds, st>>>(a, lv);
+        } else {
+            if (trees) chain_kernel<T, chain_us, chain_rt_max, true><<<grid, nt, lds, st>>>(a, lv);
+            else chain_kernel<T, chain_us, chain_rt_max, false><<<grid, nt, lds, st>>>(a, lv);
+        }
+        JITDB_LAUNCH_CHECK();
     }
     return JITDB_OK;
 }
