@@ -68,7 +68,7 @@ nary_pack_kernel(const T *__restrict__ W, const T *__restrict__ U, int D, int H,
 }
 
 // ---- stack -----------------------------------------------------------------------------
-// One thread per 16-byte piece of a row of A = [x_j | h_{k_1} | ... | h_{k_N}].  The child ids come
+// Rows of A = [x_j | h_{k_1} | ... | h_{k_N}].  The child ids come
 // with the row record (its first four children; N <= 4).  A node with more children than the cell
 // has positions sets *err; the surplus children are left out.
 template <typename T>
@@ -78,36 +78,33 @@ nary_stack_kernel(const T *__restrict__ x, int D, int Dp, const T *__restrict__ 
                   int *__restrict__ err) {
     // N: the cell's child positions; Nk <= N: positions stacked for this slot (0 for a slot of leaves)
     constexpr int VEC = Traits<T>::VEC;
-    const int cpr = (Dp + Nk * Hp) / VEC;
-    const int64_t gid = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    const int64_t row = gid / cpr;
-    const int ch = (int)(gid % cpr);
-    if (row >= n_rows) return;
-    const int4 r0 = row_rec[2 * row];
-    const int k0 = ch * VEC;
-    uint4 o = make_uint4(0u, 0u, 0u, 0u);
-    if (k0 < Dp) {
-        const T *src = x + (int64_t)r0.x * D + k0;
-        T e[VEC];
+    int64_t row0;
+    int pair;
+    stack_tile(blockIdx.x, (Dp + Nk * Hp) / (8 * VEC), row0, pair);
+    if (row0 >= n_rows) return;
+    const int kp = pair * 8 * VEC, k0 = kp + (int)(threadIdx.x & 7) * VEC;
+    const int l = kp < Dp ? -1 : (kp - Dp) / Hp;             // the pair is x's or one child's
+    u32x4 o[kStackPerThread];
+    int64_t row[kStackPerThread];
 #pragma unroll
-        for (int j = 0; j < VEC; ++j) e[j] = (k0 + j < D) ? src[j] : T(0);
-        if constexpr (sizeof(T) == 4) {
-            o.x = __float_as_uint(e[0]); o.y = __float_as_uint(e[1]);
-            o.z = __float_as_uint(e[2]); o.w = __float_as_uint(e[3]);
+    for (int i = 0; i < kStackPerThread; ++i) {
+        row[i] = row0 + i * (kStackRows / kStackPerThread) + (threadIdx.x >> 3);
+        const int64_t r = row[i] < n_rows ? row[i] : n_rows - 1;
+        const int4 r0 = row_rec[2 * r];
+        if (l < 0) {
+            o[i] = load_x_piece<T>(x + (int64_t)r0.x * D, k0, D);
+            if (pair == 0 && r0.y > N) *err = 1;
         } else {
-            o.x = (uint32_t)e[0] | ((uint32_t)e[1] << 16); o.y = (uint32_t)e[2] | ((uint32_t)e[3] << 16);
-            o.z = (uint32_t)e[4] | ((uint32_t)e[5] << 16); o.w = (uint32_t)e[6] | ((uint32_t)e[7] << 16);
-        }
-        if (ch == 0 && r0.y > N) *err = 1;
-    } else {
-        const int l = (k0 - Dp) / Hp, kh = (k0 - Dp) % Hp;
-        if (l < r0.y) {
-            const int4 kids = row_rec[2 * row + 1];
+            const int4 kids = row_rec[2 * r + 1];
             const int kid = l == 0 ? kids.x : l == 1 ? kids.y : l == 2 ? kids.z : kids.w;
-            o = *reinterpret_cast<const uint4 *>(hs + (int64_t)kid * Hp + kh);   // pad columns of hs are zero
+            o[i] = u32x4{0u, 0u, 0u, 0u};
+            if (l < r0.y) o[i] = *reinterpret_cast<const u32x4 *>(hs + (int64_t)kid * Hp + (k0 - Dp - l * Hp));   // pad columns of hs are zero
         }
     }
-    *reinterpret_cast<uint4 *>(reinterpret_cast<char *>(A) + operand_offset(row, (int64_t)k0 * sizeof(T), n_rows_alloc)) = o;
+#pragma unroll
+    for (int i = 0; i < kStackPerThread; ++i)
+        if (row[i] < n_rows)
+            *reinterpret_cast<u32x4 *>(reinterpret_cast<char *>(A) + operand_offset(row[i], (int64_t)k0 * sizeof(T), n_rows_alloc)) = o[i];
 }
 
 }  // namespace
@@ -144,11 +141,10 @@ int nary_pack(jitdb_dtype dtype, const void *W, const void *U, int D, int H, int
 int run_nary_slot(jitdb_dtype dtype, const LevelArgs &a, const NarySlot &s, hipStream_t st) {
     if (s.n_rows <= 0) return JITDB_OK;
     const size_t esz = dtype == JITDB_F32 ? 4 : 2;
-    const int vec = dtype == JITDB_F32 ? 4 : 8;
     const int Nk = s.leaves ? 0 : s.N;                       // child positions this slot stacks and multiplies
     const int Kn = a.Dp + Nk * a.Hp;
     const int rows_alloc = (int)round_up(s.n_rows, kRowPad);
-    const unsigned sblocks = (unsigned)ceil_div((int64_t)s.n_rows * (Kn / vec), kThreads);
+    const unsigned sblocks = stack_grid(s.n_rows, (int64_t)Kn * (int64_t)esz);
     if (dtype == JITDB_F32)
         nary_stack_kernel<float><<<sblocks, kThreads, 0, st>>>(static_cast<const float *>(s.x), a.D, a.Dp,
                                                               static_cast<const float *>(a.hs), a.Hp, s.N, Nk, s.row_rec,

@@ -249,20 +249,18 @@ prepare_large_kernel(const int32_t *__restrict__ perm, const int32_t *__restrict
 // The paper's "stack" step (section 4.3): the samples of one slot are laid side by
 // side on the batch axis.  Row r of the level's dense input matrix A is
 //     [ x_j (D values, zero padded to Dp) | hsum_j = sum over children of h_k (Hp values) ]
-// for the r-th node j of the level; leaves have the x part only.  One thread
-// per 16-byte piece of a row; child rows come from hs (stride Hp, pad columns zero,
-// rows by node id) in 16-byte pieces, up to four children in flight.
+// for the r-th node j of the level; leaves have the x part only.  Child rows come from hs (stride Hp, pad columns zero,
+// rows by node id) in 16-byte pieces, up to four children of each of a thread's rows in flight.
 template <typename T>
-__device__ __forceinline__ void add_piece(float (&acc)[Traits<T>::VEC], const uint4 &v) {
+__device__ __forceinline__ void add_piece(float (&acc)[Traits<T>::VEC], const u32x4 &v) {
     if constexpr (sizeof(T) == 4) {
-        acc[0] += __uint_as_float(v.x); acc[1] += __uint_as_float(v.y);
-        acc[2] += __uint_as_float(v.z); acc[3] += __uint_as_float(v.w);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[j] += __uint_as_float(v[j]);
     } else {
-        const uint32_t w[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            acc[2 * j] += __uint_as_float(w[j] << 16);
-            acc[2 * j + 1] += __uint_as_float(w[j] & 0xFFFF0000u);
+            acc[2 * j] += __uint_as_float(v[j] << 16);
+            acc[2 * j + 1] += __uint_as_float(v[j] & 0xFFFF0000u);
         }
     }
 }
@@ -273,78 +271,62 @@ struct StackArgs {
     void *A; int n_rows, n_rows_alloc;
 };
 
-// block `block` of the stack step (kThreads threads)
+// block `block` of the stack step (kThreads threads): the pair of slabs is x's or hs's, all of it
 template <typename T, bool WITH_H>
 __device__ __forceinline__ void stack_body(const T *__restrict__ x, int D, int Dp, const T *__restrict__ hs, int Hp,
                                            const int4 *__restrict__ row_rec, const int32_t *__restrict__ child_idx,
-                                           T *__restrict__ A, int n_rows, int n_rows_alloc, int64_t block) {
+                                           T *__restrict__ A, int n_rows, int n_rows_alloc, unsigned block) {
     constexpr int VEC = Traits<T>::VEC;
-    const int Kp = Dp + (WITH_H ? Hp : 0);
-    const int cpr = Kp / VEC;
-    const int64_t gid = block * kThreads + threadIdx.x;
-    const int64_t row = gid / cpr;
-    const int ch = (int)(gid % cpr);
-    if (row >= n_rows) return;
-    const int4 r0 = row_rec[2 * row];
-    const int node = r0.x;
-    const int k0 = ch * VEC;
-    uint4 o = make_uint4(0u, 0u, 0u, 0u);
-    if (k0 < Dp) {
-        const T *src = x + (int64_t)node * D + k0;
-        if ((D & 3) == 0) {
-            // rows of x are 4-element aligned: move 4-element halves, zero past D
-            if constexpr (sizeof(T) == 4) {
-                if (k0 < D) o = *reinterpret_cast<const uint4 *>(src);
-            } else {
-                if (k0 < D) { const uint2 q = *reinterpret_cast<const uint2 *>(src); o.x = q.x; o.y = q.y; }
-                if (k0 + 4 < D) { const uint2 q = *reinterpret_cast<const uint2 *>(src + 4); o.z = q.x; o.w = q.y; }
-            }
-        } else {
-            // any other D: element by element
-            T e[VEC];
+    const int n_pairs = (Dp + (WITH_H ? Hp : 0)) / (8 * VEC);
+    int64_t row0;
+    int pair;
+    stack_tile(block, n_pairs, row0, pair);
+    if (row0 >= n_rows) return;
+    const int k0 = (pair * 8 + (int)(threadIdx.x & 7)) * VEC;
+    int64_t row[kStackPerThread];
+    int4 r0[kStackPerThread];
+    u32x4 o[kStackPerThread];
 #pragma unroll
-            for (int j = 0; j < VEC; ++j) e[j] = (k0 + j < D) ? src[j] : T(0);
-            if constexpr (sizeof(T) == 4) {
-                o.x = __float_as_uint(e[0]); o.y = __float_as_uint(e[1]);
-                o.z = __float_as_uint(e[2]); o.w = __float_as_uint(e[3]);
-            } else {
-                o.x = (uint32_t)e[0] | ((uint32_t)e[1] << 16); o.y = (uint32_t)e[2] | ((uint32_t)e[3] << 16);
-                o.z = (uint32_t)e[4] | ((uint32_t)e[5] << 16); o.w = (uint32_t)e[6] | ((uint32_t)e[7] << 16);
+    for (int i = 0; i < kStackPerThread; ++i) {
+        row[i] = row0 + i * (kStackRows / kStackPerThread) + (threadIdx.x >> 3);
+        r0[i] = row_rec[2 * (row[i] < n_rows ? row[i] : n_rows - 1)];
+    }
+    if (!WITH_H || k0 < Dp) {
+#pragma unroll
+        for (int i = 0; i < kStackPerThread; ++i) o[i] = load_x_piece<T>(x + (int64_t)r0[i].x * D, k0, D);
+    } else {
+        const T *h = hs + (k0 - Dp);
+        u32x4 v[kStackPerThread][4];
+#pragma unroll
+        for (int i = 0; i < kStackPerThread; ++i) {
+            const int4 kids = row_rec[2 * (row[i] < n_rows ? row[i] : n_rows - 1) + 1];
+            const int kid[4] = {kids.x, kids.y, kids.z, kids.w};
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                v[i][j] = u32x4{0u, 0u, 0u, 0u};
+                if (j < r0[i].y) v[i][j] = *reinterpret_cast<const u32x4 *>(h + (int64_t)kid[j] * Hp);
             }
         }
-    } else if constexpr (WITH_H) {
-        const int kh = k0 - Dp;
-        const int ar = r0.y;
-        const int4 kids = row_rec[2 * row + 1];
-        const int kid[4] = {kids.x, kids.y, kids.z, kids.w};
-        float acc[VEC];
 #pragma unroll
-        for (int j = 0; j < VEC; ++j) acc[j] = 0.0f;
-        uint4 v[4];
+        for (int i = 0; i < kStackPerThread; ++i) {
+            float acc[VEC];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            v[j] = make_uint4(0u, 0u, 0u, 0u);
-            if (j < ar) v[j] = *reinterpret_cast<const uint4 *>(hs + (int64_t)kid[j] * Hp + kh);
-        }
+            for (int j = 0; j < VEC; ++j) acc[j] = 0.0f;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) add_piece<T>(acc, v[j]);   // ascending child id; zeros add nothing
-        for (int c = 4; c < ar; ++c) {
-            const int k = child_idx[r0.z + c];
-            add_piece<T>(acc, *reinterpret_cast<const uint4 *>(hs + (int64_t)k * Hp + kh));
-        }
-        if constexpr (sizeof(T) == 4) {
-            o.x = __float_as_uint(acc[0]); o.y = __float_as_uint(acc[1]);
-            o.z = __float_as_uint(acc[2]); o.w = __float_as_uint(acc[3]);
-        } else {
-            uint32_t w[4];
+            for (int j = 0; j < 4; ++j) add_piece<T>(acc, v[i][j]);   // ascending child id; zeros add nothing
+            for (int c = 4; c < r0[i].y; ++c)
+                add_piece<T>(acc, *reinterpret_cast<const u32x4 *>(h + (int64_t)child_idx[r0[i].z + c] * Hp));
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
-                w[j] = (uint32_t)f32_to_bf16(acc[2 * j]) | ((uint32_t)f32_to_bf16(acc[2 * j + 1]) << 16);
-            o.x = w[0]; o.y = w[1]; o.z = w[2]; o.w = w[3];
+            for (int j = 0; j < 4; ++j) {
+                if constexpr (sizeof(T) == 4) o[i][j] = __float_as_uint(acc[j]);
+                else o[i][j] = (uint32_t)f32_to_bf16(acc[2 * j]) | ((uint32_t)f32_to_bf16(acc[2 * j + 1]) << 16);
+            }
         }
     }
-    *reinterpret_cast<uint4 *>(reinterpret_cast<char *>(A) +
-                               operand_offset(row, (int64_t)k0 * sizeof(T), n_rows_alloc)) = o;
+#pragma unroll
+    for (int i = 0; i < kStackPerThread; ++i)
+        if (row[i] < n_rows)
+            *reinterpret_cast<u32x4 *>(reinterpret_cast<char *>(A) + operand_offset(row[i], (int64_t)k0 * sizeof(T), n_rows_alloc)) = o[i];
 }
 
 template <typename T, bool WITH_H>
@@ -797,7 +779,7 @@ thin_proj_stack_kernel(const LevelArgs a, const StackArgs s) {
     else
         stack_body<T, true>(static_cast<const T *>(s.x), s.D, s.Dp, static_cast<const T *>(s.hs), s.Hp, s.row_rec,
                             s.child_idx, static_cast<T *>(s.A), s.n_rows, s.n_rows_alloc,
-                            (int64_t)blockIdx.x - a.n_blocks);
+                            blockIdx.x - (unsigned)a.n_blocks);
 }
 
 // ---- thin slots of N-ary nodes ----------------------------------------------------------
@@ -1613,8 +1595,7 @@ int run_forward(const void *x, const void *W, const void *U, const float *b, con
         return sa;
     };
     auto stack_blocks = [&](const Seg &g) {
-        const int Kp = d.Dp + (g.l > 0 ? d.Hp : 0);
-        return (unsigned)ceil_div((int64_t)g.rows * (Kp / Traits<T>::VEC), kThreads);
+        return stack_grid(g.rows, (int64_t)(d.Dp + (g.l > 0 ? d.Hp : 0)) * sizeof(T));
     };
     bool stacked_ahead = false;     // the slot's stack step already ran with the projection before it
     const int n_unit_tiles = d.Hu / kUnit;

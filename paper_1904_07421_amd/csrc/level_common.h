@@ -216,6 +216,47 @@ __device__ __forceinline__ bool enter_range(LevelArgs &a, int tile, int &row0) {
     return false;
 }
 
+// ---- stack steps: which pieces of the K-blocked input a block writes ---------------------
+// A block of kThreads threads writes kStackRows rows x 128 bytes of K (two slabs; rows of A are padded to whole pairs): eight
+// lanes take the 128 bytes of a row, so rows are read in whole lines and a wave writes runs of 512 bytes.  The pairs of a row tile
+// follow each other on one XCD: the lines that two pairs of a misaligned x row share come from that L2.
+// Bound by memory.  Against one thread per 16 bytes in row order (64-byte writes from blocks on different XCDs, a 64-bit division per
+// piece): inner levels of 2.36 M + 296 k nodes, H 512, bf16 1666 -> 1280 us (4.4 TB/s), N-ary (x element by element) 293 -> 203.
+constexpr int kStackPerThread = 2;                       // rows of a thread, their loads side by side
+constexpr int kStackRows = kThreads / 8 * kStackPerThread;
+inline unsigned stack_grid(int64_t n_rows, int64_t k_bytes) {
+    return (unsigned)(8 * ceil_div(ceil_div(n_rows, kStackRows), 8) * (k_bytes / 128));
+}
+__device__ __forceinline__ void stack_tile(unsigned block, int n_pairs, int64_t &row0, int &pair) {
+    const unsigned q = block >> 3;
+    pair = (int)(q % (unsigned)n_pairs);
+    row0 = ((int64_t)(q / (unsigned)n_pairs) * 8 + (block & 7)) * kStackRows;
+}
+// 16 bytes of a row of x from element k0 on, zero past D (rows may start on any element boundary).
+template <typename T>
+__device__ __forceinline__ u32x4 load_x_piece(const T *row, int k0, int D) {
+    constexpr int VEC = Traits<T>::VEC;
+    u32x4 v = {0, 0, 0, 0};
+    if ((D & 3) == 0) {                      // whole or half pieces
+        if constexpr (sizeof(T) == 4) {
+            if (k0 < D) __builtin_memcpy(&v, row + k0, 16);
+        } else {
+            u32x2 lo = {0, 0}, hi = {0, 0};
+            if (k0 < D) __builtin_memcpy(&lo, row + k0, 8);
+            if (k0 + 4 < D) __builtin_memcpy(&hi, row + k0 + 4, 8);
+            v = u32x4{lo[0], lo[1], hi[0], hi[1]};
+        }
+    } else if (k0 + VEC <= D) {
+        __builtin_memcpy(&v, row + k0, 16);
+    } else if (k0 < D) {
+        T e[VEC];
+#pragma unroll
+        for (int j = 0; j < VEC; ++j) e[j] = k0 + j < D ? row[k0 + j] : T(0);
+        __builtin_memcpy(&v, e, 16);
+    }
+    return v;
+}
+
 // ---- the cell update of one wave: 32 rows x 32 hidden units ---------------------------
 // acc[g][v] holds the pre-activation (without bias) of gate g for row
 // (v/4)*8 + hf*4 + v%4 and unit l32 of the wave's unit tile.  The wave writes i*u, o and

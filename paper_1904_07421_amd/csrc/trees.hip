@@ -107,31 +107,6 @@ __device__ __forceinline__ void tree_gemm(floatx4 (&acc)[NRT ? NRT : 1][NG], ALo
         if (full * AHEAD + p < n_slabs) multiply(full * AHEAD + p, p);
 }
 
-// 16 bytes of a row of x from element k0 on, zero past D (rows may start on any element boundary).
-template <typename T>
-__device__ __forceinline__ u32x4 load_x_piece(const T *row, int k0, int D) {
-    constexpr int VEC = Traits<T>::VEC;
-    u32x4 v = {0, 0, 0, 0};
-    if ((D & 3) == 0) {                      // whole or half pieces
-        if constexpr (sizeof(T) == 4) {
-            if (k0 < D) __builtin_memcpy(&v, row + k0, 16);
-        } else {
-            u32x2 lo = {0, 0}, hi = {0, 0};
-            if (k0 < D) __builtin_memcpy(&lo, row + k0, 8);
-            if (k0 + 4 < D) __builtin_memcpy(&hi, row + k0 + 4, 8);
-            v = u32x4{lo[0], lo[1], hi[0], hi[1]};
-        }
-    } else if (k0 + VEC <= D) {
-        __builtin_memcpy(&v, row + k0, 16);
-    } else if (k0 < D) {
-        T e[VEC];
-#pragma unroll
-        for (int j = 0; j < VEC; ++j) e[j] = k0 + j < D ? row[k0 + j] : T(0);
-        __builtin_memcpy(&v, e, 16);
-    }
-    return v;
-}
-
 template <typename T>
 __device__ __forceinline__ void add_h_piece(float (&s)[Traits<T>::VEC], const u32x4 &v) {
     if constexpr (sizeof(T) == 4) {
