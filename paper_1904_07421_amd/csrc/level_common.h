@@ -221,7 +221,7 @@ __device__ __forceinline__ bool enter_range(LevelArgs &a, int tile, int &row0) {
 // lanes take the 128 bytes of a row, so rows are read in whole lines and a wave writes runs of 512 bytes.  The pairs of a row tile
 // follow each other on one XCD: the lines that two pairs of a misaligned x row share come from that L2.
 // Bound by memory.  Against one thread per 16 bytes in row order (64-byte writes from blocks on different XCDs, a 64-bit division per
-// piece): inner levels of 2.36 M + 296 k nodes, H 512, bf16 1666 -> 1280 us (4.4 TB/s), N-ary (x element by element) 293 -> 203.
+// piece): inner levels of 2.36 M + 296 k nodes, H 512, bf16 1666 -> 1280 us, N-ary (x element by element) 293 -> 203.
 constexpr int kStackPerThread = 2;                       // rows of a thread, their loads side by side
 constexpr int kStackRows = kThreads / 8 * kStackPerThread;
 inline unsigned stack_grid(int64_t n_rows, int64_t k_bytes) {
