@@ -932,6 +932,10 @@ constexpr int kChainAhead = 16;                         // weight loads in fligh
 constexpr int kChainLevels = 256;                       // levels one launch may hold (its table travels with the arguments)
 constexpr int kChainMaxKBytes = 4304;                   // of a row, RT = 1: two blocks share a CU's LDS
 constexpr int kChainMaxKBytes2 = 1840;                  // ... RT = 2
+// A level of many tiles goes alone, its tiles by block index: thousands of draws from one counter take longer than a launch (8000
+// chains of 4 - 5 nodes, D 300, all levels in one launch -> each alone, us: H 256 bf16 192 -> 172, fp32 552 -> 540, H 512 bf16 453 -> 436,
+// fp32 1369 -> 1330; tiles of 32 rows, one launch a level, 186, 481, 429, 1329).
+constexpr int kChainAloneTiles = 1536;
 constexpr int kChainWideTiles = 192;                    // (330 tiles a level: 3 % for RT = 2, 500: 10 %, 31: 13 % for RT = 1)
 // LDS pitch of an A row: K bytes + 16, so that 16 lanes' 16-byte reads of one K group fall in 64 different banks
 __host__ __device__ inline constexpr int chain_row_pitch(int k_bytes) { return k_bytes + 16; }
@@ -1016,7 +1020,7 @@ chain_kernel(const LevelArgs a, const ChainArgs lv) {
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int gate = wave & 3, half = wave >> 2;
     const int q4 = lane >> 4, l16 = lane & 15;
-    if (tid == 0) s_tile = __hip_atomic_fetch_add(lv.ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (tid == 0) s_tile = lv.n_levels == 1 ? (int)blockIdx.x : __hip_atomic_fetch_add(lv.ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const int t_lo = lv.tiles[tid < lv.n_levels ? tid : lv.n_levels], t_hi = lv.tiles[tid < lv.n_levels ? tid + 1 : lv.n_levels];
     __syncthreads();
     const int tile = __builtin_amdgcn_readfirstlane(s_tile);     // (the grid has as many blocks as there are tiles)
@@ -1249,7 +1253,7 @@ chain_kernel(const LevelArgs a, const ChainArgs lv) {
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // this wave's rows have arrived
     __syncthreads();
-    if (tid == 0) __hip_atomic_fetch_add(lv.done + (int64_t)row_tile * lv.stride, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (tid == 0 && lv.n_levels > 1) __hip_atomic_fetch_add(lv.done + (int64_t)row_tile * lv.stride, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // ---- host side ---------------------------------------------------------------------
@@ -1443,7 +1447,7 @@ int run_forward(const void *x, const void *W, const void *U, const float *b, con
         // (blocks that look at one line wait for each other: a line per word where the records' memory has room, else a fourth)
         const int64_t room = 8 * (s->n_nodes - sp[chain_from] + kRowPad) - (L - chain_from);
         chain_stride = 32 * n_chain_tiles <= room ? 32 : 4;
-        n_chain_words = n_chain_tiles * chain_stride + ceil_div(L - chain_from, chain_per_launch);
+        n_chain_words = n_chain_tiles * chain_stride + (L - chain_from);
     }
     // A forest of small trees filed one after another: its levels below the chain levels in one launch
     TreesArgs ta = {};
@@ -1757,17 +1761,22 @@ int run_forward(const void *x, const void *W, const void *U, const float *b, con
         }
     }
     int *done = chain_words, *ticket = chain_words ? chain_words + n_chain_tiles * chain_stride : nullptr;
-    for (int l0 = chain_from; l0 < L; l0 += chain_per_launch) {
+    for (int l0 = chain_from; l0 < L;) {
         ChainArgs lv;
         lv.perm = s->perm; lv.inv_perm = s->inv_perm; lv.child_ptr = s->child_ptr; lv.child_idx = s->child_idx;
-        lv.n_levels = L - l0 < chain_per_launch ? L - l0 : chain_per_launch;
+        lv.n_levels = 0;
         lv.done = done;
         lv.ticket = ticket++;
         lv.tiles[0] = 0;
         lv.pos[0] = sp[l0];
-        for (int i = 0; i < lv.n_levels; ++i) {
-            lv.tiles[i + 1] = lv.tiles[i] + (int)ceil_div(sp[l0 + i + 1] - sp[l0 + i], 16 * chain_rt);
-            lv.pos[i + 1] = sp[l0 + i + 1];
+        while (l0 < L && lv.n_levels < chain_per_launch) {
+            const int tiles = (int)ceil_div(sp[l0 + 1] - sp[l0], 16 * chain_rt), i = lv.n_levels;
+            const bool alone = (int64_t)tiles * n_unit_tiles >= kChainAloneTiles;
+            if (alone && i > 0) break;
+            lv.tiles[i + 1] = lv.tiles[i] + tiles;
+            lv.pos[i + 1] = sp[++l0];
+            lv.n_levels = i + 1;
+            if (alone) break;
         }
         const int n_tiles = lv.tiles[lv.n_levels];
         lv.stride = chain_stride;
