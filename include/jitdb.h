@@ -96,7 +96,9 @@ typedef struct {
     int32_t *host_level_kids; /* host [N+1] or NULL, out: entry l < n_levels = number of children of the nodes of
                                           level l (0 for level 0), -1 = not known.  Optional: with it the forward
                                           recognises levels in which every node has exactly one child (chains:
-                                          sequences, the thin tail of a forest) and runs them in one launch */
+                                          sequences, the thin tail of a forest) and runs many of them in one launch.
+                                          inv_perm says there which rows a row waits for; one that is not the inverse
+                                          of perm costs time, one that is NULL makes every such level a launch */
     int32_t tree_window;     /* out: > 0 = positions are in (height, id) order, the trees are filed one after
                                           another and no tree (no run of interleaved trees) is longer than this many
                                           ids: any tree_window + 1 consecutive places between ids hold one that no edge

@@ -945,7 +945,7 @@ static_assert(2 * (kChainLdsMax + 4 * 16 * kEpiStride * 4 + 1024) <= 160 * 1024,
 static_assert(chain_lds_bytes(kChainMaxKBytes2, 2) <= kChainLdsMax && 2 * (chain_lds_bytes(kChainMaxKBytes2, 2) + 4 * 32 * kEpiStride * 4 + 1024) <= 160 * 1024, "two blocks share a CU");
 
 struct ChainArgs {
-    const int32_t *perm, *inv_perm, *child_ptr, *child_idx;     // inv_perm may be nullptr: a tile then waits for the whole level below
+    const int32_t *perm, *inv_perm, *child_ptr, *child_idx;     // inv_perm is not read, and may be nullptr, where n_levels is 1
     int *ticket;                         // tiles drawn so far
     int *done;                           // per row tile of the launch, `stride` words apart: unit tiles finished
     int stride;
@@ -1055,7 +1055,6 @@ chain_kernel(const LevelArgs a, const ChainArgs lv) {
     const int rt_level = row_tile - lv.tiles[l];                 // row tile within the level
     const int row0 = lv.pos[l] + rt_level * ROWS;
     const int n_rows = lv.pos[l + 1] - row0 < ROWS ? lv.pos[l + 1] - row0 : ROWS;
-    const int rt_below = l > 0 ? lv.tiles[l - 1] : 0;
     int wait_lo = 0, wait_hi = -1;                               // row tiles of the launch
     if (wave == 0) {
         const int mine = lane & (ROWS - 1), r = mine < n_rows ? mine : n_rows - 1;   // past the end: computed twice, stored never
@@ -1068,21 +1067,21 @@ chain_kernel(const LevelArgs a, const ChainArgs lv) {
             s_kid[mine] = kid;
         }
         if (l > 0) {
-            const int last = lv.tiles[l] - 1 - rt_below;         // (the bounds hold whatever the schedule's arrays say)
-            int lo = 0, hi = last;
-            if (lv.inv_perm) {
-                int q = (lv.inv_perm[kid < 0 ? 0 : kid] - lv.pos[l - 1]) / ROWS;
-                q = q < 0 ? 0 : q > last ? last : q;
-                lo = hi = q;
+            // A position that is not the child's, or not in the level below (a schedule made by hand), says nothing: the tile then
+            // waits for every tile of the launch's levels below.
+            int q = lv.inv_perm[kid < 0 ? 0 : kid];
+            const bool below = lv.pos[l - 1] <= q && q < lv.pos[l];
+            q = below ? q : lv.pos[l - 1];
+            const bool known = lv.perm[q] == kid && below;
+            int lo = known ? lv.tiles[l - 1] + (q - lv.pos[l - 1]) / ROWS : 0, hi = known ? lo : lv.tiles[l] - 1;
 #pragma unroll
-                for (int d = 1; d < ROWS; d <<= 1) {
-                    const int lo2 = __shfl_xor(lo, d, 64), hi2 = __shfl_xor(hi, d, 64);
-                    lo = lo2 < lo ? lo2 : lo;
-                    hi = hi2 > hi ? hi2 : hi;
-                }
+            for (int d = 1; d < ROWS; d <<= 1) {
+                const int lo2 = __shfl_xor(lo, d, 64), hi2 = __shfl_xor(hi, d, 64);
+                lo = lo2 < lo ? lo2 : lo;
+                hi = hi2 > hi ? hi2 : hi;
             }
-            wait_lo = rt_below + lo;
-            wait_hi = rt_below + hi;
+            wait_lo = lo;
+            wait_hi = hi;
         }
     }
     __syncthreads();
@@ -1431,8 +1430,9 @@ int run_forward(const void *x, const void *W, const void *U, const float *b, con
             JITDB_HIP_CHECK(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, kChainLdsMax));
     }
     // The chain levels' words (a word per row tile, a counter per launch) stand where those levels' row records would.
-    // With the library's event pairs on, a launch holds one level, so that every level has a time of its own.
-    const int chain_per_launch = g_prof.on ? 1 : kChainLevels;
+    // With the library's event pairs on, a launch holds one level, so that every level has a time of its own; so it does without
+    // inv_perm, which says where the rows are that a tile waits for.
+    const int chain_per_launch = g_prof.on || !s->inv_perm ? 1 : kChainLevels;
     int *chain_words = nullptr;
     int64_t n_chain_words = 0, n_chain_tiles = 0;
     int chain_stride = 1, chain_rt = 1;

@@ -43,3 +43,79 @@ def test_chain_levels_in_one_launch(c_oracle, name, dtype, D, H):
         ho, co, _ = c_oracle(p, *seen)
         assert np.abs(h - ho).max() <= TOL[dtype]
         assert np.abs(c - co).max() <= TOL[dtype] * max(1.0, np.abs(co).max() / (8.0 if dtype == "bf16" else 50.0))
+
+
+def _by_hand(name, s):
+    """`s` without what jitdb_schedule says of whole trees, and with positions that are not known or not right."""
+    s.struct.tree_window = 0
+    n = s.inv_perm.shape[0]
+    if name == "none":
+        s.struct.inv_perm = None
+    elif name == "zeros":
+        s.inv_perm.zero_()
+    elif name == "far":
+        s.inv_perm.fill_(2 ** 31 - 1)
+    elif name == "reversed":
+        s.inv_perm.copy_(n - 1 - s.inv_perm)
+    elif name == "neighbour":                                    # the row tile beside the child's, in the same level
+        s.inv_perm.copy_((s.inv_perm + 16) % n)
+
+
+@pytest.mark.parametrize("dtype,D,H", [("f32", 20, 50), ("bf16", 64, 256), ("f32", 300, 256)])
+@pytest.mark.parametrize("name", ["right", "none", "zeros", "far", "reversed", "neighbour"])
+def test_positions_that_are_not_the_inverse_of_perm(c_oracle, name, dtype, D, H):
+    import torch
+    import paper_1904_07421_amd as J
+    from gpu_util import bf16_tensor, dev_parent
+    p = relabel(chain_forest(30, 700), 3)[0]
+    x, W, U, b = make_values(1, p.shape[0], "random", D=D, H=H)
+    print(f"by hand: {name} {dtype} N={p.shape[0]} D={D} H={H}", flush=True)
+    if dtype == "bf16":
+        (xt, xo), (Wt, Wo), (Ut, Uo) = (bf16_tensor(v) for v in (x, W, U))
+    else:
+        (xt, xo), (Wt, Wo), (Ut, Uo) = ((torch.from_numpy(v).cuda(), v) for v in (x, W, U))
+    s = J.jitdb_schedule(dev_parent(p))
+    _by_hand(name, s)
+    ho, co, _ = c_oracle(p, xo, Wo, Uo, b)
+    for _ in range(2):
+        h, c = J.jitdb_treelstm_forward(xt, Wt, Ut, torch.from_numpy(b).cuda(), s)
+        assert np.abs(h.float().cpu().numpy() - ho).max() <= TOL[dtype] and np.abs(c.cpu().numpy() - co).max() <= TOL[dtype]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_a_child_two_levels_below(c_oracle, dtype):
+    """Levels made by hand that are no heights: half of the chains pass every third level by, so that a node's child may lie two
+    levels below it; every node above level 0 has one child."""
+    import torch
+    import paper_1904_07421_amd as J
+    from gpu_util import bf16_tensor, dev_parent
+    D, H = 36, 72
+    p = _lay_out([chain_forest(20 if i % 2 else 30) for i in range(300)])
+    s = J.jitdb_schedule(dev_parent(p))
+    hgt = s.height.cpu().numpy()
+    tree = np.cumsum(p < 0) - 1                                  # (a tree's ids begin with its root)
+    level = np.where(tree % 2 == 1, hgt + hgt // 2, hgt).astype(np.int32)
+    assert (np.bincount(level) > 0).all()
+    perm = np.lexsort((np.arange(p.size), level)).astype(np.int32)
+    inv = np.empty_like(perm)
+    inv[perm] = np.arange(p.size, dtype=np.int32)
+    rows = np.bincount(level)
+    L = rows.size
+    s.struct.tree_window = 0
+    s.n_levels = s.struct.n_levels = L
+    s.height.copy_(torch.from_numpy(level))
+    s.perm.copy_(torch.from_numpy(perm))
+    s.inv_perm.copy_(torch.from_numpy(inv))
+    s.host_level_ptr[:L + 1] = np.concatenate([[0], np.cumsum(rows)])
+    s.level_ptr[:L + 1] = torch.from_numpy(s.host_level_ptr[:L + 1]).cuda()
+    s.host_level_kids[:L] = np.where(np.arange(L) > 0, rows, 0)
+    x, W, U, b = make_values(1, p.shape[0], "random", D=D, H=H)
+    print(f"two levels below: {dtype} N={p.shape[0]} L={L}", flush=True)
+    if dtype == "bf16":
+        (xt, xo), (Wt, Wo), (Ut, Uo) = (bf16_tensor(v) for v in (x, W, U))
+    else:
+        (xt, xo), (Wt, Wo), (Ut, Uo) = ((torch.from_numpy(v).cuda(), v) for v in (x, W, U))
+    ho, co, _ = c_oracle(p, xo, Wo, Uo, b)
+    for _ in range(2):
+        h, c = J.jitdb_treelstm_forward(xt, Wt, Ut, torch.from_numpy(b).cuda(), s)
+        assert np.abs(h.float().cpu().numpy() - ho).max() <= TOL[dtype] and np.abs(c.cpu().numpy() - co).max() <= TOL[dtype]
