@@ -40,6 +40,7 @@
 // exchange between lanes; rows and K are zero padded to tile multiples.
 
 #include "tile_gemm.h"
+#include "bounded_wait.h"
 
 #include <mutex>
 #include <vector>
@@ -908,14 +909,19 @@ nary_thin_kernel(const LevelArgs a, const NaryEpi e, const void *__restrict__ Bx
 //   * a tile is 16 RT rows x 32 units, wave w multiplies gate w % 4; a block takes ONE tile and is done;
 //   * blocks draw their tiles from a counter, in the order of the levels, and a tile waits for the row tiles of
 //     the level below that hold its rows' children: each has a word that counts its finished unit tiles.  Whatever a block
-//     waits for was drawn before, by a block that runs already, so every wait ends, whichever blocks share the chip;
+//     waits for was drawn before, by a block that runs already, so every wait ends, whichever blocks share the chip.  (Should something
+//     else write into the workspace meanwhile, it ends too: after kChainLooks looks the block marks the counter, no block waits any
+//     more, and c and h of the tiles that did not see their children are NaN);
 //   * everything that does not depend on the child is there before the wait: the wave's weights (the first kChainAhead K
 //     groups), the row's ids, x rows in LDS or Z.  Two or more blocks of later levels sit beside the one that multiplies;
 //   * behind the wait the block fetches the children's h once, all loads in flight together, into LDS; the K loop has no
 //     barrier (A fragments from LDS, weights kChainAhead groups ahead); the gates meet in LDS and each of
 //     the first four waves finishes eight of the tile's rows;
-//   * h and c of a child may come from another XCD's block: they are written and read past the L2s (agent-scope
-//     accesses), the word is raised once the stores have arrived (vmcnt 0 in every wave, then the block's barrier);
+//   * h and c of a child may come from another XCD's block, whose L2 is not this one's.  They, the words and the counter are only
+//     touched by atomic accesses of agent scope, which are carried out where all XCDs see them (loads and stores go past the L2s, sc1):
+//     one that vmcnt counts as done has been done for every block.  So no cache need be written back or dropped; what is left is order, and each half of it is made by hand: a block's waves
+//     wait for vmcnt 0 and meet at the barrier before the word is raised, and no wave asks for h or c before wave 0 has seen
+//     the words and met it at the barrier (a load is not started before the branch that it stands behind is decided);
 //   * US = 2 (fp32, whose MFMAs are a long chain for one wave): eight waves, wave w has units 16 (w / 4) .. of its gate;
 //   * RT = 1 spreads a level over more blocks and shortens each one's part of the chain; where bf16 levels have
 //     kChainWideTiles such tiles on average the chip is full and RT = 2 asks half as much of the weights and the words.
@@ -930,6 +936,8 @@ nary_thin_kernel(const LevelArgs a, const NaryEpi e, const void *__restrict__ Bx
 // Needs D % 4 == 0 (an 8- / 16-byte piece of an x row is inside D or outside) and rows of A that leave room for two blocks on a CU.
 constexpr int kChainAhead = 16;                         // weight loads in flight per wave
 constexpr int kChainLevels = 256;                       // levels one launch may hold (its table travels with the arguments)
+constexpr int kChainLooks = 1 << 21;                    // a microsecond or more each; the longest launches take some ten thousand
+constexpr int kChainGaveUp = 1 << 30;                   // in the counter: a block has given up waiting
 constexpr int kChainMaxKBytes = 4304;                   // of a row, RT = 1: two blocks share a CU's LDS
 constexpr int kChainMaxKBytes2 = 1840;                  // ... RT = 2
 // A level of many tiles goes alone, its tiles by block index: thousands of draws from one counter take longer than a launch (8000
@@ -1011,7 +1019,7 @@ chain_kernel(const LevelArgs a, const ChainArgs lv) {
     __shared__ __attribute__((aligned(16))) float zt[4][ROWS * kEpiStride];   // pre-activations, [gate][row][unit]
     __shared__ int s_node[ROWS];
     __shared__ int s_kid[ROWS];
-    __shared__ int s_tile, s_level;
+    __shared__ int s_tile, s_level, s_lost;
     __shared__ __attribute__((aligned(16))) float s_bias[HAS_Z ? 4 : kGateTile];
     static_assert(kChainLevels <= kThinWaves * 64, "a thread per level");
 
@@ -1023,10 +1031,11 @@ chain_kernel(const LevelArgs a, const ChainArgs lv) {
     if (tid == 0) s_tile = lv.n_levels == 1 ? (int)blockIdx.x : __hip_atomic_fetch_add(lv.ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const int t_lo = lv.tiles[tid < lv.n_levels ? tid : lv.n_levels], t_hi = lv.tiles[tid < lv.n_levels ? tid + 1 : lv.n_levels];
     __syncthreads();
-    const int tile = __builtin_amdgcn_readfirstlane(s_tile);     // (the grid has as many blocks as there are tiles)
+    const int drawn = __builtin_amdgcn_readfirstlane(s_tile), place = drawn & (kChainGaveUp - 1);
+    const int tile = place < a.n_blocks ? place : a.n_blocks - 1;     // (always below: the grid has as many blocks as there are tiles)
     const int row_tile = tile / a.n_col_tiles;
     const int col = tile - row_tile * a.n_col_tiles;             // unit tile
-    if (t_lo <= row_tile && row_tile < t_hi) s_level = tid;
+    if (t_lo <= row_tile && row_tile < t_hi) { s_level = tid; s_lost = 0; }
 
     // ---- weights: lane (l16, q4) supplies row l16 of a tile of the wave's gate, bytes [q4*16, +16) of each slab (64 bytes of K).
     //      Every load of the ring is unconditional (a slab past the end is clamped to the last one, whose data is
@@ -1056,6 +1065,7 @@ chain_kernel(const LevelArgs a, const ChainArgs lv) {
     const int row0 = lv.pos[l] + rt_level * ROWS;
     const int n_rows = lv.pos[l + 1] - row0 < ROWS ? lv.pos[l + 1] - row0 : ROWS;
     int wait_lo = 0, wait_hi = -1;                               // row tiles of the launch
+    int astray = 0;                                              // not 0: the row's child is not where inv_perm says
     if (wave == 0) {
         const int mine = lane & (ROWS - 1), r = mine < n_rows ? mine : n_rows - 1;   // past the end: computed twice, stored never
         const int node = lv.perm[row0 + r];
@@ -1067,21 +1077,19 @@ chain_kernel(const LevelArgs a, const ChainArgs lv) {
             s_kid[mine] = kid;
         }
         if (l > 0) {
-            // A position that is not the child's, or not in the level below (a schedule made by hand), says nothing: the tile then
-            // waits for every tile of the launch's levels below.
+            // (a position outside the level below is checked where the wait ends)
             int q = lv.inv_perm[kid < 0 ? 0 : kid];
-            const bool below = lv.pos[l - 1] <= q && q < lv.pos[l];
-            q = below ? q : lv.pos[l - 1];
-            const bool known = lv.perm[q] == kid && below;
-            int lo = known ? lv.tiles[l - 1] + (q - lv.pos[l - 1]) / ROWS : 0, hi = known ? lo : lv.tiles[l] - 1;
+            q = q < lv.pos[l - 1] ? lv.pos[l - 1] : q < lv.pos[l] ? q : lv.pos[l] - 1;
+            astray = lv.perm[q] - kid;
+            int lo = lv.tiles[l - 1] + (q - lv.pos[l - 1]) / ROWS, hi = lo;
 #pragma unroll
             for (int d = 1; d < ROWS; d <<= 1) {
                 const int lo2 = __shfl_xor(lo, d, 64), hi2 = __shfl_xor(hi, d, 64);
                 lo = lo2 < lo ? lo2 : lo;
                 hi = hi2 > hi ? hi2 : hi;
             }
-            wait_lo = lo;
-            wait_hi = hi;
+            wait_lo = __builtin_amdgcn_readfirstlane(lo);
+            wait_hi = __builtin_amdgcn_readfirstlane(hi);
         }
     }
     __syncthreads();
@@ -1133,9 +1141,16 @@ chain_kernel(const LevelArgs a, const ChainArgs lv) {
     }
 
     // ---- wait for the children (wave 0; the others stand at the barrier)
-    for (int w = wait_lo; w <= wait_hi; w += 64) {
+    // A position that is not the child's, or not in the level below (a schedule made by hand), says nothing: the tile then
+    // waits for every tile of the launch's levels below.
+    int looks = drawn == place ? kChainLooks : 0;
+    bool there = true;
+    for (int w = wait_lo; w <= wait_hi;) {
         const int *word = lv.done + (int64_t)(w + lane <= wait_hi ? w + lane : wait_hi) * lv.stride;
-        while (!__all(__hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= a.n_col_tiles)) __builtin_amdgcn_s_sleep(4);
+        there = wait_bounded(a.n_col_tiles, looks, [&](int least) { return __all(__hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= least); },
+                             [] { __builtin_amdgcn_s_sleep(1); });
+        w += 64;
+        if (w > wait_hi && __any(astray != 0)) { astray = 0; w = 0; wait_hi = lv.tiles[l] - 1; }
     }
     asm volatile("" ::: "memory");
     __syncthreads();
@@ -1185,6 +1200,10 @@ chain_kernel(const LevelArgs a, const ChainArgs lv) {
             if (s_kid[(tid >> 5) + RPP * j] < 0)             // (no child after all: zeros)
                 for (int kb = (tid & 31) * 16; kb < h_bytes; kb += 512)
                     *reinterpret_cast<u32x4 *>(a_lds + ((tid >> 5) + RPP * j) * pitch + x_bytes + kb) = u32x4{0u, 0u, 0u, 0u};
+    }
+    if (tid == 0 && !there) {
+        s_lost = 1;
+        __hip_atomic_fetch_or(lv.ticket, kChainGaveUp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     floatx4 acc[RT][NB];
 #pragma unroll
@@ -1239,6 +1258,7 @@ chain_kernel(const LevelArgs a, const ChainArgs lv) {
             z[g][0] = q.x + bq[g].x; z[g][1] = q.y + bq[g].y; z[g][2] = q.z + bq[g].z; z[g][3] = q.w + bq[g].w;
         }
         const float ckv[4] = {ck.x, ck.y, ck.z, ck.w};
+        const bool lost = s_lost != 0;
         float cc[4], go[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
@@ -1247,6 +1267,7 @@ chain_kernel(const LevelArgs a, const ChainArgs lv) {
             const float gu = tanh_t<T>(z[2][e]);
             const float gf = sigmoid_t<T>(z[3][e]);
             cc[e] = gi * gu + gf * ckv[e];
+            if (lost) cc[e] = __builtin_nanf("");
         }
         store_state_shared<T>(a, node, unit0, make_float4(cc[0], cc[1], cc[2], cc[3]), make_float4(go[0], go[1], go[2], go[3]));
     }
@@ -1783,7 +1804,8 @@ int run_forward(const void *x, const void *W, const void *U, const float *b, con
         done += (int64_t)n_tiles * chain_stride;
         a.Bp = w.Bp; a.bp = w.bp;
         a.n_col_tiles = n_unit_tiles;
-        const unsigned grid = (unsigned)n_tiles * (unsigned)n_unit_tiles;
+        a.n_blocks = n_tiles * n_unit_tiles;
+        const unsigned grid = (unsigned)a.n_blocks;
         const int rows = lv.pos[lv.n_levels] - lv.pos[0];
         ScopedLaunchTimer tm(JITDB_K_CHAIN, rows, st, rows);         // (one child a row)
         // (of whole trees the x part is in Z: the h part alone)
