@@ -924,7 +924,8 @@ nary_thin_kernel(const LevelArgs a, const NaryEpi e, const void *__restrict__ Bx
 //     the words and met it at the barrier (a load is not started before the branch that it stands behind is decided);
 //   * US = 2 (fp32, whose MFMAs are a long chain for one wave): eight waves, wave w has units 16 (w / 4) .. of its gate;
 //   * RT = 1 spreads a level over more blocks and shortens each one's part of the chain; where bf16 levels have
-//     kChainWideTiles such tiles on average the chip is full and RT = 2 asks half as much of the weights and the words.
+//     kChainWideTiles such tiles on average the chip is full and RT = 2 asks half as much of the weights and the words.  A launch that
+//     holds one level has no counter, no words and no wait.
 //
 // Schedule + forward, chains / stars / trees in turn, us, one launch a level (13 - 20 us each) -> RT = 2 -> RT = 1:
 // 4096 trees of up to 128 nodes, D 300, H 256 fp32 3567 -> 3231 -> 3033, bf16 2052 -> 1644 -> 1691; 500 trees H 150 fp32
@@ -940,17 +941,26 @@ constexpr int kChainLooks = 1 << 21;                    // a microsecond or more
 constexpr int kChainGaveUp = 1 << 30;                   // in the counter: a block has given up waiting
 constexpr int kChainMaxKBytes = 4304;                   // of a row, RT = 1: two blocks share a CU's LDS
 constexpr int kChainMaxKBytes2 = 1840;                  // ... RT = 2
-// A level of many tiles goes alone, its tiles by block index: thousands of draws from one counter take longer than a launch (8000
-// chains of 4 - 5 nodes, D 300, all levels in one launch -> each alone, us: H 256 bf16 192 -> 172, fp32 552 -> 540, H 512 bf16 453 -> 436,
-// fp32 1369 -> 1330; tiles of 32 rows, one launch a level, 186, 481, 429, 1329).
+// A level of many tiles goes alone, its tiles by block index: thousands of draws from one counter take longer than a launch
+// (8000 chains of 4 - 5 nodes, bf16, all levels in one launch / each alone: H 256 192 / 172 us, H 512 453 / 436).  Such a level
+// fills the chip, and what counts is no longer one block's chain but how often the weights are read and how soon a block is at work:
+// tiles of 32 rows (fp32: up to kChainAloneMaxKBytes2 of a row, above that the second block on a CU, which 32 rows leave no room
+// for, is worth more), and in fp32 half as many loads ahead.  The same forests, us: a launch a level of 32-row tiles whose
+// waves had a part of K each / 16-row tiles, 16 loads ahead / 32 rows, 16 / 32 rows, 8 / 16 rows, 8:
+//   fp32  D 64 H 384 (1792 bytes) 653 / 658 / 553 / 535 / 556    D 300 H 256 (2304) 482 / 541 / 481 / 468 / 527    H 320 (2560) 737 / 752 / 782 / 755 / 645
+//         D 512 H 128 (2560) 355 / 366 / 366 / 356 / 332    H 256 (3072) 714 / 704 / 728 / 710 / 683    D 300 H 512 (3328) 1325 / 1322 / 1380 / 1330 / 1240
+//   bf16  D 300 H 256 (1152) 185 / 173 / 171    D 512 H 512 (2048) 662 / 609 / 595    D 1024 H 512 (3072) 858 / 936 / 768    D 512 H 1024 (3072) 1595 / 1725 / 1435
 constexpr int kChainAloneTiles = 1536;
+constexpr int kChainAloneMaxKBytes2 = 2304;
+constexpr int kChainAloneAhead = 8;
 constexpr int kChainWideTiles = 192;                    // (330 tiles a level: 3 % for RT = 2, 500: 10 %, 31: 13 % for RT = 1)
 // LDS pitch of an A row: K bytes + 16, so that 16 lanes' 16-byte reads of one K group fall in 64 different banks
 __host__ __device__ inline constexpr int chain_row_pitch(int k_bytes) { return k_bytes + 16; }
 inline constexpr int chain_lds_bytes(int k_bytes, int rt) { return 16 * rt * chain_row_pitch(k_bytes); }
-constexpr int kChainLdsMax = chain_lds_bytes(kChainMaxKBytes, 1);
-static_assert(2 * (kChainLdsMax + 4 * 16 * kEpiStride * 4 + 1024) <= 160 * 1024, "two blocks share a CU");
-static_assert(chain_lds_bytes(kChainMaxKBytes2, 2) <= kChainLdsMax && 2 * (chain_lds_bytes(kChainMaxKBytes2, 2) + 4 * 32 * kEpiStride * 4 + 1024) <= 160 * 1024, "two blocks share a CU");
+constexpr int kChainLdsMax = chain_lds_bytes(kChainMaxKBytes, 2);
+static_assert(kChainLdsMax + 4 * 32 * kEpiStride * 4 + 1024 <= 160 * 1024, "a level alone: 32 rows of any width");
+static_assert(2 * (chain_lds_bytes(kChainMaxKBytes, 1) + 4 * 16 * kEpiStride * 4 + 1024) <= 160 * 1024, "two blocks share a CU");
+static_assert(2 * (chain_lds_bytes(kChainMaxKBytes2, 2) + 4 * 32 * kEpiStride * 4 + 1024) <= 160 * 1024, "two blocks share a CU");
 
 struct ChainArgs {
     const int32_t *perm, *inv_perm, *child_ptr, *child_idx;     // inv_perm is not read, and may be nullptr, where n_levels is 1
@@ -1008,13 +1018,13 @@ __device__ __forceinline__ void store_state_shared(const LevelArgs &a, int64_t n
 //
 // HAS_Z: the x part of the pre-activations (and the bias) is in Z already (tree_x_kernel has been over all nodes): A is the
 // child's h alone and K is H.
-template <typename T, int US, int RT, bool HAS_Z>
+template <typename T, int US, int RT, bool HAS_Z, int AHEAD = kChainAhead>
 __global__ void __launch_bounds__(kThinWaves * 64 * US, 4)
 chain_kernel(const LevelArgs a, const ChainArgs lv) {
     constexpr int ESZ = (int)sizeof(T);
     constexpr int ROWS = 16 * RT;
     constexpr int NB = 2 / US;                                            // tiles of 16 units per wave
-    constexpr int RING = kChainAhead / NB;                                // slabs of weights in flight
+    constexpr int RING = AHEAD / NB;                                      // slabs of weights in flight
     extern __shared__ __attribute__((aligned(16))) char a_lds[];          // [16 RT][chain_row_pitch]
     __shared__ __attribute__((aligned(16))) float zt[4][ROWS * kEpiStride];   // pre-activations, [gate][row][unit]
     __shared__ int s_node[ROWS];
@@ -1437,18 +1447,13 @@ int run_forward(const void *x, const void *W, const void *U, const float *b, con
     // below skips it too.
     int chain_from = L;
     const int chain_k_bytes = (d.Dp + d.Hp) * d.esz;
-    constexpr int chain_us = sizeof(T) == 4 ? 2 : 1, chain_rt_max = sizeof(T) == 4 ? 1 : 2;
+    constexpr int chain_us = sizeof(T) == 4 ? 2 : 1, chain_ahead = sizeof(T) == 4 ? kChainAloneAhead : kChainAhead;
     if (!SAVE && !slots && chains && s->host_level_kids && (d.D & 3) == 0 && chain_k_bytes <= kChainMaxKBytes) {
         for (int l = L - 1; l >= 1; --l) {
             const int rows = sp[l + 1] - sp[l];
             if (rows > kThinMaxRows || s->host_level_kids[l] != rows) break;
             chain_from = l;
         }
-    }
-    if (chain_from < L) {    // more dynamic LDS than a launch may ask for by default
-        for (const void *fn : {reinterpret_cast<const void *>(&chain_kernel<T, chain_us, 1, false>), reinterpret_cast<const void *>(&chain_kernel<T, chain_us, 1, true>),
-                               reinterpret_cast<const void *>(&chain_kernel<T, chain_us, chain_rt_max, false>), reinterpret_cast<const void *>(&chain_kernel<T, chain_us, chain_rt_max, true>)})
-            JITDB_HIP_CHECK(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, kChainLdsMax));
     }
     // The chain levels' words (a word per row tile, a counter per launch) stand where those levels' row records would.
     // With the library's event pairs on, a launch holds one level, so that every level has a time of its own; so it does without
@@ -1460,7 +1465,7 @@ int run_forward(const void *x, const void *W, const void *U, const float *b, con
     if (chain_from < L) {
         chain_words = reinterpret_cast<int *>(w.row_rec + 2 * (int64_t)sp[chain_from]);
         for (int l = chain_from; l < L; ++l) n_chain_tiles += ceil_div(sp[l + 1] - sp[l], 16);
-        if (chain_rt_max == 2 && chain_k_bytes <= kChainMaxKBytes2 && n_chain_tiles * (d.Hu / kUnit) >= (int64_t)kChainWideTiles * (L - chain_from)) {
+        if (sizeof(T) == 2 && chain_k_bytes <= kChainMaxKBytes2 && n_chain_tiles * (d.Hu / kUnit) >= (int64_t)kChainWideTiles * (L - chain_from)) {
             chain_rt = 2;
             n_chain_tiles = 0;
             for (int l = chain_from; l < L; ++l) n_chain_tiles += ceil_div(sp[l + 1] - sp[l], 32);
@@ -1781,6 +1786,7 @@ int run_forward(const void *x, const void *W, const void *U, const float *b, con
             JITDB_LAUNCH_CHECK();
         }
     }
+    const void *lds_set = nullptr;      // the kernel that may ask for its LDS
     int *done = chain_words, *ticket = chain_words ? chain_words + n_chain_tiles * chain_stride : nullptr;
     for (int l0 = chain_from; l0 < L;) {
         ChainArgs lv;
@@ -1790,11 +1796,14 @@ int run_forward(const void *x, const void *W, const void *U, const float *b, con
         lv.ticket = ticket++;
         lv.tiles[0] = 0;
         lv.pos[0] = sp[l0];
+        int rt = chain_rt;
+        bool alone = false;
         while (l0 < L && lv.n_levels < chain_per_launch) {
             const int tiles = (int)ceil_div(sp[l0 + 1] - sp[l0], 16 * chain_rt), i = lv.n_levels;
-            const bool alone = (int64_t)tiles * n_unit_tiles >= kChainAloneTiles;
-            if (alone && i > 0) break;
-            lv.tiles[i + 1] = lv.tiles[i] + tiles;
+            alone = (int64_t)tiles * n_unit_tiles >= kChainAloneTiles;
+            if (alone && i > 0) { alone = false; break; }
+            if (alone) rt = chain_k_bytes <= (sizeof(T) == 4 ? kChainAloneMaxKBytes2 : kChainMaxKBytes) ? 2 : 1;
+            lv.tiles[i + 1] = lv.tiles[i] + (rt == chain_rt ? tiles : (int)ceil_div(sp[l0 + 1] - sp[l0], 16 * rt));
             lv.pos[i + 1] = sp[++l0];
             lv.n_levels = i + 1;
             if (alone) break;
@@ -1809,15 +1818,18 @@ int run_forward(const void *x, const void *W, const void *U, const float *b, con
         const int rows = lv.pos[lv.n_levels] - lv.pos[0];
         ScopedLaunchTimer tm(JITDB_K_CHAIN, rows, st, rows);         // (one child a row)
         // (of whole trees the x part is in Z: the h part alone)
-        const size_t lds = (size_t)chain_lds_bytes(trees ? d.Hp * (int)d.esz : chain_k_bytes, chain_rt);
+        const size_t lds = (size_t)chain_lds_bytes(trees ? d.Hp * (int)d.esz : chain_k_bytes, rt);
         constexpr int nt = kThinWaves * 64 * chain_us;
-        if (chain_rt == 1) {
-            if (trees) chain_kernel<T, chain_us, 1, true><<<grid, nt, lds, st>>>(a, lv);
-            else chain_kernel<T, chain_us, 1, false><<<grid, nt, lds, st>>>(a, lv);
-        } else {
-            if (trees) chain_kernel<T, chain_us, chain_rt_max, true><<<grid, nt, lds, st>>>(a, lv);
-            else chain_kernel<T, chain_us, chain_rt_max, false><<<grid, nt, lds, st>>>(a, lv);
+        const auto fn = alone ? (rt == 2 ? (trees ? &chain_kernel<T, chain_us, 2, true, chain_ahead> : &chain_kernel<T, chain_us, 2, false, chain_ahead>)
+                                         : (trees ? &chain_kernel<T, chain_us, 1, true, chain_ahead> : &chain_kernel<T, chain_us, 1, false, chain_ahead>))
+                              : (rt == 2 ? (trees ? &chain_kernel<T, chain_us, 2, true> : &chain_kernel<T, chain_us, 2, false>)
+                                         : (trees ? &chain_kernel<T, chain_us, 1, true> : &chain_kernel<T, chain_us, 1, false>));
+        // more dynamic LDS than a launch may ask for by default (always the same, whatever this call needs: other threads' calls set it too)
+        if (reinterpret_cast<const void *>(fn) != lds_set) {
+            lds_set = reinterpret_cast<const void *>(fn);
+            JITDB_HIP_CHECK(hipFuncSetAttribute(lds_set, hipFuncAttributeMaxDynamicSharedMemorySize, kChainLdsMax));
         }
+        fn<<<grid, nt, lds, st>>>(a, lv);
         JITDB_LAUNCH_CHECK();
     }
     return JITDB_OK;

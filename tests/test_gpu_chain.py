@@ -119,3 +119,43 @@ def test_a_child_two_levels_below(c_oracle, dtype):
     for _ in range(2):
         h, c = J.jitdb_treelstm_forward(xt, Wt, Ut, torch.from_numpy(b).cuda(), s)
         assert np.abs(h.float().cpu().numpy() - ho).max() <= TOL[dtype] and np.abs(c.cpu().numpy() - co).max() <= TOL[dtype]
+
+
+@pytest.mark.parametrize("whole_trees", [True, False])
+@pytest.mark.parametrize("dtype,D,H,wide", [
+    ("f32", 20, 256, 3073),          # 1152 bytes of K: alone in tiles of 32 rows
+    ("f32", 36, 320, 2449),          # wider than whole trees of fp32 go
+    ("f32", 300, 320, 2449),         # 2560 bytes: alone in tiles of 16
+    ("bf16", 64, 256, 3100),         # few tiles a level on average: shared ones of 16 rows, alone 32
+    ("bf16", 512, 512, 1537),        # 2048 bytes: 32 rows leave room for one block on a CU
+])
+def test_wide_and_narrow_levels_in_one_forward(c_oracle, dtype, D, H, wide, whole_trees):
+    """Levels that go alone, then many that share launches; every level in a launch of its own (event pairs on) takes the same
+    tiles and gives the same bits."""
+    import torch
+    import paper_1904_07421_amd as J
+    from gpu_util import bf16_tensor, dev_parent
+    p = _lay_out([chain_forest(2 + (i < 100) + (i < 70) * (i % 50) + 270 * (i == 3)) for i in range(wide)])
+    x, W, U, b = make_values(1, p.shape[0], "random", D=D, H=H)
+    print(f"wide and narrow: {dtype} N={p.shape[0]} D={D} H={H}", flush=True)
+    if dtype == "bf16":
+        (xt, xo), (Wt, Wo), (Ut, Uo) = (bf16_tensor(v) for v in (x, W, U))
+    else:
+        (xt, xo), (Wt, Wo), (Ut, Uo) = ((torch.from_numpy(v).cuda(), v) for v in (x, W, U))
+    bt = torch.from_numpy(b).cuda()
+    s = J.jitdb_schedule(dev_parent(p))
+    if not whole_trees:
+        s.struct.tree_window = 0
+    outs = [J.jitdb_treelstm_forward(xt, Wt, Ut, bt, s) for _ in range(2)]
+    outs.append(J.jitdb_treelstm_forward_packed(xt, J.jitdb_treelstm_pack(Wt, Ut, bt), s))
+    J.jitdb_profile_start(4096)
+    try:
+        outs.append(J.jitdb_treelstm_forward(xt, Wt, Ut, bt, s))
+        torch.cuda.synchronize()
+    finally:
+        prof = J.jitdb_profile_stop()
+    assert prof["chain"]["launches"] == s.n_levels - 1
+    for h, c in outs[1:]:
+        assert torch.equal(h, outs[0][0]) and torch.equal(c, outs[0][1])
+    ho, co, _ = c_oracle(p, xo, Wo, Uo, b)
+    assert np.abs(outs[0][0].float().cpu().numpy() - ho).max() <= TOL[dtype] and np.abs(outs[0][1].cpu().numpy() - co).max() <= TOL[dtype]
