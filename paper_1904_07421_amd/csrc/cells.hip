@@ -78,33 +78,23 @@ nary_stack_kernel(const T *__restrict__ x, int D, int Dp, const T *__restrict__ 
                   int *__restrict__ err) {
     // N: the cell's child positions; Nk <= N: positions stacked for this slot (0 for a slot of leaves)
     constexpr int VEC = Traits<T>::VEC;
-    int64_t row0;
+    int64_t row;
     int pair;
-    stack_tile(blockIdx.x, (Dp + Nk * Hp) / (8 * VEC), row0, pair);
-    if (row0 >= n_rows) return;
+    stack_place(blockIdx.x, (Dp + Nk * Hp) / (8 * VEC), n_rows, row, pair);
+    if (row >= n_rows) return;
     const int kp = pair * 8 * VEC, k0 = kp + (int)(threadIdx.x & 7) * VEC;
     const int l = kp < Dp ? -1 : (kp - Dp) / Hp;             // the pair is x's or one child's
-    u32x4 o[kStackPerThread];
-    int64_t row[kStackPerThread];
-#pragma unroll
-    for (int i = 0; i < kStackPerThread; ++i) {
-        row[i] = row0 + i * (kStackRows / kStackPerThread) + (threadIdx.x >> 3);
-        const int64_t r = row[i] < n_rows ? row[i] : n_rows - 1;
-        const int4 r0 = row_rec[2 * r];
-        if (l < 0) {
-            o[i] = load_x_piece<T>(x + (int64_t)r0.x * D, k0, D);
-            if (pair == 0 && r0.y > N) *err = 1;
-        } else {
-            const int4 kids = row_rec[2 * r + 1];
-            const int kid = l == 0 ? kids.x : l == 1 ? kids.y : l == 2 ? kids.z : kids.w;
-            o[i] = u32x4{0u, 0u, 0u, 0u};
-            if (l < r0.y) o[i] = *reinterpret_cast<const u32x4 *>(hs + (int64_t)kid * Hp + (k0 - Dp - l * Hp));   // pad columns of hs are zero
-        }
+    const int4 r0 = row_rec[2 * row];
+    u32x4 o = {0u, 0u, 0u, 0u};
+    if (l < 0) {
+        o = load_x_piece<T>(x + (int64_t)r0.x * D, k0, D);
+        if (pair == 0 && r0.y > N) *err = 1;
+    } else {
+        const int4 kids = row_rec[2 * row + 1];
+        const int kid = l == 0 ? kids.x : l == 1 ? kids.y : l == 2 ? kids.z : kids.w;
+        if (l < r0.y) o = *reinterpret_cast<const u32x4 *>(hs + (int64_t)kid * Hp + (k0 - Dp - l * Hp));   // pad columns of hs are zero
     }
-#pragma unroll
-    for (int i = 0; i < kStackPerThread; ++i)
-        if (row[i] < n_rows)
-            *reinterpret_cast<u32x4 *>(reinterpret_cast<char *>(A) + operand_offset(row[i], (int64_t)k0 * sizeof(T), n_rows_alloc)) = o[i];
+    *reinterpret_cast<u32x4 *>(reinterpret_cast<char *>(A) + operand_offset(row, (int64_t)k0 * sizeof(T), n_rows_alloc)) = o;
 }
 
 }  // namespace

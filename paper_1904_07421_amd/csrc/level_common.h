@@ -219,18 +219,28 @@ __device__ __forceinline__ bool enter_range(LevelArgs &a, int tile, int &row0) {
 // ---- stack steps: which pieces of the K-blocked input a block writes ---------------------
 // A block of kThreads threads writes kStackRows rows x 128 bytes of K (two slabs; rows of A are padded to whole pairs): eight
 // lanes take the 128 bytes of a row, so rows are read in whole lines and a wave writes runs of 512 bytes.  The pairs of a row tile
-// follow each other on one XCD: the lines that two pairs of a misaligned x row share come from that L2.
+// follow each other on one XCD (eight row tiles side by side; the last few one after another): the lines that two pairs of a misaligned x
+// row share come from that L2.
 // Bound by memory.  Against one thread per 16 bytes in row order (64-byte writes from blocks on different XCDs, a 64-bit division per
-// piece): inner levels of 2.36 M + 296 k nodes, H 512, bf16 1666 -> 1280 us, N-ary (x element by element) 293 -> 203.
-constexpr int kStackPerThread = 2;                       // rows of a thread, their loads side by side
-constexpr int kStackRows = kThreads / 8 * kStackPerThread;
-inline unsigned stack_grid(int64_t n_rows, int64_t k_bytes) {
-    return (unsigned)(8 * ceil_div(ceil_div(n_rows, kStackRows), 8) * (k_bytes / 128));
-}
-__device__ __forceinline__ void stack_tile(unsigned block, int n_pairs, int64_t &row0, int &pair) {
-    const unsigned q = block >> 3;
-    pair = (int)(q % (unsigned)n_pairs);
-    row0 = ((int64_t)(q / (unsigned)n_pairs) * 8 + (block & 7)) * kStackRows;
+// piece): inner levels of 2.36 M + 296 k nodes, H 512, bf16 1640 -> 1250 us (4.5 TB/s), N-ary (x element by element) 293 -> 197.
+// Two rows a thread are no faster there (1250 - 1270, N-ary 203) and leave the chip idle on thin levels: 3000 trees, H 512, bf16, schedule and forward
+// 745 us against 688, the projection of a thin level with the next stack step 14.0 us against 12.4.
+constexpr int kStackRows = kThreads / 8;
+inline unsigned stack_grid(int64_t n_rows, int64_t k_bytes) { return (unsigned)(ceil_div(n_rows, kStackRows) * (k_bytes / 128)); }
+// row and pair of slabs of the thread; past n_rows in the last row tile
+__device__ __forceinline__ void stack_place(unsigned block, int n_pairs, int n_rows, int64_t &row, int &pair) {
+    const unsigned tiles = (unsigned)((n_rows + kStackRows - 1) / kStackRows), pairs = (unsigned)n_pairs, eights = (tiles & ~7u) * pairs;
+    unsigned tile;
+    if (block < eights) {
+        const unsigned q = block >> 3;
+        pair = (int)(q % pairs);
+        tile = q / pairs * 8 + (block & 7);
+    } else {
+        const unsigned q = block - eights;
+        pair = (int)(q % pairs);
+        tile = (tiles & ~7u) + q / pairs;
+    }
+    row = (int64_t)tile * kStackRows + (threadIdx.x >> 3);
 }
 // 16 bytes of a row of x from element k0 on, zero past D (rows may start on any element boundary).
 template <typename T>

@@ -1,4 +1,4 @@
-"""Stack steps (forward.hip, cells.hip): rows around the 64 of a block and the 512 of the blocks that the XCDs take in turn, widths around
+"""Stack steps (forward.hip, cells.hip): rows around the 32 of a block and the 256 of the blocks that the XCDs take in turn, widths around
 the 128 bytes of K that a block writes, rows of x on any element boundary, long child lists; against the oracles."""
 import numpy as np
 import pytest
@@ -23,7 +23,7 @@ def _stars(roots, kids):
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
-@pytest.mark.parametrize("roots,kids,D,H", [(1, 1, 1, 257), (63, 6, 31, 257), (64, 4, 32, 260), (65, 7, 33, 264), (511, 2, 63, 257),
+@pytest.mark.parametrize("roots,kids,D,H", [(1, 1, 1, 257), (31, 3, 64, 257), (32, 9, 3, 258), (33, 5, 300, 257), (63, 6, 31, 257), (64, 4, 32, 260), (65, 7, 33, 264), (255, 4, 65, 260), (256, 5, 37, 264), (257, 6, 33, 257), (511, 2, 63, 257),
                                             (512, 3, 64, 257), (513, 5, 65, 320), (700, 9, 203, 260)])
 def test_stack(c_oracle, roots, kids, D, H, dtype):
     p = _stars(roots, kids)
@@ -36,7 +36,7 @@ def test_stack(c_oracle, roots, kids, D, H, dtype):
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
-@pytest.mark.parametrize("roots,N,D,H", [(1, 1, 1, 1), (64, 2, 32, 33), (65, 3, 65, 31), (513, 4, 203, 64)])
+@pytest.mark.parametrize("roots,N,D,H", [(1, 1, 1, 1), (33, 3, 64, 32), (64, 2, 32, 33), (65, 3, 65, 31), (255, 2, 33, 40), (257, 4, 31, 33), (513, 4, 203, 64)])
 def test_stack_of_nary_cells(roots, N, D, H, dtype):
     p = _stars(roots, N)
     _check(p, np.zeros(p.shape[0], np.int32), [N], D, H, dtype, 5)
