@@ -1511,10 +1511,10 @@ int run_forward(const void *x, const void *W, const void *U, const float *b, con
             p.bp = w.bp + (size_t)d.NP * t;
             return p;
         };
-        const bool large = s->n_nodes >= kRecLargeMinNodes;
         const bool pack_here = !(packed || is_nary(0));
         // records of the levels that run one by one; the chain levels' words are cleared in the same launch
         const int rec_end = trees ? 0 : sp[chain_from * (slots ? n_sig * n_sig : 1)];
+        const bool large = rec_end > 0 && s->n_nodes >= kRecLargeMinNodes;      // (whole trees have no records: perhaps nothing to launch)
         {
             const int per_window = large ? kRecWindowLarge : kRecWindow;
             const int n_windows = (int)ceil_div((int64_t)rec_end, per_window);
