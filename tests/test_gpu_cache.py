@@ -27,12 +27,16 @@ def test_fingerprint_bit_exact(cfg):
     ("zero-word", np.array([0], dtype=np.int32)),            # not a forest: the fingerprint does not care
     ("block-edge-1024", chain_forest(4, 256)),
     ("block-edge-1025", np.concatenate([chain_forest(4, 256), [-1]]).astype(np.int32)),
+    # four words a turn, one or two turns of all 256 blocks, and what is left over
+    ("turn", np.arange(-1, 4 * 256 * 1024 - 1, dtype=np.int32)),
+    ("turn-less-one", np.arange(-1, 4 * 256 * 1024 - 2, dtype=np.int32)),
+    ("turns", np.arange(-1, 7 * 256 * 1024 + 5, dtype=np.int32)),
     ("arbitrary-values", np.array([-7, 2**31 - 1, -2**31, 5], dtype=np.int32)),
 ])
 def test_fingerprint_edges(name, parent):
     import paper_1904_07421_amd as J
     print(f"fingerprint {name}", flush=True)
-    assert J.jitdb_forest_fingerprint(dev_parent(parent)) == C.fingerprint(parent)
+    assert J.jitdb_forest_fingerprint(dev_parent(parent)) == (C.fingerprint if parent.size < 20000 else C.fingerprint_fast)(parent)
 
 
 def test_fingerprint_repeatable_and_sensitive():
