@@ -119,11 +119,15 @@ pack_weights_kernel(const PackArgs p) {
 // 117 -> 86 us), and a forest whose large windows are fewer than 32 blocks leaves the chip idle and takes the small ones.  Schedule
 // and forward with large / small windows, us: 296 k nodes H 512 bf16 1720 / 1696, H 256 1037 / 1001, four cells 1851 / 1792, N-ary
 // 1506 / 1479; 432 k nodes H 300 fp32 6298 / 6269; 595 k H 512 2993 / 2997; 1.18 M 5561 / 5631; 2.36 M 10 651 / 10 767.
+// The training forward's cell update writes the gates as well and loses more to lists of different length in one pass; it takes the large ones from
+// half as many nodes on.  Training step, us, large / small: 286 k nodes of skewed arity H 512 bf16 5725 / 5780, 468 k 8800 / 8860, 338 k H 200 fp32
+// 12 350 / 12 440, 468 k of even arity H 512 bf16 9100 / 9210, H 256 3640 / 3640, of skewed arity 3615 / 3595.
 constexpr int kRecPerThread = 16;
 constexpr int kRecWindow = kRecPerThread * kThreads;          // 4096
 constexpr int kRecThreadsLarge = 1024;
 constexpr int kRecWindowLarge = kRecPerThread * kRecThreadsLarge;   // 16384
 constexpr int64_t kRecLargeMinNodes = 524288;      // forests of at least this many nodes take the large windows
+constexpr int64_t kRecLargeMinNodesSave = 262144;  // ... in the training forward
 
 // window `window` of the records (NT threads, kRecPerThread records each) of the positions below `end`, in a forest of n nodes
 template <int NT>
@@ -1514,7 +1518,7 @@ int run_forward(const void *x, const void *W, const void *U, const float *b, con
         const bool pack_here = !(packed || is_nary(0));
         // records of the levels that run one by one; the chain levels' words are cleared in the same launch
         const int rec_end = trees ? 0 : sp[chain_from * (slots ? n_sig * n_sig : 1)];
-        const bool large = rec_end > 0 && s->n_nodes >= kRecLargeMinNodes;      // (whole trees have no records: perhaps nothing to launch)
+        const bool large = rec_end > 0 && s->n_nodes >= (SAVE ? kRecLargeMinNodesSave : kRecLargeMinNodes);      // (whole trees have no records: perhaps nothing to launch)
         {
             const int per_window = large ? kRecWindowLarge : kRecWindow;
             const int n_windows = (int)ceil_div((int64_t)rec_end, per_window);

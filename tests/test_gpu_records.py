@@ -39,3 +39,24 @@ def test_records(c_oracle, name, dtype):
     ho, co, _ = c_oracle(p, *seen)
     assert np.abs(h - ho).max() <= TOL[dtype]
     assert np.abs(c - co).max() <= TOL[dtype] * max(1.0, np.abs(co).max() / (8.0 if dtype == "bf16" else 50.0))
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_training_forward_takes_other_windows(dtype):
+    """From 262 144 nodes on the training forward orders its rows in larger windows than the forward."""
+    import torch
+    import paper_1904_07421_amd as J
+    from gpu_util import dev_parent
+    p = _lay_out([star_forest(2 + 7 * i % 23) for i in range(20300)] + [chain_forest(3)])
+    assert 262144 < p.shape[0] < 300000
+    D, H, dt = 20, 260, torch.float32 if dtype == "f32" else torch.bfloat16       # wider than whole trees go
+    g = torch.Generator(device="cuda").manual_seed(7)
+    r = lambda *s: torch.rand(s, generator=g, device="cuda") - 0.5
+    x, W, U, b = r(len(p), D).to(dt), r(4 * H, D).to(dt), (r(4 * H, H) * 0.3).to(dt), r(4 * H)
+    s = J.jitdb_schedule(dev_parent(p))
+    h, c = J.jitdb_treelstm_forward(x, W, U, b, s)
+    ht, ct, gates, fgate = J.jitdb_treelstm_forward_train(x, W, U, b, s)
+    # two forms of the same sums (the training forward has no chain levels, and other levels are thin): 24-bit sums of up to 280 products of at
+    # most 1/4, or (bf16) operands of eight bits; c adds up to 23 children
+    tol = 2e-5 if dtype == "f32" else 2e-2
+    assert (h.float() - ht.float()).abs().max() <= tol and (c - ct).abs().max() <= tol * max(1.0, float(c.abs().max()))
