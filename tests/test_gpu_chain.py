@@ -159,3 +159,17 @@ def test_wide_and_narrow_levels_in_one_forward(c_oracle, dtype, D, H, wide, whol
         assert torch.equal(h, outs[0][0]) and torch.equal(c, outs[0][1])
     ho, co, _ = c_oracle(p, xo, Wo, Uo, b)
     assert np.abs(outs[0][0].float().cpu().numpy() - ho).max() <= TOL[dtype] and np.abs(outs[0][1].cpu().numpy() - co).max() <= TOL[dtype]
+
+
+@pytest.mark.parametrize("rows", [40, 230])
+@pytest.mark.parametrize("dtype,D,H", [("f32", 300, 512), ("f32", 512, 512), ("bf16", 300, 512), ("bf16", 512, 512), ("bf16", 512, 1600)])
+def test_rows_of_many_bytes(c_oracle, dtype, D, H, rows):
+    """Rows of 1664 to 4224 bytes of K in levels that share a launch; 230 rows a level are enough tiles for bf16 tiles of 32 rows up to
+    1840 bytes."""
+    p = chain_forest(12, rows)
+    x, W, U, b = make_values(1, p.shape[0], "random", D=D, H=H)
+    print(f"wide rows: {dtype} N={p.shape[0]} D={D} H={H}", flush=True)
+    for _ in range(2):
+        s, h, c, seen = run_gpu_forward(p, x, W, U, b, dtype)
+        ho, co, _ = c_oracle(p, *seen)
+        assert np.abs(h - ho).max() <= TOL[dtype] and np.abs(c - co).max() <= TOL[dtype]

@@ -443,7 +443,7 @@ def test_default_buffers_follow_the_launch_stream(c_oracle):
         assert np.abs(h.cpu().numpy() - ho).max() <= 1e-4 and np.abs(c.cpu().numpy() - co).max() <= 1e-4
 
 
-# ---- levels of one-child nodes (one launch per level) ------------------------------------------
+# ---- levels of one-child nodes (they share launches; under the event pairs every one has its own) -
 def _profile_classes(fn):
     """Run fn() under the library's per-kernel timers; returns launches per class."""
     import torch
@@ -457,19 +457,32 @@ def _profile_classes(fn):
     return out, {k: v["launches"] for k, v in prof.items() if isinstance(v, dict)}
 
 
+def _same_without_timers(sched, h, c, seen, dtype):
+    """The chain levels of an ordinary call share launches (rows wait for their children's): the same bits as the timed call."""
+    import torch
+    import paper_1904_07421_amd as J
+    x, W, U, b = seen
+    to = (lambda a: torch.from_numpy(np.ascontiguousarray(a, np.float32)).cuda()) if dtype == "f32" else \
+        (lambda a: torch.from_numpy(np.ascontiguousarray(a, np.float32)).cuda().to(torch.bfloat16))      # (bf16 values already)
+    args = (to(x), to(W), to(U), torch.from_numpy(np.ascontiguousarray(b, np.float32)).cuda(), sched)
+    for _ in range(2):
+        h2, c2 = J.jitdb_treelstm_forward(*args)
+        assert np.array_equal(h2.float().cpu().numpy(), h) and np.array_equal(c2.cpu().numpy(), c)
+
+
 def _trees_and_sequences(n_trees, n_seqs, len_hi, seed):
     from workloads import mixed_forest
     return mixed_forest(2, n_trees, n_seqs, 2, len_hi, seed)[0]
 
 
 @pytest.mark.parametrize("dtype,D,H", [("f32", 300, 256), ("bf16", 300, 512), ("f32", 44, 50), ("bf16", 44, 50),
-                                       ("bf16", 64, 72), ("f32", 300, 512), ("f32", 512, 512), ("f32", 4, 1)])
-def test_chain_levels_run_as_one_launch_each(c_oracle, dtype, D, H):
+                                       ("bf16", 64, 72), ("f32", 300, 512), ("f32", 512, 512), ("f32", 4, 1), ("bf16", 512, 512),
+                                       ("bf16", 1024, 1024)])
+def test_chain_levels(c_oracle, dtype, D, H):
     """Parse trees plus sequences up to 90 long: above the trees' heights every level holds only nodes
-    with one child and takes the single-launch kernel (x and the child's h read in place, all four
-    gates full K); below, the usual stack / level / projection launches.  Padded widths included.
-    fp32 splits K over two waves per gate where the LDS beside the A tile allows: (300, 256), (300, 512) and the
-    small widths do, (512, 512) does not."""
+    with one child and takes the chain kernel (x and the child's h read in place, all four
+    gates full K): a launch each under the event pairs, launches of many levels without; below, the usual stack / level /
+    projection launches.  Padded widths included; rows of 256 to 4096 bytes of K."""
     parent = _trees_and_sequences(300, 700, 90, 5)
     x, W, U, b = make_values(2, parent.shape[0], "random", D=D, H=H)
     (res, launches) = _profile_classes(lambda: run_gpu_forward(parent, x, W, U, b, dtype))
@@ -489,6 +502,7 @@ def test_chain_levels_run_as_one_launch_each(c_oracle, dtype, D, H):
     ho, co = _oracle(c_oracle, parent, seen)
     eh, ec = _report(f"chain-levels/{dtype}", h, c, ho, co)
     assert eh <= TOL[dtype] and ec <= TOL[dtype] * _c_scale(dtype, co)
+    _same_without_timers(sched, h, c, seen, dtype)
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
@@ -506,6 +520,7 @@ def test_chain_levels_need_the_child_counts_and_whole_x_pieces(c_oracle, dtype):
         ho, co = _oracle(c_oracle, parent, seen)
         eh, ec = _report(f"chain D={D}/{dtype}", h, c, ho, co)
         assert eh <= TOL[dtype] and ec <= TOL[dtype] * _c_scale(dtype, co)
+        _same_without_timers(sched, h, c, seen, dtype)
         if D % 4 == 0:
             # the same schedule with the counts withheld
             sched.host_level_kids[:] = -1
@@ -519,7 +534,7 @@ def test_chain_levels_need_the_child_counts_and_whole_x_pieces(c_oracle, dtype):
 
 
 def test_chain_levels_inside_a_captured_graph(c_oracle):
-    """The single-launch kernel of chain levels asks for more dynamic LDS than the default; the attribute is
+    """The kernel of chain levels asks for more dynamic LDS than the default; the attribute is
     set outside the stream's work, so the forward still records into a HIP graph and every replay matches."""
     import torch
     import paper_1904_07421_amd as J
@@ -593,7 +608,7 @@ def test_children_per_level_are_optional_in_the_c_struct(c_oracle):
 @pytest.mark.parametrize("seed", list(range(8)))
 def test_chain_levels_random_shapes(c_oracle, seed):
     """Random widths (H from 1 up, D any multiple of 4), tree / sequence mixes and row counts around the
-    tile edges, both types: the single-launch levels against the oracle."""
+    tile edges, both types: the chain levels against the oracle."""
     rng = np.random.default_rng(100 + seed)
     D = int(rng.choice([4, 8, 12, 36, 100, 132, 300]))
     H = int(rng.integers(1, 200))
@@ -615,3 +630,4 @@ def test_chain_levels_random_shapes(c_oracle, seed):
     ho, co = _oracle(c_oracle, parent, seen)
     eh, ec = _report(f"chain-random/{seed}", h, c, ho, co)
     assert eh <= TOL[dtype] and ec <= TOL[dtype] * _c_scale(dtype, co)
+    _same_without_timers(sched, h, c, seen, dtype)
