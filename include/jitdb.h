@@ -170,8 +170,9 @@ int jitdb_schedule_append(const jitdb_schedule_t *base, const int32_t *parent_ne
  *
  *   parent    dev [n_nodes] int32 (any values: the fingerprint does not validate the forest)
  *   fp_dev    dev [2] uint64, written by the kernels
- *   fp_host   host [2] uint64 or NULL.  If given, the result is copied there and the stream is
- *             synchronised once; if NULL the call is asynchronous.
+ *   fp_host   host [2] uint64 or NULL.  If given, the call waits until the result stands there: everything
+ *             put on the stream before it has finished then, parent has been read and fp_dev written, but
+ *             a query may still find the stream busy.  If NULL the call is asynchronous.
  */
 int jitdb_forest_fingerprint(const int32_t *parent, int64_t n_nodes, uint64_t *fp_dev,
                              uint64_t *fp_host, void *hip_stream);
@@ -335,9 +336,9 @@ size_t jitdb_treelstm_workspace_bytes(int64_t n_nodes, int64_t n_edges,
  * that one stream.  N == 0 succeeds and launches nothing.
  *
  * If s->host_level_kids is set, the run of top levels in which every node has
- * exactly one child (kids == nodes of the level; sequences, thin tails) takes
- * one launch per level that reads x and the child's h, c in place; the results
- * agree with the general launches within rounding (the forget gate's two
+ * exactly one child (kids == nodes of the level; sequences, thin tails) reads x
+ * and the child's h, c in place, up to 256 levels in a launch, a level that fills the
+ * chip in one of its own; the results agree with the general launches within rounding (the forget gate's two
  * products are then summed in one accumulator).  Without it every level takes
  * the general launches.
  */
@@ -442,7 +443,8 @@ int jitdb_treelstm_backward(const void *x, const void *W, const void *U,
  * and jitdb_profile_stop every kernel launch of jitdb_treelstm_forward is
  * bracketed by a pair of HIP events recorded on the call's stream.  The event records keep
  * consecutive kernels from overlapping, so a recorded call runs a few per cent slower (much
- * slower for forests of many thin levels): time throughput without recording.
+ * slower for forests of many thin levels; levels of one-child nodes, which otherwise share launches,
+ * get one each, so that every level has its time): time throughput without recording.
  *
  *   jitdb_profile_start(capacity)  creates `capacity` event pairs (host objects)
  *                                  and switches recording on; launches beyond the

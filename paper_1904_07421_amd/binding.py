@@ -554,7 +554,7 @@ def _forward(x, W, U, b, schedule, stream, workspace, out, train):
 
 
 def jitdb_forest_fingerprint(parent, stream=None, fp_dev=None) -> Tuple[int, int]:
-    """(fp[0], fp[1]) of an int32 CUDA parent tensor; synchronises the stream."""
+    """(fp[0], fp[1]) of an int32 CUDA parent tensor; waits for them."""
     import torch
     if parent.dtype != torch.int32 or not parent.is_cuda or not parent.is_contiguous():
         raise TypeError("parent must be a contiguous int32 CUDA tensor")

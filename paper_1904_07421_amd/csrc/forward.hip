@@ -19,7 +19,7 @@
 //                      from L2; a thin level's projection and the next level's stack
 //                      step share one launch (thin_proj_stack_kernel)
 //   chain_kernel       the thin levels whose nodes all have exactly one child (sequences, the long
-//                      tail of a deep forest) in ONE launch: x and the child's h read in place,
+//                      tail of a deep forest), many of them in one launch: x and the child's h read in place,
 //                      all four gates over the full K, no stack step and no projection
 //   tree_x_kernel, trees_kernel   (trees.hip) a forest of small trees filed one after another: all of the above in two launches
 //
@@ -222,9 +222,8 @@ __device__ __forceinline__ void row_record_body(const int32_t *__restrict__ perm
     }
 }
 
-// Once per forward, in one launch: the row records of every level position from window first_window on (blocks
-// [0, n_windows)) and the first cell's packed weights (the remaining blocks); neither needs
-// the other.
+// Once per forward, in one launch: the row records of the level positions below `end` (blocks [0, n_windows)), the packed
+// weights (the remaining blocks), and zeros in the n_clear words from `clear` on (all of them); none needs the others.
 template <typename T>
 __global__ void __launch_bounds__(kThreads)
 prepare_kernel(const int32_t *__restrict__ perm, const int32_t *__restrict__ key,
@@ -905,8 +904,8 @@ nary_thin_kernel(const LevelArgs a, const NaryEpi e, const void *__restrict__ Bx
 // A level in which every node has exactly one child (sequences filed as chains, the long thin tail of a forest) needs
 // neither the stack step nor the projection: the child sum is the child's h, read in place, and U_f h_k belongs to the
 // same row, so the forget gate is a fourth full-K product like i, o and u.  What such levels cost is not their work but
-// the string of dependent trips to memory inside each of them and the gap between launches, so all of them run in
-// one launch (kChainLevels of them; more take another launch) that follows each row through the levels:
+// the string of dependent trips to memory inside each of them and the gap between launches, so up to kChainLevels of them run in
+// one launch that follows each row through the levels (one that fills the chip goes alone, kChainAloneTiles):
 //
 //   * a tile is 16 RT rows x 32 units, wave w multiplies gate w % 4; a block takes ONE tile and is done;
 //   * blocks draw their tiles from a counter, in the order of the levels, and a tile waits for the row tiles of
@@ -918,7 +917,7 @@ nary_thin_kernel(const LevelArgs a, const NaryEpi e, const void *__restrict__ Bx
 //     groups), the row's ids, x rows in LDS or Z.  Two or more blocks of later levels sit beside the one that multiplies;
 //   * behind the wait the block fetches the children's h once, all loads in flight together, into LDS; the K loop has no
 //     barrier (A fragments from LDS, weights kChainAhead groups ahead); the gates meet in LDS and each of
-//     the first four waves finishes eight of the tile's rows;
+//     the first 2 RT waves finishes eight of the tile's rows;
 //   * h and c of a child may come from another XCD's block, whose L2 is not this one's.  They, the words and the counter are only
 //     touched by atomic accesses of agent scope, which are carried out where all XCDs see them (loads and stores go past the L2s, sc1):
 //     one that vmcnt counts as done has been done for every block.  So no cache need be written back or dropped; what is left is order, and each half of it is made by hand: a block's waves
@@ -1444,7 +1443,7 @@ int run_forward(const void *x, const void *W, const void *U, const float *b, con
     if (sizeof(T) == 2 && thin_max > kThinMaxTiles * kDmaBM / (d.NP / kBN)) thin_max = kThinMaxTiles * kDmaBM / (d.NP / kBN);
 
     // Levels from chain_from on are thin and hold only nodes with exactly one child (the schedule says
-    // how many children each level has): one launch each, no stack step, no projection.  A child
+    // how many children each level has): launches they share, no stack step, no projection.  A child
     // below chain_from whose parent is such a node needs no projection either, so the level right
     // below skips it too.
     int chain_from = L;
