@@ -940,6 +940,7 @@ constexpr int kChainAhead = 16;                         // weight loads in fligh
 constexpr int kChainLevels = 256;                       // levels one launch may hold (its table travels with the arguments)
 constexpr int kChainLooks = 1 << 21;                    // a microsecond or more each; the longest launches take some ten thousand
 constexpr int kChainGaveUp = 1 << 30;                   // in the counter: a block has given up waiting
+constexpr int kChainLost = -2;                          // a child that was not seen
 constexpr int kChainMaxKBytes = 4304;                   // of a row, RT = 1: two blocks share a CU's LDS
 constexpr int kChainMaxKBytes2 = 1840;                  // ... RT = 2
 // A level of many tiles goes alone, its tiles by block index: thousands of draws from one counter take longer than a launch
@@ -1030,7 +1031,7 @@ chain_kernel(const LevelArgs a, const ChainArgs lv) {
     __shared__ __attribute__((aligned(16))) float zt[4][ROWS * kEpiStride];   // pre-activations, [gate][row][unit]
     __shared__ int s_node[ROWS];
     __shared__ int s_kid[ROWS];
-    __shared__ int s_tile, s_level, s_lost;
+    __shared__ int s_tile, s_level;
     __shared__ __attribute__((aligned(16))) float s_bias[HAS_Z ? 4 : kGateTile];
     static_assert(kChainLevels <= kThinWaves * 64, "a thread per level");
 
@@ -1046,7 +1047,7 @@ chain_kernel(const LevelArgs a, const ChainArgs lv) {
     const int tile = place < a.n_blocks ? place : a.n_blocks - 1;     // (always below: the grid has as many blocks as there are tiles)
     const int row_tile = tile / a.n_col_tiles;
     const int col = tile - row_tile * a.n_col_tiles;             // unit tile
-    if (t_lo <= row_tile && row_tile < t_hi) { s_level = tid; s_lost = 0; }
+    if (t_lo <= row_tile && row_tile < t_hi) s_level = tid;
 
     // ---- weights: lane (l16, q4) supplies row l16 of a tile of the wave's gate, bytes [q4*16, +16) of each slab (64 bytes of K).
     //      Every load of the ring is unconditional (a slab past the end is clamped to the last one, whose data is
@@ -1088,7 +1089,7 @@ chain_kernel(const LevelArgs a, const ChainArgs lv) {
             s_kid[mine] = kid;
         }
         if (l > 0) {
-            // (a position outside the level below is checked where the wait ends)
+            // (a position outside the level below, or another node's, is dealt with at the first look)
             int q = lv.inv_perm[kid < 0 ? 0 : kid];
             q = q < lv.pos[l - 1] ? lv.pos[l - 1] : q < lv.pos[l] ? q : lv.pos[l] - 1;
             astray = lv.perm[q] - kid;
@@ -1152,16 +1153,32 @@ chain_kernel(const LevelArgs a, const ChainArgs lv) {
     }
 
     // ---- wait for the children (wave 0; the others stand at the barrier)
-    // A position that is not the child's, or not in the level below (a schedule made by hand), says nothing: the tile then
-    // waits for every tile of the launch's levels below.
-    int looks = drawn == place ? kChainLooks : 0;
-    bool there = true;
-    for (int w = wait_lo; w <= wait_hi;) {
-        const int *word = lv.done + (int64_t)(w + lane <= wait_hi ? w + lane : wait_hi) * lv.stride;
-        there = wait_bounded(a.n_col_tiles, looks, [&](int least) { return __all(__hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= least); },
-                             [] { __builtin_amdgcn_s_sleep(1); });
-        w += 64;
-        if (w > wait_hi && __any(astray != 0)) { astray = 0; w = 0; wait_hi = lv.tiles[l] - 1; }
+    if (wait_lo <= wait_hi) {
+        auto look = [&](int w, int least) {
+            const int *word = lv.done + (int64_t)(w + lane <= wait_hi ? w + lane : wait_hi) * lv.stride;
+            return (bool)__all(__hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= least);
+        };
+        // A position that is not the child's, or not in the level below (a schedule made by hand), says nothing: the tile then
+        // waits for every tile of the launch's levels below.  Whether there is one is known with the first look; what stands behind the
+        // later ones is on the way of h from one block to the next.
+        int w = wait_lo;
+        const bool first = look(w, a.n_col_tiles) && w + 64 > wait_hi, stray = __any(astray != 0);
+        if (!first || stray) {
+            if (stray) {
+                w = 0;
+                wait_hi = lv.tiles[l] - 1;
+            }
+            int looks = drawn == place ? kChainLooks : 0;
+            bool there;
+            do {
+                there = wait_bounded(a.n_col_tiles, looks, [&](int least) { return look(w, least); }, [] { __builtin_amdgcn_s_sleep(1); });
+                w += 64;
+            } while (w <= wait_hi);
+            if (!there) {
+                if (lane < ROWS) s_kid[lane] = kChainLost;
+                if (lane == 0) __hip_atomic_fetch_or(lv.ticket, kChainGaveUp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+        }
     }
     asm volatile("" ::: "memory");
     __syncthreads();
@@ -1207,14 +1224,13 @@ chain_kernel(const LevelArgs a, const ChainArgs lv) {
             }
         }
 #pragma unroll 1
-        for (int j = 0; j < NJ; ++j)
-            if (s_kid[(tid >> 5) + RPP * j] < 0)             // (no child after all: zeros)
+        for (int j = 0; j < NJ; ++j) {
+            const int kid = s_kid[(tid >> 5) + RPP * j];
+            const uint32_t fill = kid == kChainLost ? 0xFFFFFFFFu : 0u;           // NaN; or no child after all: zeros
+            if (kid < 0)
                 for (int kb = (tid & 31) * 16; kb < h_bytes; kb += 512)
-                    *reinterpret_cast<u32x4 *>(a_lds + ((tid >> 5) + RPP * j) * pitch + x_bytes + kb) = u32x4{0u, 0u, 0u, 0u};
-    }
-    if (tid == 0 && !there) {
-        s_lost = 1;
-        __hip_atomic_fetch_or(lv.ticket, kChainGaveUp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    *reinterpret_cast<u32x4 *>(a_lds + ((tid >> 5) + RPP * j) * pitch + x_bytes + kb) = u32x4{fill, fill, fill, fill};
+        }
     }
     floatx4 acc[RT][NB];
 #pragma unroll
@@ -1269,7 +1285,6 @@ chain_kernel(const LevelArgs a, const ChainArgs lv) {
             z[g][0] = q.x + bq[g].x; z[g][1] = q.y + bq[g].y; z[g][2] = q.z + bq[g].z; z[g][3] = q.w + bq[g].w;
         }
         const float ckv[4] = {ck.x, ck.y, ck.z, ck.w};
-        const bool lost = s_lost != 0;
         float cc[4], go[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
@@ -1278,7 +1293,6 @@ chain_kernel(const LevelArgs a, const ChainArgs lv) {
             const float gu = tanh_t<T>(z[2][e]);
             const float gf = sigmoid_t<T>(z[3][e]);
             cc[e] = gi * gu + gf * ckv[e];
-            if (lost) cc[e] = __builtin_nanf("");
         }
         store_state_shared<T>(a, node, unit0, make_float4(cc[0], cc[1], cc[2], cc[3]), make_float4(go[0], go[1], go[2], go[3]));
     }
