@@ -80,7 +80,7 @@ nary_stack_kernel(const T *__restrict__ x, int D, int Dp, const T *__restrict__ 
     constexpr int VEC = Traits<T>::VEC;
     int64_t row;
     int pair;
-    stack_place(blockIdx.x, (Dp + Nk * Hp) / (8 * VEC), n_rows, row, pair);
+    stack_place(stack_block(), (Dp + Nk * Hp) / (8 * VEC), n_rows, row, pair);
     if (row >= n_rows) return;
     const int kp = pair * 8 * VEC, k0 = kp + (int)(threadIdx.x & 7) * VEC;
     const int l = kp < Dp ? -1 : (kp - Dp) / Hp;             // the pair is x's or one child's
@@ -134,7 +134,7 @@ int run_nary_slot(jitdb_dtype dtype, const LevelArgs &a, const NarySlot &s, hipS
     const int Nk = s.leaves ? 0 : s.N;                       // child positions this slot stacks and multiplies
     const int Kn = a.Dp + Nk * a.Hp;
     const int rows_alloc = (int)round_up(s.n_rows, kRowPad);
-    const unsigned sblocks = stack_grid(s.n_rows, (int64_t)Kn * (int64_t)esz);
+    const dim3 sblocks = stack_dims(stack_grid(s.n_rows, (int64_t)Kn * (int64_t)esz));
     if (dtype == JITDB_F32)
         nary_stack_kernel<float><<<sblocks, kThreads, 0, st>>>(static_cast<const float *>(s.x), a.D, a.Dp,
                                                               static_cast<const float *>(a.hs), a.Hp, s.N, Nk, s.row_rec,

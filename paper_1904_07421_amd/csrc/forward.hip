@@ -320,7 +320,7 @@ template <typename T>
 __global__ void __launch_bounds__(kThreads)
 stack_kernel(const StackArgs s) {
     stack_body<T>(static_cast<const T *>(s.x), s.D, s.Dp, static_cast<const T *>(s.hs), s.Hp, s.row_rec, s.child_idx,
-                  static_cast<T *>(s.A), s.n_rows, s.n_rows_alloc, blockIdx.x);
+                  static_cast<T *>(s.A), s.n_rows, s.n_rows_alloc, stack_block());
 }
 
 // Leaves: x alone.  One thread per 16 bytes in row order: a row's x is at most a few lines, and reading each of them once is worth more than
@@ -330,7 +330,7 @@ __global__ void __launch_bounds__(kThreads)
 stack_x_kernel(const StackArgs s) {
     constexpr int VEC = Traits<T>::VEC;
     const unsigned per_row = (unsigned)(s.Dp / VEC);
-    const uint64_t first = (uint64_t)blockIdx.x * kThreads, row0 = first / per_row;      // of the block
+    const uint64_t first = (uint64_t)stack_block() * kThreads, row0 = first / per_row;      // of the block
     const unsigned at = (unsigned)(first - row0 * per_row) + threadIdx.x;
     const int64_t row = (int64_t)row0 + at / per_row;
     if (row >= s.n_rows) return;
@@ -920,9 +920,10 @@ nary_thin_kernel(const LevelArgs a, const NaryEpi e, const void *__restrict__ Bx
 //     the first 2 RT waves finishes eight of the tile's rows;
 //   * h and c of a child may come from another XCD's block, whose L2 is not this one's.  They, the words and the counter are only
 //     touched by atomic accesses of agent scope, which are carried out where all XCDs see them (loads and stores go past the L2s, sc1):
-//     one that vmcnt counts as done has been done for every block.  So no cache need be written back or dropped; what is left is order, and each half of it is made by hand: a block's waves
-//     wait for vmcnt 0 and meet at the barrier before the word is raised, and no wave asks for h or c before wave 0 has seen
-//     the words and met it at the barrier (a load is not started before the branch that it stands behind is decided);
+//     one that vmcnt counts as done has been done for every block.  So no cache need be written back or dropped; what is left is
+//     order, and each half of it is made by hand: a block's waves wait for vmcnt 0 and meet at the barrier before the word is raised,
+//     and no wave asks for h or c before wave 0 has seen the words and met it at the barrier (a load is not started before the branch
+//     that it stands behind is decided);
 //   * US = 2 (fp32, whose MFMAs are a long chain for one wave): eight waves, wave w has units 16 (w / 4) .. of its gate;
 //   * RT = 1 spreads a level over more blocks and shortens each one's part of the chain; where bf16 levels have
 //     kChainWideTiles such tiles on average the chip is full and RT = 2 asks half as much of the weights and the words.  A launch that
@@ -943,15 +944,23 @@ constexpr int kChainGaveUp = 1 << 30;                   // in the counter: a blo
 constexpr int kChainLost = -2;                          // a child that was not seen
 constexpr int kChainMaxKBytes = 4304;                   // of a row, RT = 1: two blocks share a CU's LDS
 constexpr int kChainMaxKBytes2 = 1840;                  // ... RT = 2
-// A level of many tiles goes alone, its tiles by block index: thousands of draws from one counter take longer than a launch
-// (8000 chains of 4 - 5 nodes, bf16, all levels in one launch / each alone: H 256 192 / 172 us, H 512 453 / 436).  Such a level
-// fills the chip, and what counts is no longer one block's chain but how often the weights are read and how soon a block is at work:
-// tiles of 32 rows (fp32: up to kChainAloneMaxKBytes2 of a row, above that the second block on a CU, which 32 rows leave no room
-// for, is worth more), and in fp32 half as many loads ahead.  The same forests, us: a launch a level of 32-row tiles whose
-// waves had a part of K each / 16-row tiles, 16 loads ahead / 32 rows, 16 / 32 rows, 8 / 16 rows, 8:
-//   fp32  D 64 H 384 (1792 bytes) 653 / 658 / 553 / 535 / 556    D 300 H 256 (2304) 482 / 541 / 481 / 468 / 527    H 320 (2560) 737 / 752 / 782 / 755 / 645
-//         D 512 H 128 (2560) 355 / 366 / 366 / 356 / 332    H 256 (3072) 714 / 704 / 728 / 710 / 683    D 300 H 512 (3328) 1325 / 1322 / 1380 / 1330 / 1240
-//   bf16  D 300 H 256 (1152) 185 / 173 / 171    D 512 H 512 (2048) 662 / 609 / 595    D 1024 H 512 (3072) 858 / 936 / 768    D 512 H 1024 (3072) 1595 / 1725 / 1435
+// A level of many tiles goes alone, its tiles by block index: thousands of draws from one counter take longer than a launch (8000
+// chains of 4 - 5 nodes, bf16, all levels in one launch / each alone: H 256 192 / 172 us, H 512 453 / 436).  Such a level fills the
+// chip, and what counts is no longer one block's chain but how often the weights are read and how soon a block is at work: tiles of
+// 32 rows (fp32: up to kChainAloneMaxKBytes2 of a row; above that the second block on a CU, which 32 rows leave no room for, is worth
+// more), and in fp32 half as many loads ahead.  The same forests, us, (a) a launch a level of 32-row tiles whose waves had a part of K
+// each, (b) 16-row tiles, 16 loads ahead, (c) 32 rows, 16, (d) 32 rows, 8, (e) 16 rows, 8:
+//                          bytes     a      b      c      d      e
+//   fp32  D  64  H  384     1792    653    658    553    535    556
+//         D 300  H  256     2304    482    541    481    468    527
+//         D 300  H  320     2560    737    752    782    755    645
+//         D 512  H  128     2560    355    366    366    356    332
+//         D 512  H  256     3072    714    704    728    710    683
+//         D 300  H  512     3328   1325   1322   1380   1330   1240
+//   bf16  D 300  H  256     1152    185           171
+//         D 512  H  512     2048    662    609    595
+//         D 1024 H  512     3072    858    936    768
+//         D 512  H 1024     3072   1595   1725   1435
 constexpr int kChainAloneTiles = 1536;
 constexpr int kChainAloneMaxKBytes2 = 2304;
 constexpr int kChainAloneAhead = 8;
@@ -1677,9 +1686,9 @@ int run_forward(const void *x, const void *W, const void *U, const float *b, con
                 const StackArgs sa = stack_args(segs[i]);
                 ScopedLaunchTimer tm(JITDB_K_STACK, n_rows, st);
                 if (l == 0)
-                    stack_x_kernel<T><<<(unsigned)ceil_div((int64_t)n_rows * (d.Dp / Traits<T>::VEC), kThreads), kThreads, 0, st>>>(sa);
+                    stack_x_kernel<T><<<stack_dims(ceil_div((int64_t)n_rows * (d.Dp / Traits<T>::VEC), kThreads)), kThreads, 0, st>>>(sa);
                 else
-                    stack_kernel<T><<<stack_blocks(segs[i]), kThreads, 0, st>>>(sa);
+                    stack_kernel<T><<<stack_dims(stack_blocks(segs[i])), kThreads, 0, st>>>(sa);
                 JITDB_LAUNCH_CHECK();
             }
             stacked_ahead = false;

@@ -227,7 +227,13 @@ __device__ __forceinline__ bool enter_range(LevelArgs &a, int tile, int &row0) {
 // 745 us against 688, the projection of a thin level with the next stack step 14.0 us against 12.4.
 constexpr int kStackRows = kThreads / 8;
 inline unsigned stack_grid(int64_t n_rows, int64_t k_bytes) { return (unsigned)(ceil_div(n_rows, kStackRows) * (k_bytes / 128)); }
-// row and pair of slabs of the thread; past n_rows in the last row tile
+// A launch of its own for them: 2^24 blocks of 256 threads are more than one dimension of a grid takes, the rest goes into the other.
+inline dim3 stack_dims(int64_t blocks) {
+    constexpr int64_t kMost = 1 << 23;
+    return blocks <= kMost ? dim3((unsigned)blocks) : dim3((unsigned)kMost, (unsigned)ceil_div(blocks, kMost));
+}
+__device__ __forceinline__ unsigned stack_block() { return blockIdx.y * gridDim.x + blockIdx.x; }
+// row and pair of slabs of the thread; past n_rows in the last row tile (and behind it)
 __device__ __forceinline__ void stack_place(unsigned block, int n_pairs, int n_rows, int64_t &row, int &pair) {
     const unsigned tiles = (unsigned)((n_rows + kStackRows - 1) / kStackRows), pairs = (unsigned)n_pairs, eights = (tiles & ~7u) * pairs;
     unsigned tile;
